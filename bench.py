@@ -277,7 +277,7 @@ def main():
                ["im2col_rows_and_dY_tokens", "mfma_gemm", "splitk_reduce"] if conv_gemm else
                ["row_starts", "pad_dY", "mfma_conv", "partial_reduce"] if conv_padded else
                ["row_starts", "mfma_conv", "partial_reduce"] if conv_mfma else
-               ["recover_and_fma_gemm"] if fc_small else ["zero_scatter", "fma_gemm"])
+               ["recover_and_fma_gemm"] if fc_small else ["recover", "fp32_gemm_and_splitk_reduce"])
     compress_ms = float(c_med.sum())
     grad_ms = float(g_med.sum())
 
@@ -291,7 +291,7 @@ def main():
     hist_gbps = compress_bytes / (hist_ms * 1e-3) * 1e-9
 
     main_kernel = ("fc_dense_kernel" if (fc_mfma or conv_gemm or fc_fused) else "conv3x3_mfma_kernel" if conv_mfma else
-                   "fc_small_kernel" if fc_small else "fc_fma_kernel")
+                   "fc_small_kernel" if fc_small else "exact_gemm_kernel")
     select_kernel = "select_small_kernel" if w.numel // (8 if bf16 else 4) <= 8 * 1024 else "select_fused_kernel"
     dw_traffic = measured_traffic(w.name + ("+lds" if fc_fused else ""), main_kernel)
     sel_traffic = measured_traffic(w.name, select_kernel)

@@ -159,7 +159,7 @@ typedef DROPIT_ENUM(dropit_wgrad_path) {
     DROPIT_PATH_FC_MFMA = 1,        /* recover + split-K bf16 MFMA GEMM */
     DROPIT_PATH_CONV_BANDS = 2,     /* 3x3/s1/p1 bf16: row bands in LDS, implicit im2col on the matrix cores */
     DROPIT_PATH_CONV_GEMM = 3,      /* 3x3/s1/p1 bf16, small planes with many channels: explicit im2col rows + the FC GEMM */
-    DROPIT_PATH_FMA = 4,            /* exact fp32 multiply-add kernels (fp32 inputs, odd shapes) */
+    DROPIT_PATH_FMA = 4,            /* exact fp32 multiply-adds on the fp32 matrix instructions (fp32 inputs, odd shapes) */
     DROPIT_PATH_CONV_IM2COL = 5,    /* bf16, any geometry and either layout: zero-filled im2col rows written from the pairs + the FC GEMM */
     DROPIT_PATH_FC_SMALL = 6,       /* fully-connected layers of at most 16384 input elements: recover in LDS and exact fp32 multiply-adds, one launch */
     DROPIT_PATH_FC_FUSED = 7        /* the FC_MFMA product with the recover step inside it (only after dropit_set_fc_recover(1)) */
@@ -186,7 +186,7 @@ dropit_wgrad_path dropit_weight_grad_path(const int64_t *x_shape, int ndim, drop
  *     (3x3 / stride 1 / pad 1 in forms of its own, every other geometry through
  *     explicit im2col rows in the workspace, at most 1 GiB of them; see
  *     dropit_weight_grad_path); fp32 and the remaining shapes (kernel extents up
- *     to 1024, stride / pad / dilation up to 65535) take an exact but slow fp32 kernel.
+ *     to 1024, stride / pad / dilation up to 65535) take the exact fp32 product, a sixteenth of the bf16 rate.
  *     DROPIT_EINVAL if the window does not fit the padded input.
  *
  *   vals, idx [in]  device, the k pairs written by dropit_compress for a tensor

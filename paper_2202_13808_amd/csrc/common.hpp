@@ -209,8 +209,8 @@ __device__ inline void block_lower_bound2(const int32_t *__restrict__ idx, int64
 // three dependent rounds of loads, and a further round for the pairs.
 // between() runs after the window's loads are issued and before any place(): the place for the
 // caller's LDS zero fill (a barrier follows it).  All threads of the block must call this.
-template <int THREADS, int WN, typename Place, typename Between>
-__device__ inline void for_pairs_in_range(const uint16_t *__restrict__ vals, const int32_t *__restrict__ idx,
+template <int THREADS, int WN, typename RAW, typename Place, typename Between>
+__device__ inline void for_pairs_in_range(const RAW *__restrict__ vals, const int32_t *__restrict__ idx,
                                           int64_t k, int64_t numel, int64_t first, int64_t last, int64_t margin,
                                           Place &&place, Between &&between)
 {

@@ -4,9 +4,8 @@
 //   conv : dW[j][c][u][v] = sum_{n,oy,ox} dY[n][j][oy][ox] * R(a^)[n][c][oy+u-1][ox+v-1]
 //                                                                   (Eq. conv_backward_elem, 3x3/s1/p1)
 //
-// This file holds the host entry points and the generic fp32-FMA kernels
-// (exact fp32 products, fixed summation order).  They serve fp32 inputs and
-// any bf16 shape the MFMA kernels do not cover.
+// This file holds the host entry points, the choice of the path, and the one-launch
+// kernel of small fully-connected layers.
 #include "common.hpp"
 #include "wgrad_internal.hpp"
 #include "dev_hooks.hpp"
@@ -18,87 +17,10 @@ namespace {
 __device__ inline float to_f32(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 __device__ inline float to_f32(uint32_t b) { return __uint_as_float(b); }
 
-// ---- recover R(a^) into a dense buffer of the input type ------------------
-__global__ void __launch_bounds__(256) zero_kernel(uint4 *p, size_t n16)
-{
-    const uint4 z = make_uint4(0, 0, 0, 0);
-    for (size_t i = blockIdx.x * size_t(blockDim.x) + threadIdx.x; i < n16; i += size_t(gridDim.x) * blockDim.x)
-        p[i] = z;
-}
-
 __global__ void __launch_bounds__(256) zero_f32_kernel(float *p, int64_t n)
 {
     for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
         p[i] = 0.f;
-}
-
-template <typename RAW>
-__global__ void __launch_bounds__(256) scatter_kernel(const RAW *__restrict__ vals, const int32_t *__restrict__ idx,
-                                                      int64_t k, int64_t numel, RAW *__restrict__ dense)
-{
-    for (int64_t j = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; j < k; j += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t i = idx[j];
-        if (i >= 0 && i < numel) dense[i] = vals[j];   // an out-of-range index is ignored, never written
-    }
-}
-
-// ---- FC: 64x64 output tile per workgroup, 4x4 per thread, fp32 FMA --------
-constexpr int FT = 64;      // tile edge
-constexpr int FK = 64;      // tokens per step
-
-// The next step's operands are fetched into registers while the current step multiplies, so a short
-// problem (a few steps) does not pay one memory round trip per step.  Every output element still adds
-// its terms in ascending token order: the result does not depend on FK.
-template <typename RAW>
-__global__ void __launch_bounds__(256)
-fc_fma_kernel(const RAW *__restrict__ xhat, const RAW *__restrict__ dY, int64_t ntok, int cin, int cout,
-              float *__restrict__ dW)
-{
-    __shared__ float sA[FK][FT + 4];   // dY tile  [token][j]
-    __shared__ float sB[FK][FT + 4];   // x^ tile  [token][c]
-    constexpr int PER = FK * FT / 256; // elements of each tile a thread moves
-    const int tid = threadIdx.x;
-    const int j0 = blockIdx.y * FT, c0 = blockIdx.x * FT;
-    const int tj = (tid / 16) * 4, tc = (tid % 16) * 4;
-    float acc[4][4] = {};
-    float na[PER], nb[PER];
-    auto fetch = [&](int64_t n0) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = tid + u * 256, r = e / FT, q = e % FT;
-            const int64_t n = n0 + r;
-            na[u] = (n < ntok && j0 + q < cout) ? to_f32(dY[n * cout + j0 + q]) : 0.f;
-            nb[u] = (n < ntok && c0 + q < cin) ? to_f32(xhat[n * cin + c0 + q]) : 0.f;
-        }
-    };
-    fetch(0);
-    for (int64_t n0 = 0; n0 < ntok; n0 += FK) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = tid + u * 256, r = e / FT, q = e % FT;
-            sA[r][q] = na[u];
-            sB[r][q] = nb[u];
-        }
-        __syncthreads();
-        if (n0 + FK < ntok) fetch(n0 + FK);
-#pragma unroll 16
-        for (int r = 0; r < FK; ++r) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[r][tj + i]; b[i] = sB[r][tc + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[i][q] = __builtin_fmaf(a[i], b[q], acc[i][q]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (j0 + tj + i < cout && c0 + tc + q < cin)
-                dW[int64_t(j0 + tj + i) * cin + c0 + tc + q] = acc[i][q];
 }
 
 // ---- FC, small layers: recover and multiply in ONE launch --------------------------------------------
@@ -107,7 +29,7 @@ fc_fma_kernel(const RAW *__restrict__ xhat, const RAW *__restrict__ dY, int64_t 
 // slots for a few microseconds of arithmetic.  Here every workgroup rebuilds the whole R(a^) in its own LDS
 // (zero fill, then one store per pair: the k pairs are a few thousand), fetches its SMALL_JB columns of dY,
 // and multiplies: thread (j, c-group) adds its terms in ascending token order with true fp32 multiply-adds
-// (bf16 inputs are widened exactly), the same order and arithmetic as fc_fma_kernel.
+// (bf16 inputs are widened exactly).
 constexpr int SMALL_NUMEL = 16384;         // elements of x: 64 KB of fp32 in LDS
 constexpr int SMALL_TOKENS = 1024;         // tokens: the dY slice is SMALL_TOKENS x SMALL_JB fp32 = 64 KB
 constexpr int SMALL_JB = 16;               // rows of dW per workgroup
@@ -148,102 +70,6 @@ fc_small_kernel(const RAW *__restrict__ vals, const int32_t *__restrict__ idx, i
         }
         if (j0 + j < cout)
             *reinterpret_cast<float4 *>(dW + int64_t(j0 + j) * cin + c0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    }
-}
-
-// ---- conv 3x3 / stride 1 / pad 1: one workgroup per (j, c), fixed-order reduce
-template <typename RAW>
-__global__ void __launch_bounds__(256)
-conv3x3_fma_kernel(const RAW *__restrict__ xhat, const RAW *__restrict__ dY, int N, int C, int H, int W, int cout,
-                   float *__restrict__ dW)
-{
-    __shared__ float red[256][9];
-    const int j = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    float acc[9] = {};
-    const int plane = H * W;
-    for (int n = 0; n < N; ++n) {
-        const RAW *xp = xhat + (int64_t(n) * C + c) * plane;
-        const RAW *gp = dY + (int64_t(n) * cout + j) * plane;
-        for (int p = tid; p < plane; p += 256) {
-            const int oy = p / W, ox = p % W;
-            const float g = to_f32(gp[p]);
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int iy = oy + u - 1;
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    const int ix = ox + v - 1;
-                    if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-                        acc[u * 3 + v] = __builtin_fmaf(g, to_f32(xp[iy * W + ix]), acc[u * 3 + v]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 9; ++i) red[tid][i] = acc[i];
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s)
-#pragma unroll
-            for (int i = 0; i < 9; ++i) red[tid][i] += red[tid + s][i];
-        __syncthreads();
-    }
-    if (tid < 9) dW[(int64_t(j) * C + c) * 9 + tid] = red[0][tid];
-}
-
-// ---- any other convolution geometry: one workgroup per (j, c), taps in chunks of 16 ----
-// Each thread walks the output positions (n, oy, ox) with a fixed stride and keeps 16 tap sums;
-// the workgroup adds them up in a fixed tree, so the result is reproducible.  Slow (the data is
-// walked once per 16 taps) but exact, for the geometries the matrix-core kernel does not take.
-constexpr int TAP_CHUNK = 16;
-// Element strides of the two layouts: x and dY as (image, channel, row, column), dW as (filter, channel, tap).
-struct ConvStrides {
-    int64_t xn, xc, xh, xw, yn, yc, yh, yw, wj, wc, wt;
-};
-
-template <typename RAW>
-__global__ void __launch_bounds__(256)
-conv_general_fma_kernel(const RAW *__restrict__ xhat, const RAW *__restrict__ dY, int N, int C, int H, int W, int cout,
-                        int OH, int OW, int kh, int kw, int sh, int sw, int ph, int pw, int dh, int dw,
-                        ConvStrides st, float *__restrict__ dW)
-{
-    __shared__ float red[256][TAP_CHUNK + 1];
-    const int j = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    const int taps = kh * kw;
-    const int64_t oplane = int64_t(OH) * OW;
-    const int64_t positions = int64_t(N) * oplane;
-    for (int t0 = 0; t0 < taps; t0 += TAP_CHUNK) {
-        float acc[TAP_CHUNK];
-#pragma unroll
-        for (int q = 0; q < TAP_CHUNK; ++q) acc[q] = 0.f;
-        for (int64_t p = tid; p < positions; p += 256) {
-            const int n = int(p / oplane);
-            const int r = int(p - int64_t(n) * oplane);
-            const int oy = r / OW, ox = r - oy * OW;
-            const float g = to_f32(dY[n * st.yn + j * st.yc + oy * st.yh + ox * st.yw]);
-            const RAW *xp = xhat + n * st.xn + c * st.xc;
-#pragma unroll
-            for (int q = 0; q < TAP_CHUNK; ++q) {
-                const int tap = t0 + q;                         // uniform
-                if (tap < taps) {
-                    const int u = tap / kw, v = tap - u * kw;
-                    const int64_t iy = int64_t(oy) * sh - ph + int64_t(u) * dh, ix = int64_t(ox) * sw - pw + int64_t(v) * dw;
-                    if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-                        acc[q] = __builtin_fmaf(g, to_f32(xp[iy * st.xh + ix * st.xw]), acc[q]);
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < TAP_CHUNK; ++q) red[tid][q] = acc[q];
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if (tid < s)
-#pragma unroll
-                for (int q = 0; q < TAP_CHUNK; ++q) red[tid][q] += red[tid + s][q];
-            __syncthreads();
-        }
-        if (tid < TAP_CHUNK && t0 + tid < taps) dW[j * st.wj + c * st.wc + (t0 + tid) * st.wt] = red[0][tid];
-        __syncthreads();
     }
 }
 
@@ -310,44 +136,10 @@ dropit_status describe(const int64_t *x_shape, int ndim, dropit_dtype dt, int64_
     return DROPIT_OK;
 }
 
-size_t dense_bytes(const Problem &p, dropit_dtype dt)
+ExactProblem exact_of(const Problem &p, int64_t k)
 {
-    return round_up(size_t(p.numel) * (dt == DROPIT_F32 ? 4 : 2), 256);
-}
-
-template <typename RAW>
-dropit_status run_generic(const Problem &p, const void *vals, const int32_t *idx, int64_t k, const void *dY,
-                          float *dW, char *ws, size_t dense_sz, hipStream_t stream)
-{
-    RAW *dense = reinterpret_cast<RAW *>(ws);
-    trace_mark(stream);
-    zero_kernel<<<1024, 256, 0, stream>>>(reinterpret_cast<uint4 *>(dense), dense_sz / 16);
-    if (k > 0) {
-        const int blocks = static_cast<int>(std::min<int64_t>((k + 255) / 256, 4096));
-        scatter_kernel<RAW><<<blocks, 256, 0, stream>>>(static_cast<const RAW *>(vals), idx, k, p.numel, dense);
-    }
-    trace_mark(stream);
-    if (!p.conv) {
-        const dim3 grid((p.cin + FT - 1) / FT, (p.cout + FT - 1) / FT);
-        fc_fma_kernel<RAW><<<grid, 256, 0, stream>>>(dense, static_cast<const RAW *>(dY), p.ntok, int(p.cin),
-                                                      int(p.cout), dW);
-    } else {
-        const dim3 grid(p.C, p.cout);
-        const int64_t taps = p.g.kh * p.g.kw;
-        const ConvStrides st = p.nhwc
-            ? ConvStrides{p.H * p.W * p.C, 1, p.W * p.C, p.C, p.OH * p.OW * p.cout, 1, p.OW * p.cout, p.cout, taps * p.C, 1, p.C}
-            : ConvStrides{p.C * p.H * p.W, p.H * p.W, p.W, 1, p.cout * p.OH * p.OW, p.OH * p.OW, p.OW, 1, p.C * taps, taps, 1};
-        if (p.is_3x3_s1_p1 && !p.nhwc)
-            conv3x3_fma_kernel<RAW><<<grid, 256, 0, stream>>>(dense, static_cast<const RAW *>(dY), int(p.N), int(p.C),
-                                                               int(p.H), int(p.W), int(p.cout), dW);
-        else
-            conv_general_fma_kernel<RAW><<<grid, 256, 0, stream>>>(
-                dense, static_cast<const RAW *>(dY), int(p.N), int(p.C), int(p.H), int(p.W), int(p.cout), int(p.OH),
-                int(p.OW), int(p.g.kh), int(p.g.kw), int(p.g.stride_h), int(p.g.stride_w), int(p.g.pad_h),
-                int(p.g.pad_w), int(p.g.dil_h), int(p.g.dil_w), st, dW);
-    }
-    trace_mark(stream);
-    return launch_status();
+    if (!p.conv) return ExactProblem{false, false, p.numel, p.ntok, p.cin, p.cout, k, 0, 0, 0, 0, 0, p.g};
+    return ExactProblem{true, p.nhwc, p.numel, p.N * p.OH * p.OW, p.C * p.g.kh * p.g.kw, p.cout, k, p.C, p.H, p.W, p.OH, p.OW, p.g};
 }
 
 }  // namespace
@@ -406,7 +198,7 @@ static size_t workspace_need(const Problem &p, dropit_dtype dt, int64_t k)
     case DROPIT_PATH_CONV_BANDS: return conv_mfma_plan(cp).total();
     case DROPIT_PATH_CONV_IM2COL: return conv_im2col_plan(general_of(p, k)).total();
     case DROPIT_PATH_FC_SMALL: return 256;           // nothing is kept outside LDS; a token size so that callers' buffers exist
-    default: return dense_bytes(p, dt);
+    default: return exact_plan(exact_of(p, k), dt == DROPIT_F32).total();
     }
 }
 
@@ -475,8 +267,8 @@ static dropit_status run(const Problem &p, const void *vals, const int32_t *idx,
     }
     default: break;
     }
-    if (dt == DROPIT_BF16) return run_generic<uint16_t>(p, vals, idx, k, dY, dW, ws, need, stream);
-    return run_generic<uint32_t>(p, vals, idx, k, dY, dW, ws, need, stream);
+    const ExactProblem ep = exact_of(p, k);
+    return exact_run(ep, exact_plan(ep, dt == DROPIT_F32), dt == DROPIT_F32, vals, idx, dY, dW, ws, stream);
 }
 
 extern "C" dropit_status dropit_set_fc_recover(int form)

@@ -1,0 +1,403 @@
+// Weight gradient with exact fp32 products on the gfx950 fp32 matrix instructions
+// (Sec. 3.2: recover R(a^), then Eq. fc_backward_elem_save / Eq. conv_backward_elem).
+//
+// Serves fp32 tensors of every geometry and layout, and the bf16 shapes the bf16 matrix-core paths do not take
+// (bf16 widens to fp32 exactly).  One product for all of them:
+//   dW[j][col] = sum_t dY(t, j) * X(t, col)
+// t = token (FC) or output position (n, oy, ox) (convolution), col = input feature or (channel, tap).
+//
+//   1. recover : R(a^) is rebuilt as a flat dense tensor in the workspace (recover.hpp).
+//   2. product : v_mfma_f32_32x32x2_f32, one workgroup per BM x BN tile of dW and K-slice.  This instruction takes
+//      64 cycles for 4096 multiply-adds, a sixteenth of the bf16 rate, so the kernel is bound by the matrix pipe
+//      with everything else to spare -- 8 to 16 bytes of operands per clock and compute unit -- and the spare
+//      goes into the operand fetch: a convolution's im2col rows are never written anywhere, each element of a
+//      tile is fetched from R(a^) by its own address (a handful of integer operations per element and 4096 cycles
+//      of multiplying per 32-token step), NCHW tensors are read in place without a transposition, and any
+//      alignment and ragged edge is served by the same code.  The fetched step waits in registers while the
+//      previous one multiplies; one LDS buffer, two barriers per step, two or more workgroups per compute unit
+//      to cover them.
+//   3. the K-slices' sums are added in a fixed order (splitk.hpp).
+// Products and accumulation are true fp32 multiply-adds in a fixed order: dW is bit-reproducible.
+//
+// Measured, whole weight-gradient call, against vector multiply-adds on a zero-filled and scattered R(a^) (one
+// 64 x 64 tile over all tokens; one workgroup per (j, c) for convolutions): fp32 6304 x 384 -> 1536 637 -> 81 us
+// (7.4 GFLOP; 48 us at the 154 TFLOP/s a large fp32 product reaches), fp32 3x3 convolution 32 x 64 x 32 x 32 -> 64
+// 442 -> 56 us (2.4 GFLOP, 16 us).
+#include "recover.hpp"
+#include "splitk.hpp"
+#include "wgrad_internal.hpp"
+#include "dev_hooks.hpp"
+
+namespace dropit {
+namespace {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+__device__ inline float widen(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
+__device__ inline float widen(uint32_t b) { return __uint_as_float(b); }
+
+// Tile of 2 x 2 wavefronts.  LDS rows (one token each) are padded by four floats: 16-byte stores stay aligned, and
+// stores that walk down the tokens (the NCHW operands) spread over the banks.
+template <int BM_, int BN_>
+struct ExactCfg {
+    static constexpr int BM = BM_, BN = BN_, BK = 32, WAVES_M = 2, WAVES_N = 2, NTHREADS = 256;
+    static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, FM = WM / 32, FN = WN / 32;
+    static constexpr int PA = BM + 4, PB = BN + 4;
+};
+
+// How an operand tile is fetched: token-major rows with 16-byte loads, token-major rows element by element,
+// or one address per element with the lanes along the tokens (NCHW: consecutive positions are consecutive in
+// memory) or along the columns (NHWC: consecutive channels are).
+enum Fetch { ROWS16, ROWS1, ALONG_TOKENS, ALONG_COLUMNS };
+
+struct ExactGeometry {
+    uint32_t OW, P, W, H, C, taps, kw, sh, sw, ph, pw, dh, dw;   // P = OH * OW
+    uint32_t xc, xh, xw;                                         // element strides of R(a^): channel, row, column
+    int64_t xn, yn;                                              // ... and of an image, in R(a^) and in dY
+};
+
+template <typename RAW, typename C, Fetch FA, Fetch FB>
+__global__ void __launch_bounds__(256)
+exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t ntok, int M, int N, int nb_count,
+                  int mb_count, int nkb, int splits, ExactGeometry g, float *__restrict__ out)
+{
+    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NTHREADS;
+    constexpr bool CONV = FB == ALONG_TOKENS || FB == ALONG_COLUMNS;
+    static_assert(sizeof(RAW) == 4 || (FA != ROWS16 && FB != ROWS16), "16-byte fetches are for fp32");
+    __shared__ __attribute__((aligned(16))) float sA[BK * C::PA];
+    __shared__ __attribute__((aligned(16))) float sB[BK * C::PB];
+    __shared__ uint32_t col_off[CONV ? BN : 1], col_y[CONV ? BN : 1], col_x[CONV ? BN : 1];   // of a column: offset of (c, u, v), u * dh, v * dw
+    __shared__ uint32_t tok_off[FB == ALONG_COLUMNS ? 2 : 1][BK];                             // of a token: offset of (n, iy0, ix0)
+    __shared__ uint32_t tok_y[FB == ALONG_COLUMNS ? 2 : 1][BK], tok_x[FB == ALONG_COLUMNS ? 2 : 1][BK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+
+    // workgroups of one XCD (dealt round-robin) get consecutive tiles: they share operand rows in its L2
+    const int total = nb_count * mb_count * splits;
+    const int v = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (v >= total) return;
+    const int nb = v % nb_count, mb = (v / nb_count) % mb_count, split = v / (nb_count * mb_count);
+    const int m0 = mb * BM, n0 = nb * BN;
+    const int kb_begin = int(int64_t(nkb) * split / splits), kb_end = int(int64_t(nkb) * (split + 1) / splits);
+
+    if constexpr (CONV) {
+        for (int q = tid; q < BN; q += NT) {
+            const uint32_t col = uint32_t(n0 + q);
+            uint32_t c, tap;
+            if (FB == ALONG_TOKENS) {              // (channel, tap)
+                c = col / g.taps;
+                tap = col - c * g.taps;
+            } else {                               // (tap, channel)
+                tap = col / g.C;
+                c = col - tap * g.C;
+            }
+            const uint32_t u = tap / g.kw, vv = tap - u * g.kw;
+            col_y[q] = u * g.dh;
+            col_x[q] = vv * g.dw;
+            col_off[q] = c * g.xc + u * g.dh * g.xh + vv * g.dw * g.xw;    // modulo 2^32, like the addresses below
+        }
+    }
+    // image and position of a token
+    auto locate = [&](int64_t t, uint32_t &n, uint32_t &p) {
+        if (ntok <= INT32_MAX) {                   // uniform
+            n = uint32_t(t) / g.P;
+            p = uint32_t(t) - n * g.P;
+        } else {
+            n = uint32_t(t / g.P);
+            p = uint32_t(t - int64_t(n) * g.P);
+        }
+    };
+    // top-left input position of a token's window, as 32-bit words modulo 2^32 (a row or column is inside the
+    // tensor iff the word is below H or W: sizes are below 2^31, padding and taps far below 2^31)
+    auto window = [&](uint32_t p, uint32_t &iy0, uint32_t &ix0) {
+        const uint32_t oy = p / g.OW, ox = p - oy * g.OW;
+        iy0 = oy * g.sh - g.ph;
+        ix0 = ox * g.sw - g.pw;
+    };
+    auto fill_tokens = [&](int kb) {               // ALONG_COLUMNS: the step's token table
+        if (FB == ALONG_COLUMNS && tid < BK) {
+            const int64_t t = int64_t(kb) * BK + tid;
+            uint32_t iy0 = 0x80000000u, ix0 = 0;   // past the last token: below no H
+            uint32_t off = 0;
+            if (t < ntok) {
+                uint32_t n, p;
+                locate(t, n, p);
+                window(p, iy0, ix0);
+                off = n * uint32_t(g.xn) + iy0 * g.xh + ix0 * g.xw;
+            }
+            tok_off[kb & 1][tid] = off;
+            tok_y[kb & 1][tid] = iy0;
+            tok_x[kb & 1][tid] = ix0;
+        }
+    };
+
+    // ---- operand fetch: a step's tiles into registers, and from there into LDS ------------------------------
+    constexpr int EA = BM * BK / NT, EB = BN * BK / NT;    // elements per thread
+    float ra[EA], rb[EB];
+    auto fetch = [&](int kb) {
+        const int64_t t0 = int64_t(kb) * BK;
+        if constexpr (FA == ROWS16) {                      // M % 4 == 0
+#pragma unroll
+            for (int u = 0; u < EA / 4; ++u) {
+                const int i = tid + u * NT, r = i / (BM / 4), q = (i % (BM / 4)) * 4;
+                f32x4 w = {0.f, 0.f, 0.f, 0.f};
+                if (t0 + r < ntok && m0 + q < M) w = *reinterpret_cast<const f32x4 *>(dY + (t0 + r) * M + m0 + q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ra[u * 4 + e] = w[e];
+            }
+        } else if constexpr (FA == ROWS1) {
+#pragma unroll
+            for (int u = 0; u < EA; ++u) {
+                const int i = tid + u * NT, r = i / BM, q = i % BM;
+                ra[u] = (t0 + r < ntok && m0 + q < M) ? widen(dY[(t0 + r) * M + m0 + q]) : 0.f;
+            }
+        }
+        if constexpr (FB == ROWS16) {                      // N % 4 == 0
+#pragma unroll
+            for (int u = 0; u < EB / 4; ++u) {
+                const int i = tid + u * NT, r = i / (BN / 4), q = (i % (BN / 4)) * 4;
+                f32x4 w = {0.f, 0.f, 0.f, 0.f};
+                if (t0 + r < ntok && n0 + q < N) w = *reinterpret_cast<const f32x4 *>(x + (t0 + r) * N + n0 + q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rb[u * 4 + e] = w[e];
+            }
+        } else if constexpr (FB == ROWS1) {
+#pragma unroll
+            for (int u = 0; u < EB; ++u) {
+                const int i = tid + u * NT, r = i / BN, q = i % BN;
+                rb[u] = (t0 + r < ntok && n0 + q < N) ? widen(x[(t0 + r) * N + n0 + q]) : 0.f;
+            }
+        } else if constexpr (FB == ALONG_COLUMNS) {
+            constexpr int RSTEP = NT / BN;
+            const int q = tid % BN;
+            const uint32_t off = col_off[q], cy = col_y[q], cx = col_x[q];
+            const bool col_ok = n0 + q < N;
+#pragma unroll
+            for (int u = 0; u < EB; ++u) {
+                const int r = tid / BN + u * RSTEP;
+                const uint32_t iy = tok_y[kb & 1][r] + cy, ix = tok_x[kb & 1][r] + cx;
+                const bool ok = col_ok && iy < g.H && ix < g.W;
+                rb[u] = ok ? widen(x[tok_off[kb & 1][r] + off]) : 0.f;
+            }
+        }
+        if constexpr (FA == ALONG_TOKENS || FB == ALONG_TOKENS) {
+            const int r = tid % BK, q0 = tid / BK;
+            constexpr int QSTEP = NT / BK;
+            const int64_t t = t0 + r;
+            const bool tok_ok = t < ntok;
+            uint32_t n = 0, p = 0, iy0 = 0x80000000u, ix0 = 0;
+            if (tok_ok) locate(t, n, p);
+            if constexpr (FA == ALONG_TOKENS) {
+                const RAW *yp = dY + int64_t(n) * g.yn + p;
+#pragma unroll
+                for (int u = 0; u < EA; ++u) {
+                    const int q = m0 + q0 + u * QSTEP;
+                    ra[u] = (tok_ok && q < M) ? widen(yp[int64_t(q) * g.P]) : 0.f;
+                }
+            }
+            if constexpr (FB == ALONG_TOKENS) {
+                if (tok_ok) window(p, iy0, ix0);
+                // R(a^) has fewer than 2^31 elements: its offsets are 32-bit, intermediate values may wrap
+                const uint32_t base = n * uint32_t(g.xn) + iy0 * g.xh + ix0 * g.xw;
+#pragma unroll
+                for (int u = 0; u < EB; ++u) {
+                    const int q = q0 + u * QSTEP;
+                    const uint32_t iy = iy0 + col_y[q], ix = ix0 + col_x[q];
+                    const bool ok = tok_ok && n0 + q < N && iy < g.H && ix < g.W;
+                    rb[u] = ok ? widen(x[base + col_off[q]]) : 0.f;
+                }
+            }
+        }
+    };
+    auto store = [&]() {
+        if constexpr (FA == ROWS16) {
+#pragma unroll
+            for (int u = 0; u < EA / 4; ++u) {
+                const int i = tid + u * NT, r = i / (BM / 4), q = (i % (BM / 4)) * 4;
+                *reinterpret_cast<f32x4 *>(sA + r * C::PA + q) = f32x4{ra[u * 4], ra[u * 4 + 1], ra[u * 4 + 2], ra[u * 4 + 3]};
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < EA; ++u) {
+                const int r = FA == ALONG_TOKENS ? tid % BK : (tid + u * NT) / BM;
+                const int q = FA == ALONG_TOKENS ? tid / BK + u * (NT / BK) : (tid + u * NT) % BM;
+                sA[r * C::PA + q] = ra[u];
+            }
+        }
+        if constexpr (FB == ROWS16) {
+#pragma unroll
+            for (int u = 0; u < EB / 4; ++u) {
+                const int i = tid + u * NT, r = i / (BN / 4), q = (i % (BN / 4)) * 4;
+                *reinterpret_cast<f32x4 *>(sB + r * C::PB + q) = f32x4{rb[u * 4], rb[u * 4 + 1], rb[u * 4 + 2], rb[u * 4 + 3]};
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < EB; ++u) {
+                const int r = FB == ALONG_TOKENS ? tid % BK : (tid + u * NT) / BN;
+                const int q = FB == ALONG_TOKENS ? tid / BK + u * (NT / BK) : (tid + u * NT) % BN;
+                sB[r * C::PB + q] = rb[u];
+            }
+        }
+    };
+
+    f32x16 acc[C::FM][C::FN];
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    // a 32x32x2 operand wants, in lane l, row (or column) l % 32 and k = l / 32
+    const float *pa = sA + (lane >> 5) * C::PA + wm * C::WM + (lane & 31);
+    const float *pb = sB + (lane >> 5) * C::PB + wn * C::WN + (lane & 31);
+    fill_tokens(kb_begin);
+    __syncthreads();                                       // column and token tables
+    if (kb_begin < kb_end) fetch(kb_begin);
+    for (int kb = kb_begin; kb < kb_end; ++kb) {
+        __syncthreads();                                   // the previous step's tiles have been read
+        store();
+        if (kb + 1 < kb_end) fill_tokens(kb + 1);
+        __syncthreads();
+        if (kb + 1 < kb_end) fetch(kb + 1);
+#pragma unroll
+        for (int kk = 0; kk < BK / 2; ++kk) {
+            float a[C::FM], b[C::FN];
+#pragma unroll
+            for (int i = 0; i < C::FM; ++i) a[i] = pa[kk * 2 * C::PA + i * 32];
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j) b[j] = pb[kk * 2 * C::PB + j * 32];
+#pragma unroll
+            for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                for (int j = 0; j < C::FN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+
+    // acc[i][j][e] is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32 of its 32x32 block
+    if (splits == 1) {
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int m = m0 + wm * C::WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                    const int n = n0 + wn * C::WN + j * 32 + (lane & 31);
+                    if (m < M && n < N) out[int64_t(m) * N + n] = acc[i][j][e];
+                }
+    } else {                                               // the partial tile in accumulator order, see splitk.hpp
+        f32x4 *dst = reinterpret_cast<f32x4 *>(out) +
+                     (int64_t(split) * (nb_count * mb_count) + (mb * nb_count + nb)) * (BM * BN / 4) + tid;
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    dst[((i * C::FN + j) * 4 + q) * NT] =
+                        f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+    }
+}
+
+constexpr int EXACT_TILE_BYTES = 32 * 1024;                // of R(a^), per recover workgroup
+
+template <typename RAW, typename C>
+dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const RAW *dY, const RAW *x, float *partial,
+                           float *dW, hipStream_t stream)
+{
+    const int total = plan.nb_count * plan.mb_count * plan.splits;
+    const int grid = (total + 7) / 8 * 8;
+    float *out = plan.splits > 1 ? partial : dW;
+    ExactGeometry g = {};
+    if (p.conv) {
+        const int64_t taps = p.g.kh * p.g.kw;
+        g = ExactGeometry{uint32_t(p.OW), uint32_t(p.OH * p.OW), uint32_t(p.W), uint32_t(p.H), uint32_t(p.C), uint32_t(taps),
+                          uint32_t(p.g.kw), uint32_t(p.g.stride_h), uint32_t(p.g.stride_w), uint32_t(p.g.pad_h),
+                          uint32_t(p.g.pad_w), uint32_t(p.g.dil_h), uint32_t(p.g.dil_w),
+                          p.nhwc ? 1u : uint32_t(p.H * p.W), p.nhwc ? uint32_t(p.W * p.C) : uint32_t(p.W),
+                          p.nhwc ? uint32_t(p.C) : 1u, p.C * p.H * p.W, p.cout * p.OH * p.OW};
+    }
+    auto go = [&](auto kernel) {
+        kernel<<<grid, C::NTHREADS, 0, stream>>>(dY, x, p.ntok, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count,
+                                                 plan.nkb, plan.splits, g, out);
+    };
+    const bool wide_y = p.cout % 4 == 0, wide_x = p.cin % 4 == 0;      // 16-byte rows
+    if constexpr (sizeof(RAW) == 4) {
+        if (!p.conv) {
+            if (wide_y && wide_x) go(exact_gemm_kernel<RAW, C, ROWS16, ROWS16>);
+            else go(exact_gemm_kernel<RAW, C, ROWS1, ROWS1>);
+        } else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
+        else if (wide_y) go(exact_gemm_kernel<RAW, C, ROWS16, ALONG_COLUMNS>);
+        else go(exact_gemm_kernel<RAW, C, ROWS1, ALONG_COLUMNS>);
+    } else {
+        if (!p.conv) go(exact_gemm_kernel<RAW, C, ROWS1, ROWS1>);
+        else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
+        else go(exact_gemm_kernel<RAW, C, ROWS1, ALONG_COLUMNS>);
+    }
+    if (plan.splits > 1)
+        launch_splitk_sum<C>(partial, plan.splits, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count, dW, stream);
+    trace_mark(stream);
+    return launch_status();
+}
+
+template <typename RAW>
+dropit_status run_exact(const ExactProblem &p, const ExactPlan &plan, const void *vals, const int32_t *idx, const void *dY,
+                        float *dW, char *ws, hipStream_t stream)
+{
+    constexpr int E = EXACT_TILE_BYTES / int(sizeof(RAW));
+    RAW *x = reinterpret_cast<RAW *>(ws);
+    float *partial = reinterpret_cast<float *>(ws + plan.dense_bytes);
+    trace_mark(stream);
+    const int64_t rows = (p.numel + E - 1) / E;            // R(a^) as rows of E elements, the last one not full
+    launch_recover<RAW>(static_cast<const RAW *>(vals), idx, p.k, p.numel, rows, rows, E, E, 1, x, stream);
+    trace_mark(stream);
+    const RAW *y = static_cast<const RAW *>(dY);
+    if (plan.bm == 128) return launch_exact<RAW, ExactCfg<128, 128>>(p, plan, y, x, partial, dW, stream);
+    if (plan.bn == 128) return launch_exact<RAW, ExactCfg<64, 128>>(p, plan, y, x, partial, dW, stream);
+    return launch_exact<RAW, ExactCfg<64, 64>>(p, plan, y, x, partial, dW, stream);
+}
+
+}  // namespace
+
+ExactPlan exact_plan(const ExactProblem &p, bool f32)
+{
+    ExactPlan plan;
+    const int64_t E = EXACT_TILE_BYTES / (f32 ? 4 : 2);
+    plan.dense_bytes = round_up(size_t((p.numel + E - 1) / E * E) * (f32 ? 4 : 2), 256);
+    // the tile that pads the result least, the larger one where two pad the same
+    plan.bm = plan.bn = 0;
+    int64_t least = INT64_MAX;
+    const int shapes[3][2] = {{128, 128}, {64, 128}, {64, 64}};
+    for (const auto &s : shapes) {
+        const int64_t padded = round_up(p.cout, s[0]) * round_up(p.cin, s[1]);
+        if (padded < least) {
+            least = padded;
+            plan.bm = s[0];
+            plan.bn = s[1];
+        }
+    }
+    plan.mb_count = int((p.cout + plan.bm - 1) / plan.bm);
+    plan.nb_count = int((p.cin + plan.bn - 1) / plan.bn);
+    plan.nkb = int((p.ntok + 31) / 32);
+    // K-slices: two (128 x 128) to four workgroups per compute unit.  Measured with one / two / three / four: 84 / 81 /
+    // 102 / 89 us for 36 tiles of 128 x 128 over 6304 tokens, 91 / 66 / 59 / 56 us for 9 tiles of 64 x 64 over 32768.
+    // A slice writes a whole partial tile however little it summed, yet short problems want every compute unit: two
+    // 32-token steps per slice at least (435 tokens, 6 tiles: 15 us with two, 17 with four, 27 with eight).
+    const int64_t tiles = int64_t(plan.mb_count) * plan.nb_count;
+    const int64_t resident = dev_env("DROPIT_EXACT_WGS", plan.bm * plan.bn >= 128 * 128 ? 512 : 1024);
+    const int64_t splits = std::min<int64_t>(resident / std::max<int64_t>(tiles, 1), plan.nkb / dev_env("DROPIT_EXACT_MIN", 2));
+    plan.splits = int(std::max<int64_t>(1, std::min<int64_t>(splits, 256)));
+    plan.partial_bytes = plan.splits > 1 ? size_t(plan.splits) * tiles * plan.bm * plan.bn * 4 : 0;
+    return plan;
+}
+
+dropit_status exact_run(const ExactProblem &p, const ExactPlan &plan, bool f32, const void *vals, const int32_t *idx,
+                        const void *dY, float *dW, char *ws, hipStream_t stream)
+{
+    return f32 ? run_exact<uint32_t>(p, plan, vals, idx, dY, dW, ws, stream)
+               : run_exact<uint16_t>(p, plan, vals, idx, dY, dW, ws, stream);
+}
+
+}  // namespace dropit

@@ -20,6 +20,8 @@
 // so dW is bit-reproducible.
 #include "common.hpp"
 #include "wgrad_internal.hpp"
+#include "recover.hpp"
+#include "splitk.hpp"
 #include "dev_hooks.hpp"
 #include <cstdlib>
 #include <type_traits>
@@ -31,68 +33,11 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 #define DROPIT_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define DROPIT_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-#ifndef DROPIT_RECOVER_CFG
-#define DROPIT_RECOVER_CFG 256, 16384
-#endif
-constexpr int recover_cfg[2] = {DROPIT_RECOVER_CFG};
-constexpr int RECOVER_THREADS = recover_cfg[0];
-// Dense elements one recover workgroup builds in LDS.  Small tiles keep many workgroups resident
-// per compute unit, which hides the latency of each one's search; rows wider than that get the
-// large tile (64 KB of LDS), rows wider than the large tile take the generic path.
-constexpr int RECOVER_ELEMS = recover_cfg[1];
-constexpr int RECOVER_ELEMS_MAX = 32768;
-
-// ---------------------------------------------------------------------------
-// Recover R(a^): workgroup b owns rows [b * rows_per_wg, ...) of the padded dense
-// matrix.  Its pairs are one contiguous run of the index-sorted arrays (found by
-// search), so the rows are assembled in LDS (zero fill, one 16-bit store per pair)
-// and leave as full 16-byte stores: every byte of the dense matrix is written exactly
-// once, no separate zero-fill pass.
-// The pairs come through for_pairs_in_range: a window around the interpolated positions of the
-// rows' first and last flat index, one round of loads, with the exact search as the fallback.
-constexpr int RECOVER_WINDOW = 28;                    // window entries per thread, at most
-
-// (The host uses fc_recover_stream_kernel instead when the window would be several times the pairs a
-// workgroup needs.)
-__global__ void __launch_bounds__(RECOVER_THREADS)
-fc_recover_kernel(const uint16_t *__restrict__ vals, const int32_t *__restrict__ idx, int64_t k, int64_t ntok,
-                  int64_t ntok_pad, int cin, int pitch, int rows_per_wg, int64_t margin, uint16_t *__restrict__ dense)
-{
-    extern __shared__ __attribute__((aligned(16))) uint16_t tile[];   // [rows_per_wg][pitch]
-    const int tid = threadIdx.x;
-    const int64_t r0 = int64_t(blockIdx.x) * rows_per_wg;
-    const int64_t r1 = min(r0 + rows_per_wg, ntok_pad);
-    const int rows = int(r1 - r0);
-    const int chunks = rows * (pitch / 8);                            // 16-byte units
-    u32x4 *tile16 = reinterpret_cast<u32x4 *>(tile);
-    const int64_t first = min(r0, ntok) * cin, last = min(r1, ntok) * cin;   // flat index range of these rows
-    const uint32_t span = uint32_t(last - first);
-    const int64_t numel = ntok * cin;
-    auto place = [&](int32_t flat, uint32_t v) {
-        const uint32_t rel = uint32_t(int64_t(flat) - first);
-        if (rel >= span) return;                                      // not one of this workgroup's rows
-        uint32_t pos = rel;
-        if (pitch != cin) {
-            const uint32_t row = rel / uint32_t(cin);
-            pos = row * uint32_t(pitch) + (rel - row * uint32_t(cin));
-        }
-        tile[pos] = static_cast<uint16_t>(v);
-    };
-
-    for_pairs_in_range<RECOVER_THREADS, RECOVER_WINDOW>(vals, idx, k, numel, first, last, margin, place, [&] {
-        for (int i = tid; i < chunks; i += RECOVER_THREADS) tile16[i] = u32x4{0, 0, 0, 0};
-    });
-    __syncthreads();
-    u32x4 *out16 = reinterpret_cast<u32x4 *>(dense + r0 * pitch);
-    for (int i = tid; i < chunks; i += RECOVER_THREADS) out16[i] = tile16[i];
-}
 
 // Recover from the row form of the cache (16-bit positions within rows + row offsets): the offsets say
 // where a workgroup's rows start among the pairs, so there is nothing to guess or search, and a pair's
@@ -187,92 +132,6 @@ fc_recover_mask_kernel(const uint16_t *__restrict__ vals, const uint32_t *__rest
     }
     const u32x4 o = {out[0] | (out[1] << 16), out[2] | (out[3] << 16), out[4] | (out[5] << 16), out[6] | (out[7] << 16)};
     *reinterpret_cast<u32x4 *>(dense + e0) = o;
-}
-
-// Recover for large k: the error of the interpolated guess grows with sqrt(k) (and with the ties at
-// the threshold, which are all kept at the low-index end of the tensor), the pairs of a tile do not, so
-// a window per tile would be mostly overlap -- and an exact search per tile costs ~500 scattered probes
-// of the index array (measured: 15 of 33 us on a 38 M-element tensor).  Here a workgroup takes several
-// consecutive tiles, searches once for the start of its first one, and then walks the pair arrays
-// forward: a tile's pairs follow the previous tile's.  A tile is done when a batch of pairs ends with
-// an index beyond it.
-__global__ void __launch_bounds__(RECOVER_THREADS)
-fc_recover_stream_kernel(const uint16_t *__restrict__ vals, const int32_t *__restrict__ idx, int64_t k, int64_t ntok,
-                         int64_t ntok_pad, int cin, int pitch, int rows_per_tile, int tiles_per_wg,
-                         uint16_t *__restrict__ dense)
-{
-    extern __shared__ __attribute__((aligned(16))) uint16_t tile[];   // [rows_per_tile][pitch]
-    constexpr int NWAVES = RECOVER_THREADS / WAVE;
-    constexpr int BATCH = 8;
-    __shared__ uint32_t wave_taken[2][NWAVES];
-    const int tid = threadIdx.x;
-    u32x4 *tile16 = reinterpret_cast<u32x4 *>(tile);
-    const int64_t tiles = (ntok_pad + rows_per_tile - 1) / rows_per_tile;
-    const int64_t t_begin = int64_t(blockIdx.x) * tiles_per_wg, t_end = min(t_begin + tiles_per_wg, tiles);
-
-    int64_t pos, unused;
-    {
-        const int64_t start = min(t_begin * rows_per_tile, ntok) * cin;
-        block_lower_bound2<RECOVER_THREADS>(idx, start, start, 0, k, 0, k, pos, unused);
-    }
-    int32_t pi[BATCH];
-    uint32_t pv[BATCH];             // a full register each (16-bit destinations get packed and the loads serialised)
-    auto load_batch = [&]() {       // the pairs at pos, pos + 1, ... : BATCH per thread, all loads in flight together
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int64_t j = pos + int64_t(u) * RECOVER_THREADS + tid;
-            if (j < k) {
-                pi[u] = idx[j];
-                pv[u] = vals[j];
-            }
-        }
-    };
-    load_batch();
-    uint32_t parity = 0;
-    for (int64_t t = t_begin; t < t_end; ++t) {
-        const int64_t r0 = t * rows_per_tile, r1 = min(r0 + rows_per_tile, ntok_pad);
-        const int chunks = int(r1 - r0) * (pitch / 8);                // 16-byte units
-        const int64_t first = min(r0, ntok) * cin, last = min(r1, ntok) * cin;
-        const uint32_t span = uint32_t(last - first);
-        for (int i = tid; i < chunks; i += RECOVER_THREADS) tile16[i] = u32x4{0, 0, 0, 0};
-        __syncthreads();
-        for (;;) {
-            uint32_t mine = 0;
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int64_t j = pos + int64_t(u) * RECOVER_THREADS + tid;
-                if (j < k && int64_t(pi[u]) < last) {
-                    ++mine;
-                    const uint32_t rel = uint32_t(int64_t(pi[u]) - first);
-                    if (rel < span) {                                 // always, for a sorted index array
-                        uint32_t at = rel;
-                        if (pitch != cin) {
-                            const uint32_t row = rel / uint32_t(cin);
-                            at = row * uint32_t(pitch) + (rel - row * uint32_t(cin));
-                        }
-                        tile[at] = static_cast<uint16_t>(pv[u]);
-                    }
-                }
-            }
-            mine = wave_sum(mine);
-            if ((tid & (WAVE - 1)) == 0) wave_taken[parity][tid / WAVE] = mine;
-            __syncthreads();                                           // also: this batch's scatter is complete
-            uint32_t taken = 0;
-#pragma unroll
-            for (int w = 0; w < NWAVES; ++w) taken += wave_taken[parity][w];
-            parity ^= 1u;
-            const int64_t loaded = min<int64_t>(int64_t(BATCH) * RECOVER_THREADS, k - pos);
-            pos += taken;
-            // The next pairs are fetched right away: more of this tile if the batch lay wholly inside
-            // it, else the start of the next tile, whose loads then overlap this tile's write-out.
-            const bool more = int64_t(taken) == loaded && pos < k;
-            if (more || t + 1 < t_end) load_batch();
-            if (!more) break;
-        }
-        u32x4 *out16 = reinterpret_cast<u32x4 *>(dense + r0 * pitch);
-        for (int i = tid; i < chunks; i += RECOVER_THREADS) out16[i] = tile16[i];
-        __syncthreads();                                               // tile read before the next one is zeroed
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -847,92 +706,6 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
     }
 }
 
-// Sums the split-K partials in ascending split order, dW = ((p0 + p1) + p2) + ..., and moves
-// them from the accumulator order the GEMM wrote (see its epilogue) to row-major dW.
-// One thread per 4 accumulator floats: rows m .. m+3 of one column.
-template <typename C>
-__global__ void __launch_bounds__(256)
-splitk_sum_kernel(const f32x4 *__restrict__ partial, int splits, int M, int N, int nb_count, int mb_count,
-                  float *__restrict__ dW)
-{
-    constexpr int TILE4 = C::BM * C::BN / 4;            // float4 groups per tile
-    const int64_t tiles = int64_t(nb_count) * mb_count;
-    const int64_t total = tiles * TILE4;
-    for (int64_t g = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; g < total; g += int64_t(gridDim.x) * blockDim.x) {
-        // eight slices at a time: all their loads are issued before the first add
-        f32x4 s = partial[g];
-        for (int p0 = 1; p0 < splits; p0 += 8) {
-            f32x4 part[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (p0 + u < splits) part[u] = partial[(p0 + u) * total + g];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (p0 + u < splits) s += part[u];
-        }
-        const int tile = int(g / TILE4), r = int(g % TILE4);
-        const int tid = r % C::NTHREADS, slot = r / C::NTHREADS;   // slot = (i * FN + j) * 4 + q
-        const int q = slot & 3, j = (slot >> 2) % C::FN, i = (slot >> 2) / C::FN;
-        const int lane = tid & 63, wave = tid >> 6;
-        const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-        const int mb = tile / nb_count, nb = tile % nb_count;
-        const int m = mb * C::BM + wm * C::WM + i * 32 + q * 8 + (lane >> 5) * 4;
-        const int n = nb * C::BN + wn * C::WN + j * 32 + (lane & 31);
-        if (n < N) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (m + e < M) dW[int64_t(m + e) * N + n] = s[e];
-        }
-    }
-}
-
-// The same sum for many slices of few tiles (a result of one or two tiles is cut into up to 256 slices, one
-// per compute unit): 16 threads share an output group, thread p of them adds the slices p, p + 16, ... in
-// ascending order, and the 16 sums are added in ascending p through LDS -- a fixed order again, with 16
-// times the loads in flight (one thread per group took 20 us for 256 slices of a single tile).
-template <typename C>
-__global__ void __launch_bounds__(256)
-splitk_sum_wide_kernel(const f32x4 *__restrict__ partial, int splits, int M, int N, int nb_count, int mb_count,
-                       float *__restrict__ dW)
-{
-    constexpr int PARTS = 16, GPB = 16;                // slice lanes per group, groups per workgroup
-    constexpr int TILE4 = C::BM * C::BN / 4;
-    __shared__ f32x4 red[PARTS][GPB];
-    const int64_t total = int64_t(nb_count) * mb_count * TILE4;
-    const int part = threadIdx.x / GPB, gi = threadIdx.x % GPB;
-    const int64_t g = int64_t(blockIdx.x) * GPB + gi;
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    if (g < total) {
-        for (int p0 = part; p0 < splits; p0 += 4 * PARTS) {
-            f32x4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (p0 + u * PARTS < splits) v[u] = partial[(p0 + u * PARTS) * total + g];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (p0 + u * PARTS < splits) s += v[u];
-        }
-    }
-    red[part][gi] = s;
-    __syncthreads();
-    if (part != 0 || g >= total) return;
-#pragma unroll
-    for (int q = 1; q < PARTS; ++q) s += red[q][gi];
-    const int tile = int(g / TILE4), r = int(g % TILE4);
-    const int tid = r % C::NTHREADS, slot = r / C::NTHREADS;   // slot = (i * FN + j) * 4 + q
-    const int q = slot & 3, j = (slot >> 2) % C::FN, i = (slot >> 2) / C::FN;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-    const int mb = tile / nb_count, nb = tile % nb_count;
-    const int m = mb * C::BM + wm * C::WM + i * 32 + q * 8 + (lane >> 5) * 4;
-    const int n = nb * C::BN + wn * C::WN + j * 32 + (lane & 31);
-    if (n < N) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (m + e < M) dW[int64_t(m + e) * N + n] = s[e];
-    }
-}
-
 // Prep of the in-LDS form: the pairs of token block kb (pairs [kb_ptr[kb], kb_ptr[kb + 1]), in index order, that
 // is by row and then by column) are regrouped by column block of 256 as the words the product consumes, and the
 // table of where each (token block, column block) tile starts is written.  In index order the pairs of one
@@ -1122,10 +895,10 @@ static bool fc_dense_attributes()
 {
     static std::atomic<uint64_t> attr_set{0};
     return once_per_device(attr_set, [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_recover_kernel),
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_recover_kernel<uint16_t>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    RECOVER_ELEMS_MAX * 2) == hipSuccess &&
-               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_recover_stream_kernel),
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_recover_stream_kernel<uint16_t>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    RECOVER_ELEMS_MAX * 2) == hipSuccess &&
                hipFuncSetAttribute(reinterpret_cast<const void *>(fc_recover_rows_kernel),
@@ -1155,18 +928,8 @@ static dropit_status launch_gemm(const FcProblem &p, const FcDensePlan &plan, co
         plan.mb_count, plan.nkb, plan.splits, out, packed, tile_ptr, uint32_t(std::max<int64_t>(p.k, 1)));
 
     trace_mark(stream);
-    if (plan.splits > 1) {
-        const int64_t groups = int64_t(plan.nb_count) * plan.mb_count * (C::BM * C::BN / 4);
-        if (plan.splits > 16) {
-            splitk_sum_wide_kernel<C><<<int((groups + 15) / 16), 256, 0, stream>>>(
-                reinterpret_cast<const f32x4 *>(partial), plan.splits, int(p.cout), int(p.cin), plan.nb_count,
-                plan.mb_count, dW);
-        } else {
-            const int blocks = int(std::min<int64_t>((groups + 255) / 256, 1 << 20));   // one group per thread
-            splitk_sum_kernel<C><<<blocks, 256, 0, stream>>>(reinterpret_cast<const f32x4 *>(partial), plan.splits,
-                                                             int(p.cout), int(p.cin), plan.nb_count, plan.mb_count, dW);
-        }
-    }
+    if (plan.splits > 1)
+        launch_splitk_sum<C>(partial, plan.splits, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count, dW, stream);
     trace_mark(stream);
     return launch_status();
 }
@@ -1185,31 +948,11 @@ dropit_status fc_dense_run(const FcProblem &p, const FcDensePlan &plan, const vo
 {
     uint16_t *dense = reinterpret_cast<uint16_t *>(ws);
     float *partial = reinterpret_cast<float *>(ws + plan.dense_bytes);
-    const int64_t ntok_pad = plan.ntok_pad;
     if (!fc_dense_attributes() || plan.fused) return DROPIT_EHIP;
 
     trace_mark(stream);
-    const int recover_grid = int((ntok_pad + plan.rows_per_wg - 1) / plan.rows_per_wg);
-    const size_t recover_lds = size_t(plan.rows_per_wg) * plan.pitch * 2;
-    // half-width of the window of pairs a recover workgroup loads around its interpolated positions:
-    // 4 standard deviations of an evenly spread selection (sqrt(k)/2 at worst) plus a little
-    const int64_t margin = 2 * static_cast<int64_t>(__builtin_sqrt(static_cast<double>(p.k))) + 256;
-    const double pairs_per_wg = static_cast<double>(p.k) * plan.rows_per_wg / static_cast<double>(std::max<int64_t>(p.ntok, 1));
-    bool windowed = pairs_per_wg + 2.0 * margin <= double(RECOVER_WINDOW) * RECOVER_THREADS;
-    if (dev_env("DROPIT_RECOVER_STREAM", 0)) windowed = false;
-    if (windowed) {
-        fc_recover_kernel<<<recover_grid, RECOVER_THREADS, recover_lds, stream>>>(
-            static_cast<const uint16_t *>(vals), idx, p.k, p.ntok, ntok_pad, int(p.cin), plan.pitch, plan.rows_per_wg,
-            margin, dense);
-    } else {
-        // several consecutive tiles per workgroup, about two workgroups per compute unit (measured best of 1, 2, 4, 8)
-        const int tiles_per_wg = std::max(1, (recover_grid + 511) / 512);
-        const int grid = (recover_grid + tiles_per_wg - 1) / tiles_per_wg;
-        fc_recover_stream_kernel<<<grid, RECOVER_THREADS, recover_lds, stream>>>(
-            static_cast<const uint16_t *>(vals), idx, p.k, p.ntok, ntok_pad, int(p.cin), plan.pitch, plan.rows_per_wg,
-            tiles_per_wg, dense);
-    }
-
+    launch_recover<uint16_t>(static_cast<const uint16_t *>(vals), idx, p.k, p.ntok * p.cin, p.ntok, plan.ntok_pad, int(p.cin),
+                             plan.pitch, plan.rows_per_wg, dense, stream);
     trace_mark(stream);
     return fc_dense_gemm(p, plan, dY, dense, partial, dW, stream);
 }

@@ -147,4 +147,20 @@ ConvIm2colPlan conv_im2col_plan(const ConvGeneral &p);
 dropit_status conv_im2col_run(const ConvGeneral &p, const ConvIm2colPlan &plan, const void *vals, const int32_t *idx,
                               const void *dY, float *dW, char *ws, hipStream_t stream);
 
+// Exact fp32 products of any shape, geometry and layout, fp32 or bf16 (wgrad_exact.hip)
+struct ExactProblem {
+    bool conv, nhwc;
+    int64_t numel, ntok, cin, cout, k;         // cin: columns of dW (C * kh * kw for a convolution), ntok: output positions
+    int64_t C, H, W, OH, OW;                   // convolution only
+    dropit_conv2d g;
+};
+struct ExactPlan {
+    int bm, bn, nb_count, mb_count, nkb, splits;
+    size_t dense_bytes, partial_bytes;
+    size_t total() const { return dense_bytes + partial_bytes; }
+};
+ExactPlan exact_plan(const ExactProblem &p, bool f32);
+dropit_status exact_run(const ExactProblem &p, const ExactPlan &plan, bool f32, const void *vals, const int32_t *idx,
+                        const void *dY, float *dW, char *ws, hipStream_t stream);
+
 }  // namespace dropit
