@@ -101,7 +101,7 @@ dropit_status dropit_compress(const void *x, const int64_t *shape, int ndim, dro
 /*
  * dropit_compress without a workspace argument, for callers that cannot allocate device memory
  * and have none to spare: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  The select's exchange area (about 170 KB, independent of the tensor size)
+ * forbid hipMalloc.  The select's exchange area (about 200 KB, independent of the tensor size)
  * is a static device array inside the library, one copy per GPU, held until the process ends.
  * The call itself allocates and frees nothing, on the device or through any library.
  *

@@ -20,14 +20,21 @@
 // bf16: 11 + 4 bits (one hist pass); fp32: 13 + 13 + 5 bits (two hist passes).
 //
 // Default: ONE persistent kernel (select_fused_kernel) does all of it with grid
-// barriers between the steps, the chunk parked in LDS, and a serial redo path
-// should the barriers ever give up.  For large 16-bit tensors it predicts the
-// first digit from a sample of the tensor and lets the count pass, which is
-// exact, confirm the prediction (see "sampled first digit" below); the bytes
-// it writes are the same either way.  Alternative: the steps as separate kernels
+// barriers between the steps, and a serial redo path should the barriers ever give
+// up.  For 16-bit tensors it predicts the range of the threshold from a sample and
+// stages every element that can still be kept in LDS during its one pass over the
+// tensor (see "sampled first digit" and "one read of x" below); the counts are exact,
+// so a wrong prediction is noticed and repaired, and the bytes it writes are the same
+// either way.  fp32 builds the digit histograms.  Alternative: the steps as separate kernels
 // (init, hist, count, compact) with a last-workgroup-to-arrive ticket instead of
 // barriers.  Nothing here synchronises with the host; counts are integer, so the
 // result does not depend on the order in which workgroups run.
+//
+// Measured, whole call in a queue of calls on rotating inputs, with the earlier form of the persistent kernel (every
+// workgroup's exit report behind its output stores; two-level barrier counters; candidates turned through LDS; the whole
+// chunk read again where a segment overflowed) -> now:
+//   bf16 0.6 M elements 17.7 -> 12.7 us, 3.2 M 22 -> 16.0, 9.7 M 26.3 -> 20.3, 50 M (gamma 0.9) 53.8 -> 44.4,
+//   39 M (gamma 0.8) 78.7 -> 48, 51 M (gamma 0.8) 93.6 -> 65.
 #include "common.hpp"
 #include "dev_hooks.hpp"
 #include <atomic>
@@ -42,7 +49,8 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_MAX_CHUNKS = 512;
 constexpr int SEL_UNROLL = 4;
 constexpr int MAX_HIST_BITS = 13;
-constexpr int MAX_LAST_BINS = 48;       // rows of the per-chunk table: up to three 16-key bins of a sampled bracket, else 2^LAST_BITS
+constexpr int MAX_LAST_BINS = 56;       // keys of the range in the per-chunk table: up to seven 8-key bins of a sampled bracket, else 2^LAST_BITS
+constexpr int TABLE_PITCH = 64;         // words per chunk in the persistent kernel's table: the range's keys, the keys above it, padding to whole lines
 
 struct SelState {
     uint32_t prefix;     // key digits resolved so far (key >> remaining bits)
@@ -50,18 +58,20 @@ struct SelState {
     uint32_t t;          // threshold key (valid after the count pass)
     uint32_t m;          // how many keys equal to t are kept (lowest flat index first)
     uint32_t ticket[4];  // arrival counters, one per pass
-    uint32_t barrier;    // arrivals at the fused kernel's grid barriers (monotone within a call)
+    uint32_t unused;
     uint32_t error;      // hint: some workgroup ran out of patience at a grid barrier (the others stop waiting)
-    uint32_t exited;     // fused kernel: low 16 bits = workgroups done, high 16 bits = how many of them gave up
-    uint32_t path;       // fused kernel, for the tests: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry)
+    uint32_t exited;     // fused kernel: low 16 bits = workgroups past their last grid barrier or gone, high 16 bits = how many gave up
+    uint32_t path;       // fused kernel, for the tests: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry); 16-bit tensors of SAMPLE_LARGE elements or more
     unsigned long long ready;    // == the call's generation number once workgroup 0 has cleared the words above and the histograms;
                                  // the last workgroup to leave puts 0 back (no generation is 0), so a launch replayed with
                                  // the same number (a captured graph) waits for its own workgroup 0 again
     uint32_t redo;       // fused kernel, for callers and tests: 1 if the grid barriers gave up and the last workgroup redid the selection alone
     uint32_t staged;     // fused kernel, for the tests: how many workgroups compacted from candidates staged in LDS (one read of x)
-    uint32_t pad[48];
+    unsigned long long ready_hist;   // 16-bit types: the same for the digit histogram, which only the exact form needs
+    uint32_t pad[46];
 };
 static_assert(sizeof(SelState) == 256, "state block is 256 bytes");
+static_assert(MAX_LAST_BINS + 1 <= TABLE_PITCH && TABLE_PITCH == WAVE, "a lane per word of a chunk's line");
 
 // Workspace carving (in bytes from the 256-byte aligned base).
 struct SelWorkspace {
@@ -69,7 +79,7 @@ struct SelWorkspace {
     static constexpr size_t hist0_off = state_off + sizeof(SelState);
     static constexpr size_t hist1_off = hist0_off + sizeof(uint32_t) * (1u << MAX_HIST_BITS);
     static constexpr size_t table_off = hist1_off + sizeof(uint32_t) * (1u << MAX_HIST_BITS);
-    static constexpr size_t offgt_off = table_off + sizeof(uint32_t) * (MAX_LAST_BINS + 1) * SEL_MAX_CHUNKS;
+    static constexpr size_t offgt_off = table_off + sizeof(uint32_t) * TABLE_PITCH * SEL_MAX_CHUNKS;
     static constexpr size_t offeq_off = offgt_off + sizeof(uint32_t) * SEL_MAX_CHUNKS;
     static constexpr size_t xbar_off = offeq_off + sizeof(uint32_t) * SEL_MAX_CHUNKS;   // 8 arrival counters, 256 B apart
     static constexpr size_t bytes = xbar_off + 8 * 256;
@@ -456,31 +466,128 @@ __device__ inline void dev_store64(unsigned long long *p, unsigned long long v)
 }
 
 // All workgroups of the grid meet here (`round` = 1, 2, ... counts the barriers of the call).
-// Arrival is two-level: a workgroup bumps the counter of its group (launch order modulo 8, counters
-// 256 bytes apart), the last of a group bumps the top counter, everybody polls the top counter;
-// 256 atomics on ONE word take ~10 ns each, one after the other.
+// A workgroup bumps the counter of its group (launch order modulo 8, counters 256 bytes apart: 256 atomics on ONE
+// word take ~10 ns each, one after the other) and its first wavefront polls all eight with one load (eight lanes, a
+// counter each): one atomic and one load of latency, where a top counter bumped by the last of each group costs
+// another atomic's round trip.  The first poll waits until the arrivals are through (they would queue behind it).
+// 256 workgroups arriving together: 1.1 us, against 2.1 with the top counter and 1.9 with the first poll at once.
 // The grid is sized so that every workgroup is resident at once, but nothing enforces that the
 // device is not shared, so the wait is bounded: returns false (in every thread of the workgroup)
 // if the others did not all arrive within `spin_limit` polls or if some workgroup already gave
 // up.  The caller then skips to the kernel's exit protocol.
-// __syncthreads() makes every wave wait for its own outstanding atomics first.
+// Every wavefront first waits for its own outstanding stores and atomics (a workgroup barrier alone orders LDS only).
 __device__ inline bool grid_barrier(SelState *st, uint32_t *xbar, uint32_t round, uint32_t spin_limit, uint32_t *ok_slot)
 {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t G = gridDim.x, group = blockIdx.x & 7u;
-        const uint32_t groups = G < 8u ? G : 8u, members = (G - group + 7u) / 8u;
-        const uint32_t before = __hip_atomic_fetch_add(&xbar[group * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (before + 1 == round * members)
-            __hip_atomic_fetch_add(&st->barrier, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < WAVE) {
+        const uint32_t G = gridDim.x, lane = threadIdx.x;
+        if (lane == 0)
+            __hip_atomic_fetch_add(&xbar[(blockIdx.x & 7u) * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_sleep(16);           // ~0.5 us
+        const uint32_t goal = lane < 8u && lane < G ? round * ((G - lane + 7u) / 8u) : 0u;    // arrivals of group `lane`
         uint32_t spins = 0, ok = 1;
-        while (dev_load(&st->barrier) < round * groups) {
+        for (;;) {
+            const bool short_of = goal != 0u && dev_load(&xbar[lane * 64]) < goal;
+            if (__ballot(short_of) == 0ull) break;
             if (++spins > spin_limit || ((spins & 31u) == 0 && dev_load(&st->error) != 0)) {
-                dev_store(&st->error, 1u);
+                if (lane == 0) dev_store(&st->error, 1u);
                 ok = 0;
                 break;
             }
-            __builtin_amdgcn_s_sleep(8);        // ~0.2 us between polls: 256 pollers on one word compete with the arrivals
+            __builtin_amdgcn_s_sleep(8);        // 256 pollers compete with the arrivals
+        }
+        if (lane == 0) *ok_slot = ok;
+    }
+    __syncthreads();
+    return *ok_slot != 0;
+}
+
+// How a workgroup says that no grid barrier is ahead of it any more: an atomic on its group's report counter, sent right
+// after the last barrier, behind the loads of the table; the last of a group passes the
+// group's count on to the common word when it leaves (while its last output stores are on their way).  (One atomic per workgroup on
+// one word, sent on leaving behind the output stores, held every workgroup back by 3 to 6 us; sent after the barrier,
+// 256 of them slowed the table reads down by a microsecond.)
+// A report is 1, or 0x10001 from a workgroup that gave up: the high half counts those.
+constexpr int REPORT_TID = SEL_THREADS - WAVE;      // lane 0 of the last wavefront
+struct ExitReport {
+    uint32_t mine;          // the report, 0 while none has been sent (uniform over the workgroup)
+    uint32_t before;        // thread REPORT_TID: the counter before it.  Not touched until report_group: the wait for the
+                            // atomic's answer goes where its value is first used
+    uint32_t group;         // thread REPORT_TID: what the workgroup added to the common word, 0 if it is not the last of its group
+    uint32_t common;        // thread REPORT_TID: the common word before that
+};
+__device__ inline uint32_t *opaque(uint32_t *p)
+{
+    uint32_t zero = 0;      // (an address known to be uniform would be turned into a wavefront reduction, which waits for the answer)
+    asm volatile("" : "+v"(zero));
+    return p + zero;
+}
+__device__ inline void report_past_barriers(uint32_t *xbar, ExitReport &rep, bool gave_up)
+{
+    rep.mine = gave_up ? 0x10001u : 1u;
+    rep.group = 0u;
+    if (threadIdx.x == REPORT_TID)
+        rep.before = __hip_atomic_fetch_add(opaque(xbar + (blockIdx.x & 7u) * 64 + 32), rep.mine, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void report_group(SelState *st, ExitReport &rep)
+{
+    if (threadIdx.x == REPORT_TID) {
+        const uint32_t seen = rep.before + rep.mine, members = (gridDim.x - (blockIdx.x & 7u) + 7u) / 8u;
+        if ((seen & 0xFFFFu) == members) {
+            rep.group = seen;
+            rep.common = __hip_atomic_fetch_add(opaque(&st->exited), seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
+// Workgroup 0 clears what the workgroups exchange through (barrier counters and state words, histograms) and then publishes
+// this call's generation number; the others look for it before their first global atomic.  No separate clearing kernel, and
+// a workspace with arbitrary contents is fine: a stale word equals the generation (a per-process random number plus a
+// call count) with probability 2^-64.  Device-scope atomics, like everything else that is exchanged.
+// clear_words: the counters and state words, by the last wavefront of workgroup 0 and with an exchange instead of a store: its
+// answer says when it is done, without a wait for the loads that have been issued since.  `done` is that answer.
+__device__ inline void clear_words(SelState *st, uint32_t *xbar, uint32_t &done)
+{
+    const int i = static_cast<int>(threadIdx.x) - REPORT_TID;
+    if (i >= 0 && i < 20) {
+        uint32_t *w = i < 16 ? xbar + i * 32 : i == 16 ? &st->error : i == 17 ? &st->exited : i == 18 ? &st->redo : &st->staged;
+        done = __hip_atomic_exchange(w, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+__device__ inline void publish_words(SelState *st, uint32_t done, unsigned long long gen)
+{
+    if (threadIdx.x >= REPORT_TID) {
+        asm volatile("" ::"v"(done));               // (the compiler waits for the answer here; it is the wavefront's, hence all lanes')
+        if (threadIdx.x == REPORT_TID) dev_store64(&st->ready, gen);
+    }
+}
+// the digit histograms: stores by the whole workgroup, published once they are done
+__device__ inline void clear_hist(uint32_t *hist, int words)
+{
+    for (int i = threadIdx.x; i < words; i += SEL_THREADS) dev_store(hist + i, 0u);
+}
+__device__ inline void publish_hist(unsigned long long *ready, unsigned long long gen)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                // every wavefront's stores are done
+    if (threadIdx.x == 0) dev_store64(ready, gen);
+}
+
+// Waits until `ready` holds this call's generation number (`seen`: what thread 0 has already read there).  False (in every
+// thread) if that never happens.
+__device__ inline bool wait_published(const unsigned long long *ready, unsigned long long gen, unsigned long long seen, uint32_t *ok_slot)
+{
+    if (threadIdx.x == 0) {
+        uint32_t spins = 0, ok = 1;
+        while (seen != gen) {
+            if (++spins > READY_SPIN_LIMIT) {      // workgroup 0 never ran: not this workgroup's patience setting
+                ok = 0;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            seen = dev_load64(ready);
         }
         *ok_slot = ok;
     }
@@ -529,34 +636,39 @@ __device__ inline void resolve_digit_local(const uint32_t *hist, uint32_t &prefi
 // LDS atomic unit of a compute unit takes ~16 cycles per wavefront instruction whatever it adds), then
 // a merge with global atomics, a grid barrier, and a read-back of the merged histogram.  The bin that
 // holds the k-th largest key can be predicted from a sample instead, and without any exchange: EVERY
-// workgroup reads the same 512 pieces of 64 bytes (one per equal stretch of the tensor, at a hashed
+// workgroup reads the same 512 pieces of 32 bytes (one per equal stretch of the tensor, at a hashed
 // position inside it -- many small pieces, so that values that come in runs, like the tokens of an
 // activation, do not fool it; served by the L2 caches after the first reader), histograms them in its own LDS and
-// derives the same bracket of up to three adjacent bins around the sample's quantile, wide enough for
-// 5 standard deviations of the sampling error.  The bracket is only a prediction: the pass over all
+// derives the same bracket of up to seven adjacent 8-key bins around the sample's quantile, wide enough for
+// 5 standard deviations of the sampling error.  (8192 elements: twice as many narrow the bracket by a third of its
+// width and cost another microsecond of LDS atomics.)  The bracket is only a prediction: the pass over all
 // elements that follows counts exactly how many keys lie above the bracket and how many on each key
 // inside it, so a bracket that does not contain the k-th largest key is detected, and the selection
 // then runs with the exact histogram.  The result is the same in every case; only the time differs.
-constexpr int SAMPLE_VECTORS_PER_THREAD = 2;          // x 1024 threads x 8 elements = 16 384 sampled elements
-constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 21; // below this the exact histogram is cheap
-constexpr int BRACKET_MAX_BINS = 3;
+constexpr int SAMPLE_PIECES = 512;
+constexpr int SAMPLE_STRETCH = 4;                     // a piece starts at a multiple of this many vectors (64 bytes) ...
+constexpr int SAMPLE_PIECE = SEL_THREADS / SAMPLE_PIECES;   // ... and is this many vectors long: one vector per thread
+constexpr int SAMPLE_ELEMS = SEL_THREADS * 8;
+constexpr int64_t SAMPLE_LARGE = int64_t(1) << 21;    // from here on the state block says how the prediction went
+constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 16;
+static_assert(SAMPLE_MIN_NUMEL / 8 / SAMPLE_STRETCH >= SAMPLE_PIECES, "a place per stretch at least");
+constexpr int SAMPLE_SHIFT = 3, SAMPLE_BINS = 1 << (15 - SAMPLE_SHIFT);    // 8 keys per bin
+constexpr int BRACKET_MAX_BINS = MAX_LAST_BINS >> SAMPLE_SHIFT;
 
-constexpr int SAMPLE_PIECE = 4;                       // vectors per sampled piece (64 bytes: four lanes share a cache line)
-
-// First vector of sample piece i of n: stretch i of the tensor, hashed offset inside it (whole pieces).
-__device__ inline int64_t sample_piece(int i, int n, int64_t nvf)
+// First vector of sample piece i: stretch i of the tensor, hashed offset inside it.
+__device__ inline int64_t sample_piece(int i, int64_t nvf)
 {
-    const int64_t seg = (nvf / SAMPLE_PIECE) / n;                     // pieces per stretch
+    const uint32_t seg = static_cast<uint32_t>((nvf / SAMPLE_STRETCH) / SAMPLE_PIECES);   // possible places per stretch
     const uint32_t h = (static_cast<uint32_t>(i) + 1u) * 0x9E3779B1u;
-    return (int64_t(i) * seg + static_cast<int64_t>((h >> 8) % static_cast<uint32_t>(seg))) * SAMPLE_PIECE;
+    return (int64_t(i) * seg + static_cast<int64_t>((h >> 8) % seg)) * SAMPLE_STRETCH;
 }
 
-// From the sample's histogram (in LDS): the bins that hold the sample ranks r - margin and r + margin,
-// r = the sample's share of k.  Returns false (in every thread) if there is no usable bracket (a
-// quantile too close to either end of the sample, more than BRACKET_MAX_BINS bins).
+// From the sample's histogram (in LDS; bin 0 -- exact zeros -- is not counted): the bins that hold the sample ranks
+// r - margin and r + margin, r = the sample's share of k.  Returns false (in every thread) if there is no usable
+// bracket (a quantile too close to either end of the sample or among the zeros, more than BRACKET_MAX_BINS bins).
 template <int NB>
 __device__ inline bool sample_bracket(const uint32_t *hist, uint32_t k, int64_t numel, uint32_t *wave_tot,
-                                      uint32_t *bcast /*[3]*/, uint32_t &b_lo, uint32_t &b_hi)
+                                      uint32_t *bcast /*[2]*/, uint32_t &b_lo, uint32_t &b_hi)
 {
     constexpr int PER = (NB + SEL_THREADS - 1) / SEL_THREADS;
     const int tid = threadIdx.x;
@@ -568,15 +680,14 @@ __device__ inline bool sample_bracket(const uint32_t *hist, uint32_t k, int64_t 
         c[i] = (hi_bin - i >= 0) ? hist[hi_bin - i] : 0u;
         mine += c[i];
     }
+    if (tid < 2) bcast[tid] = 0xFFFFFFFFu;           // (ordered before the finders' stores by the scan's barriers)
     uint32_t total;
     const uint32_t above = block_exclusive_scan<SEL_THREADS>(mine, wave_tot, total);
     const float frac = static_cast<float>(k) / static_cast<float>(numel);
-    const float r = frac * static_cast<float>(total);
+    const float r = frac * static_cast<float>(SAMPLE_ELEMS);
     const float margin = 5.0f * __builtin_sqrtf(fmaxf(r * (1.0f - frac), 1.0f)) + 8.0f;
     const float lo_f = r - margin, hi_f = r + margin;
-    const bool usable = lo_f >= 1.0f && hi_f <= static_cast<float>(total) - 1.0f;
-    if (tid == 0) bcast[2] = usable ? 1u : 0u;
-    if (usable) {
+    if (lo_f >= 1.0f && hi_f <= static_cast<float>(SAMPLE_ELEMS) - 1.0f) {
         const uint32_t rank[2] = {static_cast<uint32_t>(lo_f), static_cast<uint32_t>(hi_f) + 1u};   // higher bin first
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -596,59 +707,114 @@ __device__ inline bool sample_bracket(const uint32_t *hist, uint32_t k, int64_t 
     __syncthreads();
     b_hi = bcast[0];
     b_lo = bcast[1];
-    const bool ok = bcast[2] != 0 && b_hi >= b_lo && b_hi - b_lo < static_cast<uint32_t>(BRACKET_MAX_BINS);
+    const bool ok = b_hi != 0xFFFFFFFFu && b_lo != 0xFFFFFFFFu && b_hi - b_lo < static_cast<uint32_t>(BRACKET_MAX_BINS);
     __syncthreads();
     return ok;
 }
 
-// ---- one read of x: candidates staged in LDS (16-bit element types, sampled bracket) ----------------
-// With the bracket [key_lo, key_lo + nf) known BEFORE the pass over the chunk, everything that can still
-// be kept is known too: the elements with key >= key_lo, a share of (1 - gamma) plus the bracket's width
-// (11-15 % at gamma = 0.9).  The pass therefore stages them in LDS, in flat-index order, as one word each
-// (value << 16 | position), and both the exact counts and the compaction then walk the staged words
-// instead of reading x again -- x is read from memory exactly once, whatever the tensor size.
-// Each wavefront owns a contiguous 1/16 of the chunk and a staging segment of its own, so the pass needs
-// no workgroup barrier: a wavefront loads ST_U x 64 vectors (coalesced), turns them through a private
-// LDS buffer so that every lane holds ST_U CONSECUTIVE vectors (flat order = lane order: one wavefront
-// scan of the per-lane candidate counts gives every candidate its slot), and copies the candidates out
-// of that buffer.  The buffer is padded by 16 bytes per 128 so that both the coalesced writes and the
-// 32-byte-per-lane reads are free of bank conflicts.
-// A chunk with more candidates than a segment holds (values that bunch up along the tensor; tensors
-// beyond ~110 MB) takes the two-read form below for that workgroup; the bytes written are the same.
-constexpr int ST_U = 2;                                    // vectors per lane per block
-constexpr int ST_BLKV = ST_U * WAVE;                       // vectors per block (1024 16-bit elements)
-constexpr int ST_EPL = ST_U * 8;                           // elements per lane per block
-constexpr int ST_TRANS_BYTES = ST_BLKV * 16 + (ST_BLKV / 8) * 16;
-constexpr int ST_LH_OFF = (SEL_THREADS / WAVE) * ST_TRANS_BYTES;
-constexpr int ST_STAGE_OFF = ST_LH_OFF + 256;
-constexpr size_t FUSED_SMEM_BYTES = 156 * 1024;            // of the 160 KB of a compute unit; the rest is static
-constexpr int ST_SEGCAP = int((FUSED_SMEM_BYTES - ST_STAGE_OFF) / 4 / (SEL_THREADS / WAVE));   // staged words per wavefront
-static_assert(ST_STAGE_OFF + 4 * ((1 << 11) + 2 * WAVE) <= int(FUSED_SMEM_BYTES), "the exact retry's histogram fits behind ST_LH_OFF");
-static_assert(ST_STAGE_OFF % 16 == 0 && ST_SEGCAP % 4 == 0, "staged words are read four at a time");
+typedef unsigned long long lane_mask;
+// number of set bits of the mask in the lanes before this one, plus base
+__device__ inline uint32_t bits_before(lane_mask a, uint32_t base)
+{
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(a >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(a), base));
+}
 
-// bit b of the result: element b of the ST_EPL consecutive 16-bit elements in r[] has key >= key_lo.
-// Per 32-bit word: one AND clears both signs, one unsigned compare per half (the upper half against
-// key_lo << 16: the lower half cannot change the outcome), and an add-with-carry shifts each outcome
-// into the mask; the elements are taken last to first so that element 0 ends in bit 0.
-__device__ inline uint32_t candidate_mask(const u32x4 (&r)[ST_U], uint32_t key_lo)
+// ---- one read of x: candidates staged in LDS (16-bit element types) ---------------------------------
+// With the range [key_lo, key_lo + nf) known BEFORE the pass over the chunk, everything that can still
+// be kept is known too: the elements with key >= key_lo, a share of (1 - gamma) plus the range's width
+// (12-15 % at gamma = 0.9).  The pass therefore stages them in LDS, in flat-index order, as one word each
+// (value << 16 | position), and both the exact counts and the compaction then walk the staged words
+// instead of reading x again.
+// Each wavefront owns a contiguous 1/16 of the chunk and a staging segment of its own, so the pass needs
+// no workgroup barrier.  It walks its range in rows of 64 vectors (a lane's vector is 8 consecutive elements, so
+// lane order is flat order), ST_ROWS of them in flight in registers: an 8-bit candidate mask per lane, one wavefront
+// scan of the counts of two rows packed into a word, then eight predicated LDS stores per row, each lane advancing its
+// slot where its bit is set.
+// When the segment is full the pass only counts; the rows that were not staged are read again once the threshold is
+// known, and go through the same segment after its first filling has been written out.
+constexpr int ST_ROWS = 4;                                 // rows in flight per wavefront
+constexpr int ST_ROW_ELEMS = WAVE * 8;
+constexpr int ST_SEGCAP = 1916;                            // staged words per wavefront: 16 segments are 122 KB
+constexpr int ST_LH_OFF = (SEL_THREADS / WAVE) * ST_SEGCAP * 4;
+constexpr size_t ST_SMEM_BYTES = ST_LH_OFF + 4 * size_t(SAMPLE_BINS);              // + the sample's or the digit's histogram
+static_assert(ST_LH_OFF % 16 == 0, "the histogram follows the segments");
+static_assert(ST_SEGCAP >= 2 * ST_ROW_ELEMS, "two rows of nothing but candidates fit an empty segment");
+static_assert(ST_SMEM_BYTES >= 4 * ((size_t(1) << 13) + 2 * WAVE), "the serial redo's histogram");
+static_assert(SAMPLE_BINS >= 2 * (SEL_THREADS / WAVE) * TABLE_PITCH, "the table's partial sums take the histogram's place");
+
+// Classification of the 8 consecutive 16-bit elements of q against a lowest key, five instructions per 32-bit word: one AND
+// clears both signs (keys[]), one unsigned compare per half (the upper half against lowest << 16: the lower half cannot
+// change the outcome), and an add-with-carry takes each outcome in.
+__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys)   // how many have key >= lowest
+{
+    uint32_t n = 0;
+    const uint32_t lo = lowest, hi = lowest << 16;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        uint32_t k;
+        const uint32_t word = q[w];
+        asm("v_and_b32 %1, 0x7fff7fff, %2\n\t"
+            "v_cmp_le_u32 vcc, %4, %1\n\t"
+            "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+            "v_cmp_le_u16 vcc, %3, %1\n\t"
+            "v_addc_co_u32 %0, vcc, 0, %0, vcc"
+            : "+v"(n), "=&v"(k)
+            : "v"(word), "s"(lo), "s"(hi)
+            : "vcc");
+        keys[w] = k;
+    }
+    return n;
+}
+__device__ inline uint32_t candidate_mask(const u32x4 &q, uint32_t lowest)                  // bit e: element e has key >= lowest
 {
     uint32_t mask = 0, k;
-    const uint32_t lo = key_lo, hi = key_lo << 16;
+    const uint32_t lo = lowest, hi = lowest << 16;
 #pragma unroll
-    for (int u = ST_U - 1; u >= 0; --u)
-#pragma unroll
-        for (int w = 3; w >= 0; --w) {
-            const uint32_t word = r[u][w];
-            asm("v_and_b32 %1, 0x7fff7fff, %2\n\t"
-                "v_cmp_le_u32 vcc, %4, %1\n\t"
-                "v_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-                "v_cmp_le_u16 vcc, %3, %1\n\t"
-                "v_addc_co_u32 %0, vcc, %0, %0, vcc"
-                : "+v"(mask), "=&v"(k)
-                : "v"(word), "s"(lo), "s"(hi)
-                : "vcc");
-        }
+    for (int w = 3; w >= 0; --w) {             // last to first: element 0 ends in bit 0
+        const uint32_t word = q[w];
+        asm("v_and_b32 %1, 0x7fff7fff, %2\n\t"
+            "v_cmp_le_u32 vcc, %4, %1\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+            "v_cmp_le_u16 vcc, %3, %1\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, vcc"
+            : "+v"(mask), "=&v"(k)
+            : "v"(word), "s"(lo), "s"(hi)
+            : "vcc");
+    }
     return mask;
+}
+// Stores the candidates of q, in the lanes of `valid`, as words value << 16 | position (pos, pos + 1, ...) from LDS byte
+// address `addr` on.  Per element: the comparison goes straight into the execution mask, so that the store and the advance
+// of the address happen in the lanes whose element is a candidate.
+__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
+                                        uint32_t addr, uint32_t pos)
+{
+    uint32_t t;
+    unsigned long long saved;
+    const uint32_t lo = lowest, hi = lowest << 16, upper = 0xFFFF0000u;
+#define STAGE_WORD(W, K)                                   \
+    "v_cmpx_le_u16 vcc, %[lo], " K "\n\t"                  \
+    "v_lshl_or_b32 %[t], " W ", 16, %[pos]\n\t"            \
+    "ds_write_b32 %[addr], %[t]\n\t"                       \
+    "v_add_u32 %[addr], 4, %[addr]\n\t"                    \
+    "s_mov_b64 exec, %[valid]\n\t"                         \
+    "v_add_u32 %[pos], 1, %[pos]\n\t"                      \
+    "v_cmpx_le_u32 vcc, %[hi], " K "\n\t"                  \
+    "v_and_or_b32 %[t], " W ", %[upper], %[pos]\n\t"       \
+    "ds_write_b32 %[addr], %[t]\n\t"                       \
+    "v_add_u32 %[addr], 4, %[addr]\n\t"                    \
+    "s_mov_b64 exec, %[valid]\n\t"                         \
+    "v_add_u32 %[pos], 1, %[pos]\n\t"
+    asm volatile("s_mov_b64 %[saved], exec\n\t"
+                 "s_mov_b64 exec, %[valid]\n\t"
+                 STAGE_WORD("%[q0]", "%[k0]") STAGE_WORD("%[q1]", "%[k1]") STAGE_WORD("%[q2]", "%[k2]") STAGE_WORD("%[q3]", "%[k3]")
+                 "s_mov_b64 exec, %[saved]\n\t"
+                 "s_nop 4"                      // (cross-lane operations must not follow a vector write of the mask closely)
+                 : [addr] "+&v"(addr), [pos] "+&v"(pos), [t] "=&v"(t), [saved] "=&s"(saved)
+                 : [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [k0] "v"(keys[0]), [k1] "v"(keys[1]),
+                   [k2] "v"(keys[2]), [k3] "v"(keys[3]), [lo] "s"(lo), [hi] "s"(hi), [upper] "s"(upper), [valid] "s"(valid)
+                 : "vcc", "memory");
+#undef STAGE_WORD
 }
 
 // The parallel selection.  Returns (the same in every thread) SEL_DONE, or SEL_GAVE_UP if a grid
@@ -656,160 +822,452 @@ __device__ inline uint32_t candidate_mask(const u32x4 (&r)[ST_U], uint32_t key_l
 // last two cases the outputs are incomplete (whatever was written is correct, nothing is out of bounds).
 enum SelOutcome { SEL_DONE = 0, SEL_GAVE_UP = 1, SEL_NEVER_READY = 2 };
 
-template <typename RAW>
-__device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
-                                         SelState *st, uint32_t *hist0, uint32_t *hist1, uint32_t *table,
-                                         RAW *__restrict__ vals, int32_t *__restrict__ idx, uint32_t spin_limit,
-                                         unsigned long long gen)
+// From the per-chunk table of a range of nf keys (a line of TABLE_PITCH words per chunk; word r < nf: the chunk's count of
+// key key_lo + r; word nf: of the keys above the range): the threshold t = the k-th largest key, the tie budget m, and the
+// counts of keys above t and equal to t in the chunks before this one.  A wavefront takes 16 chunks of every 256, a lane per
+// word, and adds them up for all chunks and for the chunks before this one; the wavefronts meet in LDS (`part`,
+// 2 * NW * TABLE_PITCH words).  False if the k-th key is not in the range.
+// (With a line per KEY a workgroup's 33 to 57 stores went to as many lines, each shared by 32 workgroups, and were
+// acknowledged a microsecond later; the sums over lanes cost a scan per row.)
+// The workgroup's report goes out behind the table loads.
+__device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_t key_lo, uint32_t k, uint32_t *part, uint32_t *bcast,
+                                     uint32_t *offs, uint32_t *verdict, uint32_t *xbar, ExitReport &rep)
 {
-    constexpr int VEC = KeyTraits<RAW>::VEC;
-    constexpr uint32_t MASK = KeyTraits<RAW>::MASK;
-    constexpr bool F32 = sizeof(RAW) == 4;
-    constexpr int BITS1 = F32 ? 13 : 11, SHIFT1 = F32 ? 18 : 4;   // first digit
-    constexpr int BITS2 = 13, SHIFT2 = 5;                         // second digit (fp32 only)
-    constexpr int LAST_BITS = F32 ? 5 : 4;
-    constexpr int LB = 1 << LAST_BITS;
+    constexpr int NW = SEL_THREADS / WAVE, PER = 16;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int G = gridDim.x, me = blockIdx.x;
+    uint32_t s = 0, sp = 0;
+    for (int c0 = wave * PER; c0 < G; c0 += NW * PER) {
+        uint32_t v[PER];
+        const uint32_t *line = table + c0 * TABLE_PITCH + lane;       // (the table has a line for every possible chunk)
+#pragma unroll
+        for (int j = 0; j < PER; ++j) v[j] = dev_load(line + j * TABLE_PITCH);
+        if (rep.mine == 0) report_past_barriers(xbar, rep, false);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            s += c0 + j < G ? v[j] : 0u;
+            sp += c0 + j < me ? v[j] : 0u;
+        }
+    }
+    if (rep.mine == 0) report_past_barriers(xbar, rep, false);         // (a wavefront without chunks)
+    part[wave * TABLE_PITCH + lane] = s;
+    part[(NW + wave) * TABLE_PITCH + lane] = sp;
+    __syncthreads();
+    if (tid < WAVE) {
+        // Lane 0 takes the keys above the range, lanes 1.. the range's keys in descending order, so a
+        // prefix scan over the lanes counts the keys above each key.  The k-th largest key is the one
+        // with  #above < k <= #above + #equal;  it is in the range iff that holds for a lane >= 1.
+        const int rr = static_cast<int>(nf) - lane;
+        uint32_t full = 0, before = 0;
+        if (rr >= 0) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                full += part[w * TABLE_PITCH + rr];
+                before += part[(NW + w) * TABLE_PITCH + rr];
+            }
+        }
+        const uint32_t incl = wave_inclusive_scan(full), incl_p = wave_inclusive_scan(before);
+        const bool here = lane >= 1 && rr >= 0 && incl - full < k && k <= incl;
+        const unsigned long long hit = __ballot(here);
+        if (lane == 0) *verdict = hit ? 1u : 0u;
+        if (here) {
+            bcast[0] = key_lo + static_cast<uint32_t>(rr);     // t
+            bcast[1] = k - (incl - full);                       // m: how many keys equal to t are kept
+            offs[0] = incl_p - before;                          // #{key > t} in the chunks before this one
+            offs[1] = before;                                   // #{key == t} there
+        }
+    }
+    __syncthreads();
+    return *verdict != 0;
+}
+
+// 16-bit element types.
+__device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
+                                           SelState *st, uint32_t *hist0, uint32_t *table, uint16_t *__restrict__ vals,
+                                           int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, ExitReport &rep)
+{
+    constexpr int VEC = 8;
+    constexpr uint32_t MASK = KeyTraits<uint16_t>::MASK;
+    constexpr int BITS1 = 11, SHIFT1 = 4, NB = 1 << BITS1;      // first digit; the last one has SHIFT1 bits
     constexpr int NW = SEL_THREADS / WAVE;
-    constexpr int TILE = SEL_THREADS * VEC;                       // elements per compaction tile
-    // The histogram and the compaction staging buffers share storage: never live together.
     extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
-    u32x4 *res = dyn_smem;                                            // [FUSED_RES][SEL_THREADS]
-    uint32_t *smem = reinterpret_cast<uint32_t *>(dyn_smem + FUSED_RES * SEL_THREADS);
-    int32_t *stage_idx = reinterpret_cast<int32_t *>(smem);
-    RAW *stage_val = reinterpret_cast<RAW *>(smem + TILE);
-    __shared__ uint32_t bcast[4];
+    char *dyn_bytes = reinterpret_cast<char *>(dyn_smem);
+    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_bytes + ST_LH_OFF);
+    __shared__ uint32_t bcast[4], offs[2], verdict, spilled;
     __shared__ uint32_t wave_tot[NW];
-    __shared__ uint32_t wave_tot2[2 * NW];
+    __shared__ uint32_t whist[NW][MAX_LAST_BINS + 1];           // per wavefront: its elements on each key of the range, and above it
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-    const int G = gridDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const bool last_chunk = blockIdx.x == gridDim.x - 1;
     const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
-    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * vpc;
-    const int64_t v1 = min(v0 + vpc, nvf);
+    uint32_t *xbar = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off);
 
     // development builds only: phase time stamps of one workgroup into the state block's spare words
-    [[maybe_unused]] unsigned long long *stamps = reinterpret_cast<unsigned long long *>(st->pad + 6);
+    [[maybe_unused]] unsigned long long *stamps = reinterpret_cast<unsigned long long *>(st->pad + 4);
 #define STAMP(i) DROPIT_DEV_STAMP(stamps, i, tid == 0 && blockIdx.x == gridDim.x / 2)
     STAMP(0);
 
-    const bool sampling = !F32 && numel >= SAMPLE_MIN_NUMEL;       // uniform over the grid
-    // The threshold lies in the key range [key_lo, key_lo + nf): predicted from the sample here (16-bit
-    // types, large tensors), else (or if the prediction fails) exactly known after the digit histograms.
-    uint32_t key_lo = 0, nf = LB;
-    bool predicted = false;
-
-    // ---- the staged form's geometry: wavefront `wave` owns vectors [wv0, wv1) of the chunk --------------
-    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
-    const int64_t vpw = ((vpc + NW - 1) / NW + 7) / 8 * 8;          // wavefront ranges start on 128-byte lines
+    // wavefront `wave` owns vectors [wv0, wv1) of the chunk, in rows of 64; ranges start on 128-byte lines
+    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * vpc, v1 = min(v0 + vpc, nvf);
+    const int64_t vpw = ((vpc + NW - 1) / NW + 7) / 8 * 8;
     const int64_t wv0 = min(v0 + int64_t(wave) * vpw, v1), wv1 = min(wv0 + vpw, v1);
-    const int nblk = static_cast<int>((wv1 - wv0 + ST_BLKV - 1) / ST_BLKV);
-    // uniform over the grid: a position within a wavefront's range must fit the 16 bits of a staged word
-    bool staged = !F32 && sampling && vpw * VEC <= 65536;
-    char *dyn_bytes = reinterpret_cast<char *>(dyn_smem);
-    uint32_t *lh = staged ? reinterpret_cast<uint32_t *>(dyn_bytes + ST_LH_OFF) : smem;
-    uint32_t *seg = reinterpret_cast<uint32_t *>(dyn_bytes + ST_STAGE_OFF) + wave * ST_SEGCAP;
-    __shared__ uint32_t wcount[NW];                                  // staged words per wavefront
-    __shared__ uint32_t whist[F32 ? 1 : NW][MAX_LAST_BINS + 1];      // per wavefront: staged keys on each key of the range, and above it
-    __shared__ uint32_t overflow;                                    // some wavefront's segment was too small
-    u32x4 qa[ST_U], qb[ST_U];                                        // two blocks of the wavefront's range in flight
-    auto issue_block = [&](u32x4 (&q)[ST_U], int blk) {
+    const int wvecs = static_cast<int>(wv1 - wv0);
+    const int nrows = (wvecs + WAVE - 1) / WAVE;
+    const u32x4 *wx = xv + (wv0 < nvf ? wv0 : nvf > 0 ? nvf - 1 : 0);   // (an empty range still has a valid address to load from)
+    const int last_vec = max(wvecs - 1, 0);
+    uint32_t *seg = reinterpret_cast<uint32_t *>(dyn_bytes) + wave * ST_SEGCAP;
+    u32x4 q[ST_ROWS];
+    // (loads are unconditional and clamped, so that the wait in front of a row's use can leave the rows behind it in flight)
+    auto issue_row = [&](u32x4 &dst, int row) { dst = wx[min(row * WAVE + lane, last_vec)]; };
+    auto issue_rows = [&](int row) {
 #pragma unroll
-        for (int u = 0; u < ST_U; ++u)
-            q[u] = xv[min(wv0 + int64_t(blk) * ST_BLKV + u * WAVE + lane, nvf - 1)];
+        for (int u = 0; u < ST_ROWS; ++u) issue_row(q[u], row + u);
     };
 
-    // ---- park the head of the chunk in LDS (each thread only ever reads its own slots) --
-    int nres = 0;
-    auto park = [&]() {
-        nres = static_cast<int>(min<int64_t>(FUSED_RES, (max<int64_t>(v1 - v0, 0) + SEL_THREADS - 1) / SEL_THREADS));
-        if (nvf > 0) {
-            u32x4 q[FUSED_RES];
-#pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i)     // unconditional, clamped: all loads in flight at once
-                q[i] = xv[min(v0 + int64_t(i) * SEL_THREADS + tid, nvf - 1)];
-#pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = q[i];
-        }
-    };
+    const bool sampling = numel >= SAMPLE_MIN_NUMEL;            // uniform over the grid
+    // The threshold lies in the key range [key_lo, key_lo + nf): predicted from the sample here, else (or if the
+    // prediction fails) exactly known after the digit histogram.
+    uint32_t key_lo = 0, nf = 1u << SHIFT1;
+    bool predicted = false, preloaded = false;
+    uint32_t cleared = 0;
+    if (blockIdx.x == 0) {
+        clear_words(st, xbar, cleared);
+        clear_hist(hist0, NB);                                  // (published when the exact form turns out to be needed)
+    }
     {
-        u32x4 q[FUSED_RES];
-        u32x4 sq[SAMPLE_VECTORS_PER_THREAD];
-        if (staged) {
-            if (nblk > 0) issue_block(qa, 0);
-            if (nblk > 1) issue_block(qb, 1);
-        } else if (nvf > 0) {
-            nres = static_cast<int>(min<int64_t>(FUSED_RES, (max<int64_t>(v1 - v0, 0) + SEL_THREADS - 1) / SEL_THREADS));
-#pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i)     // unconditional, clamped: all loads in flight at once
-                q[i] = xv[min(v0 + int64_t(i) * SEL_THREADS + tid, nvf - 1)];
-        }
-        if (sampling) {
-#pragma unroll
-            for (int j = 0; j < SAMPLE_VECTORS_PER_THREAD; ++j)
-                sq[j] = xv[sample_piece((j * SEL_THREADS + tid) / SAMPLE_PIECE,
-                                        SAMPLE_VECTORS_PER_THREAD * SEL_THREADS / SAMPLE_PIECE, nvf) + tid % SAMPLE_PIECE];
-        }
-        // Workgroup 0 clears what the workgroups exchange through (histograms, barrier counters) while its
-        // loads are in flight, then publishes this call's generation number; the others look for it before
-        // their first global atomic.  No separate clearing kernel, and a workspace with arbitrary contents
-        // is fine: a stale word equals the generation (a per-process random number plus a call count)
-        // with probability 2^-64.  Device-scope atomic stores, like everything else that is exchanged.
-        if (blockIdx.x == 0) {
-            // only the bins this element type uses: bf16 one 2048-bin pass, fp32 two 8192-bin passes (hist1 follows hist0)
-            constexpr int CLEAR_WORDS = F32 ? 2 * (1 << MAX_HIST_BITS) : (1 << BITS1);
-            for (int i = tid; i < CLEAR_WORDS; i += SEL_THREADS) dev_store(hist0 + i, 0u);
-            if (tid == 0) {
-                dev_store(&st->barrier, 0u);
-                dev_store(&st->error, 0u);
-                dev_store(&st->exited, 0u);
-                dev_store(&st->redo, 0u);
-                dev_store(&st->staged, 0u);
-            }
-            if (tid < 8)
-                dev_store(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off) + tid * 64, 0u);
-            __syncthreads();                    // every wave has waited for its stores
-            if (tid == 0) dev_store64(&st->ready, gen);
-        }
-        if (!staged && nvf > 0) {
-#pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = q[i];
-        }
+        u32x4 sq;
+        if (sampling) sq = xv[sample_piece(tid / SAMPLE_PIECE, nvf) + tid % SAMPLE_PIECE];
         STAMP(8);
         if (sampling) {
-            constexpr int NB = 1 << BITS1;
-            // the sample's histogram: where the digit histograms live, which in the staged form lies behind
-            // the transposition buffers and reaches into the (still empty) staging segments
-            for (int i = tid; i < NB + WAVE; i += SEL_THREADS) lh[i] = 0;
+            for (int i = tid; i < SAMPLE_BINS; i += SEL_THREADS) lh[i] = 0;
+            // the rows are asked for once the sample is here: ahead of it, 64 KB per compute unit, they would hold it up
+            // (bracket after 6.2 instead of 5.0 us, the whole call 45.5 instead of 44.6, on a 100 MB tensor)
+            asm volatile("" : "+v"(sq));
+            issue_rows(0);
+            preloaded = true;
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < SAMPLE_VECTORS_PER_THREAD; ++j)
-                for_each_raw(RAW(0), sq[j], [&](uint32_t raw, int) {
-                    const uint32_t dgt = ((raw & MASK) >> SHIFT1) & (NB - 1);
-                    atomicAdd(&lh[dgt ? dgt : NB + lane], 1u);          // exact zeros go to per-lane slots
-                });
+            for_each_raw(uint16_t(0), sq, [&](uint32_t raw, int) {
+                const uint32_t dgt = (raw & MASK) >> SAMPLE_SHIFT;
+                if (dgt) atomicAdd(&lh[dgt], 1u);
+            });
+            if (blockIdx.x == 0) publish_words(st, cleared, gen);
             __syncthreads();
             STAMP(9);
+            uint32_t b_lo, b_hi;
+            predicted = sample_bracket<SAMPLE_BINS>(lh, k, numel, wave_tot, bcast, b_lo, b_hi);
+            if (predicted) {
+                key_lo = b_lo << SAMPLE_SHIFT;
+                nf = (b_hi - b_lo + 1) << SAMPLE_SHIFT;
+            }
+        } else if (blockIdx.x == 0) {
+            publish_words(st, cleared, gen);
+        }
+    }
+    unsigned long long early = 0;                               // usually the generation number: asked for long before it is needed
+    if (tid == 0) early = dev_load64(&st->ready);
+    STAMP(1);
+
+    // The rows' candidates (key >= lowest) from row `first` on into the segment, in flat order; returns the first row that
+    // was not staged (nrows, or fewer when the segment is full or a position would not fit 16 bits), n = words staged.
+    // Positions count from row `first`.  Rows are staged in pairs.
+    auto stage_rows = [&](uint32_t lowest, int first, uint32_t &n) -> int {
+        const uint32_t low_s = __builtin_amdgcn_readfirstlane(lowest);
+        n = 0;
+        if (nrows == 0) return 0;
+        if (!preloaded) issue_rows(first);
+        preloaded = false;
+        const uint32_t seg_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)seg));
+        int end = nrows;
+        for (int row = first; row < end; row += ST_ROWS) {
+#pragma unroll
+            for (int u = 0; u < ST_ROWS; u += 2) {
+                if (row + u < end) {
+                    const int left = wvecs - (row + u) * WAVE - lane;              // > 0: the lane's vector of the first row exists
+                    const bool in0 = left > 0, in1 = left > WAVE;
+                    u32x4 k0, k1;
+                    const uint32_t n0 = count_candidates(q[u], low_s, k0), n1 = count_candidates(q[u + 1], low_s, k1);
+                    const uint32_t c = (in0 ? n0 : 0u) | (in1 ? n1 << 16 : 0u);
+                    const uint32_t ex = wave_inclusive_scan(c) - c;
+                    const uint32_t tot = uint32_t(__builtin_amdgcn_readlane(int(ex + c), WAVE - 1));
+                    const uint32_t t0 = tot & 0xFFFFu, t1 = tot >> 16;
+                    if (n + t0 + t1 > uint32_t(ST_SEGCAP) || (row + u + 2 - first) * ST_ROW_ELEMS > 65536) {
+                        end = row + u;                                             // full (no jump out of the body: see issue_row)
+                    } else {
+                        const uint32_t pos = uint32_t((row + u - first) * ST_ROW_ELEMS + lane * VEC);
+                        stage_candidates(q[u], k0, low_s, __ballot(in0), seg_addr + (n + (ex & 0xFFFFu)) * 4u, pos);
+                        stage_candidates(q[u + 1], k1, low_s, __ballot(in1), seg_addr + (n + t0 + (ex >> 16)) * 4u, pos + ST_ROW_ELEMS);
+                        n += t0 + t1;
+                    }
+                }
+                issue_row(q[u], row + u + ST_ROWS);
+                issue_row(q[u + 1], row + u + 1 + ST_ROWS);
+            }
+        }
+        return end;
+    };
+    // exact counts of the rows from `first` on, without staging them
+    auto count_rows = [&](int first, uint32_t &above) {
+        const uint32_t lo_s = __builtin_amdgcn_readfirstlane(key_lo), end_s = __builtin_amdgcn_readfirstlane(key_lo + nf);
+        issue_rows(first);
+        for (int row = first; row < nrows; row += ST_ROWS) {
+#pragma unroll
+            for (int u = 0; u < ST_ROWS; ++u) {
+                if (row + u < nrows) {
+                    const bool there = wvecs - (row + u) * WAVE - lane > 0;
+                    const uint32_t hi = candidate_mask(q[u], end_s);
+                    uint32_t in = there ? candidate_mask(q[u], lo_s) & ~hi : 0u;
+                    above += there ? __builtin_popcount(hi) : 0u;
+                    while (in) {
+                        const int e = __builtin_ctz(in);
+                        in &= in - 1;
+                        const uint32_t a = (e & 2) ? q[u][1] : q[u][0], b = (e & 2) ? q[u][3] : q[u][2];
+                        const uint32_t w = (e & 4) ? b : a;
+                        atomicAdd(&whist[wave][(((e & 1) ? w >> 16 : w) & MASK) - key_lo], 1u);
+                    }
+                }
+                issue_row(q[u], row + u + ST_ROWS);
+            }
+        }
+    };
+
+    uint32_t barriers = 0;
+    bool ready_seen = false, missed = false;
+    uint32_t n_w = 0;          // staged words of this wavefront
+    int staged_rows = 0;       // the rows they come from: [0, staged_rows)
+    for (;;) {
+        if (!predicted) {
+            // exact digit: every element of the chunk through an LDS histogram, merged with global atomics
+            if (blockIdx.x == 0) publish_hist(&st->ready_hist, gen);
+            __syncthreads();
+            for (int i = tid; i < NB + WAVE; i += SEL_THREADS) lh[i] = 0;
+            __syncthreads();
+            auto add = [&](uint32_t raw, int) {
+                const uint32_t d = (raw & MASK) >> SHIFT1;
+                atomicAdd(&lh[d ? d : NB + lane], 1u);                     // exact zeros go to per-lane slots
+            };
+            int64_t vb = v0;
+            for (; vb + SEL_THREADS * SEL_UNROLL <= v1; vb += SEL_THREADS * SEL_UNROLL) {
+                u32x4 h[SEL_UNROLL];
+#pragma unroll
+                for (int u = 0; u < SEL_UNROLL; ++u) h[u] = xv[vb + u * SEL_THREADS + tid];
+#pragma unroll
+                for (int u = 0; u < SEL_UNROLL; ++u) for_each_raw(uint16_t(0), h[u], add);
+            }
+            for (int64_t v = vb + tid; v < v1; v += SEL_THREADS) for_each_raw(uint16_t(0), xv[v], add);
+            if (last_chunk && tid == 0)
+                for (int64_t i = nvf * VEC; i < numel; ++i) add(x[i], 0);
+            __syncthreads();
             if (tid < WAVE) {
                 const uint32_t z = wave_sum(lh[NB + tid]);
                 if (tid == 0) lh[0] += z;
             }
             __syncthreads();
-            uint32_t b_lo, b_hi;
-            predicted = sample_bracket<NB>(lh, k, numel, wave_tot, bcast, b_lo, b_hi);
-            if (predicted) {
-                key_lo = b_lo << SHIFT1;                                // a first-digit bin is 2^SHIFT1 = 2^LAST_BITS keys
-                nf = (b_hi - b_lo + 1) << SHIFT1;
+            if (!wait_published(&st->ready_hist, gen, 0ull, &bcast[3])) return SEL_NEVER_READY;
+            if (!ready_seen && !wait_published(&st->ready, gen, early, &bcast[3])) return SEL_NEVER_READY;
+            ready_seen = true;
+            for (int i = tid; i < NB; i += SEL_THREADS) {
+                const uint32_t c = lh[i];
+                if (c) atomicAdd(&hist0[i], c);
+            }
+            if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+            uint32_t prefix = 0, k_rem = k;
+            resolve_digit_local<NB, BITS1>(hist0, prefix, k_rem, wave_tot, bcast);
+            key_lo = prefix << SHIFT1;
+            nf = 1u << SHIFT1;
+            STAMP(2);
+        }
+
+        // ---- the one pass, then exact counts over the range and above it ----------------
+        // (the histogram row of a wavefront is its own; words and counts of one wavefront need no workgroup barrier)
+        uint32_t *wh = whist[wave];
+        if (lane <= static_cast<int>(nf)) wh[lane] = 0;
+        if (tid == 0) spilled = 0;
+        staged_rows = stage_rows(key_lo, 0, n_w);
+        STAMP(3);
+        __syncthreads();                                         // `spilled` is cleared
+        const uint32_t key_end = key_lo + nf;
+        uint32_t above = 0;
+        for (uint32_t q0 = 0; q0 < n_w; q0 += 4 * WAVE) {
+            const uint32_t at = q0 + lane * 4;
+            if (at < n_w) {
+                const u32x4 w4 = *reinterpret_cast<const u32x4 *>(seg + at);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t key = (w4[j] >> 16) & MASK;
+                    const bool there = at + j < n_w;
+                    above += (there && key >= key_end) ? 1u : 0u;
+                    const uint32_t rel = key - key_lo;
+                    if (there && rel < nf) atomicAdd(&wh[rel], 1u);
+                }
             }
         }
-        if (staged && !predicted) {     // no usable bracket (uniform over the grid): the exact form, with the head parked after all
-            staged = false;
-            lh = smem;
-            park();
+        if (staged_rows < nrows) {
+            count_rows(staged_rows, above);
+            if (lane == 0) spilled = 1u;
+        }
+        above = wave_sum(above);
+        if (lane == 0) wh[nf] = above;
+        __syncthreads();
+        if (!ready_seen && !wait_published(&st->ready, gen, early, &bcast[3])) return SEL_NEVER_READY;
+        ready_seen = true;
+        if (tid <= static_cast<int>(nf)) {        // the chunk's column of the table: the wavefronts' counts added up
+            uint32_t sum = 0;
+#pragma unroll
+            for (int w2 = 0; w2 < NW; ++w2) sum += whist[w2][tid];
+            if (last_chunk)                        // the tensor's ragged end belongs to the chunk, but to no wavefront's range
+                for (int64_t i = nvf * VEC; i < numel; ++i) {
+                    const uint32_t key = x[i] & MASK;
+                    sum += (tid == static_cast<int>(nf) ? key >= key_end : key == key_lo + tid) ? 1u : 0u;
+                }
+            dev_store(&table[blockIdx.x * TABLE_PITCH + tid], sum);
+        }
+        STAMP(4);
+        if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+        STAMP(5);
+        if (resolve_table(table, nf, key_lo, k, lh, bcast, offs, &verdict, xbar, rep)) break;
+        if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
+        predicted = false;                       // the sample misled: once more with the exact histogram
+        missed = true;
+    }
+    const uint32_t t = bcast[0], m = bcast[1];
+    if (tid == REPORT_TID) {
+        if (spilled == 0) __hip_atomic_fetch_add(&st->staged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (blockIdx.x == 0) dev_store(&st->path, numel < SAMPLE_LARGE ? 0u : missed ? 2u : predicted ? 1u : 0u);
+    }
+    STAMP(6);
+
+    // ---- ordered output -------------------------------------------------------------
+    // A kept element (key > t, or one of the first m keys == t) goes to output slot #gt-before + min(#eq-before, m).
+    // #{key > t}, #{key == t} in the wavefronts' ranges, from their histograms: lane l adds up wavefront l's
+    const uint32_t trel = t - key_lo;
+    uint32_t g = 0, e = 0;
+    if (lane < NW) {
+        g = whist[lane][nf];
+        for (uint32_t r = trel + 1; r < nf; ++r) g += whist[lane][r];
+        e = whist[lane][trel];
+    }
+    const uint32_t gi = wave_inclusive_scan(g), ei = wave_inclusive_scan(e);
+    uint32_t my_gt = offs[0] + uint32_t(__builtin_amdgcn_readlane(int(gi - g), wave));
+    uint32_t my_eq = offs[1] + uint32_t(__builtin_amdgcn_readlane(int(ei - e), wave));
+    const uint32_t chunk_gt = offs[0] + uint32_t(__builtin_amdgcn_readlane(int(gi), NW - 1));
+    const uint32_t chunk_eq = offs[1] + uint32_t(__builtin_amdgcn_readlane(int(ei), NW - 1));
+    auto keep = [&](uint32_t pos, uint32_t raw, uint32_t i) {
+        if (pos < k) {                     // always true for consistent counts
+            vals[pos] = static_cast<uint16_t>(raw);
+            idx[pos] = static_cast<int32_t>(i);
+        }
+    };
+    // All or none of this wavefront's keys equal to t are kept, except in the one wavefront where the budget runs out.
+    const uint32_t wave_eq = uint32_t(__builtin_amdgcn_readlane(int(e), wave));
+    const bool split = my_eq < m && my_eq + wave_eq > m;
+    const uint32_t least = my_eq < m ? t : t + 1;      // lowest key kept (if not split)
+    uint32_t my_slot = my_gt + min(my_eq, m);
+    int first = 0;                         // the row the staged words' positions count from
+    for (;;) {
+        // the staged words, 64 at a time in lane order: neighbouring lanes write neighbouring slots
+        const uint32_t flat0 = static_cast<uint32_t>(wv0 * VEC) + static_cast<uint32_t>(first) * ST_ROW_ELEMS;
+        for (uint32_t q0 = 0; q0 < n_w; q0 += 4 * WAVE) {
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = q0 + j * WAVE + lane < n_w ? seg[q0 + j * WAVE + lane] : 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t key = (w[j] >> 16) & MASK;
+                const bool there = q0 + j * WAVE + lane < n_w;
+                if (!split) {              // uniform over the wavefront
+                    const bool kept = there && key >= least;
+                    const lane_mask b = __ballot(kept);
+                    if (kept) keep(bits_before(b, my_slot), w[j] >> 16, flat0 + (w[j] & 0xFFFFu));
+                    my_slot += __builtin_popcountll(b);
+                } else {
+                    const bool gt = there && key > t, eq = there && key == t;
+                    const lane_mask bg = __ballot(gt), be = __ballot(eq);
+                    const uint32_t eb = bits_before(be, my_eq), gb = bits_before(bg, my_gt);
+                    if (gt || (eq && eb < m)) keep(gb + min(eb, m), w[j] >> 16, flat0 + (w[j] & 0xFFFFu));
+                    my_gt += __builtin_popcountll(bg);
+                    my_eq += __builtin_popcountll(be);
+                }
+            }
+        }
+        if (staged_rows >= nrows) break;
+        first = staged_rows;               // the rows that did not fit: read again, only what is kept is staged now
+        staged_rows = stage_rows(t, first, n_w);
+    }
+    STAMP(7);
+    if (last_chunk && tid == 0) {
+        uint32_t run_gt = chunk_gt, run_eq = chunk_eq;
+        for (int64_t i = nvf * VEC; i < numel; ++i) {
+            const uint32_t raw = x[i], key = raw & MASK;
+            if (key > t) {
+                keep(run_gt + min(run_eq, m), raw, static_cast<uint32_t>(i));
+                ++run_gt;
+            } else if (key == t) {
+                if (run_eq < m) keep(run_gt + run_eq, raw, static_cast<uint32_t>(i));
+                ++run_eq;
+            }
+        }
+    }
+#undef STAMP
+    return SEL_DONE;
+}
+
+// fp32: two digit histograms of 13 bits, then exact counts over the last 5.
+__device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
+                                           SelState *st, uint32_t *hist0, uint32_t *hist1, uint32_t *table,
+                                           uint32_t *__restrict__ vals, int32_t *__restrict__ idx, uint32_t spin_limit,
+                                           unsigned long long gen, ExitReport &rep)
+{
+    constexpr int VEC = 4;
+    constexpr uint32_t MASK = KeyTraits<uint32_t>::MASK;
+    constexpr int BITS1 = 13, SHIFT1 = 18, BITS2 = 13, SHIFT2 = 5, LAST_BITS = 5;
+    constexpr uint32_t NF = 1u << LAST_BITS;
+    constexpr int NW = SEL_THREADS / WAVE;
+    constexpr int TILE = SEL_THREADS * VEC;                       // elements per compaction tile
+    // The histogram and the compaction staging buffers share storage: never live together.
+    extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
+    u32x4 *res = dyn_smem;                                            // [FUSED_RES][SEL_THREADS]
+    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_smem + FUSED_RES * SEL_THREADS);
+    int32_t *stage_idx = reinterpret_cast<int32_t *>(lh);
+    uint32_t *stage_val = lh + TILE;
+    __shared__ uint32_t bcast[4], offs[2], verdict;
+    __shared__ uint32_t wave_tot[NW];
+    __shared__ uint32_t wave_tot2[2 * NW];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const bool last_chunk = blockIdx.x == gridDim.x - 1;
+    const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
+    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * vpc;
+    const int64_t v1 = min(v0 + vpc, nvf);
+    uint32_t *xbar = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off);
+
+    // development builds only: phase time stamps of one workgroup into the state block's spare words
+    [[maybe_unused]] unsigned long long *stamps = reinterpret_cast<unsigned long long *>(st->pad + 4);
+#define STAMP(i) DROPIT_DEV_STAMP(stamps, i, tid == 0 && blockIdx.x == gridDim.x / 2)
+    STAMP(0);
+
+    // ---- park the head of the chunk in LDS (each thread only ever reads its own slots) --
+    const int nres = static_cast<int>(min<int64_t>(FUSED_RES, (max<int64_t>(v1 - v0, 0) + SEL_THREADS - 1) / SEL_THREADS));
+    {
+        u32x4 q[FUSED_RES];
+        if (nvf > 0) {
+#pragma unroll
+            for (int i = 0; i < FUSED_RES; ++i)     // unconditional, clamped: all loads in flight at once
+                q[i] = xv[min(v0 + int64_t(i) * SEL_THREADS + tid, nvf - 1)];
+        }
+        if (blockIdx.x == 0) {                      // (while the loads are in flight; two 8192-bin passes: hist1 follows hist0)
+            uint32_t cleared = 0;
+            clear_words(st, xbar, cleared);
+            clear_hist(hist0, 2 * (1 << MAX_HIST_BITS));
+            publish_hist(&st->ready, gen);
+        }
+        if (nvf > 0) {
+#pragma unroll
+            for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = q[i];
         }
     }
     const int64_t v_stream = v0 + int64_t(nres) * SEL_THREADS;        // first vector that is not parked
-    // visits the chunk: fv(vector) for every full 16-byte vector, ft(raw bits) for the ragged tail's elements
-    auto for_chunk_v = [&](auto fv, auto ft) {
+    // visits every element of the chunk: f(raw bits)
+    auto for_chunk = [&](auto f) {
+        auto fv = [&](const u32x4 &q) { for_each_raw(uint32_t(0), q, [&](uint32_t raw, int) { f(raw); }); };
         for (int i = 0; i < nres; ++i) {
             const int64_t v = v0 + int64_t(i) * SEL_THREADS + tid;
             if (v < v1) fv(res[i * SEL_THREADS + tid]);
@@ -824,41 +1282,13 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
         }
         for (int64_t v = vb + tid; v < v1; v += SEL_THREADS) fv(xv[v]);
         if (last_chunk && tid == 0)
-            for (int64_t i = nvf * VEC; i < numel; ++i) ft(x[i]);
+            for (int64_t i = nvf * VEC; i < numel; ++i) f(x[i]);
     };
-    // visits every element of the chunk: f(raw bits)
-    auto for_chunk = [&](auto f) {
-        for_chunk_v([&](const u32x4 &q) { for_each_raw(RAW(0), q, [&](uint32_t raw, int) { f(raw); }); }, f);
-    };
-
-    uint32_t prefix = 0, k_rem = k;
-    uint32_t barriers = 0;
-    uint32_t *xbar = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off);
 
     // ---- digit histograms ---------------------------------------------------------
-    __shared__ uint32_t verdict;
-    __shared__ uint32_t offs[2];
-    __shared__ uint32_t lp[MAX_LAST_BINS + 1];
-    // Waits until workgroup 0 has published this call's generation number: the exchange area is then
-    // cleared.  False (in every thread) if that never happens.
+    uint32_t prefix = 0, k_rem = k;
+    uint32_t barriers = 0;
     bool ready_seen = false;
-    auto wait_ready = [&]() -> bool {
-        if (ready_seen) return true;
-        if (tid == 0) {
-            uint32_t spins = 0, ok = 1;
-            while (dev_load64(&st->ready) != gen) {
-                if (++spins > READY_SPIN_LIMIT) {      // workgroup 0 never ran: not this workgroup's patience setting
-                    ok = 0;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            bcast[3] = ok;
-        }
-        __syncthreads();
-        ready_seen = bcast[3] != 0;
-        return ready_seen;
-    };
     // One digit's histogram of the chunk, merged into ghist; ends with a grid barrier, after which
     // ghist holds the whole tensor's histogram.
     auto hist_pass = [&](auto shift_c, auto bits_c, auto first_c, uint32_t *ghist) -> SelOutcome {
@@ -868,21 +1298,22 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
         for (int i = tid; i < NB + 2 * WAVE; i += SEL_THREADS) lh[i] = 0;
         __syncthreads();
         const uint32_t zslot = NB + lane, dslot = NB + WAVE + lane;
-        auto add = [&](uint32_t raw) {
+        for_chunk([&](uint32_t raw) {
             const uint32_t key = raw & MASK;
             const uint32_t d = (key >> SHIFT) & (NB - 1);
             uint32_t a = d ? d : zslot;
             if (!FIRST) a = ((key >> (SHIFT + BITS)) == prefix) ? a : dslot;
             atomicAdd(&lh[a], 1u);
-        };
-        for_chunk(add);
+        });
         __syncthreads();
         if (tid < WAVE) {
             const uint32_t z = wave_sum(lh[NB + tid]);
             if (tid == 0) lh[0] += z;
         }
         __syncthreads();
-        if (!wait_ready()) return SEL_NEVER_READY;      // the exchange area must have been cleared for this call
+        // the exchange area must have been cleared for this call
+        if (!ready_seen && !wait_published(&st->ready, gen, 0ull, &bcast[3])) return SEL_NEVER_READY;
+        ready_seen = true;
         for (int i = tid; i < NB; i += SEL_THREADS) {
             const uint32_t c = lh[i];
             if (c) atomicAdd(&ghist[i], c);
@@ -890,245 +1321,44 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
         if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
         return SEL_DONE;
     };
-
-    bool missed = false;
-    bool use_staged = false;     // this workgroup's candidates are all staged in LDS (uniform over the workgroup)
     STAMP(1);
-    uint32_t t = 0, m = 0;
-    for (;;) {
-        if (!predicted) {
-            // exact digits
-            prefix = 0;
-            k_rem = k;
-            if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT1>{}, std::integral_constant<int, BITS1>{},
-                                               std::true_type{}, hist0))
-                return o;
-            resolve_digit_local<(1 << BITS1), BITS1>(hist0, prefix, k_rem, wave_tot, bcast);
-            if constexpr (F32) {
-                if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT2>{}, std::integral_constant<int, BITS2>{},
-                                                   std::false_type{}, hist1))
-                    return o;
-                resolve_digit_local<(1 << BITS2), BITS2>(hist1, prefix, k_rem, wave_tot, bcast);
-            }
-            key_lo = prefix << LAST_BITS;
-            nf = LB;
-            STAMP(2);
-        }
+    if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT1>{}, std::integral_constant<int, BITS1>{},
+                                       std::true_type{}, hist0))
+        return o;
+    resolve_digit_local<(1 << BITS1), BITS1>(hist0, prefix, k_rem, wave_tot, bcast);
+    if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT2>{}, std::integral_constant<int, BITS2>{},
+                                       std::false_type{}, hist1))
+        return o;
+    resolve_digit_local<(1 << BITS2), BITS2>(hist1, prefix, k_rem, wave_tot, bcast);
+    const uint32_t key_lo = prefix << LAST_BITS;
+    STAMP(2);
 
-        // ---- exact counts over the range and above it, per chunk ----------------------
-        for (int i = tid; i <= static_cast<int>(nf); i += SEL_THREADS) lh[i] = 0;
-        if (tid == 0) overflow = 0;
-        __syncthreads();
-        bool counted = false;
-        if constexpr (!F32) {
-            if (staged && predicted) {
-                // One pass over the wavefront's range: candidates (key >= key_lo) staged in flat-index order.
-                const uint32_t key_lo_s = __builtin_amdgcn_readfirstlane(key_lo);
-                char *tb = dyn_bytes + wave * ST_TRANS_BYTES;                   // this wavefront's transposition buffer
-                char *mine = tb + lane * (ST_U * 16) + ((lane * ST_U) >> 3) * 16;   // this lane's ST_U consecutive vectors in it
-                uint32_t n_w = 0;
-                bool full = false;
-                auto process = [&](u32x4 (&q)[ST_U], int blk) {
-#pragma unroll
-                    for (int u = 0; u < ST_U; ++u) {
-                        const int vi = u * WAVE + lane;                        // as loaded: lane after lane
-                        *reinterpret_cast<u32x4 *>(tb + vi * 16 + (vi >> 3) * 16) = q[u];
-                    }
-                    if (blk + 2 < nblk) issue_block(q, blk + 2);               // the registers are free again
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // a wavefront's LDS accesses execute in order
-                    u32x4 r[ST_U];
-#pragma unroll
-                    for (int u = 0; u < ST_U; ++u) r[u] = *reinterpret_cast<const u32x4 *>(mine + u * 16);
-                    uint32_t mask = candidate_mask(r, key_lo_s);
-                    // whole vectors past the end of the wavefront's range are not there
-                    const int64_t left = (wv1 - wv0 - int64_t(blk) * ST_BLKV) - int64_t(lane) * ST_U;
-                    if (left < ST_U) mask &= left <= 0 ? 0u : (1u << (static_cast<int>(left) * VEC)) - 1u;
-                    const uint32_t cnt = __builtin_popcount(mask);
-                    const uint32_t incl = wave_inclusive_scan(cnt);
-                    const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(incl), WAVE - 1));
-                    if (n_w + total > uint32_t(ST_SEGCAP)) {
-                        full = true;
-                        return;
-                    }
-                    uint32_t slot = n_w + incl - cnt;
-                    const uint32_t pos0 = static_cast<uint32_t>(blk) * (ST_BLKV * VEC) + lane * ST_EPL;
-                    while (mask) {
-                        const int b = __builtin_ctz(mask);
-                        mask &= mask - 1;
-                        const uint32_t raw = *reinterpret_cast<const uint16_t *>(mine + 2 * b);
-                        seg[slot++] = (raw << 16) | (pos0 + b);
-                    }
-                    n_w += total;
-                };
-                for (int blk = 0; blk < nblk && !full; blk += 2) {
-                    process(qa, blk);
-                    if (blk + 1 < nblk && !full) process(qb, blk + 1);
-                }
-                if (lane == 0) {
-                    wcount[wave] = n_w;
-                    if (full) overflow = 1u;
-                }
-                __syncthreads();
-                STAMP(3);
-                if (overflow == 0) {
-                    // Exact counts from the staged words, per wavefront (whist[wave]: one counter per key of the
-                    // range, the last one for the keys above it); four words per lane and read, the segment's
-                    // capacity is a multiple of four.
-                    const uint32_t key_end = key_lo + nf;
-                    uint32_t *wh = whist[wave];
-                    if (lane <= static_cast<int>(nf)) wh[lane] = 0;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    uint32_t above = 0;
-                    for (uint32_t q0 = 0; q0 < n_w; q0 += 4 * WAVE) {
-                        const uint32_t q = q0 + lane * 4;
-                        if (q < n_w) {
-                            const u32x4 w4 = *reinterpret_cast<const u32x4 *>(seg + q);
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                const uint32_t key = (w4[j] >> 16) & MASK;
-                                const bool there = q + j < n_w;
-                                above += (there && key >= key_end) ? 1u : 0u;
-                                const uint32_t rel = key - key_lo;
-                                if (there && rel < nf) atomicAdd(&wh[rel], 1u);
-                            }
-                        }
-                    }
-                    above = wave_sum(above);
-                    if (lane == 0) atomicAdd(&wh[nf], above);
-                    __syncthreads();
-                    if (tid <= static_cast<int>(nf)) {        // the workgroup's row of the table: the wavefronts' counts added up
-                        uint32_t sum = 0;
-#pragma unroll
-                        for (int w2 = 0; w2 < NW; ++w2) sum += whist[w2][tid];
-                        lh[tid] = sum;
-                    }
-                    if (last_chunk) {                          // the tensor's ragged end belongs to the chunk, but to no wavefront's range
-                        __syncthreads();
-                        if (tid == 0)
-                            for (int64_t i = nvf * VEC; i < numel; ++i) {
-                                const uint32_t key = x[i] & MASK;
-                                if (key >= key_end) lh[nf] += 1u;
-                                else if (key - key_lo < nf) lh[key - key_lo] += 1u;
-                            }
-                    }
-                    use_staged = true;
-                    counted = true;
-                }
-            }
-        }
-        if (!counted) {
-            // Few keys fall into the range, so unlike the digit histograms this pass branches: a
-            // wavefront with no such key among its lanes skips the LDS atomic altogether (an LDS
-            // atomic costs its issue cycles whatever the number of active lanes).
-            uint32_t above = 0;
-            const uint32_t key_end = key_lo + nf;
-            auto one = [&](uint32_t raw) {
-                const uint32_t key = raw & MASK;
-                above += (key >= key_end) ? 1u : 0u;
-                const uint32_t rel = key - key_lo;             // wraps to a huge value below the range
-                if (rel < nf) atomicAdd(&lh[rel], 1u);
-            };
-            if constexpr (F32) {
-                for_chunk(one);
-            } else {
-                // Two 15-bit keys per 32-bit word are classified together: adding 0x8000 - E to a key sets
-                // its bit 15 iff key >= E, and neither half can carry into the other (E <= 0x8000).
-                const uint32_t c_end = (0x8000u - key_end) * 0x00010001u;
-                const uint32_t c_lo = (0x8000u - key_lo) * 0x00010001u;
-                for_chunk_v(
-                    [&](const u32x4 &q) {
-                        uint32_t kw[4], in_range[4], any = 0;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) {
-                            kw[w] = q[w] & 0x7FFF7FFFu;
-                            const uint32_t ge_end = kw[w] + c_end, ge_lo = kw[w] + c_lo;
-                            above += __builtin_popcount(ge_end & 0x80008000u);
-                            in_range[w] = (ge_lo ^ ge_end) & 0x80008000u;     // >= key_lo and not >= key_end
-                            any |= in_range[w];
-                        }
-                        if (any) {
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                if (in_range[w] & 0x8000u) atomicAdd(&lh[(kw[w] & 0xFFFFu) - key_lo], 1u);
-                                if (in_range[w] & 0x80000000u) atomicAdd(&lh[(kw[w] >> 16) - key_lo], 1u);
-                            }
-                        }
-                    },
-                    one);
-            }
-            above = wave_sum(above);
-            if (lane == 0 && above) atomicAdd(&lh[nf], above);
-        }
-        __syncthreads();
-        if (!wait_ready()) return SEL_NEVER_READY;      // (already seen, unless the range was predicted)
-        if (tid <= static_cast<int>(nf)) dev_store(&table[tid * G + blockIdx.x], lh[tid]);
-        STAMP(4);
-        if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
-        STAMP(5);
-
-        // Per row of the table (a key of the range; the last row = the keys above the range): the total
-        // over all chunks and the part in the chunks before this one, one wavefront per row.
-        {
-            // every wavefront takes up to ROWS rows (wave, wave + NW, ...); all their loads are issued together
-            constexpr int ROWS = (MAX_LAST_BINS + 1 + NW - 1) / NW;
-            constexpr int COLS = SEL_MAX_CHUNKS / WAVE;
-            const int wave = tid / WAVE;
-            uint32_t v[ROWS][COLS];
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) {
-                    const int row = wave + r * NW, c = lane + j * WAVE;
-                    v[r][j] = (row <= static_cast<int>(nf) && c < G) ? dev_load(&table[row * G + c]) : 0u;
-                }
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                const int row = wave + r * NW;
-                if (row > static_cast<int>(nf)) break;         // uniform over the wavefront
-                uint32_t s = 0, sp = 0;
-#pragma unroll
-                for (int j = 0; j < COLS; ++j) {
-                    s += v[r][j];
-                    sp += (lane + j * WAVE < static_cast<int>(blockIdx.x)) ? v[r][j] : 0u;
-                }
-                s = wave_sum(s);
-                sp = wave_sum(sp);
-                if (lane == 0) {
-                    lh[row] = s;
-                    lp[row] = sp;
-                }
-            }
-        }
-        __syncthreads();
-        if (tid < WAVE) {
-            // Lane 0 takes the row above the range, lanes 1.. the range's keys in descending order, so a
-            // prefix scan over the lanes counts the keys above each key.  The k-th largest key is the one
-            // with  #above < k <= #above + #equal;  it is in the range iff that holds for a lane >= 1.
-            const int rr = static_cast<int>(nf) - lane;
-            const uint32_t full = rr >= 0 ? lh[rr] : 0u, part = rr >= 0 ? lp[rr] : 0u;
-            const uint32_t incl = wave_inclusive_scan(full), incl_p = wave_inclusive_scan(part);
-            const bool here = lane >= 1 && rr >= 0 && incl - full < k && k <= incl;
-            const unsigned long long hit = __ballot(here);
-            if (lane == 0) verdict = hit ? 1u : 0u;
-            if (here) {
-                bcast[0] = key_lo + static_cast<uint32_t>(rr);   // t
-                bcast[1] = k - (incl - full);                     // m: how many keys equal to t are kept
-                offs[0] = incl_p - part;                          // #{key > t} in the chunks before this one
-                offs[1] = part;                                   // #{key == t} there
-            }
-        }
-        __syncthreads();
-        if (verdict) break;
-        if (!predicted) return SEL_GAVE_UP;     // cannot happen with exact digits; the serial path would still answer
-        predicted = false;                       // the sample misled: once more with the exact histogram
-        missed = true;
-        use_staged = false;
-        __syncthreads();                         // everybody has read the verdict before it is written again
-    }
-    t = bcast[0];
-    m = bcast[1];
-    if (blockIdx.x == 0 && tid == 0) dev_store(&st->path, missed ? 2u : predicted ? 1u : 0u);
+    // ---- exact counts over the range and above it, per chunk ----------------------
+    // Few keys fall into the range, so unlike the digit histograms this pass branches: a
+    // wavefront with no such key among its lanes skips the LDS atomic altogether (an LDS
+    // atomic costs its issue cycles whatever the number of active lanes).
+    for (int i = tid; i <= static_cast<int>(NF); i += SEL_THREADS) lh[i] = 0;
+    __syncthreads();
+    uint32_t above = 0;
+    const uint32_t key_end = key_lo + NF;
+    for_chunk([&](uint32_t raw) {
+        const uint32_t key = raw & MASK;
+        above += (key >= key_end) ? 1u : 0u;
+        const uint32_t rel = key - key_lo;             // wraps to a huge value below the range
+        if (rel < NF) atomicAdd(&lh[rel], 1u);
+    });
+    above = wave_sum(above);
+    if (lane == 0 && above) atomicAdd(&lh[NF], above);
+    __syncthreads();
+    if (tid <= static_cast<int>(NF)) dev_store(&table[blockIdx.x * TABLE_PITCH + tid], lh[tid]);
+    STAMP(4);
+    if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+    STAMP(5);
+    if (!resolve_table(table, NF, key_lo, k, lh, bcast, offs, &verdict, xbar, rep))
+        return SEL_GAVE_UP;                    // cannot happen with exact digits; the serial path would still answer
+    const uint32_t t = bcast[0], m = bcast[1];
     uint32_t run_gt = offs[0], run_eq = offs[1];   // #{key > t}, #{key == t} before this chunk
+    if (blockIdx.x == 0 && tid == 0) dev_store(&st->path, 0u);
     STAMP(6);
 
     // ---- ordered compaction -------------------------------------------------------
@@ -1136,14 +1366,14 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
     // LDS first so that the global stores are contiguous.
     auto keep = [&](uint32_t pos, uint32_t raw, int64_t i) {
         if (pos < k) {                     // always true for consistent counts
-            vals[pos] = static_cast<RAW>(raw);
+            vals[pos] = raw;
             idx[pos] = static_cast<int32_t>(i);
         }
     };
     auto emit_tile = [&](const u32x4 &q, int64_t v, bool live) {
         // bit e of gtm / eqm: element e of this thread's vector has key > t / key == t
         uint32_t gtm = 0, eqm = 0;
-        for_each_raw(RAW(0), q, [&](uint32_t raw, int e) {
+        for_each_raw(uint32_t(0), q, [&](uint32_t raw, int e) {
             const uint32_t key = raw & MASK;
             gtm |= (key > t ? 1u : 0u) << e;
             eqm |= (key == t ? 1u : 0u) << e;
@@ -1158,8 +1388,8 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
         const int64_t base = v * VEC;
         // A kept element (key > t, or one of the first m keys == t) goes to output slot
         // #gt-before + min(#eq-before, m): one formula for both cases.  Only the candidate
-        // elements are visited (a tenth of them at gamma = 0.9): every LDS store a wavefront
-        // issues costs its slot on the LDS pipe however few lanes take part.
+        // elements are visited: every LDS store a wavefront issues costs its slot on the LDS
+        // pipe however few lanes take part.
         uint32_t todo = gtm | eqm;
         while (todo) {
             const int e = __builtin_ctz(todo);
@@ -1167,10 +1397,7 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
             const bool gt = (gtm >> e) & 1u;
             if (gt || my_eq < m) {
                 const uint32_t slot = my_gt + min(my_eq, m) - tile_first;
-                uint32_t raw;
-                if constexpr (F32) raw = q[e];
-                else raw = (q[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu;
-                stage_val[slot] = static_cast<RAW>(raw);
+                stage_val[slot] = q[e];
                 stage_idx[slot] = static_cast<int32_t>(base + e);
             }
             my_gt += gt ? 1u : 0u;
@@ -1187,163 +1414,87 @@ __device__ inline SelOutcome select_fused_body(const RAW *__restrict__ x, int64_
             }
         // the next tile's scan starts with a barrier, which also protects the staging buffers
     };
-    bool compacted = false;
-    if constexpr (!F32) {
-        if (use_staged) {
-            // ---- compaction from the staged candidates: x is not read again ----
-            const uint32_t n_w = wcount[wave];
-            // #{key > t}, #{key == t} in the wavefronts' ranges, from their histograms: lane l adds up wavefront l's
-            const uint32_t trel = t - key_lo;
-            uint32_t g = 0, e = 0;
-            if (lane < NW) {
-                g = whist[lane][nf];
-                for (uint32_t r = trel + 1; r < nf; ++r) g += whist[lane][r];
-                e = whist[lane][trel];
-            }
-            const uint32_t gi = wave_inclusive_scan(g), ei = wave_inclusive_scan(e);
-            uint32_t my_gt = run_gt + uint32_t(__builtin_amdgcn_readlane(int(gi - g), wave));
-            uint32_t my_eq = run_eq + uint32_t(__builtin_amdgcn_readlane(int(ei - e), wave));
-            run_gt += uint32_t(__builtin_amdgcn_readlane(int(gi), NW - 1));
-            run_eq += uint32_t(__builtin_amdgcn_readlane(int(ei), NW - 1));
-            const uint32_t flat0 = static_cast<uint32_t>(wv0 * VEC);
-            for (uint32_t q0 = 0; q0 < n_w; q0 += 4 * WAVE) {
-                const uint32_t q = q0 + lane * 4;
-                u32x4 w4 = {0u, 0u, 0u, 0u};
-                if (q < n_w) w4 = *reinterpret_cast<const u32x4 *>(seg + q);
-                uint32_t gtm = 0, eqm = 0;                 // bit j: word j of this lane has key > t / key == t
+    __syncthreads();                       // histogram storage becomes staging storage
+    // The chunk is compacted in super-tiles of FUSED_RES x 1024 vectors that sit in the parking
+    // area: the first one is the parked head itself, the following ones are fetched (coalesced,
+    // one super-tile ahead, through registers) into the same area.  Inside a super-tile each thread
+    // takes `rows` CONSECUTIVE vectors (the other phases take every 1024th), so flat-index order is
+    // thread order and one block scan serves the whole super-tile: two barriers + a gather + a
+    // write-out per 24576 elements.  Bit (i * VEC + e) of the masks stands for element e of the
+    // thread's i-th vector.  A super-tile that keeps more than the staging buffers hold (only when
+    // most of the tensor is kept) falls back to one scan per 1024-vector row.
+    constexpr int64_t SUPER = int64_t(FUSED_RES) * SEL_THREADS;
+    u32x4 pre[FUSED_RES];
+    for (int64_t sb = v0; sb < v1; sb += SUPER) {
+        const int64_t count = min<int64_t>(v1 - sb, SUPER);          // vectors of this super-tile, all in `res`
+        const int rows = static_cast<int>((count + SEL_THREADS - 1) / SEL_THREADS);
+        const bool more = sb + SUPER < v1;
+        if (more) {                                                   // the next one, clamped loads
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t key = (w4[j] >> 16) & MASK;
-                    const bool there = q + j < n_w;
-                    gtm |= (there && key > t) ? (1u << j) : 0u;
-                    eqm |= (there && key == t) ? (1u << j) : 0u;
-                }
-                const uint32_t both = __builtin_popcount(gtm) | (__builtin_popcount(eqm) << 16);
-                const uint32_t incl = wave_inclusive_scan(both);
-                const uint32_t tot = uint32_t(__builtin_amdgcn_readlane(int(incl), WAVE - 1));
-                uint32_t gb = my_gt + ((incl - both) & 0xFFFFu), eb = my_eq + ((incl - both) >> 16);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool gt = (gtm >> j) & 1u, eq = (eqm >> j) & 1u;
-                    if (gt || (eq && eb < m)) keep(gb + min(eb, m), w4[j] >> 16, int64_t(flat0) + (w4[j] & 0xFFFFu));
-                    gb += gt ? 1u : 0u;
-                    eb += eq ? 1u : 0u;
-                }
-                my_gt += tot & 0xFFFFu;
-                my_eq += tot >> 16;
-            }
-            if (tid == 0) __hip_atomic_fetch_add(&st->staged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            compacted = true;
+            for (int i = 0; i < FUSED_RES; ++i) pre[i] = xv[min(sb + SUPER + int64_t(i) * SEL_THREADS + tid, v1 - 1)];
         }
-    }
-    if (!compacted) {
-        __syncthreads();                       // histogram storage becomes staging storage
-        // The chunk is compacted in super-tiles of FUSED_RES x 1024 vectors that sit in the parking
-        // area: the first one is the parked head itself, the following ones are fetched (coalesced,
-        // one super-tile ahead, through registers) into the same area.  Inside a super-tile each thread
-        // takes `rows` CONSECUTIVE vectors (the other phases take every 1024th), so flat-index order is
-        // thread order and one block scan serves the whole super-tile: two barriers + a gather + a
-        // write-out per 49152 elements.  Bit (i * VEC + e) of the masks stands for element e of the
-        // thread's i-th vector.  A super-tile that keeps more than the staging buffers hold (only when
-        // most of the tensor is kept) falls back to one scan per 1024-vector row.
-        constexpr int64_t SUPER = int64_t(FUSED_RES) * SEL_THREADS;
-        auto fetch = [&](u32x4 (&pre)[FUSED_RES], int64_t sb) {       // vectors [sb, sb + SUPER) n [.., v1), clamped loads
-    #pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i)
-                pre[i] = (sb < v1) ? xv[min(sb + int64_t(i) * SEL_THREADS + tid, v1 - 1)] : u32x4{0, 0, 0, 0};
-        };
-        u32x4 pre[FUSED_RES];
-        if (nres == 0 && v0 < v1) {            // nothing was parked (the staged form was abandoned): fetch the first super-tile now
-            fetch(pre, v0);
-    #pragma unroll
+        const int64_t mine0 = int64_t(tid) * rows;                    // first vector of this thread
+        unsigned long long gtm = 0, eqm = 0;
+#pragma nounroll
+        for (int i = 0; i < rows; ++i) {
+            if (mine0 + i < count) {
+                uint32_t g = 0, q = 0;
+                for_each_raw(uint32_t(0), res[mine0 + i], [&](uint32_t raw, int e) {
+                    const uint32_t key = raw & MASK;
+                    g |= (key > t ? 1u : 0u) << e;
+                    q |= (key == t ? 1u : 0u) << e;
+                });
+                gtm |= static_cast<unsigned long long>(g) << (i * VEC);
+                eqm |= static_cast<unsigned long long>(q) << (i * VEC);
+            }
+        }
+        uint32_t ex_gt, ex_eq, tot_gt, tot_eq;
+        block_exclusive_scan2<SEL_THREADS>(__builtin_popcountll(gtm), __builtin_popcountll(eqm), wave_tot2, ex_gt, ex_eq,
+                                           tot_gt, tot_eq);
+        const uint32_t part_first = run_gt + min(run_eq, m);
+        const uint32_t part_kept = (run_gt + tot_gt) + min(run_eq + tot_eq, m) - part_first;
+        if (part_kept <= uint32_t(TILE)) {                             // uniform over the workgroup
+            uint32_t my_gt = run_gt + ex_gt, my_eq = run_eq + ex_eq;
+            const uint32_t *res_raw = reinterpret_cast<const uint32_t *>(res);
+            unsigned long long todo = gtm | eqm;
+            while (todo) {
+                const int b = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const bool gt = (gtm >> b) & 1ull;
+                if (gt || my_eq < m) {
+                    const uint32_t slot = my_gt + min(my_eq, m) - part_first;
+                    const uint32_t off = static_cast<uint32_t>(mine0) * VEC + b;
+                    stage_val[slot] = res_raw[off];
+                    stage_idx[slot] = static_cast<int32_t>(sb * VEC + off);
+                }
+                my_gt += gt ? 1u : 0u;
+                my_eq += gt ? 0u : 1u;
+            }
+            run_gt += tot_gt;
+            run_eq += tot_eq;
+            __syncthreads();
+            for (uint32_t q = tid; q < part_kept; q += SEL_THREADS)
+                if (part_first + q < k) {          // always true for consistent counts
+                    vals[part_first + q] = stage_val[q];
+                    idx[part_first + q] = stage_idx[q];
+                }
+        } else {
+            for (int i = 0; i < rows; ++i) {       // row by row; a row's scan starts with a barrier, which frees the staging buffers
+                const int64_t v = sb + int64_t(i) * SEL_THREADS + tid;
+                emit_tile(res[i * SEL_THREADS + tid], v, v < v1);
+            }
+        }
+        if (more) {
+            __syncthreads();                       // everybody is done with this super-tile's vectors and staging
+#pragma unroll
             for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = pre[i];
             __syncthreads();
-        }
-        for (int64_t sb = v0; sb < v1; sb += SUPER) {
-            const int64_t count = min<int64_t>(v1 - sb, SUPER);          // vectors of this super-tile, all in `res`
-            const int rows = static_cast<int>((count + SEL_THREADS - 1) / SEL_THREADS);
-            const bool more = sb + SUPER < v1;
-            if (more) fetch(pre, sb + SUPER);
-            const int64_t mine0 = int64_t(tid) * rows;                    // first vector of this thread
-            unsigned long long gtm = 0, eqm = 0;
-    #pragma nounroll
-            for (int i = 0; i < rows; ++i) {
-                if (mine0 + i < count) {
-                    uint32_t g = 0, q = 0;
-                    for_each_raw(RAW(0), res[mine0 + i], [&](uint32_t raw, int e) {
-                        const uint32_t key = raw & MASK;
-                        g |= (key > t ? 1u : 0u) << e;
-                        q |= (key == t ? 1u : 0u) << e;
-                    });
-                    gtm |= static_cast<unsigned long long>(g) << (i * VEC);
-                    eqm |= static_cast<unsigned long long>(q) << (i * VEC);
-                }
-            }
-            uint32_t ex_gt, ex_eq, tot_gt, tot_eq;
-            block_exclusive_scan2<SEL_THREADS>(__builtin_popcountll(gtm), __builtin_popcountll(eqm), wave_tot2, ex_gt, ex_eq,
-                                               tot_gt, tot_eq);
-            const uint32_t part_first = run_gt + min(run_eq, m);
-            const uint32_t part_kept = (run_gt + tot_gt) + min(run_eq + tot_eq, m) - part_first;
-            // 16-bit elements are staged as ONE word each, value << 16 | position within the super-tile,
-            // so the staging area holds half as many again (a super-tile that keeps a fifth of its
-            // elements still fits) and the scatter issues one LDS store per kept element.
-            constexpr bool PACKED = !F32;
-            static_assert(F32 || SUPER * VEC <= 65536, "a position within a super-tile fits 16 bits");
-            constexpr uint32_t STAGE_CAP = PACKED ? uint32_t(TILE + TILE / 2) : uint32_t(TILE);
-            if (part_kept <= STAGE_CAP) {                                  // uniform over the workgroup
-                uint32_t my_gt = run_gt + ex_gt, my_eq = run_eq + ex_eq;
-                const RAW *res_raw = reinterpret_cast<const RAW *>(res);
-                uint32_t *stage_pk = smem;
-                unsigned long long todo = gtm | eqm;
-                while (todo) {
-                    const int b = __builtin_ctzll(todo);
-                    todo &= todo - 1;
-                    const bool gt = (gtm >> b) & 1ull;
-                    if (gt || my_eq < m) {
-                        const uint32_t slot = my_gt + min(my_eq, m) - part_first;
-                        const uint32_t off = static_cast<uint32_t>(mine0) * VEC + b;
-                        if constexpr (PACKED) {
-                            stage_pk[slot] = (static_cast<uint32_t>(res_raw[off]) << 16) | off;
-                        } else {
-                            stage_val[slot] = res_raw[off];
-                            stage_idx[slot] = static_cast<int32_t>(sb * VEC + off);
-                        }
-                    }
-                    my_gt += gt ? 1u : 0u;
-                    my_eq += gt ? 0u : 1u;
-                }
-                run_gt += tot_gt;
-                run_eq += tot_eq;
-                __syncthreads();
-                for (uint32_t q = tid; q < part_kept; q += SEL_THREADS)
-                    if (part_first + q < k) {          // always true for consistent counts
-                        if constexpr (PACKED) {
-                            const uint32_t w = stage_pk[q];
-                            vals[part_first + q] = static_cast<RAW>(w >> 16);
-                            idx[part_first + q] = static_cast<int32_t>(sb * VEC + (w & 0xFFFFu));
-                        } else {
-                            vals[part_first + q] = stage_val[q];
-                            idx[part_first + q] = stage_idx[q];
-                        }
-                    }
-            } else {
-                for (int i = 0; i < rows; ++i) {       // row by row; a row's scan starts with a barrier, which frees the staging buffers
-                    const int64_t v = sb + int64_t(i) * SEL_THREADS + tid;
-                    emit_tile(res[i * SEL_THREADS + tid], v, v < v1);
-                }
-            }
-            if (more) {
-                __syncthreads();                       // everybody is done with this super-tile's vectors and staging
-    #pragma unroll
-                for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = pre[i];
-                __syncthreads();
-            }
         }
     }
     STAMP(7);
     if (last_chunk && tid == 0) {
         for (int64_t i = nvf * VEC; i < numel; ++i) {
-            const RAW raw = x[i];
+            const uint32_t raw = x[i];
             const uint32_t key = raw & MASK;
             if (key > t) {
                 keep(run_gt + min(run_eq, m), raw, i);
@@ -1578,35 +1729,43 @@ select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64
                     uint32_t *hist0, uint32_t *hist1, uint32_t *table, RAW *__restrict__ vals,
                     int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen)
 {
-    const SelOutcome outcome =
-        select_fused_body<RAW>(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen);
-    // Exit protocol: one atomic per workgroup counts the leavers and, in the high half, those that
-    // gave up at a barrier.  The last to leave sees whether anybody did.  Everything the others stored
-    // to the outputs before leaving is either final or missing, never wrong, and the serial pass below
-    // uses no workspace, so it needs no ordering against their remaining traffic.
-    // A workgroup that never saw the exchange area published (workgroup 0, although dispatched first,
-    // did not get through its first few microseconds within the waiting time: not expected to happen)
-    // cannot rely on the counter either and simply redoes the selection itself; several doing so
-    // write identical bytes.
+    ExitReport rep;
+    rep.mine = 0u;
+    SelOutcome outcome;
+    if constexpr (sizeof(RAW) == 2)
+        outcome = select16_body(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, rep);
+    else
+        outcome = select32_body(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen, rep);
+    // Exit protocol: every workgroup reports once, when it is past its last grid barrier or gives up at one (the high
+    // half counts those).  Whoever's report completes the count sees whether anybody gave up, and
+    // then redoes the selection alone when it leaves.  Everything the others store to the outputs is either final or
+    // missing, never wrong, and the serial pass below uses no workspace, so it needs no ordering against their
+    // remaining traffic (both write the same bytes).
+    // A workgroup that cannot rely on the count redoes the selection itself, several doing so write identical bytes:
+    // one that never saw the exchange area published (workgroup 0, although dispatched first, did not get through its
+    // first few microseconds within the waiting time: not expected to happen), or one that gave up at a barrier of the
+    // retry after a missed prediction, when it had already reported (its group's report may then still be its own to pass on).
     extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
     __shared__ uint32_t s_redo;
     __shared__ uint32_t s_wave_tot[SEL_THREADS / WAVE];
     __shared__ uint32_t s_bcast[2];
+    const bool alone = outcome == SEL_NEVER_READY || (outcome == SEL_GAVE_UP && rep.mine != 0);
+    if (outcome == SEL_GAVE_UP && rep.mine == 0)
+        report_past_barriers(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off), rep, true);
+    if (rep.mine != 0) report_group(st, rep);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        s_redo = 1u;
-        if (outcome != SEL_NEVER_READY) {
-            const uint32_t mine = outcome == SEL_DONE ? 1u : 0x10001u;
-            const uint32_t seen = __hip_atomic_fetch_add(&st->exited, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
-            const bool last = (seen & 0xFFFFu) == gridDim.x;
-            s_redo = (last && (seen >> 16) != 0) ? 1u : 0u;
-            if (last) {
-                // Nobody looks at the exchange area any more: un-publish it, so that the next launch that carries the
-                // same generation number (a replay of a captured graph) cannot take this call's leftovers for its own.
-                dev_store64(&st->ready, 0ull);
-                if (s_redo) dev_store(&st->redo, 1u);
-            }
+    if (threadIdx.x == REPORT_TID) {
+        const uint32_t seen = rep.mine != 0 && rep.group != 0 ? rep.common + rep.group : 0u;
+        const bool last = (seen & 0xFFFFu) == gridDim.x;
+        const bool redo = alone || (last && (seen >> 16) != 0);
+        // The last report: nobody will look at the published word any more.  Take it back, so that the next launch that
+        // carries the same generation number (a replay of a captured graph) cannot take this call's leftovers for its own.
+        if (last) {
+            dev_store64(&st->ready, 0ull);
+            dev_store64(&st->ready_hist, 0ull);
         }
+        if (redo) dev_store(&st->redo, 1u);
+        s_redo = redo ? 1u : 0u;
     }
     __syncthreads();
     if (s_redo)
@@ -1736,13 +1895,10 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
     // Preferred: one persistent kernel, one workgroup per compute unit.
     if (mode != 1) {
         constexpr int VEC = KeyTraits<RAW>::VEC;
-        constexpr int TILE_WORDS = SEL_THREADS * VEC + SEL_THREADS * VEC * int(sizeof(RAW)) / 4;
-        constexpr int HIST_WORDS = (sizeof(RAW) == 4 ? (1 << 13) : (1 << 11)) + 2 * WAVE;
-        constexpr size_t parked_bytes = size_t(FUSED_RES) * SEL_THREADS * 16 +
-                                        4 * size_t(TILE_WORDS > HIST_WORDS ? TILE_WORDS : HIST_WORDS);
-        static_assert(parked_bytes <= FUSED_SMEM_BYTES, "both LDS layouts fit");
-        // 16-bit types: everything the compute unit has, the staged form's segments take what the layouts leave
-        constexpr size_t smem_bytes = sizeof(RAW) == 2 ? FUSED_SMEM_BYTES : parked_bytes;
+        // fp32: the parked chunk head, then the digit histogram or the compaction's staging buffers
+        constexpr size_t parked_bytes = size_t(FUSED_RES) * SEL_THREADS * 16 + 4 * size_t(std::max((1 << 13) + 2 * WAVE, 2 * SEL_THREADS * VEC));
+        constexpr size_t smem_bytes = sizeof(RAW) == 2 ? ST_SMEM_BYTES : parked_bytes;
+        static_assert(smem_bytes <= 156 * 1024, "of the 160 KB of a compute unit; the rest is static");
         static_assert(size_t(FUSED_RES) * SEL_THREADS * 16 >= 4 * ((size_t(1) << 13) + 2 * WAVE),
                       "the serial fallback keeps its histogram where the chunk head was parked");
         // how many workgroups of this kernel each device holds at once (asked once per element type and device)
@@ -1901,7 +2057,7 @@ extern "C" dropit_status dropit_compress(const void *x, const int64_t *shape, in
 }
 
 // ---- dropit_compress for callers that cannot allocate ----------------------------------------------
-// The select's exchange area (state, histograms, per-chunk table: SelWorkspace::bytes, about 170 KB, the
+// The select's exchange area (state, histograms, per-chunk table: SelWorkspace::bytes, about 200 KB, the
 // same for every tensor size) as a device array of this library instead of a caller's workspace.  In
 // host code `scratch` is only a handle for the runtime: the array's device address is asked for once
 // per device (each device holds its own copy) and that pointer is what the kernels get.

@@ -1,0 +1,55 @@
+"""GPU: the forms of the persistent select for 16-bit tensors at the sizes and densities where they change over -- the
+smallest tensors it takes, wavefront ranges that end inside a row of 512 elements, staging segments that overflow (part of
+the tensor is read twice), and ties whose budget runs out inside one wavefront -- bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_13808_amd as dropit
+from dropit_inputs import activation, f32_to_bf16_bits
+from gpu_util import to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def run(x, gamma):
+    xd = to_device(x)
+    ws = torch.full((dropit.compress_workspace_bytes(x.size, xd.dtype),), 0x5A, dtype=torch.uint8, device="cuda:0")
+    k = oracle.keep_count(x.size, gamma)
+    want_v, want_i = oracle.compress(x, k)
+    vals, idx = dropit.compress(xd, gamma, workspace=ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(idx), want_i) and to_host(vals).tobytes() == want_v.tobytes(), (x.size, gamma)
+    state = ws[:64].cpu().numpy().view(np.uint32)
+    return int(state[10] & 0xFFFF), int(state[15])          # workgroups, those that read the tensor once
+
+
+@pytest.mark.parametrize("numel", [65544, 65551, 8 * (8192 + 64) + 3, 131072, 300001, 524288 + 8 * 65, 1 << 20, (1 << 21) - 5])
+@pytest.mark.parametrize("dist", ["normal", "relu", "gelu"])
+def test_mid_sizes(numel, dist):
+    x = activation((numel,), dist, 3 + numel % 101, "bf16")
+    for gamma in (0.9, 0.6, 0.999, 0.02):
+        print("select mid", numel, dist, gamma, run(x, gamma), flush=True)
+
+
+@pytest.mark.parametrize("numel,gamma", [(9000011, 0.05), (12000000, 0.3), (4 * (1 << 20) + 8 * 333, 0.0)])
+def test_segments_overflow(numel, gamma):
+    """More candidates than the staging segments hold in (nearly) every workgroup."""
+    groups, once = run(activation((numel,), "normal", 5, "bf16"), gamma)
+    print("select overflow", numel, gamma, groups, once, flush=True)
+    assert groups > 1 and (once < groups or numel < 7800000)
+
+
+@pytest.mark.parametrize("numel", [300003, (1 << 21) + 777])
+def test_tie_budget_runs_out_at_any_wavefront(numel):
+    """A handful of magnitudes, so that the kept ties end in the first, a middle and the last wavefronts of the tensor."""
+    rng = np.random.default_rng(numel)
+    x = f32_to_bf16_bits(rng.choice(np.array([0.5, -0.5, 1.0, -2.0, 0.0], dtype=np.float32), size=numel))
+    mag = (x & 0x7FFF)
+    big = int((mag > 0x3F00).sum())
+    ties = int((mag == 0x3F00).sum())
+    for m in (1, 2, ties // 3, ties // 2, ties - 1, ties):
+        gamma = 1.0 - (big + m + 0.5) / numel
+        assert oracle.keep_count(numel, gamma) == big + m
+        run(x, gamma)
