@@ -17,7 +17,8 @@
 // In NHWC dY is token-major already; in NCHW a tiled transposition makes it so.  The 3x3 / stride 1
 // / pad 1 NCHW case has kernels of its own (wgrad_conv_mfma.hip, wgrad_conv_gemm.hip) that never
 // materialise the nine-fold B; this path serves everything else: 1x1, strided, dilated, large-window
-// (patch embedding) convolutions, and channels-last tensors.
+// (patch embedding) convolutions, and channels-last tensors.  A 1x1 / stride 1 / unpadded NCHW convolution needs no rows at
+// all where wgrad_conv_pointwise.hip takes it: its operands are multiplied as they lie.
 #include "wgrad_internal.hpp"
 #include "dev_hooks.hpp"
 #include <cstdlib>
@@ -346,6 +347,8 @@ ConvIm2colPlan conv_im2col_plan(const ConvGeneral &p)
     const int64_t per_unit = p.nhwc ? p.C : taps;             // columns per unit
     plan.tiled = false;
     plan.rowptr_bytes = 0;
+    plan.pointwise = conv_pointwise_preferred(p);
+    if (plan.pointwise) plan.pw = conv_pointwise_plan(p);
     int64_t blk = units_total, rowlen = plan.gemm.pitch;
     if (p.C % 8 == 0) {
         blk = (128 + per_unit - 1) / per_unit;                // 128 elements = 256 bytes
@@ -392,6 +395,7 @@ bool conv_im2col_supported(const ConvGeneral &p)
 dropit_status conv_im2col_run(const ConvGeneral &p, const ConvIm2colPlan &plan, const void *vals, const int32_t *idx,
                               const void *dY, float *dW, char *ws, hipStream_t stream)
 {
+    if (plan.pointwise) return conv_pointwise_run(p, plan.pw, vals, idx, dY, dW, ws, stream);
     uint16_t *B = reinterpret_cast<uint16_t *>(ws);
     float *partial = reinterpret_cast<float *>(ws + plan.gemm.dense_bytes);
     uint16_t *dYt = reinterpret_cast<uint16_t *>(ws + plan.gemm.dense_bytes + plan.gemm.partial_bytes);

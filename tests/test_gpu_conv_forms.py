@@ -1,0 +1,76 @@
+"""GPU: the forms of the bf16 convolution gradient that keep no im2col rows, at the edges of their tiles and segments,
+element by element against the fp64 product of the recovered tensor.
+
+Bound per element: the products of bf16 numbers are exact in fp32, and an fp32 sum of n of them, in any order and with
+any grouping, is within n * 2^-24 of the exact sum relative to the sum of the terms' magnitudes.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_13808_amd as dropit
+from dropit_inputs import activation, f32_to_bf16_bits, gradient
+from gpu_util import to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+POINT = (1, 1, 1, 1, 0, 0, 1, 1)
+
+
+def dense_dw(xh, g, geom):
+    """dW [J][C][kh][kw] of NCHW operands in fp64, a tap at a time."""
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    N, C, H, W = xh.shape
+    _, J, OH, OW = g.shape
+    xp = np.zeros((N, C, H + 2 * ph, W + 2 * pw))
+    xp[:, :, ph:ph + H, pw:pw + W] = xh
+    flat = np.ascontiguousarray(g.transpose(1, 0, 2, 3)).reshape(J, -1).astype(np.float64)
+    out = np.zeros((J, C, kh, kw))
+    for u in range(kh):
+        for v in range(kw):
+            win = xp[:, :, u * dh:u * dh + (OH - 1) * sh + 1:sh, v * dw:v * dw + (OW - 1) * sw + 1:sw]
+            out[:, :, u, v] = flat @ np.ascontiguousarray(win.transpose(1, 0, 2, 3)).reshape(C, -1).T
+    return out
+
+
+def check(x, dy, gamma, J, geom, layout="nchw"):
+    xd, dyd = to_device(x), to_device(dy)
+    vals, idx = dropit.compress(xd, gamma)
+    dW = dropit.weight_grad(vals, idx, x.shape, dyd, J, conv=geom, layout=layout)
+    again = dropit.weight_grad(vals, idx, x.shape, dyd, J, conv=geom, layout=layout)
+    torch.cuda.synchronize()
+    assert torch.equal(dW, again)
+    xh = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, gamma)), x.shape)
+    g = oracle.widen(dy)
+    if layout == "nhwc":
+        xh, g = xh.transpose(0, 3, 1, 2), g.transpose(0, 3, 1, 2)
+    ref, size = dense_dw(xh, g, geom), dense_dw(np.abs(xh), np.abs(g), geom)
+    got = to_host(dW).astype(np.float64)
+    if layout == "nhwc":
+        got = got.transpose(0, 3, 1, 2)
+    nu = (g.shape[0] * g.shape[2] * g.shape[3] + 256) * 2.0 ** -24     # the terms of a sum, and the slices that meet in it
+    excess = np.abs(got - ref) - nu / (1 - nu) * size
+    assert excess.max() <= 0.0, excess.max()
+
+
+@pytest.mark.parametrize("shape,J,gamma", [
+    ((1, 3, 4, 4), 8, 0.6), ((9, 65, 4, 8), 72, 0.9), ((17, 64, 6, 6), 64, 0.7),      # many planes to a unit, one of them not full
+    ((3, 63, 14, 14), 136, 0.8), ((2, 24, 15, 34), 264, 0.8),                           # rows of dY at 8- and 4-byte boundaries
+    ((2, 130, 16, 32), 520, 0.9), ((1, 16, 27, 38), 40, 0.9),                           # one and three segments; output channels in two blocks
+    ((2, 40, 56, 56), 64, 0.5), ((1, 8, 64, 130), 16, 0.95)])
+def test_pointwise_nchw(shape, J, gamma):
+    print("pointwise", shape, J, gamma, flush=True)
+    x = activation(shape, "relu", 31 + shape[2], "bf16")
+    check(x, gradient((shape[0], J, shape[2], shape[3]), 0.02, 32 + J, "bf16"), gamma, J, POINT)
+
+
+@pytest.mark.parametrize("shape", [(3, 70, 28, 28), (9, 16, 8, 8)])
+def test_pointwise_with_crowded_channels(shape):
+    """Runs many times longer than an even spread gives, beside empty ones."""
+    print("pointwise crowded", shape, flush=True)
+    rng = np.random.default_rng(5)
+    x = (rng.standard_normal(shape) * 0.01).astype(np.float32)
+    x[:, ::9] += 4.0
+    x[1, 3] = 0.0
+    check(f32_to_bf16_bits(x), gradient((shape[0], 24, shape[2], shape[3]), 0.02, 33, "bf16"), 0.85, 24, POINT)
