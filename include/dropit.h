@@ -158,9 +158,9 @@ typedef DROPIT_ENUM(dropit_wgrad_path) {
     DROPIT_PATH_NONE = 0,
     DROPIT_PATH_FC_MFMA = 1,        /* recover + split-K bf16 MFMA GEMM */
     DROPIT_PATH_CONV_BANDS = 2,     /* 3x3/s1/p1 bf16: row bands in LDS, implicit im2col on the matrix cores */
-    DROPIT_PATH_CONV_GEMM = 3,      /* 3x3/s1/p1 bf16, small planes with many channels: explicit im2col rows + the FC GEMM */
+    DROPIT_PATH_CONV_GEMM = 3,      /* 3x3/s1/p1 bf16, small planes with many channels: the FC GEMM over token-major operands, read through the window */
     DROPIT_PATH_FMA = 4,            /* exact fp32 multiply-adds on the fp32 matrix instructions (fp32 inputs, odd shapes) */
-    DROPIT_PATH_CONV_IM2COL = 5,    /* bf16, any geometry and either layout: zero-filled im2col rows written from the pairs + the FC GEMM */
+    DROPIT_PATH_CONV_IM2COL = 5,    /* bf16, any geometry and either layout: the FC GEMM over im2col rows written from the pairs, or, where the layout allows, over the operands as they lie */
     DROPIT_PATH_FC_SMALL = 6,       /* fully-connected layers of at most 16384 input elements: recover in LDS and exact fp32 multiply-adds, one launch */
     DROPIT_PATH_FC_FUSED = 7        /* the FC_MFMA product with the recover step inside it (only after dropit_set_fc_recover(1)) */
 } dropit_wgrad_path;

@@ -98,6 +98,64 @@ splitk_sum_wide_kernel(const f32x4 *__restrict__ partial, int splits, int M, int
     }
 }
 
+// The same sum where the product's columns are (tap, channel) of a 3 x 3 convolution and dW's are (channel, tap).  A
+// workgroup takes eight rows and 32 channels of all nine taps, a wavefront a tap of them; the sums, in ascending split
+// order, change places in LDS and leave as whole runs of 288 floats per row.  (Four-byte stores 36 bytes apart straight
+// from the sums cost 8 us of a 45 us call: 16 images of 512 -> 512 channels at 8 x 8.)  DEPTH slices are in flight
+// per thread: sixteen where a result of few tiles is cut into up to fifty of them, few where there are few, for the
+// wavefronts that the registers then leave room for.
+constexpr int SUM_TAPS = 9, SUM_CHANNELS = 32;
+template <typename C, int DEPTH>
+__global__ void __launch_bounds__(64 * SUM_TAPS)
+splitk_sum_taps_kernel(const f32x4 *__restrict__ partial, int splits, int M, int channels, int nb_count, int mb_count,
+                       float *__restrict__ dW)
+{
+    constexpr int TILE4 = C::BM * C::BN / 4, ROW = SUM_TAPS * SUM_CHANNELS;
+    __shared__ __attribute__((aligned(16))) float turn[8][ROW];
+    const int cblocks = (channels + SUM_CHANNELS - 1) / SUM_CHANNELS;
+    const int c0 = int(blockIdx.x % unsigned(cblocks)) * SUM_CHANNELS, m0 = int(blockIdx.x / unsigned(cblocks)) * 8;
+    const int tap = threadIdx.x >> 6, half = (threadIdx.x >> 5) & 1, l32 = threadIdx.x & 31;
+    const int cw = min(SUM_CHANNELS, channels - c0);                // a multiple of 8
+    if (l32 < cw) {
+        const int n = tap * channels + c0 + l32;
+        const int nb = n / C::BN, nr = n % C::BN, wn = nr / C::WN, j = (nr % C::WN) / 32;
+        const int mb = m0 / C::BM, mr = m0 % C::BM, wm = mr / C::WM, i = (mr % C::WM) / 32, q = (mr % 32) / 8;
+        const int64_t total = int64_t(nb_count) * mb_count * TILE4;
+        const f32x4 *src = partial + int64_t(mb * nb_count + nb) * TILE4 + ((i * C::FN + j) * 4 + q) * C::NTHREADS +
+                           (wm * C::WAVES_N + wn) * 64 + half * 32 + (nr & 31);
+        f32x4 s = src[0];
+        for (int p0 = 1; p0 < splits; p0 += DEPTH) {
+            f32x4 part[DEPTH];
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u)
+                if (p0 + u < splits) part[u] = src[(p0 + u) * total];
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u)
+                if (p0 + u < splits) s += part[u];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) turn[half * 4 + e][l32 * SUM_TAPS + tap] = s[e];
+    }
+    __syncthreads();
+    const int row = threadIdx.x / (ROW / 4), at = threadIdx.x % (ROW / 4) * 4;      // 8 x 72 threads of four floats
+    if (m0 + row < M && at < cw * SUM_TAPS)
+        *reinterpret_cast<f32x4 *>(dW + (int64_t(m0 + row) * channels + c0) * SUM_TAPS + at) =
+            *reinterpret_cast<const f32x4 *>(&turn[row][at]);
+}
+
+template <typename C>
+inline void launch_splitk_sum_taps(const float *partial, int splits, int M, int channels, int nb_count, int mb_count,
+                                   float *dW, hipStream_t stream)
+{
+    const int64_t blocks = int64_t((M + 7) / 8) * ((channels + SUM_CHANNELS - 1) / SUM_CHANNELS);
+    auto launch = [&](auto kernel) {
+        kernel<<<int(blocks), 64 * SUM_TAPS, 0, stream>>>(reinterpret_cast<const f32x4 *>(partial), splits, M, channels,
+                                                          nb_count, mb_count, dW);
+    };
+    if (splits > 6) launch(splitk_sum_taps_kernel<C, 16>);
+    else launch(splitk_sum_taps_kernel<C, 5>);
+}
+
 // Adds the partials of `splits` > 1 slices into dW.
 template <typename C>
 inline void launch_splitk_sum(const float *partial, int splits, int M, int N, int nb_count, int mb_count, float *dW,

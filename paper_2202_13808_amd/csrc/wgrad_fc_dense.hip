@@ -217,14 +217,18 @@ constexpr int FUSE_STAGE_WORDS = 1024;            // words of a tile staged per 
 constexpr int FUSE_SLOTS = 4;                     // staging slots: tile t uses slot t % 4 (tiles s + 2 .. s + 4 are in flight at step s)
 constexpr int FUSE_LDS_BYTES = FUSE_SLOTS * FUSE_STAGE_WORDS * 4 + 512 * 4;     // + a spare word per thread
 
-template <typename C, bool FUSED, bool PP = false>
+// WIN: column n of token t is an element under the window of output position t, read from the recovered input itself
+// (see ConvWindow): the nine-fold rows of a 3 x 3 convolution are never written.  A 16-byte unit of a B row is eight
+// channels of one tap, so a direct load's lane keeps its tap and channel for the whole slice and only moves its output
+// position on by a token block per step: some twenty vector instructions per B load, behind the matrix instructions.
+template <typename C, bool FUSED, bool PP = false, bool WIN = false>
 __global__ void __launch_bounds__(C::NTHREADS) __attribute__((amdgpu_waves_per_eu(C::WPE, C::WPE)))
 fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd, int64_t ntok, int M, int N,
                 int pitch, int nb_count, int mb_count, int nkb, int splits,
                 float *__restrict__ out /* dW or partials [splits][M][N] */,
                 const uint32_t *__restrict__ packed /* FUSED: the tiles' words */,
                 const uint32_t *__restrict__ tile_ptr /* FUSED: [(nkb + 6) * nb_count + 1] first word of each tile, then slack */,
-                uint32_t kpairs)
+                uint32_t kpairs, ConvWindow win /* WIN */)
 {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK;
     static_assert(!FUSED || (C::NTHREADS == 512 && BN == 256 && BK == 32 && C::EARLY && C::STAGES == 4),
@@ -289,6 +293,59 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
         const int n = min(n0 + b / 2, pitch - 8);
         b_off[i] = FUSED ? 0u : uint32_t(r * pitch + n) * 2u;
     }
+    // WIN: this lane's token of B load i, the input position its tap reads there, that element's byte offset, and the
+    // offset the next load takes (the element, or the row of zeros)
+    constexpr int WL = WIN ? C::B_LOADS : 1;
+    int win_t[WL], win_x[WL], win_y[WL], win_xend[WL], win_yend[WL];
+    uint32_t win_off[WL], win_sel[WL];
+    // the next block: its offsets into win_sel, then the state moves on by a token block.  Selects only, no branches
+    auto win_next = [&]() {
+        if constexpr (WIN) {
+#pragma unroll
+            for (int i = 0; i < C::B_LOADS; ++i) {
+                uint32_t sel = win_t[i] < int(ntok) ? win_off[i] : win.zero_row;
+                sel = uint32_t(win_y[i]) < uint32_t(win.H) ? sel : win.zero_row;
+                win_sel[i] = uint32_t(win_x[i]) < uint32_t(win.W) ? sel : win.zero_row;
+                win_t[i] += BK;
+                const int x = win_x[i] + win.adv_x, y = win_y[i] + win.adv_y;
+                const uint32_t off = win_off[i] + win.adv;
+                const bool row_end = x >= win_xend[i];
+                win_x[i] = row_end ? x - win.row_step : x;
+                const int y1 = row_end ? y + win.sh : y;
+                const uint32_t off1 = row_end ? off + win.carry_x : off;
+                const bool image_end = y1 >= win_yend[i];
+                win_y[i] = image_end ? y1 - win.image_step : y1;
+                win_off[i] = image_end ? off1 + win.carry_y : off1;
+            }
+        }
+    };
+    auto win_pin = [&]() {                             // keeps win_next between two of these
+        if constexpr (WIN) {
+#pragma unroll
+            for (int i = 0; i < C::B_LOADS; ++i)
+                asm volatile("" : "+v"(win_t[i]), "+v"(win_x[i]), "+v"(win_y[i]), "+v"(win_off[i]), "+v"(win_sel[i]));
+        }
+    };
+    if constexpr (WIN) {
+#pragma unroll
+        for (int i = 0; i < C::B_LOADS; ++i) {
+            const int o = (wave * C::B_LOADS + i) * 1024 + lane * 16;
+            const int r = o / C::ROW_B;
+            const int n = min(n0 + ((o % C::ROW_B) ^ ((r & 3) << 6)) / 2, N - 8);
+            const int tap = n / win.C, c = n - tap * win.C, u = tap / win.kw, v = tap - u * win.kw;
+            const int t = kb_begin * BK + r, plane = win.OH * win.OW;
+            const int img = t / plane, pos = t - img * plane, oy = pos / win.OW;
+            win_t[i] = t;
+            win_y[i] = oy * win.sh + u * win.dh - win.ph;
+            win_x[i] = (pos - oy * win.OW) * win.sw + v * win.dw - win.pw;
+            win_yend[i] = win.image_step + u * win.dh - win.ph;
+            win_xend[i] = win.row_step + v * win.dw - win.pw;
+            const int row = (img * win.H + win_y[i]) * win.W + win_x[i];
+            win_off[i] = (uint32_t(row) * uint32_t(win.C) + uint32_t(c)) * 2u;     // (modulo 2^32; used inside the input only)
+        }
+        win_next();
+    }
+    (void)win_pin; (void)win_x; (void)win_y; (void)win_t; (void)win_xend; (void)win_yend; (void)win_off; (void)win_sel;
     // FUSED: first word of the tile whose words are being staged this step (tile s + 4), and the staging slot
     char *stg = lds + C::LDS_BYTES;                    // [FUSE_SLOTS][FUSE_STAGE_WORDS] words behind the stages
     uint32_t dma_start = 0;
@@ -313,6 +370,12 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
             __builtin_amdgcn_global_load_lds(DROPIT_GPTR(src + pk_off[i]),            // followed by a slot's worth of slack
                                              DROPIT_LPTR(stg + dma_slot * (FUSE_STAGE_WORDS * 4) + (i * C::NTHREADS + wave * 64) * 4),
                                              4, 0, 0);
+        } else if constexpr (WIN) {
+            // past the slice's last block the state goes on, to positions of the input or to the row of zeros; what these
+            // loads bring is never multiplied
+            constexpr int i = q - C::A_LOADS;
+            char *sb = lds + stage * C::STAGE_BYTES + C::A_BYTES + wave * (C::B_LOADS * 1024);
+            __builtin_amdgcn_global_load_lds(DROPIT_GPTR(reinterpret_cast<const char *>(xd) + win_sel[i]), DROPIT_LPTR(sb + i * 1024), 16, 0, 0);
         } else {
             constexpr int i = q - C::A_LOADS;
             const char *bbase = reinterpret_cast<const char *>(xd) + int64_t(kb) * BK * pitch * 2;
@@ -322,6 +385,7 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
     };
     auto issue_loads = [&](int stage, int kb) {
         static_for<0, STEP_LOADS>([&](auto q_) { issue_load(q_, stage, kb); });
+        win_next();
     };
     // ---- FUSED: the B tile of a step is zero-filled and the staged words placed, by hand-written LDS accesses
     // (the compiler would put vmcnt(0) in front of LDS accesses it knows about, see below) ----
@@ -540,7 +604,11 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
                 __builtin_amdgcn_sched_barrier(0);
                 workgroup_barrier();
                 __builtin_amdgcn_sched_barrier(0);
-                // C: the block's MFMAs, back to back, nothing between them
+                // C: the block's MFMAs, back to back, nothing between them but (WIN) the next block's addresses, three vector
+                // instructions behind each MFMA: in front of the loads they made M the longer phase (14 x 14, 256 channels:
+                // 29.8 us against 25.7)
+                win_pin();
+                win_next();
                 static_for<0, 2>([&](auto kk_) {
                     constexpr int kk = decltype(kk_)::value;
                     bf16x8 af[C::FM], bfv[C::FN];
@@ -557,9 +625,16 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
                     static_for<0, NM>([&](auto m_) {
                         constexpr int m = decltype(m_)::value, i = m / C::FN, j = m % C::FN;
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfv[j], acc[i][j], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (!WIN) __builtin_amdgcn_sched_barrier(0);
                     });
                 });
+                if constexpr (WIN)
+                    static_for<0, 2 * NM>([&](auto) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);       // three vector instructions
+                    });
+                win_pin();
+                __builtin_amdgcn_sched_barrier(0);
                 if (!(late && s + 1 == steps)) workgroup_barrier();
                 __builtin_amdgcn_sched_barrier(0);
                 stage = stage + 1 == C::STAGES ? 0 : stage + 1;
@@ -662,6 +737,7 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
                     substep(kk_, std::integral_constant<int, 0>{}, std::integral_constant<bool, C::EARLY>{}, next_base,
                             fill, load_kb);
             });
+            win_next();
             stage = next;
             fill = fill + 1 == C::STAGES ? 0 : fill + 1;
             if constexpr (FUSED) {
@@ -676,7 +752,7 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
     }
 
     // epilogue: acc[i][j][e] is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32 of its 32x32 block.
-    if (splits == 1) {                                  // straight into dW, row-major
+    if (splits == 1 && !(WIN && win.channel_major)) {   // straight into dW, row-major
 #pragma unroll
         for (int i = 0; i < C::FM; ++i)
 #pragma unroll
@@ -911,24 +987,32 @@ static bool fc_dense_attributes()
                hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgFused, true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, CfgFused::LDS_BYTES + FUSE_LDS_BYTES) == hipSuccess &&
                hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgNarrow, false>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgNarrow::LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<Cfg, false, true, true>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgNarrow, false, false, true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, CfgNarrow::LDS_BYTES) == hipSuccess;
     });
 }
 
-template <typename C, bool FUSED = false, bool PP = false>
+template <typename C, bool FUSED = false, bool PP = false, bool WIN = false>
 static dropit_status launch_gemm(const FcProblem &p, const FcDensePlan &plan, const void *dY, const uint16_t *dense,
                                  float *partial, float *dW, hipStream_t stream, const uint32_t *packed = nullptr,
-                                 const uint32_t *tile_ptr = nullptr)
+                                 const uint32_t *tile_ptr = nullptr, const ConvWindow &win = ConvWindow{})
 {
     const int total = plan.nb_count * plan.mb_count * plan.splits;
     const int grid = (total + 7) / 8 * 8;
-    float *out = plan.splits > 1 ? partial : dW;
-    fc_dense_kernel<C, FUSED, PP><<<grid, C::NTHREADS, C::LDS_BYTES + (FUSED ? FUSE_LDS_BYTES : 0), stream>>>(
+    if (WIN && win.channel_major && (win.taps != SUM_TAPS || win.C % 8 != 0)) return DROPIT_EINVAL;
+    const bool summed = plan.splits > 1 || (WIN && win.channel_major);
+    float *out = summed ? partial : dW;
+    fc_dense_kernel<C, FUSED, PP, WIN><<<grid, C::NTHREADS, C::LDS_BYTES + (FUSED ? FUSE_LDS_BYTES : 0), stream>>>(
         static_cast<const uint16_t *>(dY), dense, p.ntok, int(p.cout), int(p.cin), plan.pitch, plan.nb_count,
-        plan.mb_count, plan.nkb, plan.splits, out, packed, tile_ptr, uint32_t(std::max<int64_t>(p.k, 1)));
+        plan.mb_count, plan.nkb, plan.splits, out, packed, tile_ptr, uint32_t(std::max<int64_t>(p.k, 1)), win);
 
     trace_mark(stream);
-    if (plan.splits > 1)
+    if (WIN && win.channel_major)
+        launch_splitk_sum_taps<C>(partial, plan.splits, int(p.cout), win.C, plan.nb_count, plan.mb_count, dW, stream);
+    else if (summed)
         launch_splitk_sum<C>(partial, plan.splits, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count, dW, stream);
     trace_mark(stream);
     return launch_status();
@@ -941,6 +1025,56 @@ dropit_status fc_dense_gemm(const FcProblem &p, const FcDensePlan &plan, const v
     if (plan.narrow) return launch_gemm<CfgNarrow>(p, plan, dY, dense, partial, dW, stream);
     if (dev_env("DROPIT_GEMM_LOCKSTEP", 0)) return launch_gemm<Cfg>(p, plan, dY, dense, partial, dW, stream);
     return launch_gemm<Cfg, false, true>(p, plan, dY, dense, partial, dW, stream);
+}
+
+ConvWindow conv_window(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OH, int64_t OW, const dropit_conv2d &g,
+                       bool channel_major)
+{
+    ConvWindow w = {int(C), int(H), int(W), int(OH), int(OW), int(g.kw), int(g.stride_h), int(g.stride_w), int(g.pad_h),
+                    int(g.pad_w), int(g.dil_h), int(g.dil_w), int(g.kh * g.kw), channel_major, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int64_t plane = OH * OW, images = Cfg::BK / plane, rest = Cfg::BK % plane;
+    const int64_t rows = rest / OW, cols = rest % OW;
+    w.adv_y = int(rows * g.stride_h);
+    w.adv_x = int(cols * g.stride_w);
+    w.image_step = int(OH * g.stride_h);
+    w.row_step = int(OW * g.stride_w);
+    auto bytes = [&](int64_t rows, int64_t cols) { return uint32_t((rows * W + cols) * C * 2); };     // modulo 2^32
+    w.zero_row = bytes(N * H, 0);
+    w.adv = bytes(images * H + w.adv_y, w.adv_x);
+    w.carry_x = bytes(g.stride_h, -OW * g.stride_w);
+    w.carry_y = bytes(H - OH * g.stride_h, 0);
+    return w;
+}
+
+// whole 16-byte units of one tap; 32-bit byte offsets (the row of zeros included); a row in a recover workgroup's LDS
+bool conv_window_supported(int64_t N, int64_t C, int64_t H, int64_t W)
+{
+    return C % 8 == 0 && C <= RECOVER_ELEMS_MAX && (N * H * W + 1) * C * 2 <= int64_t(UINT32_MAX);
+}
+
+size_t conv_window_partial_bytes(const FcDensePlan &plan, bool channel_major)
+{
+    if (plan.splits > 1 || !channel_major) return plan.partial_bytes;
+    return size_t(plan.nb_count) * plan.mb_count * (plan.narrow ? CfgNarrow::BM * CfgNarrow::BN : Cfg::BM * Cfg::BN) * 4;
+}
+
+dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *vals, const int32_t *idx, int64_t k,
+                                  uint16_t *xd, hipStream_t stream)
+{
+    if (!fc_dense_attributes()) return DROPIT_EHIP;
+    const int64_t rows = N * w.H * w.W;
+    const int rows_per_wg = std::max(1, (w.C <= RECOVER_ELEMS ? RECOVER_ELEMS : RECOVER_ELEMS_MAX) / w.C);
+    launch_recover<uint16_t>(static_cast<const uint16_t *>(vals), idx, k, rows * w.C, rows, rows + 1, w.C, w.C, rows_per_wg,
+                             xd, stream);
+    return launch_status();
+}
+
+dropit_status conv_window_gemm(const FcProblem &p, const FcDensePlan &plan, const ConvWindow &w, const void *dY,
+                               const uint16_t *xd, float *partial, float *dW, hipStream_t stream)
+{
+    if (!fc_dense_attributes()) return DROPIT_EHIP;
+    if (plan.narrow) return launch_gemm<CfgNarrow, false, false, true>(p, plan, dY, xd, partial, dW, stream, nullptr, nullptr, w);
+    return launch_gemm<Cfg, false, true, true>(p, plan, dY, xd, partial, dW, stream, nullptr, nullptr, w);
 }
 
 dropit_status fc_dense_run(const FcProblem &p, const FcDensePlan &plan, const void *vals, const int32_t *idx,

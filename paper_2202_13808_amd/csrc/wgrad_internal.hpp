@@ -69,6 +69,30 @@ __device__ inline uint32_t quotient(uint32_t f, Divisor v)
     return q;
 }
 
+// A convolution's product with its operand rows read through the window: token t (output position) of the FC form has
+// the input elements under its window as columns (u, v, c), which are kh * kw runs of C consecutive elements of the
+// recovered input kept token-major, xd [N * H * W][C] followed by one row of zeros (what hangs over the padding reads
+// those).  C % 8 == 0.  channel_major: dW is [J][C][taps], else [J][taps][C].
+struct ConvWindow {
+    int C, H, W, OH, OW, kw, sh, sw, ph, pw, dh, dw, taps;
+    bool channel_major;
+    uint32_t zero_row;                         // byte offset of the row of zeros
+    int adv_y, adv_x;                          // input rows and columns a token block moves on by (beyond whole images)
+    int image_step, row_step;                  // input rows and columns that OH output rows, OW output columns move on by
+    uint32_t adv, carry_x, carry_y;            // bytes: a token block; the end of an output row; the end of an image
+};
+ConvWindow conv_window(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OH, int64_t OW, const dropit_conv2d &g,
+                       bool channel_major);
+bool conv_window_supported(int64_t N, int64_t C, int64_t H, int64_t W);
+inline size_t conv_window_bytes(int64_t N, int64_t C, int64_t H, int64_t W) { return round_up(size_t(N * H * W + 1) * C * 2, 256); }
+// bytes of `partial` for the product (a channel-major dW always goes through the slice sum, which reorders it)
+size_t conv_window_partial_bytes(const FcDensePlan &plan, bool channel_major);
+// xd from the pairs of an NHWC tensor; the product (dY token-major)
+dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *vals, const int32_t *idx, int64_t k,
+                                  uint16_t *xd, hipStream_t stream);
+dropit_status conv_window_gemm(const FcProblem &p, const FcDensePlan &plan, const ConvWindow &w, const void *dY,
+                               const uint16_t *xd, float *partial, float *dW, hipStream_t stream);
+
 // Row starts of the index-sorted pairs: row_ptr[r] = number of pairs whose flat index lies before row r, r = 0..R
 // (row_ptr[R] = k).  The tensor is a run of planes, a plane is cut into `nseg` rows of `seg` consecutive elements (the
 // last one may be shorter); one row per plane is the plain case of rows of equal length.  One pass over idx: every
@@ -151,14 +175,14 @@ ConvPlan conv_mfma_plan(const ConvProblem &p);
 dropit_status conv_mfma_run(const ConvProblem &p, const ConvPlan &plan, const void *vals, const int32_t *idx,
                             const void *dY, float *dW, char *ws, hipStream_t stream);
 
-// The same gradient as one GEMM over explicit im2col rows, for small planes with many channels
+// The same gradient as one GEMM over token-major operands, for small planes with many channels
 // (wgrad_conv_gemm.hip)
 struct ConvGemmPlan {
     FcProblem fp;                              // tokens = N*H*W output positions, c_in = 9*C taps, c_out = J
     FcDensePlan gemm;
-    int cb, cblocks;                           // input channels per im2col workgroup
-    size_t lds_bytes, dyt_bytes;
-    size_t total() const { return gemm.dense_bytes + gemm.partial_bytes + dyt_bytes; }
+    int cb, cblocks;                           // input channels per preparing workgroup
+    size_t lds_bytes, dyt_bytes, xd_bytes, partial_bytes;
+    size_t total() const { return xd_bytes + partial_bytes + dyt_bytes; }
 };
 bool conv_gemm_supported(const ConvProblem &p);
 bool conv_gemm_preferred(const ConvProblem &p);
@@ -188,11 +212,12 @@ struct ConvIm2colPlan {
     bool tiled;                                // im2col rows assembled in LDS tiles (else zero fill + scatter)
     int nblocks, blk, bands, rb, rowlen;       // tiled form: column blocks, their width, row bands, rows per band, tile row length
     size_t lds_bytes, rowptr_bytes;
-    bool pointwise;                            // the form without im2col rows takes this problem
+    bool pointwise, window;                    // the forms without im2col rows that take this problem
     PointwisePlan pw;
+    size_t xd_bytes;                           // window: the recovered input
     size_t total() const
     {
-        return pointwise ? pw.total() : gemm.dense_bytes + gemm.partial_bytes + dyt_bytes + rowptr_bytes;
+        return pointwise ? pw.total() : window ? xd_bytes + gemm.partial_bytes : gemm.dense_bytes + gemm.partial_bytes + dyt_bytes + rowptr_bytes;
     }
 };
 bool conv_pointwise_preferred(const ConvGeneral &p);

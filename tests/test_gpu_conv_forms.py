@@ -74,3 +74,28 @@ def test_pointwise_with_crowded_channels(shape):
     x[:, ::9] += 4.0
     x[1, 3] = 0.0
     check(f32_to_bf16_bits(x), gradient((shape[0], 24, shape[2], shape[3]), 0.02, 33, "bf16"), 0.85, 24, POINT)
+
+
+@pytest.mark.parametrize("shape,J,geom", [
+    ((5, 3, 4, 8), 8, (3, 3, 1, 1, 1, 1, 1, 1)), ((40, 1, 5, 24), 136, (1, 3, 1, 1, 0, 1, 1, 1)),     # planes below a token block of 32
+    ((7, 9, 9, 40), 264, (3, 3, 1, 1, 1, 1, 1, 1)), ((3, 33, 29, 16), 40, (3, 3, 2, 2, 1, 1, 1, 1)),
+    ((2, 20, 31, 72), 144, (5, 3, 1, 2, 2, 3, 1, 2)), ((1, 17, 64, 8), 64, (7, 7, 2, 1, 3, 0, 2, 3)),
+    ((2, 6, 6, 512), 128, (3, 3, 1, 1, 2, 2, 2, 2)), ((1, 8, 40, 24), 520, (3, 3, 1, 1, 0, 0, 1, 1)),
+    ((64, 14, 14, 64), 64, (3, 3, 1, 1, 1, 1, 1, 1))])
+def test_channels_last_window(shape, J, geom):
+    print("window nhwc", shape, J, geom, flush=True)
+    N, H, W, C = shape
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    x = activation(shape, "relu", 41 + H, "bf16")
+    assert dropit.weight_grad_path(shape, torch.bfloat16, x.size // 4, J, geom, layout="nhwc") == "conv_im2col"
+    check(x, gradient((N, OH, OW, J), 0.02, 42 + W, "bf16"), 0.7, J, geom, layout="nhwc")
+
+
+@pytest.mark.parametrize("shape,J", [((33, 128, 14, 14), 128), ((64, 136, 7, 7), 264), ((17, 200, 13, 15), 136)])
+def test_small_planes_token_major(shape, J):
+    print("small planes", shape, J, flush=True)
+    geom = (3, 3, 1, 1, 1, 1, 1, 1)
+    x = activation(shape, "relu", 51 + shape[1], "bf16")
+    assert dropit.weight_grad_path(shape, torch.bfloat16, x.size // 4, J, geom) == "conv_gemm"
+    check(x, gradient((shape[0], J, shape[2], shape[3]), 0.02, 52 + J, "bf16"), 0.75, J, geom)
