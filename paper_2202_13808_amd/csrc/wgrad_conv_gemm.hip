@@ -142,15 +142,16 @@ bool conv_gemm_supported(const ConvProblem &p)
     return fc_dense_supported(FcProblem{p.N * HW, 9 * p.C, p.J, p.k});
 }
 
-// Taken for small planes with many channels, where a plane fits a preparing workgroup and the product is
-// large enough to be worth three dispatches: measured against the row-band kernel on
-// ResNet-50's 3x3 layers at batch 64 (56x56x64 and 28x28x128 stay there; 14x14x256 and 7x7x512
-// come here).
+// Taken for small planes with many channels, where a plane fits a preparing workgroup and the product is large enough
+// to be worth three dispatches: 56x56x64 and 28x28x128 stay on the row bands (the plane is too large here), planes up
+// to the 256 positions the preparation holds come here.  Calls at gamma 0.8, row bands against this form: 64 images of
+// 256 channels at 16 x 16 83 -> 56 us, 512 channels 238 -> 105, 128 channels 42.1 -> 39.7; 12 images of 128 channels at
+// 16 x 15 38 -> 29.
 bool conv_gemm_preferred(const ConvProblem &p)
 {
     if (!conv_gemm_supported(p)) return false;
     const ConvGemmPlan plan = conv_gemm_plan(p);
-    return p.H * p.W <= 200 && p.C >= 128 &&
+    return p.H * p.W <= 256 && p.C >= 128 &&
            int64_t(plan.gemm.nb_count) * plan.gemm.mb_count * plan.gemm.nkb >= 256;
 }
 

@@ -92,7 +92,8 @@ def test_channels_last_window(shape, J, geom):
     check(x, gradient((N, OH, OW, J), 0.02, 42 + W, "bf16"), 0.7, J, geom, layout="nhwc")
 
 
-@pytest.mark.parametrize("shape,J", [((33, 128, 14, 14), 128), ((64, 136, 7, 7), 264), ((17, 200, 13, 15), 136)])
+@pytest.mark.parametrize("shape,J", [((33, 128, 14, 14), 128), ((64, 136, 7, 7), 264), ((17, 200, 13, 15), 136),
+                                     ((9, 128, 16, 16), 136)])
 def test_small_planes_token_major(shape, J):
     print("small planes", shape, J, flush=True)
     geom = (3, 3, 1, 1, 1, 1, 1, 1)
