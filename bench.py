@@ -260,6 +260,9 @@ def main():
     fc_mfma = path == "fc_mfma"
     fc_fused = path == "fc_fused"                          # token-block starts, pairs regrouped by tile, product, slice sum
     conv_gemm = path in ("conv_gemm", "conv_im2col")      # operand preparation, then the fully-connected GEMM
+    # 1x1 / stride 1 / unpadded NCHW with an even plane of at least 16 positions: a kernel of its own, the operands as they lie
+    plane = w.x_shape[2] * w.x_shape[3] if path == "conv_im2col" and args.layout == "nchw" else 0
+    pointwise = plane >= 16 and plane % 2 == 0 and tuple(conv)[:6] == (1, 1, 1, 1, 0, 0)
     conv_mfma = path == "conv_bands"
     conv_padded = conv_mfma and w.x_shape[3] % 8 != 0       # one more kernel: the zero-padded copy of dY
     mfma = fc_mfma or fc_fused or conv_mfma or conv_gemm
@@ -273,8 +276,9 @@ def main():
     c_names = ["select"]
     g_names = (["recover", "mfma_gemm", "splitk_reduce"] if fc_mfma else
                ["token_block_starts", "pairs_by_tile", "mfma_gemm_with_recover", "splitk_reduce"] if fc_fused else
-               ["im2col_recover_and_dY_tokens", "mfma_gemm", "splitk_reduce"] if path == "conv_gemm" else
-               ["im2col_rows_and_dY_tokens", "mfma_gemm", "splitk_reduce"] if conv_gemm else
+               ["recover_and_dY_tokens", "mfma_gemm", "splitk_reduce"] if path == "conv_gemm" else
+               ["row_starts", "mfma_pointwise", "partial_reduce"] if pointwise else
+               ["operand_rows", "mfma_gemm", "splitk_reduce"] if conv_gemm else
                ["row_starts", "pad_dY", "mfma_conv", "partial_reduce"] if conv_padded else
                ["row_starts", "mfma_conv", "partial_reduce"] if conv_mfma else
                ["recover_and_fma_gemm"] if fc_small else ["recover", "fp32_gemm_and_splitk_reduce"])
@@ -290,7 +294,7 @@ def main():
     hist_ms = float(np.mean(c_ms[:, 0]))
     hist_gbps = compress_bytes / (hist_ms * 1e-3) * 1e-9
 
-    main_kernel = ("fc_dense_kernel" if (fc_mfma or conv_gemm or fc_fused) else "conv3x3_mfma_kernel" if conv_mfma else
+    main_kernel = ("conv_pointwise_kernel" if pointwise else "fc_dense_kernel" if (fc_mfma or conv_gemm or fc_fused) else "conv3x3_mfma_kernel" if conv_mfma else
                    "fc_small_kernel" if fc_small else "exact_gemm_kernel")
     select_kernel = "select_small_kernel" if w.numel // (8 if bf16 else 4) <= 8 * 1024 else "select_fused_kernel"
     dw_traffic = measured_traffic(w.name + ("+lds" if fc_fused else ""), main_kernel)
