@@ -575,24 +575,36 @@ __device__ inline void publish_hist(unsigned long long *ready, unsigned long lon
     if (threadIdx.x == 0) dev_store64(ready, gen);
 }
 
-// Waits until `ready` holds this call's generation number (`seen`: what thread 0 has already read there).  False (in every
-// thread) if that never happens.
-__device__ inline bool wait_published(const unsigned long long *ready, unsigned long long gen, unsigned long long seen, uint32_t *ok_slot)
+// How a wait, or the whole parallel selection, ended (the same in every thread of a workgroup): SEL_GAVE_UP if a grid
+// barrier ran out of patience, here or in another workgroup, SEL_NEVER_READY if the exchange area was never published.  In
+// the last two cases the outputs are incomplete (whatever was written is correct, nothing is out of bounds).
+enum SelOutcome { SEL_DONE = 0, SEL_GAVE_UP = 1, SEL_NEVER_READY = 2 };
+
+// Waits until `ready` holds this call's generation number (`seen`: what thread 0 has already read there).
+// `error` is the state's word where that is this call's already (the state words have been seen published), else null: a
+// workgroup that gave up may have been the one to publish, or the last to leave, which takes `ready` back, so the wait
+// ends with that word as a grid barrier does.
+__device__ inline SelOutcome wait_published(const unsigned long long *ready, unsigned long long gen, unsigned long long seen,
+                                            const uint32_t *error, uint32_t *slot)
 {
     if (threadIdx.x == 0) {
-        uint32_t spins = 0, ok = 1;
+        uint32_t spins = 0, outcome = SEL_DONE;
         while (seen != gen) {
             if (++spins > READY_SPIN_LIMIT) {      // workgroup 0 never ran: not this workgroup's patience setting
-                ok = 0;
+                outcome = SEL_NEVER_READY;
+                break;
+            }
+            if (error != nullptr && (spins & 31u) == 0 && dev_load(error) != 0) {
+                outcome = SEL_GAVE_UP;
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
             seen = dev_load64(ready);
         }
-        *ok_slot = ok;
+        *slot = outcome;
     }
     __syncthreads();
-    return *ok_slot != 0;
+    return static_cast<SelOutcome>(*slot);
 }
 
 // Finds the digit d with #{digit > d} < k_rem <= #{digit >= d} in the merged histogram
@@ -816,11 +828,6 @@ __device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint3
                  : "vcc", "memory");
 #undef STAGE_WORD
 }
-
-// The parallel selection.  Returns (the same in every thread) SEL_DONE, or SEL_GAVE_UP if a grid
-// barrier ran out of patience, or SEL_NEVER_READY if the exchange area was never published; in the
-// last two cases the outputs are incomplete (whatever was written is correct, nothing is out of bounds).
-enum SelOutcome { SEL_DONE = 0, SEL_GAVE_UP = 1, SEL_NEVER_READY = 2 };
 
 // From the per-chunk table of a range of nf keys (a line of TABLE_PITCH words per chunk; word r < nf: the chunk's count of
 // key key_lo + r; word nf: of the keys above the range): the threshold t = the k-th largest key, the tie budget m, and the
@@ -1062,9 +1069,10 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
                 if (tid == 0) lh[0] += z;
             }
             __syncthreads();
-            if (!wait_published(&st->ready_hist, gen, 0ull, &bcast[3])) return SEL_NEVER_READY;
-            if (!ready_seen && !wait_published(&st->ready, gen, early, &bcast[3])) return SEL_NEVER_READY;
+            if (!ready_seen)
+                if (const SelOutcome o = wait_published(&st->ready, gen, early, nullptr, &bcast[3])) return o;
             ready_seen = true;
+            if (const SelOutcome o = wait_published(&st->ready_hist, gen, 0ull, &st->error, &bcast[2])) return o;   // (a word of its own: others may still read the first wait's)
             for (int i = tid; i < NB; i += SEL_THREADS) {
                 const uint32_t c = lh[i];
                 if (c) atomicAdd(&hist0[i], c);
@@ -1108,7 +1116,8 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
         above = wave_sum(above);
         if (lane == 0) wh[nf] = above;
         __syncthreads();
-        if (!ready_seen && !wait_published(&st->ready, gen, early, &bcast[3])) return SEL_NEVER_READY;
+        if (!ready_seen)
+            if (const SelOutcome o = wait_published(&st->ready, gen, early, nullptr, &bcast[3])) return o;
         ready_seen = true;
         if (tid <= static_cast<int>(nf)) {        // the chunk's column of the table: the wavefronts' counts added up
             uint32_t sum = 0;
@@ -1312,7 +1321,8 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         }
         __syncthreads();
         // the exchange area must have been cleared for this call
-        if (!ready_seen && !wait_published(&st->ready, gen, 0ull, &bcast[3])) return SEL_NEVER_READY;
+        if (!ready_seen)
+            if (const SelOutcome o = wait_published(&st->ready, gen, 0ull, nullptr, &bcast[3])) return o;
         ready_seen = true;
         for (int i = tid; i < NB; i += SEL_THREADS) {
             const uint32_t c = lh[i];

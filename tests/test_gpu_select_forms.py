@@ -1,6 +1,8 @@
 """GPU: the forms of the persistent select for 16-bit tensors at the sizes and densities where they change over -- the
 smallest tensors it takes, wavefront ranges that end inside a row of 512 elements, staging segments that overflow (part of
 the tensor is read twice), and ties whose budget runs out inside one wavefront -- bit for bit against the oracle."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -53,3 +55,41 @@ def test_tie_budget_runs_out_at_any_wavefront(numel):
         gamma = 1.0 - (big + m + 0.5) / numel
         assert oracle.keep_count(numel, gamma) == big + m
         run(x, gamma)
+
+
+def misleading(numel, scale, seed=99):
+    """A tensor whose sampled pieces (512 of them, two vectors each, one per equal stretch at a hashed place) have another
+    scale than the rest.  numel: a power of two, so that the stretches are equal."""
+    nvf = numel // 8
+    seg = nvf // 4 // 512
+    sampled = np.zeros(nvf, dtype=bool)
+    for i in range(512):
+        first = (i * seg + ((((i + 1) * 0x9E3779B1) & 0xFFFFFFFF) >> 8) % seg) * 4
+        sampled[first:first + 2] = True
+    base = np.random.default_rng(seed).standard_normal(numel, dtype=np.float32)
+    return f32_to_bf16_bits(base * np.where(np.repeat(sampled, 8), np.float32(scale), np.float32(1.0)))
+
+
+@pytest.mark.parametrize("numel", [1 << 17, 1 << 18, 1 << 21, 1 << 23])
+@pytest.mark.parametrize("scale", [0.01, 100.0])
+def test_misled_without_patience(numel, scale):
+    """A sample that misleads together with workgroups that give up at the grid barriers (mode 3): those that got past the
+    first barrier enter the exact form, whose histogram the others no longer publish.  Every wait ends, in milliseconds,
+    and the bytes are the oracle's."""
+    x = misleading(numel, scale)
+    want_v, want_i = oracle.compress(x, oracle.keep_count(numel, 0.9))
+    xd = to_device(x)
+    ws = torch.empty(dropit.compress_workspace_bytes(numel, xd.dtype), dtype=torch.uint8, device="cuda:0")
+    dropit.set_select_mode(3)
+    try:
+        for rep in range(12):
+            print("misled", numel, scale, rep, flush=True)
+            ws.fill_(rep)
+            torch.cuda.synchronize()
+            start = time.perf_counter()
+            vals, idx = dropit.compress(xd, 0.9, workspace=ws)
+            torch.cuda.synchronize()
+            assert time.perf_counter() - start < 0.5
+            assert np.array_equal(to_host(idx), want_i) and to_host(vals).tobytes() == want_v.tobytes()
+    finally:
+        dropit.set_select_mode(0)
