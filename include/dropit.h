@@ -196,7 +196,10 @@ dropit_wgrad_path dropit_weight_grad_path(const int64_t *x_shape, int ndim, drop
  *   workspace       device, 256-byte aligned, >= dropit_weight_grad_workspace_bytes
  *
  * bf16 inputs are multiplied exactly and accumulated in fp32; fp32 inputs use
- * true fp32 multiply-adds.  k == 0 gives dW = 0.  The bias gradient does not
+ * true fp32 multiply-adds.  Infinities and NaN: a window position over the padding
+ * is no term of the sum on the exact path (DROPIT_PATH_FMA); the bf16 matrix-core
+ * convolutions multiply the zeros that stand there, so an infinity or NaN of dY at
+ * a border also makes the taps that hang over it NaN.  k == 0 gives dW = 0.  The bias gradient does not
  * depend on the cached input and is not computed here.
  */
 dropit_status dropit_weight_grad(const void *vals, const int32_t *idx, int64_t k,

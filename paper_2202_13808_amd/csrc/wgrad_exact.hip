@@ -18,6 +18,10 @@
 //      to cover them.
 //   3. the K-slices' sums are added in a fixed order (splitk.hpp).
 // Products and accumulation are true fp32 multiply-adds in a fixed order: dW is bit-reproducible.
+// A window position over the padding is no term of the sum: an infinity or NaN of dY must not meet the zero that stands
+// there in the tile.  A workgroup whose sums are not all finite (padded convolutions only: one look at them at the end)
+// does its slice again, with the tokens whose dY is not finite taken out of the matrix product and added by vector
+// multiply-adds, position by position.
 //
 // Measured, whole weight-gradient call, against vector multiply-adds on a zero-filled and scattered R(a^) (one
 // 64 x 64 tile over all tokens; one workgroup per (j, c) for convolutions): fp32 6304 x 384 -> 1536 637 -> 81 us
@@ -27,6 +31,7 @@
 #include "splitk.hpp"
 #include "wgrad_internal.hpp"
 #include "dev_hooks.hpp"
+#include <type_traits>
 
 namespace dropit {
 namespace {
@@ -69,6 +74,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     __shared__ uint32_t col_off[CONV ? BN : 1], col_y[CONV ? BN : 1], col_x[CONV ? BN : 1];   // of a column: offset of (c, u, v), u * dh, v * dw
     __shared__ uint32_t tok_off[FB == ALONG_COLUMNS ? 2 : 1][BK];                             // of a token: offset of (n, iy0, ix0)
     __shared__ uint32_t tok_y[FB == ALONG_COLUMNS ? 2 : 1][BK], tok_x[FB == ALONG_COLUMNS ? 2 : 1][BK];
+    __shared__ uint32_t not_finite[2];                             // bit r: the tile of dY of an even / odd step holds an infinity or NaN for its token r
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
 
@@ -114,7 +120,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
         iy0 = oy * g.sh - g.ph;
         ix0 = ox * g.sw - g.pw;
     };
-    auto fill_tokens = [&](int kb) {               // ALONG_COLUMNS: the step's token table
+    auto fill_tokens = [&](int kb) __attribute__((always_inline)) {   // ALONG_COLUMNS: the step's token table
         if (FB == ALONG_COLUMNS && tid < BK) {
             const int64_t t = int64_t(kb) * BK + tid;
             uint32_t iy0 = 0x80000000u, ix0 = 0;   // past the last token: below no H
@@ -134,7 +140,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     // ---- operand fetch: a step's tiles into registers, and from there into LDS ------------------------------
     constexpr int EA = BM * BK / NT, EB = BN * BK / NT;    // elements per thread
     float ra[EA], rb[EB];
-    auto fetch = [&](int kb) {
+    auto fetch = [&](int kb) __attribute__((always_inline)) {   // (two callers)
         const int64_t t0 = int64_t(kb) * BK;
         if constexpr (FA == ROWS16) {                      // M % 4 == 0
 #pragma unroll
@@ -209,7 +215,15 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
             }
         }
     };
-    auto store = [&]() {
+    auto row_a = [&](int u) {                              // token of this thread's element u of the dY tile
+        return FA == ALONG_TOKENS ? tid % BK : FA == ROWS16 ? (tid + u / 4 * NT) / (BM / 4) : (tid + u * NT) / BM;
+    };
+    auto note_not_finite = [&](int kb) {
+#pragma unroll
+        for (int u = 0; u < EA; ++u)
+            if ((__float_as_uint(ra[u]) & 0x7fffffffu) >= 0x7f800000u) atomicOr(&not_finite[kb & 1], 1u << row_a(u));
+    };
+    auto store = [&]() __attribute__((always_inline)) {
         if constexpr (FA == ROWS16) {
 #pragma unroll
             for (int u = 0; u < EA / 4; ++u) {
@@ -219,9 +233,8 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
         } else {
 #pragma unroll
             for (int u = 0; u < EA; ++u) {
-                const int r = FA == ALONG_TOKENS ? tid % BK : (tid + u * NT) / BM;
                 const int q = FA == ALONG_TOKENS ? tid / BK + u * (NT / BK) : (tid + u * NT) % BM;
-                sA[r * C::PA + q] = ra[u];
+                sA[row_a(u) * C::PA + q] = ra[u];
             }
         }
         if constexpr (FB == ROWS16) {
@@ -241,37 +254,91 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     };
 
     f32x16 acc[C::FM][C::FN];
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
     // a 32x32x2 operand wants, in lane l, row (or column) l % 32 and k = l / 32
     const float *pa = sA + (lane >> 5) * C::PA + wm * C::WM + (lane & 31);
     const float *pb = sB + (lane >> 5) * C::PB + wn * C::WN + (lane & 31);
-    fill_tokens(kb_begin);
-    __syncthreads();                                       // column and token tables
-    if (kb_begin < kb_end) fetch(kb_begin);
-    for (int kb = kb_begin; kb < kb_end; ++kb) {
-        __syncthreads();                                   // the previous step's tiles have been read
-        store();
-        if (kb + 1 < kb_end) fill_tokens(kb + 1);
+    // The tokens of `skip` into the sums, window position by window position, and out of the tiles.
+    auto take_out = [&](int kb, uint32_t skip) {
+        for (uint32_t left = skip; left != 0; left &= left - 1) {
+            const int r = __builtin_ctz(left);
+            uint32_t n, p, iy0, ix0;
+            locate(int64_t(kb) * BK + r, n, p);            // (a token past the last has dY = 0)
+            window(p, iy0, ix0);
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j) {
+                const int q = wn * C::WN + j * 32 + (lane & 31);
+                const float xv = sB[r * C::PB + q];
+                const bool inside = iy0 + col_y[q] < g.H && ix0 + col_x[q] < g.W;
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float yv = sA[r * C::PA + wm * C::WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
+                        if (inside) acc[i][j][e] = __builtin_fmaf(yv, xv, acc[i][j][e]);
+                        __builtin_amdgcn_sched_barrier(0);  // (one value at a time: this path must not cost the other its registers)
+                    }
+            }
+        }
         __syncthreads();
-        if (kb + 1 < kb_end) fetch(kb + 1);
+        for (uint32_t left = skip; left != 0; left &= left - 1) {
+            const int r = __builtin_ctz(left);
+            for (int q = tid; q < BM; q += NT) sA[r * C::PA + q] = 0.f;
+            for (int q = tid; q < BN; q += NT) sB[r * C::PB + q] = 0.f;
+        }
+        __syncthreads();
+    };
+    // The slice's product.  CAREFUL: with the tokens whose dY is not finite taken out of the matrix instructions.
+    auto accumulate = [&](auto careful_) {
+        constexpr bool CAREFUL = decltype(careful_)::value;
 #pragma unroll
-        for (int kk = 0; kk < BK / 2; ++kk) {
-            float a[C::FM], b[C::FN];
+        for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-            for (int i = 0; i < C::FM; ++i) a[i] = pa[kk * 2 * C::PA + i * 32];
+            for (int j = 0; j < C::FN; ++j)
 #pragma unroll
-            for (int j = 0; j < C::FN; ++j) b[j] = pb[kk * 2 * C::PB + j * 32];
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        fill_tokens(kb_begin);
+        if (CAREFUL && tid < 2) not_finite[tid] = 0;
+        __syncthreads();                                   // column and token tables
+        if (!CAREFUL && kb_begin < kb_end) fetch(kb_begin);
+        for (int kb = kb_begin; kb < kb_end; ++kb) {
+            if constexpr (CAREFUL) {                       // (not a step ahead: take_out has the registers)
+                fetch(kb);
+                note_not_finite(kb);
+            }
+            __syncthreads();                               // the previous step's tiles have been read
+            store();
+            if (CAREFUL && tid == 0) not_finite[(kb + 1) & 1] = 0;
+            if (kb + 1 < kb_end) fill_tokens(kb + 1);
+            __syncthreads();
+            if (!CAREFUL && kb + 1 < kb_end) fetch(kb + 1);
+            if constexpr (CAREFUL)
+                if (const uint32_t skip = __builtin_amdgcn_readfirstlane(not_finite[kb & 1]); skip != 0) take_out(kb, skip);
+#pragma unroll
+            for (int kk = 0; kk < BK / 2; ++kk) {
+                float a[C::FM], b[C::FN];
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i) a[i] = pa[kk * 2 * C::PA + i * 32];
+#pragma unroll
+                for (int j = 0; j < C::FN; ++j) b[j] = pb[kk * 2 * C::PB + j * 32];
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+    accumulate(std::false_type{});
+    if constexpr (CONV) {
+        if ((g.ph | g.pw) != 0) {                          // uniform
+            float z = 0.f;
 #pragma unroll
             for (int i = 0; i < C::FM; ++i)
 #pragma unroll
                 for (int j = 0; j < C::FN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) z = __builtin_fmaf(acc[i][j][e], 0.f, z);
+            if (__syncthreads_or(!(z == 0.f))) accumulate(std::true_type{});
         }
     }
 

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import paper_2202_13808_amd as dropit
-from dropit_inputs import activation, gradient
+from dropit_inputs import activation, f32_to_bf16_bits, gradient
 from gpu_util import to_device, to_host
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +59,42 @@ def test_conv_geometries(dtype, layout, shape, J, geom):
         return r.transpose(0, 2, 3, 1) if layout == "nhwc" else r
 
     check(x, dy, 0.6, J, dense, shape[0] * OH * OW, conv=geom, layout=layout)
+
+
+@pytest.mark.parametrize("dtype,layout,shape,J,geom", [
+    ("f32", "nchw", (2, 5, 6, 7), 6, (3, 3, 1, 1, 1, 1, 1, 1)), ("f32", "nchw", (3, 40, 9, 12), 130, (3, 3, 1, 1, 1, 1, 1, 1)),
+    ("f32", "nchw", (2, 9, 11, 8), 70, (5, 3, 2, 1, 2, 1, 1, 2)), ("f32", "nhwc", (2, 9, 8, 24), 68, (3, 3, 1, 1, 1, 1, 1, 1)),
+    ("f32", "nhwc", (2, 7, 10, 6), 5, (3, 3, 2, 2, 1, 1, 1, 1)), ("bf16", "nchw", (2, 9, 13, 10), 12, (5, 3, 1, 2, 2, 1, 1, 1)),
+    ("bf16", "nhwc", (2, 8, 6, 16), 9, (3, 3, 1, 1, 2, 2, 2, 2)), ("f32", "nchw", (2, 6, 5, 5), 8, (2, 2, 1, 1, 0, 0, 1, 1))])
+def test_infinities_do_not_meet_the_padding(dtype, layout, shape, J, geom):
+    """Infinities and NaN of dY, at borders and inside, and of x: a window position over the padding is no term of the sum
+    (as in the oracle), so a tap that hangs over the border there stays what the other terms make it."""
+    print("exact non-finite", dtype, layout, shape, J, geom, flush=True)
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    H, W = (shape[1], shape[2]) if layout == "nhwc" else (shape[2], shape[3])
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    xf = oracle.widen(activation(shape, "normal", 23 + H, dtype)).astype(np.float32)
+    g = oracle.widen(gradient((shape[0], J, OH, OW), 0.02, 24 + W, dtype)).astype(np.float32)
+    g[0, 1, 0, 0], g[1, 2, OH - 1, OW - 1], g[0, 3, OH // 2, 0] = np.inf, np.nan, -np.inf
+    g[1, 4, 0, :] = np.inf
+    xf.reshape(-1)[5] = np.inf
+    if layout == "nhwc":
+        g = np.ascontiguousarray(g.transpose(0, 2, 3, 1))
+    x, dy = (xf, g) if dtype == "f32" else (f32_to_bf16_bits(xf), f32_to_bf16_bits(g))
+    for gamma in (0.0, 0.5):
+        vals, idx = dropit.compress(to_device(x), gamma)
+        assert dropit.weight_grad_path(shape, vals.dtype, vals.numel(), J, geom, layout=layout) == "fma"
+        got = to_host(dropit.weight_grad(vals, idx, shape, to_device(dy), J, conv=geom, layout=layout)).astype(np.float64)
+        xh, yh = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, gamma)), shape), oracle.widen(dy)
+        if layout == "nhwc":
+            xh, yh = np.ascontiguousarray(xh.transpose(0, 3, 1, 2)), np.ascontiguousarray(yh.transpose(0, 3, 1, 2))
+            got = got.transpose(0, 3, 1, 2)
+        ref = oracle.dw_conv(xh, yh, kh, kw, (sh, sw), (ph, pw), (dh, dw))
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any() and np.isfinite(ref).any()
+        inf = np.isinf(ref)
+        assert np.array_equal(got[inf], ref[inf])
+        fin = np.isfinite(ref)
+        size = oracle.dw_conv(np.abs(np.where(np.isfinite(xh), xh, 0)), np.abs(np.where(np.isfinite(yh), yh, 0)), kh, kw, (sh, sw),
+                              (ph, pw), (dh, dw))
+        nu = (shape[0] * OH * OW + 256) * 2.0 ** -24
+        assert (np.abs(got[fin] - ref[fin]) <= nu / (1 - nu) * size[fin]).all()
