@@ -58,10 +58,10 @@ struct SelState {
     uint32_t t;          // threshold key (valid after the count pass)
     uint32_t m;          // how many keys equal to t are kept (lowest flat index first)
     uint32_t ticket[4];  // arrival counters, one per pass
-    uint32_t unused;
+    uint32_t form;       // fused kernel, for the tests, at every size: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry)
     uint32_t error;      // hint: some workgroup ran out of patience at a grid barrier (the others stop waiting)
     uint32_t exited;     // fused kernel: low 16 bits = workgroups past their last grid barrier or gone, high 16 bits = how many gave up
-    uint32_t path;       // fused kernel, for the tests: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry); 16-bit tensors of SAMPLE_LARGE elements or more
+    uint32_t path;       // `form` for 16-bit tensors of SAMPLE_LARGE elements or more, 0 below: what readers of this word were told when smaller ones had no sampled form
     unsigned long long ready;    // == the call's generation number once workgroup 0 has cleared the words above and the histograms;
                                  // the last workgroup to leave puts 0 back (no generation is 0), so a launch replayed with
                                  // the same number (a captured graph) waits for its own workgroup 0 again
@@ -661,7 +661,7 @@ constexpr int SAMPLE_PIECES = 512;
 constexpr int SAMPLE_STRETCH = 4;                     // a piece starts at a multiple of this many vectors (64 bytes) ...
 constexpr int SAMPLE_PIECE = SEL_THREADS / SAMPLE_PIECES;   // ... and is this many vectors long: one vector per thread
 constexpr int SAMPLE_ELEMS = SEL_THREADS * 8;
-constexpr int64_t SAMPLE_LARGE = int64_t(1) << 21;    // from here on the state block says how the prediction went
+constexpr int64_t SAMPLE_LARGE = int64_t(1) << 21;    // from here on the state's `path` says how the prediction went
 constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 16;
 static_assert(SAMPLE_MIN_NUMEL / 8 / SAMPLE_STRETCH >= SAMPLE_PIECES, "a place per stretch at least");
 constexpr int SAMPLE_SHIFT = 3, SAMPLE_BINS = 1 << (15 - SAMPLE_SHIFT);    // 8 keys per bin
@@ -1141,7 +1141,11 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
     const uint32_t t = bcast[0], m = bcast[1];
     if (tid == REPORT_TID) {
         if (spilled == 0) __hip_atomic_fetch_add(&st->staged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (blockIdx.x == 0) dev_store(&st->path, numel < SAMPLE_LARGE ? 0u : missed ? 2u : predicted ? 1u : 0u);
+        if (blockIdx.x == 0) {
+            const uint32_t form = missed ? 2u : predicted ? 1u : 0u;
+            dev_store(&st->form, form);
+            dev_store(&st->path, numel < SAMPLE_LARGE ? 0u : form);
+        }
     }
     STAMP(6);
 
@@ -1368,7 +1372,10 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         return SEL_GAVE_UP;                    // cannot happen with exact digits; the serial path would still answer
     const uint32_t t = bcast[0], m = bcast[1];
     uint32_t run_gt = offs[0], run_eq = offs[1];   // #{key > t}, #{key == t} before this chunk
-    if (blockIdx.x == 0 && tid == 0) dev_store(&st->path, 0u);
+    if (blockIdx.x == 0 && tid == 0) {
+        dev_store(&st->form, 0u);
+        dev_store(&st->path, 0u);
+    }
     STAMP(6);
 
     // ---- ordered compaction -------------------------------------------------------

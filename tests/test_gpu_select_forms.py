@@ -70,6 +70,29 @@ def misleading(numel, scale, seed=99):
     return f32_to_bf16_bits(base * np.where(np.repeat(sampled, 8), np.float32(scale), np.float32(1.0)))
 
 
+def form_of(x, gamma):
+    """White box: word 8 of the state block, 0 exact digit histograms, 1 sampled bracket confirmed, 2 missed."""
+    xd = to_device(x)
+    ws = torch.full((dropit.compress_workspace_bytes(x.size, xd.dtype),), 0x33, dtype=torch.uint8, device="cuda:0")
+    want_v, want_i = oracle.compress(x, oracle.keep_count(x.size, gamma))
+    vals, idx = dropit.compress(xd, gamma, workspace=ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(idx), want_i) and to_host(vals).tobytes() == want_v.tobytes()
+    return int(ws[:64].cpu().numpy().view(np.uint32)[8])
+
+
+@pytest.mark.parametrize("numel", [1 << 17, 1 << 19, 1 << 20, 1 << 22])
+def test_prediction_confirmed_and_missed(numel):
+    """Below 2 M elements too: a bracket that holds, one that does not (both ways), a quantile without one, fp32."""
+    base = np.random.default_rng(7).standard_normal(numel, dtype=np.float32)
+    assert form_of(f32_to_bf16_bits(base), 0.9) == 1
+    assert form_of(f32_to_bf16_bits(base), 0.99999) == 0
+    for gamma in (0.9, 0.5):
+        assert form_of(misleading(numel, 0.01), gamma) == 2
+        assert form_of(misleading(numel, 100.0), gamma) == 2
+    assert form_of(base, 0.9) == 0
+
+
 @pytest.mark.parametrize("numel", [1 << 17, 1 << 18, 1 << 21, 1 << 23])
 @pytest.mark.parametrize("scale", [0.01, 100.0])
 def test_misled_without_patience(numel, scale):
