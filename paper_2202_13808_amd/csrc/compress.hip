@@ -667,12 +667,14 @@ static_assert(SAMPLE_MIN_NUMEL / 8 / SAMPLE_STRETCH >= SAMPLE_PIECES, "a place p
 constexpr int SAMPLE_SHIFT = 3, SAMPLE_BINS = 1 << (15 - SAMPLE_SHIFT);    // 8 keys per bin
 constexpr int BRACKET_MAX_BINS = MAX_LAST_BINS >> SAMPLE_SHIFT;
 
-// First vector of sample piece i: stretch i of the tensor, hashed offset inside it.
+// First vector of sample piece i: stretch i of the tensor's places (512 of them, as even as they divide: the last one ends
+// at the tensor's end), hashed offset inside it.
 __device__ inline int64_t sample_piece(int i, int64_t nvf)
 {
-    const uint32_t seg = static_cast<uint32_t>((nvf / SAMPLE_STRETCH) / SAMPLE_PIECES);   // possible places per stretch
+    const int64_t places = nvf / SAMPLE_STRETCH;
+    const int64_t first = i * places / SAMPLE_PIECES, end = (i + 1) * places / SAMPLE_PIECES;
     const uint32_t h = (static_cast<uint32_t>(i) + 1u) * 0x9E3779B1u;
-    return (int64_t(i) * seg + static_cast<int64_t>((h >> 8) % seg)) * SAMPLE_STRETCH;
+    return (first + static_cast<int64_t>((h >> 8) % static_cast<uint32_t>(end - first))) * SAMPLE_STRETCH;
 }
 
 // From the sample's histogram (in LDS; bin 0 -- exact zeros -- is not counted): the bins that hold the sample ranks

@@ -93,6 +93,16 @@ def test_prediction_confirmed_and_missed(numel):
     assert form_of(base, 0.9) == 0
 
 
+@pytest.mark.parametrize("numel", [65552, 70000, 32 * (512 * 5 - 1) + 17, 32 * (512 * 7 - 3), 300001])
+def test_sample_covers_the_whole_tensor(numel):
+    """Magnitudes that grow with the index, at sizes whose 64-byte places do not divide into 512 equal stretches: the
+    sample reaches the end of the tensor, so the prediction holds."""
+    x = f32_to_bf16_bits(np.sqrt(np.linspace(0.0, 4.0, numel, dtype=np.float32)))
+    for gamma in (0.9, 0.8, 0.5):
+        print("stretches", numel, gamma, flush=True)
+        assert form_of(x, gamma) == 1
+
+
 @pytest.mark.parametrize("numel", [1 << 17, 1 << 18, 1 << 21, 1 << 23])
 @pytest.mark.parametrize("scale", [0.01, 100.0])
 def test_misled_without_patience(numel, scale):
