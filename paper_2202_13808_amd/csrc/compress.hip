@@ -475,7 +475,9 @@ __device__ inline void dev_store64(unsigned long long *p, unsigned long long v)
 // device is not shared, so the wait is bounded: returns false (in every thread of the workgroup)
 // if the others did not all arrive within `spin_limit` polls or if some workgroup already gave
 // up.  The caller then skips to the kernel's exit protocol.
-// Every wavefront first waits for its own outstanding stores and atomics (a workgroup barrier alone orders LDS only).
+// Every wavefront first waits for its own outstanding stores and atomics: a workgroup barrier alone orders LDS only, and
+// without this wait the arrival could overtake the histogram merges of the other wavefronts.  (With 8192 bins to merge it
+// is 1.5 us of each fp32 digit pass.)
 __device__ inline bool grid_barrier(SelState *st, uint32_t *xbar, uint32_t round, uint32_t spin_limit, uint32_t *ok_slot)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -677,11 +679,23 @@ __device__ inline int64_t sample_piece(int i, int64_t nvf)
     return (first + static_cast<int64_t>((h >> 8) % static_cast<uint32_t>(end - first))) * SAMPLE_STRETCH;
 }
 
-// From the sample's histogram (in LDS; bin 0 -- exact zeros -- is not counted): the bins that hold the sample ranks
-// r - margin and r + margin, r = the sample's share of k.  Returns false (in every thread) if there is no usable
-// bracket (a quantile too close to either end of the sample or among the zeros, more than BRACKET_MAX_BINS bins).
+// The sample ranks around the k-th largest key's quantile, r - margin and r + margin with r = the sample's share of k.
+// False if one of them lies outside the sample: no bracket then, whatever the sample holds, and none is taken (a sample of
+// few magnitudes costs up to 5 us of LDS atomics on the same bins).
+__device__ inline bool sample_ranks(uint32_t k, int64_t numel, float &lo, float &hi)
+{
+    const float frac = static_cast<float>(k) / static_cast<float>(numel);
+    const float r = frac * static_cast<float>(SAMPLE_ELEMS);
+    const float margin = 5.0f * __builtin_sqrtf(fmaxf(r * (1.0f - frac), 1.0f)) + 8.0f;
+    lo = r - margin;
+    hi = r + margin;
+    return lo >= 1.0f && hi <= static_cast<float>(SAMPLE_ELEMS) - 1.0f;
+}
+
+// From the sample's histogram (in LDS; bin 0 -- exact zeros -- is not counted): the bins that hold the two ranks.
+// Returns false (in every thread) if there is no usable bracket (a rank among the zeros, more than BRACKET_MAX_BINS bins).
 template <int NB>
-__device__ inline bool sample_bracket(const uint32_t *hist, uint32_t k, int64_t numel, uint32_t *wave_tot,
+__device__ inline bool sample_bracket(const uint32_t *hist, float lo_f, float hi_f, uint32_t *wave_tot,
                                       uint32_t *bcast /*[2]*/, uint32_t &b_lo, uint32_t &b_hi)
 {
     constexpr int PER = (NB + SEL_THREADS - 1) / SEL_THREADS;
@@ -697,24 +711,18 @@ __device__ inline bool sample_bracket(const uint32_t *hist, uint32_t k, int64_t 
     if (tid < 2) bcast[tid] = 0xFFFFFFFFu;           // (ordered before the finders' stores by the scan's barriers)
     uint32_t total;
     const uint32_t above = block_exclusive_scan<SEL_THREADS>(mine, wave_tot, total);
-    const float frac = static_cast<float>(k) / static_cast<float>(numel);
-    const float r = frac * static_cast<float>(SAMPLE_ELEMS);
-    const float margin = 5.0f * __builtin_sqrtf(fmaxf(r * (1.0f - frac), 1.0f)) + 8.0f;
-    const float lo_f = r - margin, hi_f = r + margin;
-    if (lo_f >= 1.0f && hi_f <= static_cast<float>(SAMPLE_ELEMS) - 1.0f) {
-        const uint32_t rank[2] = {static_cast<uint32_t>(lo_f), static_cast<uint32_t>(hi_f) + 1u};   // higher bin first
+    const uint32_t rank[2] = {static_cast<uint32_t>(lo_f), static_cast<uint32_t>(hi_f) + 1u};   // higher bin first
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (above < rank[q] && rank[q] <= above + mine) {
-                uint32_t a = above;
+    for (int q = 0; q < 2; ++q) {
+        if (above < rank[q] && rank[q] <= above + mine) {
+            uint32_t a = above;
 #pragma unroll
-                for (int i = 0; i < PER; ++i) {
-                    if (a + c[i] >= rank[q]) {
-                        bcast[q] = static_cast<uint32_t>(hi_bin - i);
-                        break;
-                    }
-                    a += c[i];
+            for (int i = 0; i < PER; ++i) {
+                if (a + c[i] >= rank[q]) {
+                    bcast[q] = static_cast<uint32_t>(hi_bin - i);
+                    break;
                 }
+                a += c[i];
             }
         }
     }
@@ -933,7 +941,8 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
         for (int u = 0; u < ST_ROWS; ++u) issue_row(q[u], row + u);
     };
 
-    const bool sampling = numel >= SAMPLE_MIN_NUMEL;            // uniform over the grid
+    float rank_lo, rank_hi;
+    const bool sampling = sample_ranks(k, numel, rank_lo, rank_hi) && numel >= SAMPLE_MIN_NUMEL;    // uniform over the grid
     // The threshold lies in the key range [key_lo, key_lo + nf): predicted from the sample here, else (or if the
     // prediction fails) exactly known after the digit histogram.
     uint32_t key_lo = 0, nf = 1u << SHIFT1;
@@ -963,7 +972,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
             __syncthreads();
             STAMP(9);
             uint32_t b_lo, b_hi;
-            predicted = sample_bracket<SAMPLE_BINS>(lh, k, numel, wave_tot, bcast, b_lo, b_hi);
+            predicted = sample_bracket<SAMPLE_BINS>(lh, rank_lo, rank_hi, wave_tot, bcast, b_lo, b_hi);
             if (predicted) {
                 key_lo = b_lo << SAMPLE_SHIFT;
                 nf = (b_hi - b_lo + 1) << SAMPLE_SHIFT;
