@@ -692,8 +692,9 @@ __device__ inline bool sample_ranks(uint32_t k, int64_t numel, float &lo, float 
     return lo >= 1.0f && hi <= static_cast<float>(SAMPLE_ELEMS) - 1.0f;
 }
 
-// From the sample's histogram (in LDS; bin 0 -- exact zeros -- is not counted): the bins that hold the two ranks.
-// Returns false (in every thread) if there is no usable bracket (a rank among the zeros, more than BRACKET_MAX_BINS bins).
+// From the sample's histogram (in LDS; bin 0, the zeros, is not counted: it holds what the others leave of the sample): the
+// bins that hold the two ranks.
+// Returns false (in every thread) if there is no usable bracket (more than BRACKET_MAX_BINS bins).
 template <int NB>
 __device__ inline bool sample_bracket(const uint32_t *hist, float lo_f, float hi_f, uint32_t *wave_tot,
                                       uint32_t *bcast /*[2]*/, uint32_t &b_lo, uint32_t &b_hi)
@@ -714,6 +715,7 @@ __device__ inline bool sample_bracket(const uint32_t *hist, float lo_f, float hi
     const uint32_t rank[2] = {static_cast<uint32_t>(lo_f), static_cast<uint32_t>(hi_f) + 1u};   // higher bin first
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
+        if (tid == 0 && rank[q] > total) bcast[q] = 0u;              // among the zeros
         if (above < rank[q] && rank[q] <= above + mine) {
             uint32_t a = above;
 #pragma unroll

@@ -91,6 +91,9 @@ def test_prediction_confirmed_and_missed(numel):
         assert form_of(misleading(numel, 0.01), gamma) == 2
         assert form_of(misleading(numel, 100.0), gamma) == 2
     assert form_of(base, 0.9) == 0
+    for gamma in (0.05, 0.4):                          # the threshold is zero: half of the tensor ties there
+        assert form_of(f32_to_bf16_bits(np.maximum(base, 0)), gamma) == 1
+    assert form_of(np.zeros(numel, dtype=np.uint16), 0.7) == 1
 
 
 @pytest.mark.parametrize("numel", [65552, 70000, 32 * (512 * 5 - 1) + 17, 32 * (512 * 7 - 3), 300001])
