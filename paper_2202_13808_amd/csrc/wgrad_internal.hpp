@@ -97,15 +97,16 @@ dropit_status conv_window_gemm(const FcProblem &p, const FcDensePlan &plan, cons
 // (row_ptr[R] = k).  The tensor is a run of planes, a plane is cut into `nseg` rows of `seg` consecutive elements (the
 // last one may be shorter); one row per plane is the plain case of rows of equal length.  One pass over idx: every
 // pair is compared with its predecessor and fills the row starts that fall between them; the entry j == k closes the
-// table.  A thread takes eight consecutive pairs (two 16-byte loads when idx is 16-byte aligned).  Bound by reading
-// idx: 10.3 M pairs take 13.6 us, 4.3 TB/s beside the launch.
-template <bool VEC>
+// table.  A thread takes PER consecutive pairs: eight (two 16-byte loads when idx is 16-byte aligned), or one where the rows
+// are so short or sparse that filling their starts, one store after the other, is the longer part.  Bound by reading
+// idx where it is not: 10.3 M pairs take 13.6 us, 4.3 TB/s beside the launch.
+template <bool VEC, int PER>
 static __global__ void __launch_bounds__(256)
 row_starts_kernel(const int32_t *__restrict__ idx, int64_t k, Divisor plane, Divisor seg, uint32_t nseg, int64_t R,
                   uint32_t *__restrict__ row_ptr)
 {
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int PER = 8;
+    static_assert(!VEC || PER % 4 == 0, "whole vectors");
     auto row_of = [&](int32_t flat) -> int64_t {
         if (flat < 0) return R;                                           // (a malformed index; valid ones are below 2^31)
         uint32_t r = quotient(uint32_t(flat), plane);
@@ -142,12 +143,17 @@ row_starts_kernel(const int32_t *__restrict__ idx, int64_t k, Divisor plane, Div
 inline void launch_row_starts(const int32_t *idx, int64_t k, uint32_t plane, uint32_t seg, int64_t R, uint32_t *row_ptr,
                               hipStream_t stream)
 {
-    const int blocks = int(std::min<int64_t>((k / 8 + 1 + 255) / 256, 4096));
     const uint32_t nseg = (plane + seg - 1) / seg;
-    if (aligned(idx, 16))
-        row_starts_kernel<true><<<blocks, 256, 0, stream>>>(idx, k, divisor(plane), divisor(seg), nseg, R, row_ptr);
-    else
-        row_starts_kernel<false><<<blocks, 256, 0, stream>>>(idx, k, divisor(plane), divisor(seg), nseg, R, row_ptr);
+    // Fewer than eight pairs per row.  (2.5 thousand pairs in 82 thousand rows: 45.4 us with eight to a thread; 500 calls
+    // of random shapes and gammas did best with the line at eight, against one and three.)
+    const bool sparse = k < 8 * R;
+    const int blocks = int(std::min<int64_t>((k / (sparse ? 1 : 8) + 1 + 255) / 256, 4096));
+    auto launch = [&](auto kernel) {
+        kernel<<<blocks, 256, 0, stream>>>(idx, k, divisor(plane), divisor(seg), nseg, R, row_ptr);
+    };
+    if (sparse) launch(row_starts_kernel<false, 1>);
+    else if (aligned(idx, 16)) launch(row_starts_kernel<true, 8>);
+    else launch(row_starts_kernel<false, 8>);
 }
 
 inline void launch_row_starts(const int32_t *idx, int64_t k, uint32_t row_len, int64_t R, uint32_t *row_ptr,

@@ -100,3 +100,16 @@ def test_small_planes_token_major(shape, J):
     x = activation(shape, "relu", 51 + shape[1], "bf16")
     assert dropit.weight_grad_path(shape, torch.bfloat16, x.size // 4, J, geom) == "conv_gemm"
     check(x, gradient((shape[0], J, shape[2], shape[3]), 0.02, 52 + J, "bf16"), 0.75, J, geom)
+
+
+@pytest.mark.parametrize("gamma", [0.0, 0.6, 0.99])
+@pytest.mark.parametrize("shape,J,geom", [((4, 96, 21, 3), 16, (3, 3, 1, 1, 0, 0, 1, 1)), ((3, 40, 16, 19), 24, (3, 3, 2, 2, 0, 0, 1, 1)),
+                                          ((2, 24, 9, 130), 8, (3, 3, 1, 1, 1, 1, 1, 1))])
+def test_sparse_and_full_rows(shape, J, geom, gamma):
+    """Row starts with one pair per thread (fewer than eight pairs to a row) and with eight."""
+    print("row starts", shape, gamma, flush=True)
+    N, C, H, W = shape
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    x = activation(shape, "relu", 61 + H, "bf16")
+    check(x, gradient((N, J, OH, OW), 0.02, 62 + W, "bf16"), gamma, J, geom)
