@@ -22,6 +22,7 @@ constexpr int RECOVER_THREADS = recover_cfg[0];
 // large tile (64 KB of LDS), rows wider than the large tile take the generic path.
 constexpr int RECOVER_ELEMS = recover_cfg[1];
 constexpr int RECOVER_ELEMS_MAX = 32768;
+constexpr int RECOVER_ELEMS_MIN = 1024;
 
 // ---------------------------------------------------------------------------
 // Recover R(a^): workgroup b owns rows [b * rows_per_wg, ...) of the padded dense
@@ -157,6 +158,17 @@ fc_recover_stream_kernel(const RAW *__restrict__ vals, const int32_t *__restrict
     }
 }
 
+
+// Dense elements of a recover workgroup's tile for a tensor of `numel`: at most `most`, fewer where that leaves compute
+// units without a tile: one workgroup on a large tile of a small tensor is a chain of loads (17 thousand elements, gamma 0,
+// two tiles of 8192: 12.6 us, and 10 to 16 where zero fill and scatter as two kernels took 4).  Tiles down to 1024 elements
+// and 256 of them: within 1 % of 512 and 2048, and of 512 to 2048 tiles, over 700 calls of random shapes.
+inline int64_t recover_tile(int64_t numel, int64_t most)
+{
+    int64_t tile = most;
+    while (tile > RECOVER_ELEMS_MIN && (numel + tile - 1) / tile < 256) tile /= 2;
+    return tile;
+}
 
 // Dense elements of one recover workgroup's tile, and the launch: rows of `cin` elements, `pitch` elements apart in
 // the dense matrix (a multiple of 16 bytes), ntok_pad rows of which those from ntok on are zero; `numel` is the

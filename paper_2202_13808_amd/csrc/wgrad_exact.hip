@@ -368,7 +368,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     }
 }
 
-constexpr int EXACT_TILE_BYTES = 32 * 1024;                // of R(a^), per recover workgroup
+constexpr int EXACT_TILE_BYTES = 32 * 1024;                // of R(a^), per recover workgroup, at most
 
 template <typename RAW, typename C>
 dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const RAW *dY, const RAW *x, float *partial,
@@ -413,12 +413,11 @@ template <typename RAW>
 dropit_status run_exact(const ExactProblem &p, const ExactPlan &plan, const void *vals, const int32_t *idx, const void *dY,
                         float *dW, char *ws, hipStream_t stream)
 {
-    constexpr int E = EXACT_TILE_BYTES / int(sizeof(RAW));
     RAW *x = reinterpret_cast<RAW *>(ws);
     float *partial = reinterpret_cast<float *>(ws + plan.dense_bytes);
     trace_mark(stream);
-    const int64_t rows = (p.numel + E - 1) / E;            // R(a^) as rows of E elements, the last one not full
-    launch_recover<RAW>(static_cast<const RAW *>(vals), idx, p.k, p.numel, rows, rows, E, E, 1, x, stream);
+    const int64_t rows = (p.numel + plan.tile - 1) / plan.tile;   // R(a^) as rows of a tile each, the last one not full
+    launch_recover<RAW>(static_cast<const RAW *>(vals), idx, p.k, p.numel, rows, rows, plan.tile, plan.tile, 1, x, stream);
     trace_mark(stream);
     const RAW *y = static_cast<const RAW *>(dY);
     if (plan.bm == 128) return launch_exact<RAW, ExactCfg<128, 128>>(p, plan, y, x, partial, dW, stream);
@@ -431,8 +430,8 @@ dropit_status run_exact(const ExactProblem &p, const ExactPlan &plan, const void
 ExactPlan exact_plan(const ExactProblem &p, bool f32)
 {
     ExactPlan plan;
-    const int64_t E = EXACT_TILE_BYTES / (f32 ? 4 : 2);
-    plan.dense_bytes = round_up(size_t((p.numel + E - 1) / E * E) * (f32 ? 4 : 2), 256);
+    plan.tile = int(recover_tile(p.numel, EXACT_TILE_BYTES / (f32 ? 4 : 2)));
+    plan.dense_bytes = round_up(size_t((p.numel + plan.tile - 1) / plan.tile * plan.tile) * (f32 ? 4 : 2), 256);
     // the tile that pads the result least, the larger one where two pad the same
     plan.bm = plan.bn = 0;
     int64_t least = INT64_MAX;
@@ -445,9 +444,9 @@ ExactPlan exact_plan(const ExactProblem &p, bool f32)
             plan.bn = s[1];
         }
     }
+    plan.nkb = int((p.ntok + 31) / 32);
     plan.mb_count = int((p.cout + plan.bm - 1) / plan.bm);
     plan.nb_count = int((p.cin + plan.bn - 1) / plan.bn);
-    plan.nkb = int((p.ntok + 31) / 32);
     // K-slices: two (128 x 128) to four workgroups per compute unit.  Measured with one / two / three / four: 84 / 81 /
     // 102 / 89 us for 36 tiles of 128 x 128 over 6304 tokens, 91 / 66 / 59 / 56 us for 9 tiles of 64 x 64 over 32768.
     // A slice writes a whole partial tile however little it summed, yet short problems want every compute unit: two

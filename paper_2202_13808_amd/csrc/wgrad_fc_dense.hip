@@ -1063,7 +1063,7 @@ dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *va
 {
     if (!fc_dense_attributes()) return DROPIT_EHIP;
     const int64_t rows = N * w.H * w.W;
-    const int rows_per_wg = std::max(1, (w.C <= RECOVER_ELEMS ? RECOVER_ELEMS : RECOVER_ELEMS_MAX) / w.C);
+    const int rows_per_wg = std::max(1, int(w.C <= RECOVER_ELEMS ? recover_tile(rows * w.C, RECOVER_ELEMS) : RECOVER_ELEMS_MAX) / w.C);
     launch_recover<uint16_t>(static_cast<const uint16_t *>(vals), idx, k, rows * w.C, rows, rows + 1, w.C, w.C, rows_per_wg,
                              xd, stream);
     return launch_status();

@@ -244,6 +244,7 @@ struct ExactProblem {
 };
 struct ExactPlan {
     int bm, bn, nb_count, mb_count, nkb, splits;
+    int tile;                                  // elements of R(a^) per recover workgroup
     size_t dense_bytes, partial_bytes;
     size_t total() const { return dense_bytes + partial_bytes; }
 };

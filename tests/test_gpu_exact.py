@@ -39,6 +39,17 @@ def test_fc_tile_edges(dtype, ntok, cin, cout):
     check(x, dy, 0.7, cout, oracle.dw_fc, ntok)
 
 
+@pytest.mark.parametrize("gamma", [0.0, 0.9])
+@pytest.mark.parametrize("dtype,ntok,cin,cout", [
+    ("f32", 65, 1009, 3), ("f32", 257, 1021, 2), ("f32", 300, 3500, 5), ("bf16", 47, 372, 5), ("bf16", 33, 32001, 9),
+    ("f32", 8200, 257, 3), ("f32", 390, 72, 96), ("f32", 16384, 129, 1)])
+def test_small_recover_tiles_and_slices(dtype, ntok, cin, cout, gamma):
+    """Recover tiles of 1024 elements up to the largest, with the tensor's end inside one; slices of one step and of two."""
+    print("exact small tiles", dtype, ntok, cin, cout, gamma, flush=True)
+    x, dy = activation((ntok, cin), "normal", 13 + ntok, dtype), gradient((ntok, cout), 0.02, 14 + ntok, dtype)
+    check(x, dy, gamma, cout, oracle.dw_fc, ntok)
+
+
 @pytest.mark.parametrize("dtype,layout,shape,J,geom", [
     ("f32", "nchw", (3, 7, 9, 11), 5, (3, 3, 1, 1, 1, 1, 1, 1)), ("f32", "nchw", (2, 64, 16, 16), 64, (3, 3, 1, 1, 1, 1, 1, 1)),
     ("f32", "nchw", (1, 15, 33, 31), 130, (3, 2, 2, 1, 0, 1, 1, 2)), ("f32", "nhwc", (3, 15, 17, 33), 66, (3, 3, 2, 2, 1, 1, 1, 1)),
