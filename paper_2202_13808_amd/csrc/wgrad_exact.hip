@@ -445,15 +445,22 @@ ExactPlan exact_plan(const ExactProblem &p, bool f32)
         }
     }
     plan.nkb = int((p.ntok + 31) / 32);
+    // ... and the smallest where a workgroup per tile and two steps would leave compute units idle: a quarter of the work
+    // each (390 tokens, 72 columns, 96 rows: 17.5 us in six workgroups of 128 x 128)
+    const int64_t whole = (p.cout + plan.bm - 1) / plan.bm * ((p.cin + plan.bn - 1) / plan.bn);
+    if (whole * std::max(plan.nkb / 2, 1) < 256) plan.bm = plan.bn = 64;
     plan.mb_count = int((p.cout + plan.bm - 1) / plan.bm);
     plan.nb_count = int((p.cin + plan.bn - 1) / plan.bn);
     // K-slices: two (128 x 128) to four workgroups per compute unit.  Measured with one / two / three / four: 84 / 81 /
     // 102 / 89 us for 36 tiles of 128 x 128 over 6304 tokens, 91 / 66 / 59 / 56 us for 9 tiles of 64 x 64 over 32768.
     // A slice writes a whole partial tile however little it summed, yet short problems want every compute unit: two
-    // 32-token steps per slice at least (435 tokens, 6 tiles: 15 us with two, 17 with four, 27 with eight).
+    // 32-token steps per slice at least (435 tokens, 6 tiles of 128 x 128: 15 us with two, 17 with four, 27 with eight),
+    // one as long as that makes no more than 256 workgroups (the 28 of 700 small calls that took over 1.2 times the vector
+    // kernels' time with two steps were 5 with one; 315 tiles over 41 tokens lost 12 -> 18 us by cutting them).
     const int64_t tiles = int64_t(plan.mb_count) * plan.nb_count;
     const int64_t resident = dev_env("DROPIT_EXACT_WGS", plan.bm * plan.bn >= 128 * 128 ? 512 : 1024);
-    const int64_t splits = std::min<int64_t>(resident / std::max<int64_t>(tiles, 1), plan.nkb / dev_env("DROPIT_EXACT_MIN", 2));
+    const int64_t most = std::max<int64_t>(plan.nkb / 2, std::min<int64_t>(plan.nkb, 256 / std::max<int64_t>(tiles, 1)));
+    const int64_t splits = std::min<int64_t>(resident / std::max<int64_t>(tiles, 1), most);
     plan.splits = int(std::max<int64_t>(1, std::min<int64_t>(splits, 256)));
     plan.partial_bytes = plan.splits > 1 ? size_t(plan.splits) * tiles * plan.bm * plan.bn * 4 : 0;
     return plan;
