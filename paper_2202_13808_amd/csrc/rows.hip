@@ -20,13 +20,15 @@ namespace {
 // predecessor and itself; j == k closes the table.  A thread takes eight consecutive pairs: two 16-byte loads and one
 // 16-byte store where both arrays are 16-byte aligned (VEC).  Bound by memory: 7.7 M pairs, 46 MB, took 17.5 us a pair
 // per thread with two divisions each, 11.0 in this form.
-template <bool VEC>
+// Where rows are short or sparse, a thread takes one pair (PER = 1): filling the offsets between its pairs, one store after
+// the other, is the longer part there.
+template <bool VEC, int PER>
 __global__ void __launch_bounds__(256)
 rows_from_idx_kernel(const int32_t *__restrict__ idx, int64_t k, Divisor row_len, int64_t rows,
                      uint16_t *__restrict__ col, int32_t *__restrict__ rowptr)
 {
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int PER = 8;
+    static_assert(!VEC || PER == 8, "two loads and one store");
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x * PER;
     for (int64_t j0 = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * PER; j0 <= k; j0 += stride) {
         int32_t v[PER];
@@ -35,10 +37,7 @@ rows_from_idx_kernel(const int32_t *__restrict__ idx, int64_t k, Divisor row_len
         if (whole) {
             const i32x4 a = *reinterpret_cast<const i32x4 *>(idx + j0), b = *reinterpret_cast<const i32x4 *>(idx + j0 + 4);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[e] = a[e];
-                v[4 + e] = b[e];
-            }
+            for (int e = 0; e < PER; ++e) v[e] = e < 4 ? a[e & 3] : b[e & 3];
         } else {
 #pragma unroll
             for (int e = 0; e < PER; ++e) v[e] = j0 + e < k ? idx[j0 + e] : 0;
@@ -131,11 +130,14 @@ extern "C" dropit_status dropit_compress_rows(const void *x, const int64_t *shap
     if (st != DROPIT_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const Divisor len = divisor(static_cast<uint32_t>(rs.row_len));
-    const unsigned grid = grid_for(k / 8 + 1);
-    if (aligned(idx, 16) && aligned(col, 16))
-        rows_from_idx_kernel<true><<<grid, 256, 0, stream>>>(idx, k, len, rs.rows, col, rowptr);
-    else
-        rows_from_idx_kernel<false><<<grid, 256, 0, stream>>>(idx, k, len, rs.rows, col, rowptr);
+    // Fewer than eight pairs per row (2 M rows of two, gamma 0.99: call 43.6 us with one pair to a thread and two divisions,
+    // 94.2 with eight, 35.6 now), or too few pairs for eight to a thread to fill the chip.
+    const bool one = k < 8 * rs.rows || k < (1 << 16);
+    const unsigned grid = grid_for(k / (one ? 1 : 8) + 1);
+    auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(idx, k, len, rs.rows, col, rowptr); };
+    if (one) launch(rows_from_idx_kernel<false, 1>);
+    else if (aligned(idx, 16) && aligned(col, 16)) launch(rows_from_idx_kernel<true, 8>);
+    else launch(rows_from_idx_kernel<false, 8>);
     trace_mark(stream);
     return launch_status();
 }
