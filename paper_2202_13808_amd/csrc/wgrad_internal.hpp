@@ -144,14 +144,14 @@ inline void launch_row_starts(const int32_t *idx, int64_t k, uint32_t plane, uin
                               hipStream_t stream)
 {
     const uint32_t nseg = (plane + seg - 1) / seg;
-    // Fewer than eight pairs per row.  (2.5 thousand pairs in 82 thousand rows: 45.4 us with eight to a thread; 500 calls
+    // Fewer than eight pairs per row, or too few pairs for eight to a thread to fill the chip.  (2.5 thousand pairs in 82 thousand rows: 45.4 us with eight to a thread; 500 calls
     // of random shapes and gammas did best with the line at eight, against one and three.)
-    const bool sparse = k < 8 * R;
-    const int blocks = int(std::min<int64_t>((k / (sparse ? 1 : 8) + 1 + 255) / 256, 4096));
+    const bool one = k < 8 * R || k < (1 << 16);
+    const int blocks = int(std::min<int64_t>((k / (one ? 1 : 8) + 1 + 255) / 256, 4096));
     auto launch = [&](auto kernel) {
         kernel<<<blocks, 256, 0, stream>>>(idx, k, divisor(plane), divisor(seg), nseg, R, row_ptr);
     };
-    if (sparse) launch(row_starts_kernel<false, 1>);
+    if (one) launch(row_starts_kernel<false, 1>);
     else if (aligned(idx, 16)) launch(row_starts_kernel<true, 8>);
     else launch(row_starts_kernel<false, 8>);
 }
