@@ -113,3 +113,67 @@ def test_sparse_and_full_rows(shape, J, geom, gamma):
     OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
     x = activation(shape, "relu", 61 + H, "bf16")
     check(x, gradient((N, J, OH, OW), 0.02, 62 + W, "bf16"), gamma, J, geom)
+
+
+@pytest.mark.parametrize("shape,J,geom", [
+    ((3, 17, 21, 40), 24, (3, 3, 4, 4, 1, 1, 1, 1)), ((2, 20, 33, 128), 16, (2, 2, 3, 3, 0, 0, 1, 1)),
+    ((2, 31, 18, 24), 40, (3, 5, 5, 4, 1, 2, 1, 1)), ((5, 12, 16, 64), 8, (1, 1, 2, 2, 0, 0, 1, 1))])
+def test_channels_last_written_rows(shape, J, geom):
+    """Channels-last windows whose rows hold less than the input does keep the written rows: several blocks of taps, the
+    last one not full."""
+    print("rows nhwc", shape, J, geom, flush=True)
+    N, H, W, C = shape
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    assert OH * OW * kh * kw < H * W
+    x = activation(shape, "relu", 71 + H, "bf16")
+    for gamma in (0.3, 0.9):
+        check(x, gradient((N, OH, OW, J), 0.02, 72 + W, "bf16"), gamma, J, geom, layout="nhwc")
+
+
+def integers(shape, seed, zeros):
+    """Whole numbers of magnitude up to 8: any sum of fewer than 2^18 of their products is exact in fp32."""
+    rng = np.random.default_rng(seed)
+    return f32_to_bf16_bits((rng.integers(-8, 9, shape) * (rng.random(shape) >= zeros)).astype(np.float32))
+
+
+@pytest.mark.parametrize("layout,shape,J,geom", [
+    ("nchw", (9, 65, 28, 28), 72, POINT), ("nchw", (2, 40, 56, 56), 64, POINT), ("nchw", (64, 24, 14, 14), 264, POINT),
+    ("nhwc", (64, 14, 14, 64), 64, (3, 3, 1, 1, 1, 1, 1, 1)), ("nhwc", (5, 29, 40, 72), 136, (3, 3, 1, 1, 1, 1, 1, 1)),
+    ("nhwc", (9, 31, 29, 24), 40, (3, 3, 2, 2, 1, 1, 1, 1)), ("nhwc", (2, 33, 41, 128), 16, (2, 2, 3, 3, 0, 0, 1, 1)),
+    ("nchw", (33, 128, 14, 14), 128, (3, 3, 1, 1, 1, 1, 1, 1)), ("nchw", (64, 136, 7, 7), 264, (3, 3, 1, 1, 1, 1, 1, 1)),
+    ("nchw", (9, 128, 16, 16), 136, (3, 3, 1, 1, 1, 1, 1, 1)), ("nchw", (7, 40, 28, 30), 24, (3, 3, 1, 1, 1, 1, 1, 1)),
+    ("nchw", (11, 24, 33, 31), 16, (3, 3, 2, 2, 1, 1, 1, 1))])
+def test_integer_sums_are_exact(layout, shape, J, geom):
+    """No term left out, taken twice or misplaced, at sizes of many slices: the sums are whole numbers and must be equal."""
+    print("integers", layout, shape, J, geom, flush=True)
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    N, C, H, W = shape if layout == "nchw" else (shape[0], shape[3], shape[1], shape[2])
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    x, dy = integers(shape, 81, 0.3), integers((N, J, OH, OW) if layout == "nchw" else (N, OH, OW, J), 82, 0.0)
+    vals, idx = dropit.compress(to_device(x), 0.45)
+    got = to_host(dropit.weight_grad(vals, idx, shape, to_device(dy), J, conv=geom, layout=layout)).astype(np.float64)
+    xh, g = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, 0.45)), shape), oracle.widen(dy)
+    if layout == "nhwc":
+        xh, g, got = xh.transpose(0, 3, 1, 2), g.transpose(0, 3, 1, 2), got.transpose(0, 3, 1, 2)
+    assert np.array_equal(got, dense_dw(xh, g, geom))
+
+
+@pytest.mark.parametrize("shape,J", [((2, 512, 14, 14), 512), ((1, 520, 16, 16), 520)])
+def test_small_planes_in_one_slice(shape, J):
+    """Many tiles and few tokens: the product runs in one slice, which the channel-major order still takes through the
+    partial tiles."""
+    geom = (3, 3, 1, 1, 1, 1, 1, 1)
+    print("one slice", shape, J, flush=True)
+    N, C, H, W = shape
+    x, dy = integers(shape, 83, 0.3), integers((N, J, H, W), 84, 0.0)
+    k = oracle.keep_count(x.size, 0.45)
+    assert dropit.weight_grad_path(shape, torch.bfloat16, k, J, geom) == "conv_gemm"
+    up = lambda n: (n + 255) // 256 * 256
+    tiles = ((9 * C + 255) // 256) * ((J + 255) // 256)
+    need = dropit.weight_grad_workspace_bytes(shape, torch.bfloat16, k, J, geom)
+    assert need == up((N * H * W + 1) * C * 2) + tiles * 256 * 256 * 4 + up(N * H * W * J * 2)       # one partial tile per tile
+    vals, idx = dropit.compress(to_device(x), 0.45)
+    got = to_host(dropit.weight_grad(vals, idx, shape, to_device(dy), J, conv=geom)).astype(np.float64)
+    xh = oracle.densify(*oracle.compress(x, k), shape)
+    assert np.array_equal(got, dense_dw(xh, oracle.widen(dy), geom))

@@ -109,3 +109,36 @@ def test_infinities_do_not_meet_the_padding(dtype, layout, shape, J, geom):
                               (ph, pw), (dh, dw))
         nu = (shape[0] * OH * OW + 256) * 2.0 ** -24
         assert (np.abs(got[fin] - ref[fin]) <= nu / (1 - nu) * size[fin]).all()
+
+
+@pytest.mark.parametrize("dtype,ntok,cin,cout", [("f32", 20000, 12, 4), ("f32", 6304, 384, 260), ("f32", 32001, 61, 67), ("bf16", 9000, 130, 129)])
+def test_integer_sums_are_exact(dtype, ntok, cin, cout):
+    """Whole numbers of magnitude up to 8, whose sums are exact in fp32 in any order: no term of a long sum left out, taken
+    twice or misplaced."""
+    print("exact integers", dtype, ntok, cin, cout, flush=True)
+    rng = np.random.default_rng(ntok)
+    xf, g = rng.integers(-8, 9, (ntok, cin)).astype(np.float32), rng.integers(-8, 9, (ntok, cout)).astype(np.float32)
+    x, dy = (xf, g) if dtype == "f32" else (f32_to_bf16_bits(xf), f32_to_bf16_bits(g))
+    vals, idx = dropit.compress(to_device(x), 0.4)
+    assert dropit.weight_grad_path(x.shape, vals.dtype, vals.numel(), cout) == "fma"
+    got = to_host(dropit.weight_grad(vals, idx, x.shape, to_device(dy), cout)).astype(np.float64)
+    xh = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, 0.4)), x.shape)
+    assert np.array_equal(got, oracle.widen(dy).astype(np.float64).T @ xh)
+
+
+@pytest.mark.parametrize("layout,shape,J,geom", [("nchw", (32, 24, 32, 32), 40, (3, 3, 1, 1, 1, 1, 1, 1)),
+                                                 ("nhwc", (9, 41, 37, 20), 70, (3, 3, 2, 2, 1, 1, 1, 1))])
+def test_integer_convolution_sums_are_exact(layout, shape, J, geom):
+    print("exact integer conv", layout, shape, J, geom, flush=True)
+    kh, kw, sh, sw, ph, pw, dh, dw = geom
+    N, C, H, W = shape if layout == "nchw" else (shape[0], shape[3], shape[1], shape[2])
+    OH, OW = (H + 2 * ph - dh * (kh - 1) - 1) // sh + 1, (W + 2 * pw - dw * (kw - 1) - 1) // sw + 1
+    rng = np.random.default_rng(H)
+    x = rng.integers(-8, 9, shape).astype(np.float32)
+    dy = rng.integers(-8, 9, (N, J, OH, OW) if layout == "nchw" else (N, OH, OW, J)).astype(np.float32)
+    vals, idx = dropit.compress(to_device(x), 0.4)
+    got = to_host(dropit.weight_grad(vals, idx, shape, to_device(dy), J, conv=geom, layout=layout)).astype(np.float64)
+    xh, g = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, 0.4)), shape), dy
+    if layout == "nhwc":
+        xh, g, got = (np.ascontiguousarray(a.transpose(0, 3, 1, 2)) for a in (xh, g, got))
+    assert np.array_equal(got, oracle.dw_conv(xh, g, kh, kw, (sh, sw), (ph, pw), (dh, dw)))

@@ -295,11 +295,11 @@ GEOMETRIES = [
     ((2, 3, 32, 48), 40, (16, 16, 16, 16, 0, 0, 1, 1)),    # 16x16 / stride 16 (ViT patch embedding)
     ((1, 4, 13, 17), 8, (3, 2, 1, 2, 2, 0, 2, 3)),         # asymmetric kernel, stride, pad, dilation
     ((2, 5, 12, 10), 16, (3, 3, 1, 1, 1, 1, 2, 2)),        # dilated 3x3
-    ((5, 24, 20, 20), 72, (3, 3, 1, 1, 1, 1, 1, 1)),       # 3x3 / stride 1 / pad 1 (channels-last only: NCHW has kernels of its own)
+    ((5, 24, 20, 20), 72, (3, 3, 1, 1, 1, 1, 1, 1)),       # 3x3 / stride 1 / pad 1 (channels-last only, through the window: NCHW has kernels of its own)
     ((3, 20, 37, 23), 136, (5, 5, 3, 2, 2, 1, 1, 1)),      # more than 256 output positions per image, three filter blocks
     ((2, 8, 6, 6), 8, (3, 3, 1, 1, 4, 4, 1, 1)),           # padding wider than the window: whole rows of taps see only zeros
     ((128, 8, 18, 18), 8, (3, 3, 1, 1, 0, 0, 1, 1)),       # many images: bands of several output rows per im2col tile
-    ((2, 256, 9, 32), 16, (3, 3, 2, 2, 1, 1, 1, 1)),       # a row of tokens beyond one tile: blocks of channels (NCHW) / taps (NHWC), ragged last block
+    ((2, 256, 9, 32), 16, (3, 3, 2, 2, 1, 1, 1, 1)),       # a row of tokens beyond one tile: blocks of channels (NCHW); channels-last reads the input through the window
     ((2, 20, 9, 300), 8, (5, 5, 1, 1, 2, 2, 1, 1)),        # ... with channels not a multiple of 8: zero fill + scatter instead of tiles
 ]
 
