@@ -183,9 +183,11 @@ dropit_wgrad_path dropit_weight_grad_path(const int64_t *x_shape, int ndim, drop
  *     dW  [c_out, C, kh, kw] fp32:
  *     dW[j][c][u][v] = sum_{n,oy,ox} dY[n][j][oy][ox] * R(a^)[n][c][oy*sh-ph+u*dh][ox*sw-pw+v*dw]
  *     bf16 with c_out % 8 == 0 and C*kh*kw <= 32768 runs on the matrix cores
- *     (3x3 / stride 1 / pad 1 and 1x1 / stride 1 in forms of their own, every other
- *     geometry through im2col rows in the workspace; shapes whose rows would exceed
- *     1 GiB are not taken; see dropit_weight_grad_path); fp32 and the remaining shapes (kernel extents up
+ *     (3x3 / stride 1 / pad 1 and 1x1 / stride 1 in forms of their own, channels-last
+ *     windows over the recovered input, every other geometry through im2col rows in
+ *     the workspace; outside the 3x3 form, shapes whose rows would exceed 1 GiB are not
+ *     taken, also where the form would write none: a limit of this library, not of those
+ *     forms; see dropit_weight_grad_path); fp32 and the remaining shapes (kernel extents up
  *     to 1024, stride / pad / dilation up to 65535) take the exact fp32 product, a sixteenth of the bf16 rate.
  *     DROPIT_EINVAL if the window does not fit the padded input.
  *

@@ -1639,7 +1639,7 @@ __device__ inline void select_serial(const RAW *__restrict__ x, int64_t numel, i
 }
 
 // ---- small tensors: one workgroup, everything in registers ------------------------------------------
-// Up to SMALL_VECTORS 16-byte vectors per thread (64 K fp32 or 128 K 16-bit elements): the tensor is read
+// Up to SMALL_VECTORS 16-byte vectors per thread (32 K fp32 or 64 K 16-bit elements): the tensor is read
 // once into registers and the whole selection -- the same digits, tie rule and slot formula as above --
 // runs in ONE workgroup with workgroup barriers only.  No workspace, no grid barrier, no residency
 // question; at this size the 256-workgroup form spends its time on its own machinery (a 64 KB tensor took

@@ -1,5 +1,5 @@
 // Split-K sums of the weight-gradient products (internal header): the K-slices' partial tiles, written in the
-// accumulators' own order by wgrad_fc_dense.hip and wgrad_f32.hip, are added in a fixed order and moved to
+// accumulators' own order by wgrad_fc_dense.hip and wgrad_exact.hip, are added in a fixed order and moved to
 // row-major dW.  A configuration C names the tile: BM, BN, NTHREADS, WAVES_N, WM, WN, FN (32 x 32 accumulators).
 #pragma once
 
