@@ -297,8 +297,8 @@ def main():
     main_kernel = ("conv_pointwise_kernel" if pointwise else "fc_dense_kernel" if (fc_mfma or conv_gemm or fc_fused) else "conv3x3_mfma_kernel" if conv_mfma else
                    "fc_small_kernel" if fc_small else "exact_gemm_kernel")
     select_kernel = "select_small_kernel" if w.numel // (8 if bf16 else 4) <= 8 * 1024 else "select_fused_kernel"
-    dw_traffic = measured_traffic(w.name + ("+lds" if fc_fused else ""), main_kernel)
-    sel_traffic = measured_traffic(w.name, select_kernel)
+    dw_traffic = measured_traffic(w.name + ("+nhwc" if nhwc else "+lds" if fc_fused else ""), main_kernel)
+    sel_traffic = measured_traffic(w.name + ("+nhwc" if nhwc else ""), select_kernel)
     out = {
         "metric": "min-k compress GB/s (% HBM peak) + sparse-input dW TFLOP/s (% MFMA peak)",
         "value": flops / (ms_per_step * 1e-3) * 1e-12,
