@@ -680,23 +680,25 @@ __device__ inline int64_t sample_piece(int i, int64_t nvf)
 }
 
 // The sample ranks around the k-th largest key's quantile, r - margin and r + margin with r = the sample's share of k.
-// False if one of them lies outside the sample: no bracket then, whatever the sample holds, and none is taken (a sample of
-// few magnitudes costs up to 5 us of LDS atomics on the same bins).
-__device__ inline bool sample_ranks(uint32_t k, int64_t numel, float &lo, float &hi)
+// No sample (lo = 0) if one of them lies outside of it: there is no bracket then, whatever the sample holds (a sample of
+// few magnitudes costs up to 5 us of LDS atomics on the same bins), or if the tensor is too small for one.
+struct SampleRanks {
+    float lo, hi;
+};
+inline SampleRanks sample_ranks(uint32_t k, int64_t numel)
 {
     const float frac = static_cast<float>(k) / static_cast<float>(numel);
     const float r = frac * static_cast<float>(SAMPLE_ELEMS);
-    const float margin = 5.0f * __builtin_sqrtf(fmaxf(r * (1.0f - frac), 1.0f)) + 8.0f;
-    lo = r - margin;
-    hi = r + margin;
-    return lo >= 1.0f && hi <= static_cast<float>(SAMPLE_ELEMS) - 1.0f;
+    const float margin = 5.0f * __builtin_sqrtf(std::max(r * (1.0f - frac), 1.0f)) + 8.0f;
+    const bool inside = r - margin >= 1.0f && r + margin <= static_cast<float>(SAMPLE_ELEMS) - 1.0f;
+    return inside && numel >= SAMPLE_MIN_NUMEL ? SampleRanks{r - margin, r + margin} : SampleRanks{0.0f, 0.0f};
 }
 
 // From the sample's histogram (in LDS; bin 0, the zeros, is not counted: it holds what the others leave of the sample): the
 // bins that hold the two ranks.
 // Returns false (in every thread) if there is no usable bracket (more than BRACKET_MAX_BINS bins).
 template <int NB>
-__device__ inline bool sample_bracket(const uint32_t *hist, float lo_f, float hi_f, uint32_t *wave_tot,
+__device__ inline bool sample_bracket(const uint32_t *hist, SampleRanks ranks, uint32_t *wave_tot,
                                       uint32_t *bcast /*[2]*/, uint32_t &b_lo, uint32_t &b_hi)
 {
     constexpr int PER = (NB + SEL_THREADS - 1) / SEL_THREADS;
@@ -712,7 +714,7 @@ __device__ inline bool sample_bracket(const uint32_t *hist, float lo_f, float hi
     if (tid < 2) bcast[tid] = 0xFFFFFFFFu;           // (ordered before the finders' stores by the scan's barriers)
     uint32_t total;
     const uint32_t above = block_exclusive_scan<SEL_THREADS>(mine, wave_tot, total);
-    const uint32_t rank[2] = {static_cast<uint32_t>(lo_f), static_cast<uint32_t>(hi_f) + 1u};   // higher bin first
+    const uint32_t rank[2] = {static_cast<uint32_t>(ranks.lo), static_cast<uint32_t>(ranks.hi) + 1u};   // higher bin first
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         if (tid == 0 && rank[q] > total) bcast[q] = 0u;              // among the zeros
@@ -903,7 +905,8 @@ __device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_
 // 16-bit element types.
 __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
                                            SelState *st, uint32_t *hist0, uint32_t *table, uint16_t *__restrict__ vals,
-                                           int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, ExitReport &rep)
+                                           int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks,
+                                           ExitReport &rep)
 {
     constexpr int VEC = 8;
     constexpr uint32_t MASK = KeyTraits<uint16_t>::MASK;
@@ -943,8 +946,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
         for (int u = 0; u < ST_ROWS; ++u) issue_row(q[u], row + u);
     };
 
-    float rank_lo, rank_hi;
-    const bool sampling = sample_ranks(k, numel, rank_lo, rank_hi) && numel >= SAMPLE_MIN_NUMEL;    // uniform over the grid
+    const bool sampling = ranks.lo > 0.0f;                      // uniform over the grid
     // The threshold lies in the key range [key_lo, key_lo + nf): predicted from the sample here, else (or if the
     // prediction fails) exactly known after the digit histogram.
     uint32_t key_lo = 0, nf = 1u << SHIFT1;
@@ -974,7 +976,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
             __syncthreads();
             STAMP(9);
             uint32_t b_lo, b_hi;
-            predicted = sample_bracket<SAMPLE_BINS>(lh, rank_lo, rank_hi, wave_tot, bcast, b_lo, b_hi);
+            predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, wave_tot, bcast, b_lo, b_hi);
             if (predicted) {
                 key_lo = b_lo << SAMPLE_SHIFT;
                 nf = (b_hi - b_lo + 1) << SAMPLE_SHIFT;
@@ -1757,13 +1759,13 @@ template <typename RAW>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k, SelState *st,
                     uint32_t *hist0, uint32_t *hist1, uint32_t *table, RAW *__restrict__ vals,
-                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen)
+                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks /* 16-bit types */)
 {
     ExitReport rep;
     rep.mine = 0u;
     SelOutcome outcome;
     if constexpr (sizeof(RAW) == 2)
-        outcome = select16_body(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, rep);
+        outcome = select16_body(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, ranks, rep);
     else
         outcome = select32_body(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen, rep);
     // Exit protocol: every workgroup reports once, when it is past its last grid barrier or gives up at one (the high
@@ -1963,11 +1965,12 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
             uint32_t spin_limit = mode == 3 ? 0u : SPIN_LIMIT;
             RAW *vals_t = static_cast<RAW *>(vals);
             unsigned long long gen = next_generation();
+            SampleRanks ranks = sample_ranks(k32, numel);
             trace_mark(stream);
             if (mode == 2) {               // the runtime guarantees co-residency, at the price of slow queue switches
                 void *args[] = {(void *)&xr, (void *)&numel, (void *)&nvf, (void *)&vpc, (void *)&k32, (void *)&st,
                                 (void *)&hist0, (void *)&hist1, (void *)&table, (void *)&vals_t, (void *)&idx,
-                                (void *)&spin_limit, (void *)&gen};
+                                (void *)&spin_limit, (void *)&gen, (void *)&ranks};
                 if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(select_fused_kernel<RAW>),
                                                dim3(static_cast<unsigned>(chunks)), dim3(SEL_THREADS), args,
                                                smem_bytes, stream) == hipSuccess) {
@@ -1977,7 +1980,7 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
                 (void)hipGetLastError();   // cooperative launch unavailable (e.g. stream capture): ordinary launch
             }
             select_fused_kernel<RAW><<<dim3(static_cast<unsigned>(chunks)), dim3(SEL_THREADS), smem_bytes, stream>>>(
-                xr, numel, nvf, vpc, k32, st, hist0, hist1, table, vals_t, idx, spin_limit, gen);
+                xr, numel, nvf, vpc, k32, st, hist0, hist1, table, vals_t, idx, spin_limit, gen, ranks);
             trace_mark(stream);
             return launch_status();
         }
