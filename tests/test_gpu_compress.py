@@ -158,7 +158,7 @@ def _run_with_path(x, gamma):
 
 def test_sampled_bracket_paths():
     """Large 16-bit tensors predict the threshold's bin from a sample every workgroup reads for itself (512 pieces
-    of 32 elements, one per equal stretch of the tensor at a hashed position inside it) and confirm it with exact
+    of 16 elements, one per equal stretch of the tensor at a hashed position inside it) and confirm it with exact
     counts.  All three outcomes must give the oracle's bytes: confirmed, unusable (quantile too close to an
     end), and missed -- forced here by giving exactly the sampled pieces a different scale from the rest, which
     no confidence margin can cover."""
@@ -169,7 +169,7 @@ def test_sampled_bracket_paths():
     assert _run_with_path(f32_to_bf16_bits(base), 0.99999) == 0          # k = 41: no usable margin
     assert _run_with_path(base, 0.9) == 0                                 # fp32 always builds the exact histograms
     nvf = numel // 8
-    seg = (nvf // 4) // 512                                               # 512 pieces of 4 vectors
+    seg = (nvf // 4) // 512                                               # 512 pieces, in the first two of 4 vectors each
     sampled = np.zeros(nvf, dtype=bool)
     for i in range(512):
         h = ((i + 1) * 0x9E3779B1) & 0xFFFFFFFF
@@ -224,6 +224,8 @@ def test_large_structured_inputs(kind):
 
 @pytest.mark.parametrize("numel", [(1 << 21) - 1, 1 << 21, (1 << 21) + 1, 3000017, 5 * (1 << 20) + 77])
 def test_sizes_around_the_sampling_threshold(numel):
+    """Around the size from which word 11 of the state block reports the prediction.  (The sampled form itself starts at
+    64 K elements: word 8 reports it at every size, see test_gpu_select_forms.)"""
     rng = np.random.default_rng(numel)
     x = f32_to_bf16_bits(rng.standard_normal(numel, dtype=np.float32))
     expect_sampling = numel >= (1 << 21)
