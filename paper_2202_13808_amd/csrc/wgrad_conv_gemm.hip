@@ -128,7 +128,7 @@ ConvGemmPlan conv_gemm_plan(const ConvProblem &p)
     plan.cblocks = int((p.C + plan.cb - 1) / plan.cb);
     plan.lds_bytes = size_t(HW) * (plan.cb + 2) * 2;
     plan.xd_bytes = conv_window_bytes(p.N, p.C, p.H, p.W);
-    plan.partial_bytes = round_up(conv_window_partial_bytes(plan.gemm, true), 256);
+    plan.partial_bytes = round_up(conv_window_partial_bytes(plan.fp, plan.gemm, true), 256);
     plan.dyt_bytes = round_up(size_t(plan.fp.ntok) * p.J * 2, 256);
     return plan;
 }
@@ -150,9 +150,8 @@ bool conv_gemm_supported(const ConvProblem &p)
 bool conv_gemm_preferred(const ConvProblem &p)
 {
     if (!conv_gemm_supported(p)) return false;
-    const ConvGemmPlan plan = conv_gemm_plan(p);
-    return p.H * p.W <= 256 && p.C >= 128 &&
-           int64_t(plan.gemm.nb_count) * plan.gemm.mb_count * plan.gemm.nkb >= 256;
+    const int64_t units = (9 * p.C + 255) / 256 * ((p.J + 255) / 256) * ((p.N * p.H * p.W + 31) / 32);   // 256 x 256 tiles times token blocks
+    return p.H * p.W <= 256 && p.C >= 128 && units >= 256;
 }
 
 dropit_status conv_gemm_run(const ConvProblem &p, const ConvGemmPlan &plan, const void *vals, const int32_t *idx,

@@ -531,7 +531,7 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
             // reads (sub-step 0) and the placement (sub-step 1)
             if constexpr (FUSED && kk == 0) {
                 if constexpr (m == NM / 2 || m == NM / 2 + 1) zero_b_half(fz_zero_stage, m - NM / 2);
-                if constexpr (m == NM / 2 + 2) read_staged(fz_place_stage);      // (tile t is staged in slot t % 4 = its stage)
+                if constexpr (m == std::min(NM / 2 + 2, NM - 1)) read_staged(fz_place_stage);      // (tile t is staged in slot t % 4 = its stage)
             }
             if constexpr (FUSED && kk == 1 && m >= NM / 2 && m < NM / 2 + FUSE_STAGE_WORDS / C::NTHREADS)
                 place_staged_one(std::integral_constant<int, m - NM / 2>{}, fz_place_stage, fz_place_count);
@@ -768,17 +768,33 @@ fc_dense_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ xd
         // [thread] x 4 floats, so every store is 16 bytes per lane and 1 KB contiguous per wavefront.
         // The seven-fold partial traffic then moves in full lines, and the one pass that adds the
         // slices (splitk_sum_kernel) does the transposition into row-major dW.
-        f32x4 *dst = reinterpret_cast<f32x4 *>(out) +
-                     (int64_t(split) * (nb_count * mb_count) + (mb * nb_count + nb)) * (BM * BN / 4) + threadIdx.x;
+        // FUSED: as the 128 x 128 tiles of four 64 x 64 wavefronts that the dense-operand form's small tile writes, whatever
+        // this tile is, and those alone that hold a column of dW: no more workspace than that form's partial tiles.
+        auto put = [&](f32x4 *dst, int i, int j, int stride, int slot) {
 #pragma unroll
-        for (int i = 0; i < C::FM; ++i)
+            for (int q = 0; q < 4; ++q)
+                dst[(slot * 4 + q) * stride] = f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+        };
+        f32x4 *part = reinterpret_cast<f32x4 *>(out);
+        if constexpr (FUSED) {
+            const int nbs = (N + 127) / 128, mbs = (M + 127) / 128;
 #pragma unroll
-            for (int j = 0; j < C::FN; ++j)
+            for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v4 = {acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
-                    dst[((i * C::FN + j) * 4 + q) * C::NTHREADS] = v4;
+                for (int j = 0; j < C::FN; ++j) {
+                    const int m = m0 + wm * C::WM + i * 32, n = n0 + wn * C::WN + j * 32;
+                    if (m / 128 < mbs && n / 128 < nbs)
+                        put(part + (int64_t(split) * (nbs * mbs) + (m / 128 * nbs + n / 128)) * (128 * 128 / 4) +
+                                (m % 128 / 64 * 2 + n % 128 / 64) * 64 + lane,
+                            i, j, 256, m % 64 / 32 * 2 + n % 64 / 32);
                 }
+        } else {
+            part += (int64_t(split) * (nb_count * mb_count) + (mb * nb_count + nb)) * (BM * BN / 4) + threadIdx.x;
+#pragma unroll
+            for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                for (int j = 0; j < C::FN; ++j) put(part, i, j, C::NTHREADS, i * C::FN + j);
+        }
     }
 }
 
@@ -883,48 +899,71 @@ fc_bucket_kernel(const uint16_t *__restrict__ vals, const int32_t *__restrict__ 
 #ifndef DROPIT_GEMM_CFG
 #define DROPIT_GEMM_CFG 256, 256, 32, 4, 2, 4, 2, 1
 #endif
-// For layers with at most 128 output channels: half the rows, wavefronts 2 x 4 of 64 x 64 each.  A 128-row
-// tile multiplies at ~0.7 of the wide tile's rate per flop (more LDS bytes per flop), but the wide one
-// would spend half its rows or more on padding there.
-#ifndef DROPIT_GEMM_CFG_NARROW
-#define DROPIT_GEMM_CFG_NARROW 128, 256, 32, 2, 4, 4, 2, 1
+// Four wavefronts of 64 x 64, two workgroups per compute unit: half the rate of the wide tile at best (its fragments and
+// direct loads keep the LDS busy for 768 of the 512 cycles that its MFMAs need), but a quarter of the result: less padding,
+// more workgroups where there are few tiles, and half the partial tiles where the whole chip works.  Which of the two a
+// product takes: choose_tile.  (Eight wavefronts of 32 x 64: the same time.  Three stages and three workgroups per compute
+// unit, or 128 x 256 and 256 x 128 tiles of four wavefronts with three stages: up to a fifth slower over 37 shapes.)
+#ifndef DROPIT_GEMM_CFG_SMALL
+#define DROPIT_GEMM_CFG_SMALL 128, 128, 32, 2, 2, 4, 2, 1
 #endif
 using Cfg = GemmCfg<DROPIT_GEMM_CFG>;
-using CfgFused = GemmCfg<256, 256, 32, 4, 2, 4, 2, 1>;          // the in-LDS recover form is laid out for four stages
-using CfgNarrow = GemmCfg<DROPIT_GEMM_CFG_NARROW>;
-static_assert(Cfg::BK == CfgNarrow::BK && Cfg::BN == CfgNarrow::BN, "the recovered operand is laid out once for both");
-static_assert(Cfg::BM == CfgFused::BM && Cfg::BN == CfgFused::BN && Cfg::BK == CfgFused::BK, "one plan serves both forms");
+using CfgSmall = GemmCfg<DROPIT_GEMM_CFG_SMALL>;
+static_assert(CfgSmall::BM == 128 && CfgSmall::BN == 128 && CfgSmall::WM == 64 && CfgSmall::WN == 64, "the in-LDS form writes its partial tiles");
+using CfgFused = GemmCfg<256, 256, 32, 4, 2, 4, 2, 1>;          // the in-LDS recover form is laid out for four stages ...
+using CfgFusedHalf = GemmCfg<128, 256, 32, 2, 4, 4, 2, 1>;      // ... of 32 x 256 elements of R(a^)
+static_assert(Cfg::BK == CfgSmall::BK, "the recovered operand is laid out once for both");
+static_assert(Cfg::BM == CfgFused::BM && Cfg::BN == CfgFused::BN && Cfg::BK == CfgFused::BK && Cfg::BN == CfgFusedHalf::BN &&
+              Cfg::BK == CfgFusedHalf::BK, "one regrouping serves both fused tiles");
+
+// A product over `nkb` token blocks in tiles of C: how it is cut, and what it costs beyond the other choices' common part.
+struct Cut {
+    int nb_count, mb_count, splits;
+    double us;
+};
 
 template <typename C>
-int tuned_splits(int tiles, int nkb)
+Cut cut_product(const FcProblem &p, int nkb)
 {
-    // as many K-slices as fill the 256 compute units (one or two resident workgroups each)
-    // without starting a second round -- but a slice of at least ~20 token blocks: every slice
-    // writes a whole partial tile however little it summed, and below that depth the partial
-    // traffic costs more than the idle compute units (measured on 3136 and 12544 tokens:
-    // the best slice count was the one with 19.6 blocks per slice both times)
-    int splits = std::min(256 * C::WGS_PER_CU / tiles, std::max(1, (nkb + 10) / 20));
-    splits = int(dev_env("DROPIT_FC_SPLITS", splits));
-    if (splits > nkb) splits = nkb;
-    if (splits < 1) splits = 1;
-    if (splits > 256) splits = 256;      // one slice per compute unit when the whole result is a single tile
-    return splits;
+    Cut c;
+    c.nb_count = int((p.cin + C::BN - 1) / C::BN);
+    c.mb_count = int((p.cout + C::BM - 1) / C::BM);
+    const int64_t tiles = int64_t(c.nb_count) * c.mb_count, slots = 256 * C::WGS_PER_CU;
+    constexpr bool WIDE = C::WGS_PER_CU == 1;
+    // Fitted to the calls of 37 shapes (both tiles each, worst miss 8 us of 103 where the two differ by 25): a round of
+    // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.47 in small ones (two; 0.33 where one
+    // has the compute unit to itself), and the partial tiles 0.24 us per MB, written and read; whatever its size a wide
+    // product takes another 3.3 us.
+    auto cost = [&](int64_t splits) {
+        const int64_t groups = tiles * splits, rounds = (groups + slots - 1) / slots, steps = (nkb + splits - 1) / splits;
+        const double partial_mb = splits > 1 ? double(groups) * C::BM * C::BN * 4e-6 : 0.0;
+        return double(rounds * steps) * (WIDE ? 0.66 : groups <= 256 ? 0.33 : 0.47) + 0.24 * partial_mb + (WIDE ? 3.3 : 0.0);
+    };
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(slots / tiles, nkb), 256));
+    auto allowed = [&](int64_t splits) { return std::max<int64_t>(1, std::min<int64_t>(splits, most)); };
+    // K-slices: each writes a whole partial tile however little it summed, which the slice sum reads again, so the count
+    // that costs least grows with the square root of the blocks over the tiles, wide and small tile alike (a sweep over 25
+    // shapes from 64 x 72 -> 128 to 25216 x 384 -> 1152; the earlier rule, 20 blocks to a slice, was up to 21 % slower
+    // where tiles are few: 2048 tokens of 256 -> 256, 16.7 -> 13.8 us).
+    int64_t splits = allowed(int64_t(3.0 * __builtin_sqrt(double(nkb) / double(tiles)) + 0.5));
+    // A second workgroup on a few compute units only holds the others up: fill them, or take one each (8312 x 1208 -> 360
+    // 38.6 -> 35.1 us, 64 images of 512 -> 512 channels at 7 x 7 44.5 -> 41.6; worst of 34 shapes + 1.8 %).
+    if (!WIDE && tiles * splits > 256 && tiles * splits < 384)
+        for (const int64_t other : {allowed(512 / tiles), allowed(256 / tiles)})
+            if (cost(other) < cost(splits)) splits = other;
+    splits = allowed(dev_env("DROPIT_FC_SPLITS", splits));
+    c.splits = int(splits);
+    c.us = cost(splits);
+    return c;
 }
 
-bool use_narrow(const FcProblem &p)
+// Calls in wide / small tiles: 1576 x 384 -> 1536 26.9 / 19.4 us, 25216 x 384 -> 1152 54 / 43, 25216 x 1536 -> 384 79 / 64,
+// 8192 x 1024 -> 1024 42 / 38; 12608 x 768 -> 3072 70.7 / 76.9, 16384 x 3072 -> 768 103 / 127 (large results that wide
+// tiles divide evenly keep them).
+GemmTile choose_tile(const FcProblem &p, int nkb)
 {
-    if (const long forced = dev_env("DROPIT_GEMM_NARROW", -1); forced >= 0) return forced == 1;
-    return p.cout <= CfgNarrow::BM;
-}
-
-template <typename C>
-void plan_tiles(const FcProblem &p, FcDensePlan &plan)
-{
-    plan.nb_count = int((p.cin + C::BN - 1) / C::BN);
-    plan.mb_count = int((p.cout + C::BM - 1) / C::BM);
-    plan.splits = tuned_splits<C>(plan.nb_count * plan.mb_count, plan.nkb);
-    // K-slice partials are whole tiles (ragged edge tiles included) in accumulator order
-    plan.partial_bytes = plan.splits > 1 ? size_t(plan.splits) * plan.nb_count * plan.mb_count * C::BM * C::BN * 4 : 0;
+    if (const long forced = dev_env("DROPIT_GEMM_TILE", -1); forced >= 0) return forced == 0 ? GemmTile::WIDE : GemmTile::SMALL;
+    return cut_product<Cfg>(p, nkb).us < cut_product<CfgSmall>(p, nkb).us ? GemmTile::WIDE : GemmTile::SMALL;
 }
 
 }  // namespace
@@ -941,19 +980,36 @@ bool fc_dense_supported(const FcProblem &p)
 bool fc_fused_supported(const FcProblem &p)
 {
     // the wide tile only; the column blocks of a token block are counted in LDS; pair positions are 32-bit
-    return fc_dense_supported(p) && !use_narrow(p) && (p.cin + Cfg::BN - 1) / Cfg::BN <= BUCKET_MAX_NB &&
+    return fc_dense_supported(p) && p.cout > 128 && (p.cin + Cfg::BN - 1) / Cfg::BN <= BUCKET_MAX_NB &&
            p.k < (int64_t(1) << 31);
+}
+
+static size_t tile_elems(GemmTile t)
+{
+    return t == GemmTile::WIDE ? Cfg::BM * Cfg::BN : CfgSmall::BM * CfgSmall::BN;
 }
 
 FcDensePlan fc_dense_plan(const FcProblem &p, bool fused)
 {
     FcDensePlan plan;
     plan.nkb = int((p.ntok + Cfg::BK - 1) / Cfg::BK);
-    plan.narrow = use_narrow(p);
-    if (plan.narrow)
-        plan_tiles<CfgNarrow>(p, plan);
-    else
-        plan_tiles<Cfg>(p, plan);
+    plan.tile = choose_tile(p, plan.nkb);
+    const Cut cut = plan.tile == GemmTile::WIDE ? cut_product<Cfg>(p, plan.nkb) : cut_product<CfgSmall>(p, plan.nkb);
+    plan.nb_count = cut.nb_count;
+    plan.mb_count = cut.mb_count;
+    plan.splits = cut.splits;
+    if (fused) {
+        // The same slices, so that every sum is the dense-operand form's bit for bit, in the tile that takes fewer rounds of
+        // 256 workgroups (a step of the half tile takes two thirds of the wide one's)
+        plan.nb_count = int((p.cin + Cfg::BN - 1) / Cfg::BN);
+        const int64_t wide = (p.cout + 255) / 256, half = (p.cout + 127) / 128;
+        auto rounds = [&](int64_t mb) { return (mb * plan.nb_count * plan.splits + 255) / 256; };
+        plan.tile = 3 * rounds(wide) <= 2 * rounds(half) ? GemmTile::WIDE : GemmTile::HALF;
+        plan.mb_count = int(plan.tile == GemmTile::WIDE ? wide : half);
+    }
+    // K-slice partials are whole tiles (ragged edge tiles included) in accumulator order; the in-LDS form writes small ones
+    const int64_t tiles = fused ? ((p.cin + 127) / 128) * ((p.cout + 127) / 128) : int64_t(plan.nb_count) * plan.mb_count;
+    plan.partial_bytes = plan.splits > 1 ? size_t(plan.splits) * tiles * tile_elems(fused ? GemmTile::SMALL : plan.tile) * 4 : 0;
     plan.pitch = int((p.cin + 7) / 8 * 8);
     plan.rows_per_wg = std::max(1, (plan.pitch <= RECOVER_ELEMS ? RECOVER_ELEMS : RECOVER_ELEMS_MAX) / plan.pitch);
     plan.ntok_pad = int64_t(plan.nkb) * Cfg::BK;
@@ -986,12 +1042,14 @@ static bool fc_dense_attributes()
                                    hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES) == hipSuccess &&
                hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgFused, true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, CfgFused::LDS_BYTES + FUSE_LDS_BYTES) == hipSuccess &&
-               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgNarrow, false>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgNarrow::LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgFusedHalf, true>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgFusedHalf::LDS_BYTES + FUSE_LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgSmall, false>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgSmall::LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgSmall, false, false, true>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgSmall::LDS_BYTES) == hipSuccess &&
                hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<Cfg, false, true, true>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES) == hipSuccess &&
-               hipFuncSetAttribute(reinterpret_cast<const void *>(fc_dense_kernel<CfgNarrow, false, false, true>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, CfgNarrow::LDS_BYTES) == hipSuccess;
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES) == hipSuccess;
     });
 }
 
@@ -1012,6 +1070,9 @@ static dropit_status launch_gemm(const FcProblem &p, const FcDensePlan &plan, co
     trace_mark(stream);
     if (WIN && win.channel_major)
         launch_splitk_sum_taps<C>(partial, plan.splits, int(p.cout), win.C, plan.nb_count, plan.mb_count, dW, stream);
+    else if (summed && FUSED)
+        launch_splitk_sum<CfgSmall>(partial, plan.splits, int(p.cout), int(p.cin), int((p.cin + 127) / 128),
+                                    int((p.cout + 127) / 128), dW, stream);
     else if (summed)
         launch_splitk_sum<C>(partial, plan.splits, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count, dW, stream);
     trace_mark(stream);
@@ -1022,7 +1083,8 @@ dropit_status fc_dense_gemm(const FcProblem &p, const FcDensePlan &plan, const v
                             float *partial, float *dW, hipStream_t stream)
 {
     if (!fc_dense_attributes()) return DROPIT_EHIP;
-    if (plan.narrow) return launch_gemm<CfgNarrow>(p, plan, dY, dense, partial, dW, stream);
+    if (plan.tile == GemmTile::HALF) return DROPIT_EHIP;             // (a fused plan)
+    if (plan.tile == GemmTile::SMALL) return launch_gemm<CfgSmall>(p, plan, dY, dense, partial, dW, stream);
     if (dev_env("DROPIT_GEMM_LOCKSTEP", 0)) return launch_gemm<Cfg>(p, plan, dY, dense, partial, dW, stream);
     return launch_gemm<Cfg, false, true>(p, plan, dY, dense, partial, dW, stream);
 }
@@ -1052,10 +1114,10 @@ bool conv_window_supported(int64_t N, int64_t C, int64_t H, int64_t W)
     return C % 8 == 0 && C <= RECOVER_ELEMS_MAX && (N * H * W + 1) * C * 2 <= int64_t(UINT32_MAX);
 }
 
-size_t conv_window_partial_bytes(const FcDensePlan &plan, bool channel_major)
+size_t conv_window_partial_bytes(const FcProblem &p, const FcDensePlan &plan, bool channel_major)
 {
     if (plan.splits > 1 || !channel_major) return plan.partial_bytes;
-    return size_t(plan.nb_count) * plan.mb_count * (plan.narrow ? CfgNarrow::BM * CfgNarrow::BN : Cfg::BM * Cfg::BN) * 4;
+    return size_t((p.cin + 255) / 256) * ((p.cout + 255) / 256) * (256 * 256) * 4;     // whole 256 x 256 blocks: either tile's
 }
 
 dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *vals, const int32_t *idx, int64_t k,
@@ -1072,8 +1134,9 @@ dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *va
 dropit_status conv_window_gemm(const FcProblem &p, const FcDensePlan &plan, const ConvWindow &w, const void *dY,
                                const uint16_t *xd, float *partial, float *dW, hipStream_t stream)
 {
-    if (!fc_dense_attributes()) return DROPIT_EHIP;
-    if (plan.narrow) return launch_gemm<CfgNarrow, false, false, true>(p, plan, dY, xd, partial, dW, stream, nullptr, nullptr, w);
+    if (!fc_dense_attributes() || plan.tile == GemmTile::HALF) return DROPIT_EHIP;
+    if (plan.tile == GemmTile::SMALL)
+        return launch_gemm<CfgSmall, false, false, true>(p, plan, dY, xd, partial, dW, stream, nullptr, nullptr, w);
     return launch_gemm<Cfg, false, true, true>(p, plan, dY, xd, partial, dW, stream, nullptr, nullptr, w);
 }
 
@@ -1094,7 +1157,7 @@ dropit_status fc_dense_run(const FcProblem &p, const FcDensePlan &plan, const vo
 dropit_status fc_fused_run(const FcProblem &p, const FcDensePlan &plan, const void *vals, const int32_t *idx,
                            const void *dY, float *dW, char *ws, hipStream_t stream)
 {
-    if (!fc_dense_attributes() || !plan.fused || plan.narrow || p.k < 1) return DROPIT_EHIP;
+    if (!fc_dense_attributes() || !plan.fused || p.k < 1) return DROPIT_EHIP;
     uint32_t *packed = reinterpret_cast<uint32_t *>(ws);
     uint32_t *tile_ptr = reinterpret_cast<uint32_t *>(ws + plan.packed_bytes);
     uint32_t *kb_ptr = reinterpret_cast<uint32_t *>(ws + plan.packed_bytes + plan.table_bytes);
@@ -1107,6 +1170,7 @@ dropit_status fc_fused_run(const FcProblem &p, const FcDensePlan &plan, const vo
                                                                 uint32_t(p.cin), plan.nb_count, plan.nkb, kb_ptr, packed,
                                                                 tile_ptr);
     trace_mark(stream);
+    if (plan.tile == GemmTile::HALF) return launch_gemm<CfgFusedHalf, true>(p, plan, dY, nullptr, partial, dW, stream, packed, tile_ptr);
     return launch_gemm<CfgFused, true>(p, plan, dY, nullptr, partial, dW, stream, packed, tile_ptr);
 }
 

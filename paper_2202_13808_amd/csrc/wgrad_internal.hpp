@@ -11,9 +11,11 @@ struct FcProblem {
     int64_t ntok, cin, cout, k;
 };
 
+// the product's tile of dW: 256 x 256 or 128 x 128; 128 x 256 in the in-LDS recover form only
+enum class GemmTile { WIDE, SMALL, HALF };
 struct FcDensePlan {
     int nkb, nb_count, mb_count, splits, pitch, rows_per_wg;
-    bool narrow;                               // the 128-row tile configuration (layers with few output channels)
+    GemmTile tile;
     int64_t ntok_pad;                          // rows of the dense operand: the tokens rounded up to whole token blocks
     size_t dense_bytes, partial_bytes;
     // the in-LDS form keeps no dense operand: the pairs regrouped by tile (a word each), the table of tile starts
@@ -86,7 +88,7 @@ ConvWindow conv_window(int64_t N, int64_t C, int64_t H, int64_t W, int64_t OH, i
 bool conv_window_supported(int64_t N, int64_t C, int64_t H, int64_t W);
 inline size_t conv_window_bytes(int64_t N, int64_t C, int64_t H, int64_t W) { return round_up(size_t(N * H * W + 1) * C * 2, 256); }
 // bytes of `partial` for the product (a channel-major dW always goes through the slice sum, which reorders it)
-size_t conv_window_partial_bytes(const FcDensePlan &plan, bool channel_major);
+size_t conv_window_partial_bytes(const FcProblem &p, const FcDensePlan &plan, bool channel_major);
 // xd from the pairs of an NHWC tensor; the product (dY token-major)
 dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *vals, const int32_t *idx, int64_t k,
                                   uint16_t *xd, hipStream_t stream);
