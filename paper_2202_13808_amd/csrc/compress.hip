@@ -664,7 +664,7 @@ constexpr int SAMPLE_STRETCH = 4;                     // a piece starts at a mul
 constexpr int SAMPLE_PIECE = SEL_THREADS / SAMPLE_PIECES;   // ... and is this many vectors long: one vector per thread
 constexpr int SAMPLE_ELEMS = SEL_THREADS * 8;
 constexpr int64_t SAMPLE_LARGE = int64_t(1) << 21;    // from here on the state's `path` says how the prediction went
-constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 16;
+constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 15;
 static_assert(SAMPLE_MIN_NUMEL / 8 / SAMPLE_STRETCH >= SAMPLE_PIECES, "a place per stretch at least");
 constexpr int SAMPLE_SHIFT = 3, SAMPLE_BINS = 1 << (15 - SAMPLE_SHIFT);    // 8 keys per bin
 constexpr int BRACKET_MAX_BINS = MAX_LAST_BINS >> SAMPLE_SHIFT;
@@ -681,17 +681,17 @@ __device__ inline int64_t sample_piece(int i, int64_t nvf)
 
 // The sample ranks around the k-th largest key's quantile, r - margin and r + margin with r = the sample's share of k.
 // No sample (lo = 0) if one of them lies outside of it: there is no bracket then, whatever the sample holds (a sample of
-// few magnitudes costs up to 5 us of LDS atomics on the same bins), or if the tensor is too small for one.
+// few magnitudes costs up to 5 us of LDS atomics on the same bins).
 struct SampleRanks {
     float lo, hi;
 };
-inline SampleRanks sample_ranks(uint32_t k, int64_t numel)
+inline SampleRanks sample_ranks(uint32_t k, int64_t numel, int sample)
 {
     const float frac = static_cast<float>(k) / static_cast<float>(numel);
-    const float r = frac * static_cast<float>(SAMPLE_ELEMS);
+    const float r = frac * static_cast<float>(sample);
     const float margin = 5.0f * __builtin_sqrtf(std::max(r * (1.0f - frac), 1.0f)) + 8.0f;
-    const bool inside = r - margin >= 1.0f && r + margin <= static_cast<float>(SAMPLE_ELEMS) - 1.0f;
-    return inside && numel >= SAMPLE_MIN_NUMEL ? SampleRanks{r - margin, r + margin} : SampleRanks{0.0f, 0.0f};
+    const bool inside = r - margin >= 1.0f && r + margin <= static_cast<float>(sample) - 1.0f;
+    return inside ? SampleRanks{r - margin, r + margin} : SampleRanks{0.0f, 0.0f};
 }
 
 // From the sample's histogram (in LDS; bin 0, the zeros, is not counted: it holds what the others leave of the sample): the
@@ -1640,118 +1640,442 @@ __device__ inline void select_serial(const RAW *__restrict__ x, int64_t numel, i
     }
 }
 
+// ---- candidates of 32-bit elements ------------------------------------------------------------------
+// As count_candidates / stage_candidates above: the four consecutive elements of q against a lowest key; a staged candidate
+// is two words, the element and its position.
+__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint32_t)
+{
+    uint32_t n = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        keys[e] = q[e] & KeyTraits<uint32_t>::MASK;
+        n += keys[e] >= lowest ? 1u : 0u;
+    }
+    return n;
+}
+__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
+                                        uint32_t addr, uint32_t pos, uint32_t)
+{
+    unsigned long long saved;
+    const uint32_t lo = lowest;
+#define STAGE_ELEMENT(W, K)                                      \
+    "v_cmpx_le_u32 vcc, %[lo], " K "\n\t"                        \
+    "ds_write2_b32 %[addr], " W ", %[pos] offset1:1\n\t"         \
+    "v_add_u32 %[addr], 8, %[addr]\n\t"                          \
+    "s_mov_b64 exec, %[valid]\n\t"                               \
+    "v_add_u32 %[pos], 1, %[pos]\n\t"
+    asm volatile("s_mov_b64 %[saved], exec\n\t"
+                 "s_mov_b64 exec, %[valid]\n\t"
+                 STAGE_ELEMENT("%[q0]", "%[k0]") STAGE_ELEMENT("%[q1]", "%[k1]") STAGE_ELEMENT("%[q2]", "%[k2]") STAGE_ELEMENT("%[q3]", "%[k3]")
+                 "s_mov_b64 exec, %[saved]\n\t"
+                 "s_nop 4"                      // (cross-lane operations must not follow a vector write of the mask closely)
+                 : [addr] "+&v"(addr), [pos] "+&v"(pos), [saved] "=&s"(saved)
+                 : [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [k0] "v"(keys[0]), [k1] "v"(keys[1]),
+                   [k2] "v"(keys[2]), [k3] "v"(keys[3]), [lo] "s"(lo), [valid] "s"(valid)
+                 : "vcc", "memory");
+#undef STAGE_ELEMENT
+}
+__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint16_t) { return count_candidates(q, lowest, keys); }
+__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
+                                        uint32_t addr, uint32_t pos, uint16_t)
+{
+    stage_candidates(q, keys, lowest, valid, addr, pos);
+}
+
+// A staged candidate of either type.
+template <typename RAW> struct Staged;
+template <> struct Staged<uint16_t> {
+    typedef uint32_t word;
+    __device__ static uint32_t raw(word w) { return w >> 16; }
+    __device__ static uint32_t pos(word w) { return w & 0xFFFFu; }
+    __device__ static word make(uint32_t raw, uint32_t pos) { return raw << 16 | pos; }
+};
+template <> struct Staged<uint32_t> {
+    typedef unsigned long long word;
+    __device__ static uint32_t raw(word w) { return uint32_t(w); }
+    __device__ static uint32_t pos(word w) { return uint32_t(w >> 32); }
+    __device__ static word make(uint32_t raw, uint32_t pos) { return static_cast<unsigned long long>(pos) << 32 | raw; }
+};
+
 // ---- small tensors: one workgroup, everything in registers ------------------------------------------
 // Up to SMALL_VECTORS 16-byte vectors per thread (32 K fp32 or 64 K 16-bit elements): the tensor is read
-// once into registers and the whole selection -- the same digits, tie rule and slot formula as above --
+// once into registers and the whole selection -- the same tie rule and slot formula as above --
 // runs in ONE workgroup with workgroup barriers only.  No workspace, no grid barrier, no residency
-// question; at this size the 256-workgroup form spends its time on its own machinery (a 64 KB tensor took
-// 22 us there).  Thread t holds vectors t, t + 1024, ...; the compaction goes row by row (1024 vectors).
+// question.  Bound by the instructions of one compute unit: a vector instruction per element is 0.1 us for 16 K elements, an
+// LDS atomic per element 2 us, and digit histograms over all elements (13 + 13 + 5 bits for fp32) were three of those.
+// Instead one element of every vector is histogrammed (4096 bins, the key's upper 12 bits), which gives a bracket of the
+// k-th key as the sample of the large form does; what is not below it, little more than k elements, is staged in LDS in
+// flat order, a segment per wavefront and its contiguous range, and everything after that -- the counts that confirm the
+// bracket, the digits of the threshold (10 bits at a time; 64 elements or fewer are ranked by a wavefront), the output --
+// walks the staged words.  Rows of 64 vectors that the segment does not hold are read again for each of these, and staged
+// when it has been written out.  A bracket that fails, and small tensors, take the bin of the exact histogram.
+// fp32 of 16 K elements at gamma 0.9 13.2 -> 9.2 us, 32 K 20.0 -> 11.9; 16-bit 32 K 14.2 -> 10.8; all magnitudes equal, fp32
+// of 16 K 25.4 -> 22.3.
 constexpr int SMALL_VECTORS = 8;
+constexpr int SMALL_BINS = 4096, SMALL_DIGIT = 10;
+constexpr int SMALL_SAMPLE_MIN = 2048;                         // vectors: below, all elements are as quickly histogrammed
+constexpr int SMALL_SEG_BYTES = 9216;                          // per wavefront, at most: 1152 staged fp32 elements, 2304 16-bit ones
+template <typename RAW>
+inline uint32_t small_cap(int nvf)                             // staged words per wavefront: as many as its range has elements, if they fit
+{
+    constexpr int VEC = KeyTraits<RAW>::VEC, NW = SEL_THREADS / WAVE;
+    const int most = SMALL_SEG_BYTES / int(sizeof(typename Staged<RAW>::word));
+    static_assert(SMALL_SEG_BYTES / int(sizeof(typename Staged<RAW>::word)) >= WAVE * VEC + VEC, "a row and a ragged end");
+    const int vectors = std::max((nvf + NW - 1) / NW + 3, WAVE) + 1;
+    return uint32_t(std::min(vectors * VEC / 4 * 4, most));
+}
 
 template <typename RAW>
 __global__ void __launch_bounds__(SEL_THREADS)
-select_small_kernel(const RAW *__restrict__ x, int64_t numel, int nvf, uint32_t k, RAW *__restrict__ vals,
-                    int32_t *__restrict__ idx)
+select_small_kernel(const RAW *__restrict__ x, int numel, int nvf, uint32_t k, SampleRanks ranks, uint32_t cap,
+                    RAW *__restrict__ vals, int32_t *__restrict__ idx)
 {
     constexpr int VEC = KeyTraits<RAW>::VEC;
     constexpr uint32_t MASK = KeyTraits<RAW>::MASK;
-    constexpr bool F32 = sizeof(RAW) == 4;
-    constexpr int LAST_BITS = F32 ? 5 : 4;
-    __shared__ uint32_t lh[(1 << MAX_HIST_BITS) + 2 * WAVE];
+    constexpr int SHIFT = (sizeof(RAW) == 4 ? 31 : 15) - 12;
+    constexpr int NW = SEL_THREADS / WAVE;
+    typedef typename Staged<RAW>::word word;
+    static_assert(SMALL_BINS == 4 * SEL_THREADS && (1 << SMALL_DIGIT) == SEL_THREADS, "four bins, one digit bin per thread");
+    extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
+    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_smem);
+    __shared__ uint32_t digit_bins[1 << SMALL_DIGIT], few[WAVE];
+    __shared__ uint32_t wave_tot[2][NW], wave_gt[NW], wave_eq[NW];
+    __shared__ uint32_t bcast[4], in_n, above_n, few_n;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
+    word *seg = reinterpret_cast<word *>(dyn_smem) + wave * cap;      // `cap` staged words: a row of candidates and a ragged end at least
+    const uint32_t seg_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) word *)seg));
+
+    // wavefront `wave` owns vectors [wv0, wv0 + wvecs), in rows of 64; the last one also the ragged end, an element per lane
+    const int vpw = ((nvf + NW - 1) / NW + 3) / 4 * 4;
+    const int wv0 = min(wave * vpw, nvf), wvecs = min(wv0 + vpw, nvf) - wv0;
+    const int nrows = (wvecs + WAVE - 1) / WAVE;                    // <= SMALL_VECTORS (checked by the host)
+    const int ntail = wave == NW - 1 ? numel - nvf * VEC : 0;
+    u32x4 q[SMALL_VECTORS];
+#pragma unroll
+    for (int i = 0; i < SMALL_VECTORS; ++i)
+        q[i] = i * WAVE + lane < wvecs ? xv[wv0 + i * WAVE + lane] : u32x4{0u, 0u, 0u, 0u};
+    const uint32_t tail = lane < ntail ? uint32_t(x[nvf * VEC + lane]) : 0u;
+    auto load_row = [&](int i) { return i * WAVE + lane < wvecs ? xv[wv0 + i * WAVE + lane] : u32x4{0u, 0u, 0u, 0u}; };
+    // f(key) for the elements of the rows from `first` on and of the ragged end, the rows read again: a loop over the
+    // registers would be unrolled eight-fold wherever it is used, and fetching instructions bounds the smallest tensors
+    auto for_rows = [&](int first, auto f) {
+#pragma nounroll
+        for (int i = first; i < nrows; ++i) {
+            const u32x4 v = load_row(i);
+            if (i * WAVE + lane < wvecs) for_each_raw(RAW(0), v, [&](uint32_t raw, int) { f(raw & MASK); });
+        }
+        if (lane < ntail) f(tail & MASK);
+    };
+    // counts of a thread's bins, the workgroup's bins in descending order: what lies above the thread's
+    auto above_mine = [&](uint32_t mine, int slot, uint32_t &total) -> uint32_t {
+        const uint32_t inc = wave_inclusive_scan(mine);
+        if (lane == WAVE - 1) wave_tot[slot][wave] = inc;
+        __syncthreads();
+        const uint32_t t = lane < NW ? wave_tot[slot][lane] : 0u, tinc = wave_inclusive_scan(t);
+        total = uint32_t(__builtin_amdgcn_readlane(int(tinc), WAVE - 1));
+        return uint32_t(__builtin_amdgcn_readlane(int(tinc - t), wave)) + inc - mine;
+    };
+    // The candidates (key >= lowest) of row i, v, behind the n words of the segment; false if it does not hold them.
+    uint32_t n = 0;
+    auto stage_row = [&](const u32x4 &v, int i, uint32_t lowest) -> bool {
+        const bool there = i * WAVE + lane < wvecs;
+        u32x4 keys;
+        const uint32_t cn = count_candidates(v, lowest, keys, RAW(0)), c = there ? cn : 0u;
+        const uint32_t inc = wave_inclusive_scan(c);
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(inc), WAVE - 1));
+        if (n + total > cap) return false;
+        stage_candidates(v, keys, lowest, __ballot(there), seg_addr + (n + inc - c) * uint32_t(sizeof(word)),
+                         uint32_t((i * WAVE + lane) * VEC), RAW(0));
+        n += total;
+        return true;
+    };
+    auto stage_tail = [&](uint32_t lowest) -> bool {
+        const bool in = lane < ntail && (tail & MASK) >= lowest;
+        const lane_mask b = __ballot(in);
+        const uint32_t total = uint32_t(__builtin_popcountll(b));
+        if (n + total > cap) return false;
+        if (in) seg[bits_before(b, n)] = Staged<RAW>::make(tail, uint32_t(wvecs * VEC + lane));
+        n += total;
+        return true;
+    };
+
+    uint32_t lo = 0, width = 0, k_rem = k, left = 0;  // keys [lo, lo + width) hold the k-th largest: the k_rem-th largest of the `left` in it
+    bool sampled = ranks.lo > 0.0f;                   // uniform
+    int staged_rows = 0;                              // rows from here on are not in the segment; the ragged end counts as row nrows
+    // f(key) for the wavefront's elements with key >= lo
+    auto for_candidates = [&](auto f) {
+        for (uint32_t j = lane; j < n; j += WAVE) f(Staged<RAW>::raw(seg[j]) & MASK);
+        if (staged_rows <= nrows) for_rows(staged_rows, [&](uint32_t key) { if (key >= lo) f(key); });
+    };
+    for (;;) {
+        reinterpret_cast<u32x4 *>(lh)[tid] = u32x4{0u, 0u, 0u, 0u};
+        digit_bins[tid] = 0u;
+        if (tid == 0) in_n = above_n = few_n = 0u;
+        __syncthreads();
+        auto count = [&](uint32_t key) {
+            if (key >> SHIFT) atomicAdd(&lh[key >> SHIFT], 1u);      // bin 0, the zeros, holds what the others leave
+        };
+        if (sampled) {
+#pragma unroll
+            for (int i = 0; i < SMALL_VECTORS; ++i)
+                if (i * WAVE + lane < wvecs) {                       // one element of each vector, another one from vector to vector
+                    const uint32_t e = uint32_t(lane + (lane >> 3) + i) % VEC;
+                    if constexpr (VEC == 4) {
+                        const uint32_t a = e & 1 ? q[i][1] : q[i][0], b = e & 1 ? q[i][3] : q[i][2];
+                        count((e & 2 ? b : a) & MASK);
+                    } else {
+                        const uint32_t a = e & 2 ? q[i][1] : q[i][0], b = e & 2 ? q[i][3] : q[i][2];
+                        count((e & 4 ? b : a) >> (e & 1 ? 16 : 0) & MASK);
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (i * WAVE + lane < wvecs) for_each_raw(RAW(0), q[i], [&](uint32_t raw, int) { count(raw & MASK); });
+            for_rows(2, count);
+        }
+        __syncthreads();
+        uint32_t c[4], total;
+        {
+            const u32x4 w = reinterpret_cast<const u32x4 *>(lh)[SEL_THREADS - 1 - tid];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] = w[3 - i];
+        }
+        const int hi_bin = SMALL_BINS - 1 - tid * 4;
+        const uint32_t mine = c[0] + c[1] + c[2] + c[3];
+        const uint32_t above = above_mine(mine, 0, total);
+        const uint32_t rank[2] = {sampled ? uint32_t(ranks.lo) : k, sampled ? uint32_t(ranks.hi) + 1u : k};   // higher bin first
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (tid == 0 && rank[r] > total) {
+                bcast[r] = 0u;
+                bcast[2] = k - total;
+                bcast[3] = uint32_t(numel) - total;
+            }
+            if (above < rank[r] && rank[r] <= above + mine) {
+                uint32_t a = above;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (a < rank[r] && rank[r] <= a + c[i]) {
+                        bcast[r] = uint32_t(hi_bin - i);
+                        bcast[2] = k - a;              // (of the exact histogram; a sample's mean nothing)
+                        bcast[3] = c[i];
+                    }
+                    a += c[i];
+                }
+            }
+        }
+        __syncthreads();                               // (also: the histogram is read, its place is the segments')
+        lo = bcast[1] << SHIFT;
+        width = (bcast[0] - bcast[1] + 1u) << SHIFT;
+        const uint32_t low_s = __builtin_amdgcn_readfirstlane(lo);
+        n = 0;
+        bool fits = true;
+        staged_rows = 0;
+#pragma unroll
+        for (int i = 0; i < SMALL_VECTORS; ++i)
+            if (fits && i < nrows) {                   // uniform over the wavefront
+                fits = stage_row(q[i], i, low_s);
+                staged_rows += fits ? 1 : 0;
+            }
+        if (fits && stage_tail(low_s)) staged_rows = nrows + 1;
+        if (!sampled) {
+            k_rem = bcast[2];
+            left = bcast[3];
+            break;
+        }
+        uint32_t in_range = 0, above_range = 0;
+        for_candidates([&](uint32_t key) {
+            in_range += key - lo < width ? 1u : 0u;
+            above_range += key - lo < width ? 0u : 1u;
+        });
+        in_range = wave_sum(in_range);
+        above_range = wave_sum(above_range);
+        if (lane == 0) {
+            atomicAdd(&in_n, in_range);
+            atomicAdd(&above_n, above_range);
+        }
+        __syncthreads();
+        k_rem = k - above_n;
+        left = in_n;
+        if (above_n < k && k_rem <= left) break;
+        sampled = false;                               // the sample misled
+        __syncthreads();                               // everybody has read the counts
+    }
+
+    // the digits of the k_rem-th largest key of the range, ten bits at a time
+    auto for_range = [&](auto f) {
+        for_candidates([&](uint32_t key) { if (key - lo < width) f(key - lo); });
+    };
+    int rem = 32 - __builtin_clz(width - 1u);          // bits of a key's distance from lo that are not known yet (width is 8 at least)
+    uint32_t prefix = 0;
+    for (bool again = false; rem > 0; again = true) {
+        const int take = min(rem, SMALL_DIGIT), shift = rem - take;
+        if (again) {
+            digit_bins[tid] = 0u;
+            __syncthreads();
+        }
+        for_range([&](uint32_t rel) {
+            const uint32_t digit = (rel >> shift) & ((1u << take) - 1u);
+            // (0 is what the others leave of `left`: zeros, and values that fill the upper bits only, would crowd it)
+            if ((!again || rel >> rem == prefix) && digit != 0) atomicAdd(&digit_bins[digit], 1u);
+        });
+        __syncthreads();
+        const uint32_t cnt = digit_bins[SEL_THREADS - 1 - tid];
+        uint32_t total;
+        const uint32_t above = above_mine(cnt, 1, total);
+        if (tid == 0 && k_rem > total) {
+            bcast[0] = 0u;
+            bcast[1] = k_rem - total;
+            bcast[2] = left - total;
+        }
+        if (above < k_rem && k_rem <= above + cnt) {
+            bcast[0] = uint32_t(SEL_THREADS - 1 - tid);
+            bcast[1] = k_rem - above;
+            bcast[2] = cnt;
+        }
+        __syncthreads();
+        prefix = prefix << take | bcast[0];
+        k_rem = bcast[1];
+        rem = shift;
+        left = bcast[2];
+        if (rem > 0 && left <= uint32_t(WAVE)) {       // uniform: every wavefront ranks what is left
+            for_range([&](uint32_t rel) {
+                if (rel >> rem == prefix) few[atomicAdd(&few_n, 1u) & (WAVE - 1)] = rel;
+            });
+            __syncthreads();
+            const uint32_t own = few[lane];
+            uint32_t gt = 0, eq = 0;
+            for (uint32_t j = 0; j < left; ++j) {
+                const uint32_t other = uint32_t(__builtin_amdgcn_readlane(int(own), int(j)));
+                gt += other > own ? 1u : 0u;
+                eq += other == own ? 1u : 0u;
+            }
+            const lane_mask hit = __ballot(uint32_t(lane) < left && gt < k_rem && k_rem <= gt + eq);
+            const int at = hit ? __builtin_ctzll(hit) : 0;                 // (always found)
+            prefix = uint32_t(__builtin_amdgcn_readlane(int(own), at));
+            k_rem -= uint32_t(__builtin_amdgcn_readlane(int(gt), at));
+            rem = 0;
+        }
+        if (rem > 0) __syncthreads();                  // bins and broadcast words are read
+    }
+    const uint32_t t = lo + prefix, m = k_rem;         // the threshold key and its tie budget
+
+    // ordered output: slot = #gt-before + min(#eq-before, m)
+    uint32_t g = 0, e = 0;
+    for_candidates([&](uint32_t key) {
+        g += key > t ? 1u : 0u;
+        e += key == t ? 1u : 0u;
+    });
+    g = wave_sum(g);
+    e = wave_sum(e);
+    if (lane == 0) {
+        wave_gt[wave] = g;
+        wave_eq[wave] = e;
+    }
+    __syncthreads();
+    const uint32_t og = lane < wave ? wave_gt[lane] : 0u, oe = lane < wave ? wave_eq[lane] : 0u;      // (wave < NW)
+    uint32_t my_gt = wave_sum(og), my_eq = wave_sum(oe);
+    auto keep = [&](uint32_t pos, word w) {
+        if (pos < k) {                                 // always true for consistent counts
+            vals[pos] = static_cast<RAW>(Staged<RAW>::raw(w));
+            idx[pos] = static_cast<int32_t>(uint32_t(wv0 * VEC) + Staged<RAW>::pos(w));
+        }
+    };
+    for (;;) {
+        for (uint32_t q0 = 0; q0 < n; q0 += WAVE) {    // 64 words in lane order: neighbouring lanes write neighbouring slots
+            const bool there = q0 + lane < n;
+            const word w = there ? seg[q0 + lane] : word(0);
+            const uint32_t key = Staged<RAW>::raw(w) & MASK;
+            const bool gt = there && key > t, eq = there && key == t;
+            const lane_mask bg = __ballot(gt), be = __ballot(eq);
+            const uint32_t eb = bits_before(be, my_eq), gb = bits_before(bg, my_gt);
+            if (gt || (eq && eb < m)) keep(gb + min(eb, m), w);
+            my_gt += uint32_t(__builtin_popcountll(bg));
+            my_eq += uint32_t(__builtin_popcountll(be));
+        }
+        if (staged_rows > nrows) break;
+        const uint32_t t_s = __builtin_amdgcn_readfirstlane(t);
+        n = 0;                                         // what did not fit: only what can be kept now
+        while (staged_rows < nrows && stage_row(load_row(staged_rows), staged_rows, t_s)) ++staged_rows;
+        if (staged_rows == nrows && stage_tail(t_s)) staged_rows = nrows + 1;
+    }
+}
+
+// 16-bit tensors of one vector per thread: digit histograms over all elements (11 + 4 bits) are the shorter program, and at
+// this size fetching it and the barriers are all there is: 1 K elements 5.1 us against 6.9 in the form above, 8 K 6.3 against
+// 7.2; 16 K 8.9 against 8.6.
+__global__ void __launch_bounds__(SEL_THREADS)
+select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k, uint16_t *__restrict__ vals,
+                  int32_t *__restrict__ idx)
+{
+    constexpr int VEC = 8, NB = 1 << 11;
+    constexpr uint32_t MASK = KeyTraits<uint16_t>::MASK;
+    __shared__ uint32_t lh[NB + 2 * WAVE];
     __shared__ uint32_t wave_tot[SEL_THREADS / WAVE];
     __shared__ uint32_t bcast[2];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-    const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
-    const int rows = (nvf + SEL_THREADS - 1) / SEL_THREADS;          // <= SMALL_VECTORS (checked by the host)
-    u32x4 q[SMALL_VECTORS];
-#pragma unroll
-    for (int i = 0; i < SMALL_VECTORS; ++i) {
-        const int v = tid + i * SEL_THREADS;
-        q[i] = v < nvf ? xv[v] : u32x4{0u, 0u, 0u, 0u};
-    }
+    const int ntail = numel - nvf * VEC;                             // the ragged end, in thread 0
+    const u32x4 q = tid < nvf ? reinterpret_cast<const u32x4 *>(x)[tid] : u32x4{0u, 0u, 0u, 0u};
     auto for_all = [&](auto f) {
-#pragma unroll
-        for (int i = 0; i < SMALL_VECTORS; ++i)
-            if (tid + i * SEL_THREADS < nvf) for_each_raw(RAW(0), q[i], [&](uint32_t raw, int) { f(raw); });
+        if (tid < nvf) for_each_raw(uint16_t(0), q, [&](uint32_t raw, int) { f(raw); });
         if (tid == 0)
-            for (int64_t i = int64_t(nvf) * VEC; i < numel; ++i) f(x[i]);
+            for (int e = 0; e < ntail; ++e) f(x[nvf * VEC + e]);
     };
     uint32_t prefix = 0, k_rem = k;
-    auto pass = [&](auto shift_c, auto bits_c, auto first_c) {
+    auto pass = [&](auto shift_c, auto bits_c) {
         constexpr int SHIFT = decltype(shift_c)::value, BITS = decltype(bits_c)::value;
-        constexpr bool FIRST = decltype(first_c)::value;
-        constexpr int NB = 1 << BITS;
+        constexpr bool FIRST = SHIFT + BITS == 15;
         __syncthreads();
-        for (int i = tid; i < NB + 2 * WAVE; i += SEL_THREADS) lh[i] = 0;
+        for (int i = tid; i < (1 << BITS) + 2 * WAVE; i += SEL_THREADS) lh[i] = 0;
         __syncthreads();
-        const uint32_t zslot = NB + lane, dslot = NB + WAVE + lane;
         for_all([&](uint32_t raw) {
             const uint32_t key = raw & MASK;
-            const uint32_t d = (key >> SHIFT) & (NB - 1);
-            uint32_t a = d ? d : zslot;
-            if (!FIRST) a = ((key >> (SHIFT + BITS)) == prefix) ? a : dslot;
+            const uint32_t d = (key >> SHIFT) & ((1u << BITS) - 1u);
+            uint32_t a = d ? d : (1u << BITS) + lane;                // zeros, and keys of another prefix, to a slot per lane
+            if (!FIRST) a = key >> (SHIFT + BITS) == prefix ? a : (1u << BITS) + WAVE + lane;
             atomicAdd(&lh[a], 1u);
         });
         __syncthreads();
         if (tid < WAVE) {
-            const uint32_t z = wave_sum(lh[NB + tid]);
+            const uint32_t z = wave_sum(lh[(1 << BITS) + tid]);
             if (tid == 0) lh[0] += z;
         }
         __syncthreads();
-        resolve_digit_local<NB, BITS>(lh, prefix, k_rem, wave_tot, bcast);
+        resolve_digit_local<(1 << BITS), BITS>(lh, prefix, k_rem, wave_tot, bcast);
     };
-    if constexpr (F32) {
-        pass(std::integral_constant<int, 18>{}, std::integral_constant<int, 13>{}, std::true_type{});
-        pass(std::integral_constant<int, 5>{}, std::integral_constant<int, 13>{}, std::false_type{});
-    } else {
-        pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 11>{}, std::true_type{});
-    }
-    pass(std::integral_constant<int, 0>{}, std::integral_constant<int, LAST_BITS>{}, std::false_type{});
-    const uint32_t t = prefix, m = k_rem;   // all digits resolved: the threshold key and its tie budget
-
-    uint32_t run_gt = 0, run_eq = 0;
-    auto keep = [&](uint32_t pos, uint32_t raw, int64_t i) {
-        if (pos < k) {
-            vals[pos] = static_cast<RAW>(raw);
-            idx[pos] = static_cast<int32_t>(i);
-        }
-    };
-#pragma unroll
-    for (int i = 0; i < SMALL_VECTORS; ++i) {
-        if (i < rows) {                        // uniform over the workgroup
-            const int v = tid + i * SEL_THREADS;
-            uint32_t cnt = 0;                  // low 16 bits: #gt, high 16 bits: #eq (a row is <= 8192 elements)
-            if (v < nvf)
-                for_each_raw(RAW(0), q[i], [&](uint32_t raw, int) {
-                    const uint32_t key = raw & MASK;
-                    cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
-                });
-            uint32_t total;
-            const uint32_t excl = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
-            uint32_t my_gt = run_gt + (excl & 0xFFFFu);
-            uint32_t my_eq = run_eq + (excl >> 16);
-            if (cnt) {
-                for_each_raw(RAW(0), q[i], [&](uint32_t raw, int e) {
-                    const uint32_t key = raw & MASK;
-                    const bool gt = key > t, eq = key == t;
-                    if (gt || (eq && my_eq < m)) keep(my_gt + min(my_eq, m), raw, int64_t(v) * VEC + e);
-                    my_gt += gt ? 1u : 0u;
-                    my_eq += eq ? 1u : 0u;
-                });
-            }
-            run_gt += total & 0xFFFFu;
-            run_eq += total >> 16;
-        }
-    }
-    if (tid == 0) {
-        for (int64_t i = int64_t(nvf) * VEC; i < numel; ++i) {
-            const RAW raw = x[i];
+    pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 11>{});
+    pass(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
+    const uint32_t t = prefix, m = k_rem;                            // the threshold key and its tie budget
+    uint32_t cnt = 0;                                                // low 16 bits: #gt, high 16 bits: #eq (8192 elements at most)
+    if (tid < nvf)
+        for_each_raw(uint16_t(0), q, [&](uint32_t raw, int) {
             const uint32_t key = raw & MASK;
-            const bool gt = key > t, eq = key == t;
-            if (gt || (eq && run_eq < m)) keep(run_gt + min(run_eq, m), raw, i);
-            run_gt += gt ? 1u : 0u;
-            run_eq += eq ? 1u : 0u;
+            cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
+        });
+    uint32_t total;
+    const uint32_t before = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
+    uint32_t my_gt = before & 0xFFFFu, my_eq = before >> 16;
+    auto emit = [&](uint32_t raw, int i) {
+        const uint32_t key = raw & MASK;
+        const bool gt = key > t, eq = key == t;
+        if (gt || (eq && my_eq < m)) {
+            const uint32_t pos = my_gt + min(my_eq, m);
+            if (pos < k) {                                           // always true for consistent counts
+                vals[pos] = static_cast<uint16_t>(raw);
+                idx[pos] = i;
+            }
         }
+        my_gt += gt ? 1u : 0u;
+        my_eq += eq ? 1u : 0u;
+    };
+    if (cnt) for_each_raw(uint16_t(0), q, [&](uint32_t raw, int e) { emit(raw, tid * VEC + e); });
+    if (tid == 0) {
+        my_gt = total & 0xFFFFu;
+        my_eq = total >> 16;
+        for (int e = 0; e < ntail; ++e) emit(x[nvf * VEC + e], nvf * VEC + e);
     }
 }
 
@@ -1916,11 +2240,35 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
                                             static_cast<uint32_t>(k));
     };
     const int mode = select_mode();
-    // Small tensors (default mode only: the other modes are there to exercise the other forms): one workgroup.
-    if (mode == 0 && numel / KeyTraits<RAW>::VEC <= int64_t(SMALL_VECTORS) * SEL_THREADS) {
+    const SampleRanks spread = numel >= SAMPLE_MIN_NUMEL ? sample_ranks(static_cast<uint32_t>(k), numel, SAMPLE_ELEMS) : SampleRanks{0.0f, 0.0f};
+    // Small tensors (default mode only: the other modes are there to exercise the other forms): one workgroup.  16-bit ones
+    // only up to 32 K elements where the persistent kernel can predict the threshold: it takes 11.1 to 11.5 us from there to
+    // 128 K, this form 10.5 (gamma 0.9) or 15.6 (0.6) at 32 K and 15 or 25 at 64 K.
+    const int64_t nvec = numel / KeyTraits<RAW>::VEC;
+    if (mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS &&
+        (sizeof(RAW) == 4 || nvec <= SMALL_VECTORS / 2 * SEL_THREADS || spread.lo == 0.0f)) {
         trace_mark(stream);
-        select_small_kernel<RAW><<<1, SEL_THREADS, 0, stream>>>(xr, numel, int(numel / KeyTraits<RAW>::VEC),
-                                                                static_cast<uint32_t>(k), static_cast<RAW *>(vals), idx);
+        const int vectors = int(nvec);
+        if constexpr (sizeof(RAW) == 2) {
+            if (vectors <= SEL_THREADS) {
+                select_row_kernel<<<1, SEL_THREADS, 0, stream>>>(xr, int(numel), vectors, static_cast<uint32_t>(k),
+                                                                 static_cast<RAW *>(vals), idx);
+                trace_mark(stream);
+                return launch_status();
+            }
+        }
+        const SampleRanks ranks = vectors >= SMALL_SAMPLE_MIN ? sample_ranks(static_cast<uint32_t>(k), numel, vectors)
+                                                              : SampleRanks{0.0f, 0.0f};
+        static std::atomic<uint64_t> set_up{0};
+        if (!once_per_device(set_up, [] {
+                return hipFuncSetAttribute(reinterpret_cast<const void *>(select_small_kernel<RAW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, SEL_THREADS / WAVE * SMALL_SEG_BYTES) == hipSuccess;
+            }))
+            return DROPIT_EHIP;
+        const uint32_t cap = small_cap<RAW>(vectors);
+        const size_t smem = std::max(size_t(SEL_THREADS / WAVE) * cap * sizeof(typename Staged<RAW>::word), 4 * size_t(SMALL_BINS));
+        select_small_kernel<RAW><<<1, SEL_THREADS, smem, stream>>>(xr, int(numel), vectors, static_cast<uint32_t>(k), ranks, cap,
+                                                                   static_cast<RAW *>(vals), idx);
         trace_mark(stream);
         return launch_status();
     }
@@ -1965,7 +2313,7 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
             uint32_t spin_limit = mode == 3 ? 0u : SPIN_LIMIT;
             RAW *vals_t = static_cast<RAW *>(vals);
             unsigned long long gen = next_generation();
-            SampleRanks ranks = sample_ranks(k32, numel);
+            SampleRanks ranks = spread;
             trace_mark(stream);
             if (mode == 2) {               // the runtime guarantees co-residency, at the price of slow queue switches
                 void *args[] = {(void *)&xr, (void *)&numel, (void *)&nvf, (void *)&vpc, (void *)&k32, (void *)&st,
