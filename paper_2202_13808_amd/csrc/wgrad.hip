@@ -27,50 +27,121 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(float *p, int64_t n)
 // A layer whose whole input fits the LDS of a compute unit (numel <= SMALL_NUMEL fp32 values) is bound by
 // launches, not by work: the zero fill, the scatter and the product as three kernels cost three dispatch
 // slots for a few microseconds of arithmetic.  Here every workgroup rebuilds the whole R(a^) in its own LDS
-// (zero fill, then one store per pair: the k pairs are a few thousand), fetches its SMALL_JB columns of dY,
-// and multiplies: thread (j, c-group) adds its terms in ascending token order with true fp32 multiply-adds
-// (bf16 inputs are widened exactly).
+// (zero fill, then one store per pair: the k pairs are a few thousand), fetches its JB columns of dY,
+// and multiplies with true fp32 multiply-adds (bf16 inputs are widened exactly): a thread sums four neighbouring columns
+// of a row of dW over its share of the tokens, a contiguous one, in ascending order, and the shares are added in ascending
+// order through LDS.  Four rows of dW to a workgroup and up to sixteen shares: the chain of dependent LDS reads, one per
+// token, is what a few workgroups of 256 threads with all tokens each spent their time on (calls in a queue
+// of calls: 256 tokens of 64 -> 128 10.9 us, 4.8 now; 1024 of 16 -> 64 29.7 and 5.5; 128 of 128 -> 4096 10.2 and 7.1).
+// Sixteen rows where four would make more workgroups than the chip holds.
 constexpr int SMALL_NUMEL = 16384;         // elements of x: 64 KB of fp32 in LDS
-constexpr int SMALL_TOKENS = 1024;         // tokens: the dY slice is SMALL_TOKENS x SMALL_JB fp32 = 64 KB
-constexpr int SMALL_JB = 16;               // rows of dW per workgroup
+constexpr int SMALL_TOKENS = 1024;         // tokens: the dY slice is SMALL_TOKENS x JB fp32, 64 KB at most
+constexpr int SMALL_THREADS = 1024, SMALL_SHARES = 16, SMALL_MAX_JB = 16;
 
-template <typename RAW>
-__global__ void __launch_bounds__(256)
+inline int small_rows(int64_t cout) { return cout <= 2048 ? 4 : SMALL_MAX_JB; }
+
+template <typename RAW, int JB>
+__global__ void __launch_bounds__(SMALL_THREADS)
 fc_small_kernel(const RAW *__restrict__ vals, const int32_t *__restrict__ idx, int k, const RAW *__restrict__ dY,
-                int ntok, int cin, int cout, float *__restrict__ dW)
+                int ntok, int cin, int cout, int shares, float *__restrict__ dW)
 {
     extern __shared__ __attribute__((aligned(16))) float small_lds[];
-    float *xs = small_lds;                                 // R(a^)  [ntok][cin]
-    float *gs = small_lds + ntok * cin;                    // dY     [ntok][SMALL_JB], columns j0 ..
+    float *xs = small_lds;                                 // R(a^)  [ntok][cin]; afterwards the shares' sums
+    float *gs = small_lds + ntok * cin;                    // dY     [ntok][JB], columns j0 ..
     const int tid = threadIdx.x;
-    const int j0 = blockIdx.x * SMALL_JB;
+    const int j0 = blockIdx.x * JB;
     const int numel = ntok * cin;                          // a multiple of 4 (cin is)
-    float4 *xs4 = reinterpret_cast<float4 *>(xs);
-    for (int i = tid; i < numel / 4; i += 256) xs4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int e = tid; e < ntok * SMALL_JB; e += 256) {
-        const int n = e / SMALL_JB, j = j0 + e % SMALL_JB;
+    // the first pairs and dY are on their way while the zeros are written
+    constexpr int PRE = 2;
+    int pi[PRE];
+    RAW pv[PRE];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) {
+        const int q = tid + u * SMALL_THREADS;
+        pi[u] = q < k ? idx[q] : -1;
+        pv[u] = q < k ? vals[q] : RAW(0);
+    }
+    for (int e = tid; e < ntok * JB; e += SMALL_THREADS) {
+        const int n = e / JB, j = j0 + e % JB;
         gs[e] = j < cout ? to_f32(dY[int64_t(n) * cout + j]) : 0.f;
     }
+    float4 *xs4 = reinterpret_cast<float4 *>(xs);
+    for (int i = tid; i < numel / 4; i += SMALL_THREADS) xs4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    for (int q = tid; q < k; q += 256) {
-        const int i = idx[q];
-        if (i >= 0 && i < numel) xs[i] = to_f32(vals[q]);  // an out-of-range index is ignored, never written
-    }
+    auto place = [&](int i, RAW v) {
+        if (i >= 0 && i < numel) xs[i] = to_f32(v);        // an out-of-range index is ignored, never written
+    };
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) place(pi[u], pv[u]);
+    for (int q = tid + PRE * SMALL_THREADS; q < k; q += SMALL_THREADS) place(idx[q], vals[q]);
     __syncthreads();
-    const int j = tid / 16;                                // 16 rows of dW x 16 groups of 4 columns per pass
-    for (int c0 = (tid % 16) * 4; c0 < cin; c0 += 64) {
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int n = 0; n < ntok; ++n) {
-            const float g = gs[n * SMALL_JB + j];
-            const float4 b = *reinterpret_cast<const float4 *>(xs + n * cin + c0);
-            acc[0] = __builtin_fmaf(g, b.x, acc[0]);
-            acc[1] = __builtin_fmaf(g, b.y, acc[1]);
-            acc[2] = __builtin_fmaf(g, b.z, acc[2]);
-            acc[3] = __builtin_fmaf(g, b.w, acc[3]);
+    const int cq = cin / 4, items = JB * cq;               // (row, four columns): the columns run fastest over the lanes
+    if (shares > 1) {                                      // items * shares <= SMALL_THREADS
+        const int share = tid / items, item = tid % items, j = item / cq, c0 = item % cq * 4;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (share < shares) {
+            const int n1 = ntok * (share + 1) / shares;
+#pragma unroll 4
+            for (int n = ntok * share / shares; n < n1; ++n) {
+                const float g = gs[n * JB + j];
+                const float4 b = *reinterpret_cast<const float4 *>(xs + n * cin + c0);
+                s.x = __builtin_fmaf(g, b.x, s.x);
+                s.y = __builtin_fmaf(g, b.y, s.y);
+                s.z = __builtin_fmaf(g, b.z, s.z);
+                s.w = __builtin_fmaf(g, b.w, s.w);
+            }
         }
-        if (j0 + j < cout)
-            *reinterpret_cast<float4 *>(dW + int64_t(j0 + j) * cin + c0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        __syncthreads();                                   // R(a^) has been read
+        if (share < shares) xs4[tid] = s;
+        __syncthreads();
+        if (tid < items && j0 + j < cout) {
+            for (int h = 1; h < shares; ++h) {
+                const float4 o = xs4[h * items + tid];
+                s.x += o.x;
+                s.y += o.y;
+                s.z += o.z;
+                s.w += o.w;
+            }
+            *reinterpret_cast<float4 *>(dW + int64_t(j0 + j) * cin + c0) = s;
+        }
+    } else {
+        for (int item = tid; item < items; item += SMALL_THREADS) {
+            const int j = item / cq, c0 = item % cq * 4;
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+            for (int n = 0; n < ntok; ++n) {
+                const float g = gs[n * JB + j];
+                const float4 b = *reinterpret_cast<const float4 *>(xs + n * cin + c0);
+                s.x = __builtin_fmaf(g, b.x, s.x);
+                s.y = __builtin_fmaf(g, b.y, s.y);
+                s.z = __builtin_fmaf(g, b.z, s.z);
+                s.w = __builtin_fmaf(g, b.w, s.w);
+            }
+            if (j0 + j < cout) *reinterpret_cast<float4 *>(dW + int64_t(j0 + j) * cin + c0) = s;
+        }
     }
+}
+
+template <typename RAW, int JB>
+dropit_status launch_fc_small(const void *vals, const int32_t *idx, int64_t k, const void *dY, int64_t ntok, int64_t cin,
+                              int64_t cout, float *dW, hipStream_t stream)
+{
+    static std::atomic<uint64_t> set_up{0};
+    if (!once_per_device(set_up, [] {
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_small_kernel<RAW, JB>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       int((SMALL_NUMEL + SMALL_TOKENS * JB) * sizeof(float))) == hipSuccess;
+        }))
+        return DROPIT_EHIP;
+    // as many shares of the tokens as threads are left for, four tokens each at least
+    const int64_t items = JB * (cin / 4);
+    int shares = 1;
+    while (shares < SMALL_SHARES && 2 * shares * items <= SMALL_THREADS && 8 * shares <= ntok) shares *= 2;
+    const size_t sums = shares > 1 ? size_t(shares) * items * 16 : 0;
+    const size_t lds = std::max(size_t(ntok * cin + ntok * JB) * sizeof(float), sums);
+    fc_small_kernel<RAW, JB><<<unsigned((cout + JB - 1) / JB), SMALL_THREADS, lds, stream>>>(
+        static_cast<const RAW *>(vals), idx, int(k), static_cast<const RAW *>(dY), int(ntok), int(cin), int(cout), shares, dW);
+    return launch_status();
 }
 
 struct Problem {
@@ -236,32 +307,13 @@ static dropit_status run(const Problem &p, const void *vals, const int32_t *idx,
         return conv_im2col_run(cg, conv_im2col_plan(cg), vals, idx, dY, dW, ws, stream);
     }
     case DROPIT_PATH_FC_SMALL: {
-        const size_t lds = size_t(p.numel + p.ntok * SMALL_JB) * sizeof(float);
-        const unsigned grid = unsigned((p.cout + SMALL_JB - 1) / SMALL_JB);
         trace_mark(stream);
-        if (dt == DROPIT_BF16) {
-            static std::atomic<uint64_t> set_up{0};
-            if (!once_per_device(set_up, [] {
-                    return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_small_kernel<uint16_t>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               int((SMALL_NUMEL + SMALL_TOKENS * SMALL_JB) * sizeof(float))) == hipSuccess;
-                }))
-                return DROPIT_EHIP;
-            fc_small_kernel<uint16_t><<<grid, 256, lds, stream>>>(static_cast<const uint16_t *>(vals), idx, int(k),
-                                                                  static_cast<const uint16_t *>(dY), int(p.ntok),
-                                                                  int(p.cin), int(p.cout), dW);
-        } else {
-            static std::atomic<uint64_t> set_up{0};
-            if (!once_per_device(set_up, [] {
-                    return hipFuncSetAttribute(reinterpret_cast<const void *>(fc_small_kernel<uint32_t>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               int((SMALL_NUMEL + SMALL_TOKENS * SMALL_JB) * sizeof(float))) == hipSuccess;
-                }))
-                return DROPIT_EHIP;
-            fc_small_kernel<uint32_t><<<grid, 256, lds, stream>>>(static_cast<const uint32_t *>(vals), idx, int(k),
-                                                                  static_cast<const uint32_t *>(dY), int(p.ntok),
-                                                                  int(p.cin), int(p.cout), dW);
-        }
+        auto go = [&](auto raw_) {
+            using RAW = decltype(raw_);
+            return small_rows(p.cout) == 4 ? launch_fc_small<RAW, 4>(vals, idx, k, dY, p.ntok, p.cin, p.cout, dW, stream)
+                                           : launch_fc_small<RAW, SMALL_MAX_JB>(vals, idx, k, dY, p.ntok, p.cin, p.cout, dW, stream);
+        };
+        if (const dropit_status st = dt == DROPIT_BF16 ? go(uint16_t(0)) : go(uint32_t(0)); st != DROPIT_OK) return st;
         trace_mark(stream);
         return launch_status();
     }
