@@ -21,11 +21,11 @@
 //
 // Default: ONE persistent kernel (select_fused_kernel) does all of it with grid
 // barriers between the steps, and a serial redo path should the barriers ever give
-// up.  For 16-bit tensors it predicts the range of the threshold from a sample and
+// up.  It predicts the range of the threshold from a sample and
 // stages every element that can still be kept in LDS during its one pass over the
 // tensor (see "sampled first digit" and "one read of x" below); the counts are exact,
 // so a wrong prediction is noticed and repaired, and the bytes it writes are the same
-// either way.  fp32 builds the digit histograms.  Alternative: the steps as separate kernels
+// either way.  Small tensors take one workgroup.  Alternative: the steps as separate kernels
 // (init, hist, count, compact) with a last-workgroup-to-arrive ticket instead of
 // barriers.  Nothing here synchronises with the host; counts are integer, so the
 // result does not depend on the order in which workgroups run.
@@ -35,6 +35,8 @@
 // chunk read again where a segment overflowed) -> now:
 //   bf16 0.6 M elements 17.7 -> 12.7 us, 3.2 M 22 -> 16.0, 9.7 M 26.3 -> 20.3, 50 M (gamma 0.9) 53.8 -> 44.4,
 //   39 M (gamma 0.8) 78.7 -> 48, 51 M (gamma 0.8) 93.6 -> 65.
+// fp32, digit histograms of the whole tensor -> sample, staged candidates and the threshold's bin as a list (gamma 0.9):
+//   0.07 M elements 24.1 -> 17.1 us, 0.6 M 26.9 -> 18.9, 2.4 M 33.9 -> 21.3, 8.4 M 47.4 -> 25.2, 50 M 152.6 -> 88.8.
 #include "common.hpp"
 #include "dev_hooks.hpp"
 #include <atomic>
@@ -58,7 +60,7 @@ struct SelState {
     uint32_t t;          // threshold key (valid after the count pass)
     uint32_t m;          // how many keys equal to t are kept (lowest flat index first)
     uint32_t ticket[4];  // arrival counters, one per pass
-    uint32_t form;       // fused kernel, for the tests, at every size: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry)
+    uint32_t form;       // fused kernel, for the tests, 16-bit types at every size: 0 exact digit histograms, 1 sampled bracket confirmed, 2 sampled bracket missed (exact retry)
     uint32_t error;      // hint: some workgroup ran out of patience at a grid barrier (the others stop waiting)
     uint32_t exited;     // fused kernel: low 16 bits = workgroups past their last grid barrier or gone, high 16 bits = how many gave up
     uint32_t path;       // `form` for 16-bit tensors of SAMPLE_LARGE elements or more, 0 below: what readers of this word were told when smaller ones had no sampled form
@@ -68,7 +70,8 @@ struct SelState {
     uint32_t redo;       // fused kernel, for callers and tests: 1 if the grid barriers gave up and the last workgroup redid the selection alone
     uint32_t staged;     // fused kernel, for the tests: how many workgroups compacted from candidates staged in LDS (one read of x)
     unsigned long long ready_hist;   // 16-bit types: the same for the digit histogram, which only the exact form needs
-    uint32_t pad[46];
+    uint32_t pad[45];
+    uint32_t form32;     // fp32, for the tests: as `form`, + 4 where the threshold's bin went through a histogram and a second table
 };
 static_assert(sizeof(SelState) == 256, "state block is 256 bytes");
 static_assert(MAX_LAST_BINS + 1 <= TABLE_PITCH && TABLE_PITCH == WAVE, "a lane per word of a chunk's line");
@@ -415,11 +418,8 @@ compact_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vp
 
 // ---------------------------------------------------------------------------
 // Fused path: the whole select + compaction as ONE persistent kernel with one
-// workgroup per compute unit.  Each workgroup parks the first FUSED_RES x 16 KB of its
-// chunk in LDS across all phases (the whole chunk for tensors up to ~25 MB; anything
-// beyond is re-read, mostly from the Infinity Cache), and the phases are separated by
-// grid barriers instead of kernel boundaries.  Loops over the parked vectors are rolled
-// on purpose: unrolling them 8x made the kernel 48 KB of code and instruction-fetch bound.  Every workgroup resolves the digits itself
+// workgroup per compute unit; the phases are separated by
+// grid barriers instead of kernel boundaries.  Every workgroup resolves the digits itself
 // from the merged histogram, so the select state lives in registers.
 //
 // The kernel is an ordinary launch (a cooperative launch costs ~14 us of queue switching before and
@@ -439,7 +439,6 @@ compact_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vp
 // group counter, release on the top counter, an acquire fence after the wait, all at agent
 // scope -- was measured beside it: 3.4-4.8 us more per call on every benchmark tensor (one
 // barrier per call), for the L2 write-back and invalidate it implies; the relaxed form stays.
-constexpr int FUSED_RES = 6;             // 16-byte vectors per thread parked in LDS
 // Patience in polls (~0.25 us each); every wave exits even if it runs out.  A resident grid meets at a barrier within
 // microseconds (a millisecond for the largest tensors), so the barriers give up after ~15 ms: a grid that is not
 // resident all at once then costs those milliseconds plus the serial redo, not a second.  Waiting for workgroup 0's
@@ -850,9 +849,9 @@ __device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint3
 // 2 * NW * TABLE_PITCH words).  False if the k-th key is not in the range.
 // (With a line per KEY a workgroup's 33 to 57 stores went to as many lines, each shared by 32 workgroups, and were
 // acknowledged a microsecond later; the sums over lanes cost a scan per row.)
-// The workgroup's report goes out behind the table loads.
+// The workgroup's report goes out behind the table loads, if no barrier comes after it (`last`).
 __device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_t key_lo, uint32_t k, uint32_t *part, uint32_t *bcast,
-                                     uint32_t *offs, uint32_t *verdict, uint32_t *xbar, ExitReport &rep)
+                                     uint32_t *offs, uint32_t *verdict, uint32_t *xbar, ExitReport &rep, bool last)
 {
     constexpr int NW = SEL_THREADS / WAVE, PER = 16;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -863,14 +862,14 @@ __device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_
         const uint32_t *line = table + c0 * TABLE_PITCH + lane;       // (the table has a line for every possible chunk)
 #pragma unroll
         for (int j = 0; j < PER; ++j) v[j] = dev_load(line + j * TABLE_PITCH);
-        if (rep.mine == 0) report_past_barriers(xbar, rep, false);
+        if (last && rep.mine == 0) report_past_barriers(xbar, rep, false);
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             s += c0 + j < G ? v[j] : 0u;
             sp += c0 + j < me ? v[j] : 0u;
         }
     }
-    if (rep.mine == 0) report_past_barriers(xbar, rep, false);         // (a wavefront without chunks)
+    if (last && rep.mine == 0) report_past_barriers(xbar, rep, false); // (a wavefront without chunks)
     part[wave * TABLE_PITCH + lane] = s;
     part[(NW + wave) * TABLE_PITCH + lane] = sp;
     __syncthreads();
@@ -894,6 +893,7 @@ __device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_
         if (here) {
             bcast[0] = key_lo + static_cast<uint32_t>(rr);     // t
             bcast[1] = k - (incl - full);                       // m: how many keys equal to t are kept
+            bcast[2] = full;                                    // ... of how many
             offs[0] = incl_p - before;                          // #{key > t} in the chunks before this one
             offs[1] = before;                                   // #{key == t} there
         }
@@ -1148,7 +1148,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
         STAMP(4);
         if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
         STAMP(5);
-        if (resolve_table(table, nf, key_lo, k, lh, bcast, offs, &verdict, xbar, rep)) break;
+        if (resolve_table(table, nf, key_lo, k, lh, bcast, offs, &verdict, xbar, rep, true)) break;
         if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
         predicted = false;                       // the sample misled: once more with the exact histogram
         missed = true;
@@ -1239,300 +1239,554 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
     return SEL_DONE;
 }
 
-// fp32: two digit histograms of 13 bits, then exact counts over the last 5.
+// ---- candidates of 32-bit elements ------------------------------------------------------------------
+// As count_candidates / stage_candidates above: the four consecutive elements of q against a lowest key; a staged candidate
+// is two words, the element and its position.
+__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint32_t)
+{
+    uint32_t n = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        keys[e] = q[e] & KeyTraits<uint32_t>::MASK;
+        n += keys[e] >= lowest ? 1u : 0u;
+    }
+    return n;
+}
+__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
+                                        uint32_t addr, uint32_t pos, uint32_t)
+{
+    unsigned long long saved;
+    const uint32_t lo = lowest;
+#define STAGE_ELEMENT(W, K)                                      \
+    "v_cmpx_le_u32 vcc, %[lo], " K "\n\t"                        \
+    "ds_write2_b32 %[addr], " W ", %[pos] offset1:1\n\t"         \
+    "v_add_u32 %[addr], 8, %[addr]\n\t"                          \
+    "s_mov_b64 exec, %[valid]\n\t"                               \
+    "v_add_u32 %[pos], 1, %[pos]\n\t"
+    asm volatile("s_mov_b64 %[saved], exec\n\t"
+                 "s_mov_b64 exec, %[valid]\n\t"
+                 STAGE_ELEMENT("%[q0]", "%[k0]") STAGE_ELEMENT("%[q1]", "%[k1]") STAGE_ELEMENT("%[q2]", "%[k2]") STAGE_ELEMENT("%[q3]", "%[k3]")
+                 "s_mov_b64 exec, %[saved]\n\t"
+                 "s_nop 4"                      // (cross-lane operations must not follow a vector write of the mask closely)
+                 : [addr] "+&v"(addr), [pos] "+&v"(pos), [saved] "=&s"(saved)
+                 : [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [k0] "v"(keys[0]), [k1] "v"(keys[1]),
+                   [k2] "v"(keys[2]), [k3] "v"(keys[3]), [lo] "s"(lo), [valid] "s"(valid)
+                 : "vcc", "memory");
+#undef STAGE_ELEMENT
+}
+__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint16_t) { return count_candidates(q, lowest, keys); }
+__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
+                                        uint32_t addr, uint32_t pos, uint16_t)
+{
+    stage_candidates(q, keys, lowest, valid, addr, pos);
+}
+
+// A staged candidate of either type.
+template <typename RAW> struct Staged;
+template <> struct Staged<uint16_t> {
+    typedef uint32_t word;
+    __device__ static uint32_t raw(word w) { return w >> 16; }
+    __device__ static uint32_t pos(word w) { return w & 0xFFFFu; }
+    __device__ static word make(uint32_t raw, uint32_t pos) { return raw << 16 | pos; }
+};
+template <> struct Staged<uint32_t> {
+    typedef unsigned long long word;
+    __device__ static uint32_t raw(word w) { return uint32_t(w); }
+    __device__ static uint32_t pos(word w) { return uint32_t(w >> 32); }
+    __device__ static word make(uint32_t raw, uint32_t pos) { return static_cast<unsigned long long>(pos) << 32 | raw; }
+};
+
+// fp32: the sampled form as for 16-bit elements, with a key range of up to 56 bins of 2^16 keys (7 of the sample's 2^19): a
+// sample cannot narrow 31-bit keys down to single ones.  The first exchange, the table, tells which bin holds the k-th key and
+// how many elements of every chunk it has; few in all (0.2 % of a normal tensor's per bin), so they are exchanged next, as a
+// list in flat order, and every workgroup finds the threshold in the list by itself: two exchanges and one read of x, where
+// digit histograms (13 + 13 + 5 bits) take three and read the tensor, or its parked head, four times.  A bin of more elements
+// than the list holds (large tensors, ties) is histogrammed by the next 11 bits instead, and a second table settles the rest.
+// No bracket, one that fails, or a threshold among the smallest magnitudes: the exact histogram of the first 13 bits gives
+// the range, and the same steps follow.
+constexpr int SEG32_CAP = 1152;                            // staged elements (8 bytes) per wavefront: 16 segments are 144 KB
+constexpr int PART32_OFF = (SEL_THREADS / WAVE) * SEG32_CAP * 8;           // the table's partial sums, the second digit's histogram
+constexpr int PART32_WORDS = 2 * (SEL_THREADS / WAVE) * TABLE_PITCH;
+constexpr size_t SMEM32_BYTES = PART32_OFF + 4 * size_t(PART32_WORDS);
+constexpr int LIST32_PER = 16, LIST32_CAP = LIST32_PER * SEL_THREADS;      // list entries per thread; the list takes the digit histograms' place
+constexpr int BITS32_FIRST = 13, BITS32_SECOND = 11;
+static_assert(SEG32_CAP >= 2 * 4 * WAVE, "two rows of nothing but candidates fit an empty segment");
+static_assert(PART32_OFF >= 4 * ((1 << BITS32_FIRST) + WAVE) && PART32_OFF >= 4 * SAMPLE_BINS, "histograms are done with before anything is staged");
+static_assert(PART32_WORDS == 1 << BITS32_SECOND && BITS32_SECOND <= MAX_HIST_BITS, "the second digit's histogram");
+static_assert(LIST32_CAP <= 2 << MAX_HIST_BITS, "the two digit histograms hold the list");
+
 __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
                                            SelState *st, uint32_t *hist0, uint32_t *hist1, uint32_t *table,
                                            uint32_t *__restrict__ vals, int32_t *__restrict__ idx, uint32_t spin_limit,
-                                           unsigned long long gen, ExitReport &rep)
+                                           unsigned long long gen, SampleRanks ranks, ExitReport &rep)
 {
-    constexpr int VEC = 4;
+    constexpr int VEC = 4, ROW_ELEMS = WAVE * VEC;
     constexpr uint32_t MASK = KeyTraits<uint32_t>::MASK;
-    constexpr int BITS1 = 13, SHIFT1 = 18, BITS2 = 13, SHIFT2 = 5, LAST_BITS = 5;
-    constexpr uint32_t NF = 1u << LAST_BITS;
+    constexpr int SAMPLE_SHIFT32 = 31 - 12, BIN_SHIFT = SAMPLE_SHIFT32 - 3;    // a sample bin is eight bins of the table
     constexpr int NW = SEL_THREADS / WAVE;
-    constexpr int TILE = SEL_THREADS * VEC;                       // elements per compaction tile
-    // The histogram and the compaction staging buffers share storage: never live together.
+    typedef unsigned long long word;
     extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
-    u32x4 *res = dyn_smem;                                            // [FUSED_RES][SEL_THREADS]
-    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_smem + FUSED_RES * SEL_THREADS);
-    int32_t *stage_idx = reinterpret_cast<int32_t *>(lh);
-    uint32_t *stage_val = lh + TILE;
+    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_smem);                     // (before anything is staged)
+    uint32_t *part = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(dyn_smem) + PART32_OFF);
     __shared__ uint32_t bcast[4], offs[2], verdict;
     __shared__ uint32_t wave_tot[NW];
-    __shared__ uint32_t wave_tot2[2 * NW];
+    __shared__ uint32_t whist[NW][MAX_LAST_BINS + 1];           // per wavefront: its elements in each bin of the range, and above it
+    __shared__ __attribute__((aligned(16))) uint32_t digits[2][256];
+    __shared__ uint32_t wave_gt[NW], wave_eq[NW], list_gt[NW], list_eq[NW];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const bool last_chunk = blockIdx.x == gridDim.x - 1;
     const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
-    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * vpc;
-    const int64_t v1 = min(v0 + vpc, nvf);
     uint32_t *xbar = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(st) + SelWorkspace::xbar_off);
+    uint32_t *list = hist0;                                     // (hist1 follows hist0)
 
     // development builds only: phase time stamps of one workgroup into the state block's spare words
     [[maybe_unused]] unsigned long long *stamps = reinterpret_cast<unsigned long long *>(st->pad + 4);
 #define STAMP(i) DROPIT_DEV_STAMP(stamps, i, tid == 0 && blockIdx.x == gridDim.x / 2)
     STAMP(0);
 
-    // ---- park the head of the chunk in LDS (each thread only ever reads its own slots) --
-    const int nres = static_cast<int>(min<int64_t>(FUSED_RES, (max<int64_t>(v1 - v0, 0) + SEL_THREADS - 1) / SEL_THREADS));
-    {
-        u32x4 q[FUSED_RES];
-        if (nvf > 0) {
+    // wavefront `wave` owns vectors [wv0, wv1) of the chunk, in rows of 64; ranges start on 128-byte lines
+    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * vpc, v1 = min(v0 + vpc, nvf);
+    const int64_t vpw = ((vpc + NW - 1) / NW + 7) / 8 * 8;
+    const int64_t wv0 = min(v0 + int64_t(wave) * vpw, v1), wv1 = min(wv0 + vpw, v1);
+    const int wvecs = static_cast<int>(wv1 - wv0);
+    const int nrows = (wvecs + WAVE - 1) / WAVE;
+    const uint32_t flat0 = static_cast<uint32_t>(wv0 * VEC);
+    const u32x4 *wx = xv + (wv0 < nvf ? wv0 : nvf > 0 ? nvf - 1 : 0);   // (an empty range still has a valid address to load from)
+    const int last_vec = max(wvecs - 1, 0);
+    word *seg = reinterpret_cast<word *>(dyn_smem) + wave * SEG32_CAP;
+    const uint32_t seg_addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) word *)seg));
+    u32x4 q[ST_ROWS];
+    auto issue_row = [&](u32x4 &dst, int row) { dst = wx[min(row * WAVE + lane, last_vec)]; };
+    auto issue_rows = [&](int row) {
 #pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i)     // unconditional, clamped: all loads in flight at once
-                q[i] = xv[min(v0 + int64_t(i) * SEL_THREADS + tid, nvf - 1)];
-        }
-        if (blockIdx.x == 0) {                      // (while the loads are in flight; two 8192-bin passes: hist1 follows hist0)
-            uint32_t cleared = 0;
-            clear_words(st, xbar, cleared);
-            clear_hist(hist0, 2 * (1 << MAX_HIST_BITS));
-            publish_hist(&st->ready, gen);
-        }
-        if (nvf > 0) {
-#pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = q[i];
-        }
-    }
-    const int64_t v_stream = v0 + int64_t(nres) * SEL_THREADS;        // first vector that is not parked
-    // visits every element of the chunk: f(raw bits)
-    auto for_chunk = [&](auto f) {
-        auto fv = [&](const u32x4 &q) { for_each_raw(uint32_t(0), q, [&](uint32_t raw, int) { f(raw); }); };
-        for (int i = 0; i < nres; ++i) {
-            const int64_t v = v0 + int64_t(i) * SEL_THREADS + tid;
-            if (v < v1) fv(res[i * SEL_THREADS + tid]);
-        }
-        int64_t vb = v_stream;
-        for (; vb + SEL_THREADS * SEL_UNROLL <= v1; vb += SEL_THREADS * SEL_UNROLL) {
-            u32x4 q[SEL_UNROLL];
-#pragma unroll
-            for (int u = 0; u < SEL_UNROLL; ++u) q[u] = xv[vb + u * SEL_THREADS + tid];
-#pragma unroll
-            for (int u = 0; u < SEL_UNROLL; ++u) fv(q[u]);
-        }
-        for (int64_t v = vb + tid; v < v1; v += SEL_THREADS) fv(xv[v]);
-        if (last_chunk && tid == 0)
-            for (int64_t i = nvf * VEC; i < numel; ++i) f(x[i]);
+        for (int u = 0; u < ST_ROWS; ++u) issue_row(q[u], row + u);
     };
+    const int64_t tail0 = nvf * VEC;                            // the tensor's ragged end belongs to the last chunk, but to no wavefront's range
 
-    // ---- digit histograms ---------------------------------------------------------
-    uint32_t prefix = 0, k_rem = k;
+    const bool sampling = ranks.lo > 0.0f;                      // uniform over the grid
+    uint32_t key_lo = 0, nf = 0;                                // the range: nf bins of 2^shift keys from key_lo on
+    int shift = BIN_SHIFT;
+    bool predicted = false, preloaded = false;
+    uint32_t cleared = 0;
+    if (blockIdx.x == 0) {
+        clear_words(st, xbar, cleared);
+        clear_hist(hist0, 2 << MAX_HIST_BITS);                  // (done when this workgroup arrives at its first barrier)
+    }
+    if (sampling) {
+        u32x4 sq[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int s = tid + u * SEL_THREADS;
+            sq[u] = xv[sample_piece(s / SAMPLE_STRETCH, nvf) + s % SAMPLE_STRETCH];
+        }
+        for (int i = tid; i < SAMPLE_BINS; i += SEL_THREADS) lh[i] = 0;
+        asm volatile("" : "+v"(sq[0]), "+v"(sq[1]));            // (the rows are asked for once the sample is here)
+        issue_rows(0);
+        preloaded = true;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            for_each_raw(uint32_t(0), sq[u], [&](uint32_t raw, int) {
+                const uint32_t dgt = (raw & MASK) >> SAMPLE_SHIFT32;
+                if (dgt) atomicAdd(&lh[dgt], 1u);
+            });
+        if (blockIdx.x == 0) publish_words(st, cleared, gen);
+        __syncthreads();
+        uint32_t b_lo, b_hi;
+        // (a range that reaches down to the smallest keys would make every element a candidate)
+        predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, wave_tot, bcast, b_lo, b_hi) && b_lo > 0;
+        if (predicted) {
+            key_lo = b_lo << SAMPLE_SHIFT32;
+            nf = (b_hi - b_lo + 1) << (SAMPLE_SHIFT32 - BIN_SHIFT);
+        }
+    } else if (blockIdx.x == 0) {
+        publish_words(st, cleared, gen);
+    }
+    unsigned long long early = 0;                               // usually the generation number: asked for long before it is needed
+    if (tid == 0) early = dev_load64(&st->ready);
+    STAMP(1);
+
+    // The rows' candidates (key >= lowest) from row `first` on into the segment, in flat order, with their flat indices;
+    // returns the first row that was not staged (nrows, or fewer when the segment is full), n = elements staged.  Rows are
+    // staged in pairs.
+    auto stage_rows = [&](uint32_t lowest, int first, uint32_t &n) -> int {
+        const uint32_t low_s = __builtin_amdgcn_readfirstlane(lowest);
+        n = 0;
+        if (nrows == 0) return 0;
+        if (!preloaded) issue_rows(first);
+        preloaded = false;
+        int end = nrows;
+        for (int row = first; row < end; row += ST_ROWS) {
+#pragma unroll
+            for (int u = 0; u < ST_ROWS; u += 2) {
+                if (row + u < end) {
+                    const int left = wvecs - (row + u) * WAVE - lane;              // > 0: the lane's vector of the first row exists
+                    const bool in0 = left > 0, in1 = left > WAVE;
+                    u32x4 k0, k1;
+                    const uint32_t n0 = count_candidates(q[u], low_s, k0, 0u), n1 = count_candidates(q[u + 1], low_s, k1, 0u);
+                    const uint32_t c = (in0 ? n0 : 0u) | (in1 ? n1 << 16 : 0u);
+                    const uint32_t ex = wave_inclusive_scan(c) - c;
+                    const uint32_t tot = uint32_t(__builtin_amdgcn_readlane(int(ex + c), WAVE - 1));
+                    const uint32_t t0 = tot & 0xFFFFu, t1 = tot >> 16;
+                    if (n + t0 + t1 > uint32_t(SEG32_CAP)) {
+                        end = row + u;                                             // full
+                    } else {
+                        const uint32_t at = flat0 + uint32_t((row + u) * ROW_ELEMS + lane * VEC);
+                        stage_candidates(q[u], k0, low_s, __ballot(in0), seg_addr + (n + (ex & 0xFFFFu)) * 8u, at, 0u);
+                        stage_candidates(q[u + 1], k1, low_s, __ballot(in1), seg_addr + (n + t0 + (ex >> 16)) * 8u, at + ROW_ELEMS, 0u);
+                        n += t0 + t1;
+                    }
+                }
+                issue_row(q[u], row + u + ST_ROWS);
+                issue_row(q[u + 1], row + u + 1 + ST_ROWS);
+            }
+        }
+        return end;
+    };
+    uint32_t n_w = 0;          // staged elements of this wavefront
+    int staged_rows = 0;       // the rows they come from: [0, staged_rows)
+    // f(key) for the wavefront's candidates: the staged ones, and those of the rows that were not staged, read again
+    auto for_candidates = [&](auto f) {
+        for (uint32_t j = lane; j < n_w; j += 4 * WAVE) {
+            uint32_t raw[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) raw[u] = uint32_t(seg[min(j + u * WAVE, n_w - 1)]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (j + u * WAVE < n_w) f(raw[u] & MASK);
+        }
+        if (staged_rows < nrows) {
+            issue_rows(staged_rows);
+            for (int row = staged_rows; row < nrows; row += ST_ROWS) {
+#pragma unroll
+                for (int u = 0; u < ST_ROWS; ++u) {
+                    if ((row + u) * WAVE + lane < wvecs)
+                        for_each_raw(uint32_t(0), q[u], [&](uint32_t raw, int) {
+                            if ((raw & MASK) >= key_lo) f(raw & MASK);
+                        });
+                    issue_row(q[u], row + u + ST_ROWS);
+                }
+            }
+        }
+    };
+    // Exact counts over the range and above it, the chunk's line of the table, a barrier, the table: false if somebody gave up.
     uint32_t barriers = 0;
     bool ready_seen = false;
-    // One digit's histogram of the chunk, merged into ghist; ends with a grid barrier, after which
-    // ghist holds the whole tensor's histogram.
-    auto hist_pass = [&](auto shift_c, auto bits_c, auto first_c, uint32_t *ghist) -> SelOutcome {
-        constexpr int SHIFT = decltype(shift_c)::value, BITS = decltype(bits_c)::value;
-        constexpr bool FIRST = decltype(first_c)::value;
-        constexpr int NB = 1 << BITS;
-        for (int i = tid; i < NB + 2 * WAVE; i += SEL_THREADS) lh[i] = 0;
-        __syncthreads();
-        const uint32_t zslot = NB + lane, dslot = NB + WAVE + lane;
-        for_chunk([&](uint32_t raw) {
-            const uint32_t key = raw & MASK;
-            const uint32_t d = (key >> SHIFT) & (NB - 1);
-            uint32_t a = d ? d : zslot;
-            if (!FIRST) a = ((key >> (SHIFT + BITS)) == prefix) ? a : dslot;
-            atomicAdd(&lh[a], 1u);
+    auto exchange_counts = [&]() -> SelOutcome {
+        uint32_t *wh = whist[wave];
+        if (lane <= static_cast<int>(nf)) wh[lane] = 0;
+        uint32_t above = 0;
+        const uint32_t bins = nf;
+        for_candidates([&](uint32_t key) {
+            const uint32_t rel = (key - key_lo) >> shift;      // (a key below the range wraps to a huge one)
+            if (key >= key_lo && rel >= bins) ++above;
+            if (rel < bins) atomicAdd(&wh[rel], 1u);
         });
+        above = wave_sum(above);
+        if (lane == 0) wh[nf] = above;
         __syncthreads();
-        if (tid < WAVE) {
-            const uint32_t z = wave_sum(lh[NB + tid]);
-            if (tid == 0) lh[0] += z;
+        if (!ready_seen)
+            if (const SelOutcome o = wait_published(&st->ready, gen, early, nullptr, &bcast[3])) return o;
+        ready_seen = true;
+        if (tid <= static_cast<int>(nf)) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int w2 = 0; w2 < NW; ++w2) sum += whist[w2][tid];
+            if (last_chunk)
+                for (int64_t i = tail0; i < numel; ++i) {
+                    const uint32_t key = x[i] & MASK, rel = (key - key_lo) >> shift;
+                    sum += (tid == static_cast<int>(nf) ? key >= key_lo && rel >= nf : key >= key_lo && rel == uint32_t(tid)) ? 1u : 0u;
+                }
+            dev_store(&table[blockIdx.x * TABLE_PITCH + tid], sum);
+        }
+        return grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3]) ? SEL_DONE : SEL_GAVE_UP;
+    };
+
+    bool missed = false;
+    for (;;) {
+        if (!predicted) {
+            // exact first digit: every element of the chunk through an LDS histogram, merged with global atomics
+            constexpr int NB = 1 << BITS32_FIRST, SHIFT1 = 31 - BITS32_FIRST;
+            if (!missed && blockIdx.x == 0) publish_hist(&st->ready_hist, gen);
+            __syncthreads();
+            for (int i = tid; i < NB + WAVE; i += SEL_THREADS) lh[i] = 0;
+            __syncthreads();
+            auto add = [&](uint32_t raw, int) {
+                const uint32_t d = (raw & MASK) >> SHIFT1;
+                atomicAdd(&lh[d ? d : NB + lane], 1u);                     // exact zeros go to per-lane slots
+            };
+            int64_t vb = v0;
+            for (; vb + SEL_THREADS * SEL_UNROLL <= v1; vb += SEL_THREADS * SEL_UNROLL) {
+                u32x4 h[SEL_UNROLL];
+#pragma unroll
+                for (int u = 0; u < SEL_UNROLL; ++u) h[u] = xv[vb + u * SEL_THREADS + tid];
+#pragma unroll
+                for (int u = 0; u < SEL_UNROLL; ++u) for_each_raw(uint32_t(0), h[u], add);
+            }
+            for (int64_t v = vb + tid; v < v1; v += SEL_THREADS) for_each_raw(uint32_t(0), xv[v], add);
+            if (last_chunk && tid == 0)
+                for (int64_t i = tail0; i < numel; ++i) add(x[i], 0);
+            __syncthreads();
+            if (tid < WAVE) {
+                const uint32_t z = wave_sum(lh[NB + tid]);
+                if (tid == 0) lh[0] += z;
+            }
+            __syncthreads();
+            if (!ready_seen)
+                if (const SelOutcome o = wait_published(&st->ready, gen, early, nullptr, &bcast[3])) return o;
+            ready_seen = true;
+            if (!missed)                               // (past a barrier the histograms are known to be cleared)
+                if (const SelOutcome o = wait_published(&st->ready_hist, gen, 0ull, &st->error, &bcast[2])) return o;
+            for (int i = tid; i < NB; i += SEL_THREADS) {
+                const uint32_t c = lh[i];
+                if (c) atomicAdd(&hist0[i], c);
+            }
+            if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+            uint32_t prefix = 0, k_rem = k;
+            resolve_digit_local<NB, BITS32_FIRST>(hist0, prefix, k_rem, wave_tot, bcast);
+            key_lo = prefix << SHIFT1;
+            nf = 32;
+            shift = SHIFT1 - 5;
+        }
+        STAMP(2);
+        staged_rows = stage_rows(key_lo, 0, n_w);
+        STAMP(3);
+        if (const SelOutcome o = exchange_counts()) return o;
+        STAMP(5);
+        if (resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, false)) break;
+        if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
+        predicted = false;                       // the sample misled: once more with the exact histogram
+        missed = true;
+    }
+    // The k-th key is the k_rem-th largest of the `left` keys in bin `bin`; offs: the chunks before this one, above that bin
+    // and in it.
+    const uint32_t bin = bcast[0], left = bcast[2];
+    uint32_t k_rem = bcast[1];
+    const uint32_t above_before = offs[0], in_before = offs[1];
+    const uint32_t bin_lo = key_lo + (bin << shift), bin_size = 1u << shift;
+    uint32_t t, m, my_gt, my_eq, chunk_gt, chunk_eq, wave_eq_mine;
+    if (left <= uint32_t(LIST32_CAP)) {
+        // ---- the bin's keys as a list in flat order ----
+        uint32_t before = 0, mine = whist[wave][bin], all = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            before += w < wave ? whist[w][bin] : 0u;
+            all += whist[w][bin];
+        }
+        const uint32_t own = in_before + before;                 // this wavefront's first entry
+        uint32_t at = own;
+        auto put = [&](bool in, uint32_t rel) {                   // in lane order
+            const lane_mask b = __ballot(in);
+            if (in) {
+                const uint32_t pos = bits_before(b, at);
+                if (pos < uint32_t(LIST32_CAP)) dev_store(&list[pos], rel);     // (always, for consistent counts)
+            }
+            at += uint32_t(__builtin_popcountll(b));
+        };
+        for (uint32_t q0 = 0; q0 < n_w; q0 += WAVE) {
+            const uint32_t rel = (uint32_t(seg[min(q0 + lane, n_w - 1)]) & MASK) - bin_lo;
+            put(q0 + lane < n_w && rel < bin_size, rel);
+        }
+        for (int row = staged_rows; row < nrows; ++row) {         // (element by element of 64 vectors: the order within a
+            u32x4 v;                                              // wavefront's share of the list does not matter)
+            issue_row(v, row);
+            const bool there = row * WAVE + lane < wvecs;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const uint32_t rel = (v[e] & MASK) - bin_lo;
+                put(there && rel < bin_size, rel);
+            }
+        }
+        if (last_chunk && tid == 0) {
+            uint32_t pos = in_before + all;
+            for (int64_t i = tail0; i < numel; ++i) {
+                const uint32_t rel = (x[i] & MASK) - bin_lo;
+                if (rel < bin_size && pos < uint32_t(LIST32_CAP)) dev_store(&list[pos++], rel);
+            }
+        }
+        if (tid < 512) digits[tid >> 8][tid & 255] = 0u;
+        if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+        STAMP(6);
+        uint32_t e[LIST32_PER], mine0 = 0;
+#pragma unroll
+        for (int j = 0; j < LIST32_PER; ++j)
+            if (uint32_t(j * SEL_THREADS + tid) < left) e[j] = dev_load(list + j * SEL_THREADS + tid);
+        if (uint32_t(lane) < mine) mine0 = dev_load(list + own + lane);
+        report_past_barriers(xbar, rep, false);
+        // two digits of 8 bits at most; every wavefront resolves each for itself, a lane four bins in descending order
+        uint32_t rel_t = 0;
+        int rem = shift;
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const int take = min(rem, 8), low = rem - take;
+#pragma unroll
+            for (int j = 0; j < LIST32_PER; ++j) {
+                const bool in = uint32_t(j * SEL_THREADS + tid) < left && (pass == 0 || e[j] >> rem == rel_t);
+                const lane_mask some = __ballot(in);
+                if (some == 0) continue;
+                // ties: one addition for a wavefront of the same digit (14 K equal entries took 20 us one by one)
+                const uint32_t d = in ? (e[j] >> low) & ((1u << take) - 1u) : 0u;
+                const int leader = __builtin_ctzll(some);
+                const uint32_t d0 = uint32_t(__builtin_amdgcn_readlane(int(d), leader));
+                if (__ballot(in && d != d0) != 0) {
+                    if (in) atomicAdd(&digits[pass][d], 1u);
+                } else if (lane == leader) {
+                    atomicAdd(&digits[pass][d0], uint32_t(__builtin_popcountll(some)));
+                }
+            }
+            __syncthreads();
+            const u32x4 d4 = reinterpret_cast<const u32x4 *>(digits[pass])[WAVE - 1 - lane];
+            const uint32_t c[4] = {d4[3], d4[2], d4[1], d4[0]}, sum = c[0] + c[1] + c[2] + c[3];
+            const uint32_t inc = wave_inclusive_scan(sum);
+            uint32_t a = inc - sum, digit = 0, rest = 0;
+            const lane_mask hit = __ballot(a < k_rem && k_rem <= inc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (a < k_rem && k_rem <= a + c[i]) {
+                    digit = uint32_t((WAVE - 1 - lane) * 4 + 3 - i);
+                    rest = k_rem - a;
+                }
+                a += c[i];
+            }
+            const int finder = hit ? __builtin_ctzll(hit) : 0;    // (always found)
+            rel_t = rel_t << take | uint32_t(__builtin_amdgcn_readlane(int(digit), finder));
+            k_rem = uint32_t(__builtin_amdgcn_readlane(int(rest), finder));
+            rem = low;
+        }
+        t = bin_lo + rel_t;
+        m = k_rem;
+        // above and equal to t: in the list before this chunk, in this wavefront's own entries and above the bin
+        uint32_t lg = 0, le = 0, g = 0, eq = 0;
+#pragma unroll
+        for (int j = 0; j < LIST32_PER; ++j) {
+            const uint32_t i = uint32_t(j * SEL_THREADS + tid);
+            if (i < left && i < in_before) {
+                lg += e[j] > rel_t ? 1u : 0u;
+                le += e[j] == rel_t ? 1u : 0u;
+            }
+        }
+        for (uint32_t j = lane; j < mine; j += WAVE) {
+            const uint32_t v = j == uint32_t(lane) ? mine0 : dev_load(list + own + j);
+            g += v > rel_t ? 1u : 0u;
+            eq += v == rel_t ? 1u : 0u;
+        }
+        if (uint32_t(lane) <= nf && uint32_t(lane) > bin) g += whist[wave][lane];           // (bin nf: above the range)
+        lg = wave_sum(lg);
+        le = wave_sum(le);
+        g = wave_sum(g);
+        eq = wave_sum(eq);
+        if (lane == 0) {
+            list_gt[wave] = lg;
+            list_eq[wave] = le;
+            wave_gt[wave] = g;
+            wave_eq[wave] = eq;
         }
         __syncthreads();
-        // the exchange area must have been cleared for this call
-        if (!ready_seen)
-            if (const SelOutcome o = wait_published(&st->ready, gen, 0ull, nullptr, &bcast[3])) return o;
-        ready_seen = true;
-        for (int i = tid; i < NB; i += SEL_THREADS) {
-            const uint32_t c = lh[i];
-            if (c) atomicAdd(&ghist[i], c);
+        const uint32_t gw = lane < NW ? wave_gt[lane] : 0u, ew = lane < NW ? wave_eq[lane] : 0u;
+        const uint32_t gi = wave_inclusive_scan(gw), ei = wave_inclusive_scan(ew);
+        const uint32_t gt0 = above_before + wave_sum(lane < NW ? list_gt[lane] : 0u), eq0 = wave_sum(lane < NW ? list_eq[lane] : 0u);
+        my_gt = gt0 + uint32_t(__builtin_amdgcn_readlane(int(gi - gw), wave));
+        my_eq = eq0 + uint32_t(__builtin_amdgcn_readlane(int(ei - ew), wave));
+        wave_eq_mine = uint32_t(__builtin_amdgcn_readlane(int(ew), wave));
+        chunk_gt = gt0 + uint32_t(__builtin_amdgcn_readlane(int(gi), NW - 1));
+        chunk_eq = eq0 + uint32_t(__builtin_amdgcn_readlane(int(ei), NW - 1));
+    } else {
+        // ---- the bin's next 11 bits from a histogram, then single keys from a second table ----
+        const int low = shift - BITS32_SECOND;                    // 5 or 2 bits are left after it
+        for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) part[i] = 0;
+        __syncthreads();
+        for_candidates([&](uint32_t key) {
+            const uint32_t rel = key - bin_lo;
+            if (rel < bin_size) atomicAdd(&part[rel >> low], 1u);
+        });
+        if (last_chunk && tid == 0)
+            for (int64_t i = tail0; i < numel; ++i) {
+                const uint32_t rel = (x[i] & MASK) - bin_lo;
+                if (rel < bin_size) atomicAdd(&part[rel >> low], 1u);
+            }
+        __syncthreads();
+        for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) {
+            const uint32_t c = part[i];
+            if (c) atomicAdd(&hist1[i], c);
         }
         if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
-        return SEL_DONE;
-    };
-    STAMP(1);
-    if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT1>{}, std::integral_constant<int, BITS1>{},
-                                       std::true_type{}, hist0))
-        return o;
-    resolve_digit_local<(1 << BITS1), BITS1>(hist0, prefix, k_rem, wave_tot, bcast);
-    if (const SelOutcome o = hist_pass(std::integral_constant<int, SHIFT2>{}, std::integral_constant<int, BITS2>{},
-                                       std::false_type{}, hist1))
-        return o;
-    resolve_digit_local<(1 << BITS2), BITS2>(hist1, prefix, k_rem, wave_tot, bcast);
-    const uint32_t key_lo = prefix << LAST_BITS;
-    STAMP(2);
-
-    // ---- exact counts over the range and above it, per chunk ----------------------
-    // Few keys fall into the range, so unlike the digit histograms this pass branches: a
-    // wavefront with no such key among its lanes skips the LDS atomic altogether (an LDS
-    // atomic costs its issue cycles whatever the number of active lanes).
-    for (int i = tid; i <= static_cast<int>(NF); i += SEL_THREADS) lh[i] = 0;
-    __syncthreads();
-    uint32_t above = 0;
-    const uint32_t key_end = key_lo + NF;
-    for_chunk([&](uint32_t raw) {
-        const uint32_t key = raw & MASK;
-        above += (key >= key_end) ? 1u : 0u;
-        const uint32_t rel = key - key_lo;             // wraps to a huge value below the range
-        if (rel < NF) atomicAdd(&lh[rel], 1u);
-    });
-    above = wave_sum(above);
-    if (lane == 0 && above) atomicAdd(&lh[NF], above);
-    __syncthreads();
-    if (tid <= static_cast<int>(NF)) dev_store(&table[blockIdx.x * TABLE_PITCH + tid], lh[tid]);
-    STAMP(4);
-    if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
-    STAMP(5);
-    if (!resolve_table(table, NF, key_lo, k, lh, bcast, offs, &verdict, xbar, rep))
-        return SEL_GAVE_UP;                    // cannot happen with exact digits; the serial path would still answer
-    const uint32_t t = bcast[0], m = bcast[1];
-    uint32_t run_gt = offs[0], run_eq = offs[1];   // #{key > t}, #{key == t} before this chunk
-    if (blockIdx.x == 0 && tid == 0) {
-        dev_store(&st->form, 0u);
-        dev_store(&st->path, 0u);
+        uint32_t digit = 0;
+        resolve_digit_local<1 << BITS32_SECOND, BITS32_SECOND>(hist1, digit, k_rem, wave_tot, bcast);
+        key_lo = bin_lo + (digit << low);
+        nf = 1u << low;
+        shift = 0;
+        if (const SelOutcome o = exchange_counts()) return o;
+        if (!resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, true)) return SEL_GAVE_UP;   // cannot happen
+        t = key_lo + bcast[0];
+        m = bcast[1];
+        const uint32_t trel = bcast[0];
+        uint32_t g = 0, eq = 0;
+        if (lane < NW) {
+            g = whist[lane][nf];
+            for (uint32_t r = trel + 1; r < nf; ++r) g += whist[lane][r];
+            eq = whist[lane][trel];
+        }
+        const uint32_t gi = wave_inclusive_scan(g), ei = wave_inclusive_scan(eq);
+        my_gt = offs[0] + uint32_t(__builtin_amdgcn_readlane(int(gi - g), wave));
+        my_eq = offs[1] + uint32_t(__builtin_amdgcn_readlane(int(ei - eq), wave));
+        wave_eq_mine = uint32_t(__builtin_amdgcn_readlane(int(eq), wave));
+        chunk_gt = offs[0] + uint32_t(__builtin_amdgcn_readlane(int(gi), NW - 1));
+        chunk_eq = offs[1] + uint32_t(__builtin_amdgcn_readlane(int(ei), NW - 1));
     }
-    STAMP(6);
+    if (tid == REPORT_TID && blockIdx.x == 0) {
+        dev_store(&st->form, 0u);                                 // (what these two words say is for 16-bit tensors)
+        dev_store(&st->path, 0u);
+        dev_store(&st->form32, (missed ? 2u : predicted ? 1u : 0u) + (left <= uint32_t(LIST32_CAP) ? 0u : 4u));
+    }
+    STAMP(7);
 
-    // ---- ordered compaction -------------------------------------------------------
-    // The kept elements of a tile occupy consecutive output slots; they are gathered in
-    // LDS first so that the global stores are contiguous.
-    auto keep = [&](uint32_t pos, uint32_t raw, int64_t i) {
+    // ---- ordered output, as for 16-bit elements -----------------------------------
+    auto keep = [&](uint32_t pos, uint32_t raw, uint32_t i) {
         if (pos < k) {                     // always true for consistent counts
             vals[pos] = raw;
             idx[pos] = static_cast<int32_t>(i);
         }
     };
-    auto emit_tile = [&](const u32x4 &q, int64_t v, bool live) {
-        // bit e of gtm / eqm: element e of this thread's vector has key > t / key == t
-        uint32_t gtm = 0, eqm = 0;
-        for_each_raw(uint32_t(0), q, [&](uint32_t raw, int e) {
-            const uint32_t key = raw & MASK;
-            gtm |= (key > t ? 1u : 0u) << e;
-            eqm |= (key == t ? 1u : 0u) << e;
-        });
-        if (!live) gtm = eqm = 0;
-        const uint32_t cnt = __builtin_popcount(gtm) | (__builtin_popcount(eqm) << 16);
-        uint32_t total;
-        const uint32_t excl = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
-        const uint32_t tile_first = run_gt + min(run_eq, m);           // output slot of the tile's first kept element
-        uint32_t my_gt = run_gt + (excl & 0xFFFFu);
-        uint32_t my_eq = run_eq + (excl >> 16);
-        const int64_t base = v * VEC;
-        // A kept element (key > t, or one of the first m keys == t) goes to output slot
-        // #gt-before + min(#eq-before, m): one formula for both cases.  Only the candidate
-        // elements are visited: every LDS store a wavefront issues costs its slot on the LDS
-        // pipe however few lanes take part.
-        uint32_t todo = gtm | eqm;
-        while (todo) {
-            const int e = __builtin_ctz(todo);
-            todo &= todo - 1;
-            const bool gt = (gtm >> e) & 1u;
-            if (gt || my_eq < m) {
-                const uint32_t slot = my_gt + min(my_eq, m) - tile_first;
-                stage_val[slot] = q[e];
-                stage_idx[slot] = static_cast<int32_t>(base + e);
-            }
-            my_gt += gt ? 1u : 0u;
-            my_eq += gt ? 0u : 1u;
-        }
-        run_gt += total & 0xFFFFu;
-        run_eq += total >> 16;
-        const uint32_t tile_kept = run_gt + min(run_eq, m) - tile_first;
-        __syncthreads();
-        for (uint32_t s = tid; s < tile_kept; s += SEL_THREADS)
-            if (tile_first + s < k) {      // always true for consistent counts
-                vals[tile_first + s] = stage_val[s];
-                idx[tile_first + s] = stage_idx[s];
-            }
-        // the next tile's scan starts with a barrier, which also protects the staging buffers
-    };
-    __syncthreads();                       // histogram storage becomes staging storage
-    // The chunk is compacted in super-tiles of FUSED_RES x 1024 vectors that sit in the parking
-    // area: the first one is the parked head itself, the following ones are fetched (coalesced,
-    // one super-tile ahead, through registers) into the same area.  Inside a super-tile each thread
-    // takes `rows` CONSECUTIVE vectors (the other phases take every 1024th), so flat-index order is
-    // thread order and one block scan serves the whole super-tile: two barriers + a gather + a
-    // write-out per 24576 elements.  Bit (i * VEC + e) of the masks stands for element e of the
-    // thread's i-th vector.  A super-tile that keeps more than the staging buffers hold (only when
-    // most of the tensor is kept) falls back to one scan per 1024-vector row.
-    constexpr int64_t SUPER = int64_t(FUSED_RES) * SEL_THREADS;
-    u32x4 pre[FUSED_RES];
-    for (int64_t sb = v0; sb < v1; sb += SUPER) {
-        const int64_t count = min<int64_t>(v1 - sb, SUPER);          // vectors of this super-tile, all in `res`
-        const int rows = static_cast<int>((count + SEL_THREADS - 1) / SEL_THREADS);
-        const bool more = sb + SUPER < v1;
-        if (more) {                                                   // the next one, clamped loads
+    const bool split = my_eq < m && my_eq + wave_eq_mine > m;
+    const uint32_t least = my_eq < m ? t : t + 1;      // lowest key kept (if not split)
+    uint32_t my_slot = my_gt + min(my_eq, m);
+    for (;;) {
+        for (uint32_t q0 = 0; q0 < n_w; q0 += 4 * WAVE) {
+            word w[4];
 #pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i) pre[i] = xv[min(sb + SUPER + int64_t(i) * SEL_THREADS + tid, v1 - 1)];
-        }
-        const int64_t mine0 = int64_t(tid) * rows;                    // first vector of this thread
-        unsigned long long gtm = 0, eqm = 0;
-#pragma nounroll
-        for (int i = 0; i < rows; ++i) {
-            if (mine0 + i < count) {
-                uint32_t g = 0, q = 0;
-                for_each_raw(uint32_t(0), res[mine0 + i], [&](uint32_t raw, int e) {
-                    const uint32_t key = raw & MASK;
-                    g |= (key > t ? 1u : 0u) << e;
-                    q |= (key == t ? 1u : 0u) << e;
-                });
-                gtm |= static_cast<unsigned long long>(g) << (i * VEC);
-                eqm |= static_cast<unsigned long long>(q) << (i * VEC);
-            }
-        }
-        uint32_t ex_gt, ex_eq, tot_gt, tot_eq;
-        block_exclusive_scan2<SEL_THREADS>(__builtin_popcountll(gtm), __builtin_popcountll(eqm), wave_tot2, ex_gt, ex_eq,
-                                           tot_gt, tot_eq);
-        const uint32_t part_first = run_gt + min(run_eq, m);
-        const uint32_t part_kept = (run_gt + tot_gt) + min(run_eq + tot_eq, m) - part_first;
-        if (part_kept <= uint32_t(TILE)) {                             // uniform over the workgroup
-            uint32_t my_gt = run_gt + ex_gt, my_eq = run_eq + ex_eq;
-            const uint32_t *res_raw = reinterpret_cast<const uint32_t *>(res);
-            unsigned long long todo = gtm | eqm;
-            while (todo) {
-                const int b = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                const bool gt = (gtm >> b) & 1ull;
-                if (gt || my_eq < m) {
-                    const uint32_t slot = my_gt + min(my_eq, m) - part_first;
-                    const uint32_t off = static_cast<uint32_t>(mine0) * VEC + b;
-                    stage_val[slot] = res_raw[off];
-                    stage_idx[slot] = static_cast<int32_t>(sb * VEC + off);
-                }
-                my_gt += gt ? 1u : 0u;
-                my_eq += gt ? 0u : 1u;
-            }
-            run_gt += tot_gt;
-            run_eq += tot_eq;
-            __syncthreads();
-            for (uint32_t q = tid; q < part_kept; q += SEL_THREADS)
-                if (part_first + q < k) {          // always true for consistent counts
-                    vals[part_first + q] = stage_val[q];
-                    idx[part_first + q] = stage_idx[q];
-                }
-        } else {
-            for (int i = 0; i < rows; ++i) {       // row by row; a row's scan starts with a barrier, which frees the staging buffers
-                const int64_t v = sb + int64_t(i) * SEL_THREADS + tid;
-                emit_tile(res[i * SEL_THREADS + tid], v, v < v1);
-            }
-        }
-        if (more) {
-            __syncthreads();                       // everybody is done with this super-tile's vectors and staging
+            for (int j = 0; j < 4; ++j) w[j] = seg[min(q0 + j * WAVE + lane, n_w - 1)];
 #pragma unroll
-            for (int i = 0; i < FUSED_RES; ++i) res[i * SEL_THREADS + tid] = pre[i];
-            __syncthreads();
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t raw = uint32_t(w[j]), key = raw & MASK;
+                const bool there = q0 + j * WAVE + lane < n_w;
+                if (!split) {              // uniform over the wavefront
+                    const bool kept = there && key >= least;
+                    const lane_mask b = __ballot(kept);
+                    if (kept) keep(bits_before(b, my_slot), raw, uint32_t(w[j] >> 32));
+                    my_slot += __builtin_popcountll(b);
+                } else {
+                    const bool gt = there && key > t, eq = there && key == t;
+                    const lane_mask bg = __ballot(gt), be = __ballot(eq);
+                    const uint32_t eb = bits_before(be, my_eq), gb = bits_before(bg, my_gt);
+                    if (gt || (eq && eb < m)) keep(gb + min(eb, m), raw, uint32_t(w[j] >> 32));
+                    my_gt += __builtin_popcountll(bg);
+                    my_eq += __builtin_popcountll(be);
+                }
+            }
         }
+        if (staged_rows >= nrows) break;
+        staged_rows = stage_rows(t, staged_rows, n_w);            // the rows that did not fit: only what is kept is staged now
     }
-    STAMP(7);
     if (last_chunk && tid == 0) {
-        for (int64_t i = nvf * VEC; i < numel; ++i) {
-            const uint32_t raw = x[i];
-            const uint32_t key = raw & MASK;
+        uint32_t run_gt = chunk_gt, run_eq = chunk_eq;
+        for (int64_t i = tail0; i < numel; ++i) {
+            const uint32_t raw = x[i], key = raw & MASK;
             if (key > t) {
-                keep(run_gt + min(run_eq, m), raw, i);
+                keep(run_gt + min(run_eq, m), raw, static_cast<uint32_t>(i));
                 ++run_gt;
             } else if (key == t) {
-                if (run_eq < m) keep(run_gt + run_eq, raw, i);
+                if (run_eq < m) keep(run_gt + run_eq, raw, static_cast<uint32_t>(i));
                 ++run_eq;
             }
         }
@@ -1639,63 +1893,6 @@ __device__ inline void select_serial(const RAW *__restrict__ x, int64_t numel, i
         }
     }
 }
-
-// ---- candidates of 32-bit elements ------------------------------------------------------------------
-// As count_candidates / stage_candidates above: the four consecutive elements of q against a lowest key; a staged candidate
-// is two words, the element and its position.
-__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint32_t)
-{
-    uint32_t n = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        keys[e] = q[e] & KeyTraits<uint32_t>::MASK;
-        n += keys[e] >= lowest ? 1u : 0u;
-    }
-    return n;
-}
-__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
-                                        uint32_t addr, uint32_t pos, uint32_t)
-{
-    unsigned long long saved;
-    const uint32_t lo = lowest;
-#define STAGE_ELEMENT(W, K)                                      \
-    "v_cmpx_le_u32 vcc, %[lo], " K "\n\t"                        \
-    "ds_write2_b32 %[addr], " W ", %[pos] offset1:1\n\t"         \
-    "v_add_u32 %[addr], 8, %[addr]\n\t"                          \
-    "s_mov_b64 exec, %[valid]\n\t"                               \
-    "v_add_u32 %[pos], 1, %[pos]\n\t"
-    asm volatile("s_mov_b64 %[saved], exec\n\t"
-                 "s_mov_b64 exec, %[valid]\n\t"
-                 STAGE_ELEMENT("%[q0]", "%[k0]") STAGE_ELEMENT("%[q1]", "%[k1]") STAGE_ELEMENT("%[q2]", "%[k2]") STAGE_ELEMENT("%[q3]", "%[k3]")
-                 "s_mov_b64 exec, %[saved]\n\t"
-                 "s_nop 4"                      // (cross-lane operations must not follow a vector write of the mask closely)
-                 : [addr] "+&v"(addr), [pos] "+&v"(pos), [saved] "=&s"(saved)
-                 : [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [k0] "v"(keys[0]), [k1] "v"(keys[1]),
-                   [k2] "v"(keys[2]), [k3] "v"(keys[3]), [lo] "s"(lo), [valid] "s"(valid)
-                 : "vcc", "memory");
-#undef STAGE_ELEMENT
-}
-__device__ inline uint32_t count_candidates(const u32x4 &q, uint32_t lowest, u32x4 &keys, uint16_t) { return count_candidates(q, lowest, keys); }
-__device__ inline void stage_candidates(const u32x4 &q, const u32x4 &keys, uint32_t lowest, unsigned long long valid,
-                                        uint32_t addr, uint32_t pos, uint16_t)
-{
-    stage_candidates(q, keys, lowest, valid, addr, pos);
-}
-
-// A staged candidate of either type.
-template <typename RAW> struct Staged;
-template <> struct Staged<uint16_t> {
-    typedef uint32_t word;
-    __device__ static uint32_t raw(word w) { return w >> 16; }
-    __device__ static uint32_t pos(word w) { return w & 0xFFFFu; }
-    __device__ static word make(uint32_t raw, uint32_t pos) { return raw << 16 | pos; }
-};
-template <> struct Staged<uint32_t> {
-    typedef unsigned long long word;
-    __device__ static uint32_t raw(word w) { return uint32_t(w); }
-    __device__ static uint32_t pos(word w) { return uint32_t(w >> 32); }
-    __device__ static word make(uint32_t raw, uint32_t pos) { return static_cast<unsigned long long>(pos) << 32 | raw; }
-};
 
 // ---- small tensors: one workgroup, everything in registers ------------------------------------------
 // Up to SMALL_VECTORS 16-byte vectors per thread (32 K fp32 or 64 K 16-bit elements): the tensor is read
@@ -2083,7 +2280,7 @@ template <typename RAW>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k, SelState *st,
                     uint32_t *hist0, uint32_t *hist1, uint32_t *table, RAW *__restrict__ vals,
-                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks /* 16-bit types */)
+                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks)
 {
     ExitReport rep;
     rep.mine = 0u;
@@ -2091,7 +2288,7 @@ select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64
     if constexpr (sizeof(RAW) == 2)
         outcome = select16_body(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, ranks, rep);
     else
-        outcome = select32_body(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen, rep);
+        outcome = select32_body(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen, ranks, rep);
     // Exit protocol: every workgroup reports once, when it is past its last grid barrier or gives up at one (the high
     // half counts those).  Whoever's report completes the count sees whether anybody gave up, and
     // then redoes the selection alone when it leaves.  Everything the others store to the outputs is either final or
@@ -2275,12 +2472,9 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
     // Preferred: one persistent kernel, one workgroup per compute unit.
     if (mode != 1) {
         constexpr int VEC = KeyTraits<RAW>::VEC;
-        // fp32: the parked chunk head, then the digit histogram or the compaction's staging buffers
-        constexpr size_t parked_bytes = size_t(FUSED_RES) * SEL_THREADS * 16 + 4 * size_t(std::max((1 << 13) + 2 * WAVE, 2 * SEL_THREADS * VEC));
-        constexpr size_t smem_bytes = sizeof(RAW) == 2 ? ST_SMEM_BYTES : parked_bytes;
+        constexpr size_t smem_bytes = sizeof(RAW) == 2 ? ST_SMEM_BYTES : SMEM32_BYTES;
         static_assert(smem_bytes <= 156 * 1024, "of the 160 KB of a compute unit; the rest is static");
-        static_assert(size_t(FUSED_RES) * SEL_THREADS * 16 >= 4 * ((size_t(1) << 13) + 2 * WAVE),
-                      "the serial fallback keeps its histogram where the chunk head was parked");
+        static_assert(smem_bytes >= 4 * ((size_t(1) << 13) + 2 * WAVE), "the serial redo's histogram");
         // how many workgroups of this kernel each device holds at once (asked once per element type and device)
         static std::atomic<uint64_t> asked{0};
         static int capacity_of[64] = {};
