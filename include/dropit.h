@@ -159,7 +159,7 @@ typedef DROPIT_ENUM(dropit_wgrad_path) {
     DROPIT_PATH_FC_MFMA = 1,        /* recover + split-K bf16 MFMA GEMM */
     DROPIT_PATH_CONV_BANDS = 2,     /* 3x3/s1/p1 bf16: row bands in LDS, implicit im2col on the matrix cores */
     DROPIT_PATH_CONV_GEMM = 3,      /* 3x3/s1/p1 bf16, small planes with many channels: the FC GEMM over token-major operands, read through the window */
-    DROPIT_PATH_FMA = 4,            /* exact fp32 multiply-adds on the fp32 matrix instructions (fp32 inputs, odd shapes) */
+    DROPIT_PATH_FMA = 4,            /* fp32 products: multiply-adds on the fp32 matrix instructions, or bf16 thirds (fp32 inputs, odd shapes) */
     DROPIT_PATH_CONV_IM2COL = 5,    /* bf16, any geometry and either layout: the FC GEMM over im2col rows written from the pairs, or, where the layout allows, over the operands as they lie */
     DROPIT_PATH_FC_SMALL = 6,       /* fully-connected layers of at most 16384 input elements: recover in LDS and exact fp32 multiply-adds, one launch */
     DROPIT_PATH_FC_FUSED = 7        /* the FC_MFMA product with the recover step inside it (only after dropit_set_fc_recover(1)) */
@@ -198,7 +198,8 @@ dropit_wgrad_path dropit_weight_grad_path(const int64_t *x_shape, int ndim, drop
  *   workspace       device, 256-byte aligned, >= dropit_weight_grad_workspace_bytes
  *
  * bf16 inputs are multiplied exactly and accumulated in fp32; fp32 inputs use
- * true fp32 multiply-adds.  Infinities and NaN: a window position over the padding
+ * true fp32 multiply-adds, or, for large fully-connected layers, the products of three bf16
+ * parts of each factor, which leave out less than 2^-25 of a product, accumulated in fp32.  Infinities and NaN: a window position over the padding
  * is no term of the sum on the exact path (DROPIT_PATH_FMA); the bf16 matrix-core
  * convolutions multiply the zeros that stand there, so an infinity or NaN of dY at
  * a border also makes the taps that hang over it NaN.  k == 0 gives dW = 0.  The bias gradient does not

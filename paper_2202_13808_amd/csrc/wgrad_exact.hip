@@ -17,7 +17,8 @@
 //      previous one multiplies; one LDS buffer, two barriers per step, two or more workgroups per compute unit
 //      to cover them.
 //   3. the K-slices' sums are added in a fixed order (splitk.hpp).
-// Products and accumulation are true fp32 multiply-adds in a fixed order: dW is bit-reproducible.
+// Products and accumulation are true fp32 multiply-adds in a fixed order: dW is bit-reproducible.  (Large fp32 fully-connected
+// layers take a faster product of the same accuracy, see "fp32 products from bf16 thirds".)
 // A window position over the padding is no term of the sum: an infinity or NaN of dY must not meet the zero that stands
 // there in the tile.  A workgroup whose sums are not all finite (padded convolutions only: one look at them at the end)
 // does its slice again, with the tokens whose dY is not finite taken out of the matrix product and added by vector
@@ -60,6 +61,37 @@ struct ExactGeometry {
     uint32_t xc, xh, xw;                                         // element strides of R(a^): channel, row, column
     int64_t xn, yn;                                              // ... and of an image, in R(a^) and in dY
 };
+
+// acc[i][j][e] is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32 of its 32x32 block
+template <typename C>
+__device__ inline void exact_epilogue(const f32x16 (&acc)[C::FM][C::FN], int splits, int split, int nb_count, int mb_count,
+                                      int nb, int mb, int M, int N, float *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+    if (splits == 1) {
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int m = mb * C::BM + wm * C::WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                    const int n = nb * C::BN + wn * C::WN + j * 32 + (lane & 31);
+                    if (m < M && n < N) out[int64_t(m) * N + n] = acc[i][j][e];
+                }
+    } else {                                               // the partial tile in accumulator order, see splitk.hpp
+        f32x4 *dst = reinterpret_cast<f32x4 *>(out) +
+                     (int64_t(split) * (nb_count * mb_count) + (mb * nb_count + nb)) * (C::BM * C::BN / 4) + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    dst[((i * C::FN + j) * 4 + q) * C::NTHREADS] =
+                        f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+    }
+}
 
 template <typename RAW, typename C, Fetch FA, Fetch FB>
 __global__ void __launch_bounds__(256)
@@ -342,30 +374,215 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
         }
     }
 
-    // acc[i][j][e] is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32 of its 32x32 block
-    if (splits == 1) {
+    exact_epilogue<C>(acc, splits, split, nb_count, mb_count, nb, mb, M, N, out);
+}
+
+// ---- fp32 products from bf16 thirds -----------------------------------------------------------------
+// A fp32 number is the sum of three bf16 numbers, 8 significand bits each (a = a1 + a2 + a3, every difference exact), so a
+// product of two is the sum of nine bf16 products, exact in fp32; the six of a1 b1, a1 b2, a2 b1, a2 b2, a1 b3 and a3 b1
+// leave out less than 2^-25 of |a b| -- below the rounding of a single fp32 addition -- and take 192 cycles of the bf16 matrix
+// instructions for 16 tokens of a 32 x 32 block, where the fp32 instruction takes 512.  a1 b1 has sums of its own, so that
+// they are rounded once per 16 tokens and not six times (against 64 bits, 6304 tokens, gamma 0.9: 0.8e-7 in the 2-norm; the
+// fp32 instruction 1.4e-7; one set of sums 2.4e-7).
+// The thirds are made on the way from the fetch to LDS (five vector instructions per element, beside the other workgroup's
+// matrix instructions) and lie there as [third][column][32 tokens], so that an operand is one 16-byte read; the 16-byte unit o
+// of column c is kept at o ^ swizzle(c), which spreads the reads (consecutive columns, one o) and the stores over the banks.
+// Two workgroups per compute unit, one converting while the other multiplies.  Whole call 6304 x 384 -> 1536 80 -> 59 us (the matrix
+// instructions of the product alone take 20), 6304 x 1536 -> 384 93 -> 74.5; two LDS stages and
+// one 256 x 128 workgroup of eight wavefronts 65, loads of four bytes instead of eight 68.
+// What the thirds cannot carry shows in the sums: an infinity, a NaN, or a value that rounds to infinity in bf16 makes one of
+// them not finite; and where the last third of a value is below the normal numbers (2^-126, taken as lost here) a sum of n
+// terms is off by n 2^-126 of the other operand's largest value.  A workgroup with a sum that is not finite, or not zero and
+// so small that this would be 2^-25 of it, does its slice again with the fp32 instruction.
+constexpr int SPLIT_BM = 128, SPLIT_BN = 128;
+
+__device__ inline void split_thirds(float a, float b, uint32_t &p1, uint32_t &p2, uint32_t &p3)      // a in the lower halves
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    auto pack = [](float lo, float hi) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2)); };
+    p1 = pack(a, b);
+    a -= __uint_as_float(p1 << 16);
+    b -= __uint_as_float(p1 & 0xFFFF0000u);
+    p2 = pack(a, b);
+    a -= __uint_as_float(p2 << 16);
+    b -= __uint_as_float(p2 & 0xFFFF0000u);
+    p3 = pack(a, b);
+}
+
+__global__ void __launch_bounds__(256, 2)
+exact_split_kernel(const float *__restrict__ dY, const float *__restrict__ x, int64_t ntok, int M, int N, int nb_count,
+                   int mb_count, int nkb, int splits, float *__restrict__ out)
+{
+    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    using C = ExactCfg<SPLIT_BM, SPLIT_BN>;
+    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, THIRD = BM * BK * 2;      // bytes of a third of an operand tile
+    static_assert(BM == BN && BK == 32 && C::NTHREADS == 256 && C::WM == 64 && C::WN == 64, "a wavefront per 8 tokens, two columns per lane");
+    __shared__ __attribute__((aligned(16))) char lds[6 * THIRD];
+    static_assert(6 * THIRD >= BK * (C::PA + C::PB) * 4, "the fp32 tiles of the other form");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+    const int total = nb_count * mb_count * splits;
+    const int v = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;          // (workgroups of one XCD share operand rows in its L2)
+    if (v >= total) return;
+    const int nb = v % nb_count, mb = (v / nb_count) % mb_count, split = v / (nb_count * mb_count);
+    const int m0 = mb * BM, n0 = nb * BN;
+    const int kb_begin = int(int64_t(nkb) * split / splits), kb_end = int(int64_t(nkb) * (split + 1) / splits);
+    f32x16 acc[C::FM][C::FN], small[C::FM][C::FN];         // a1 b1, and the others
+    auto clear = [&](f32x16 (&s)[C::FM][C::FN]) {
 #pragma unroll
         for (int i = 0; i < C::FM; ++i)
 #pragma unroll
             for (int j = 0; j < C::FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = m0 + wm * C::WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                    const int n = n0 + wn * C::WN + j * 32 + (lane & 31);
-                    if (m < M && n < N) out[int64_t(m) * N + n] = acc[i][j][e];
+                for (int e = 0; e < 16; ++e) s[i][j][e] = 0.f;
+    };
+
+    // a step's tiles: lane = two columns, wavefront = 8 tokens, of dY and of R(a^)
+    f32x2 ra[8], rb[8];
+    // (columns past the last re-read the last two, those sums are not stored; tokens past the last are zero)
+    const int q = lane * 2, qm = min(m0 + q, M - 2), qn = min(n0 + q, N - 2);   // M and N are even
+    auto fetch = [&](int kb) {
+        const int64_t t = int64_t(kb) * BK + wave * 8;
+        const float *pa = dY + t * M + qm, *pb = x + t * N + qn;
+        if (t + 8 <= ntok) {                                                    // uniform
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                ra[r] = *reinterpret_cast<const f32x2 *>(pa + int64_t(r) * M);
+                rb[r] = *reinterpret_cast<const f32x2 *>(pb + int64_t(r) * N);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                ra[r] = rb[r] = f32x2{0.f, 0.f};
+                if (t + r < ntok) {
+                    ra[r] = *reinterpret_cast<const f32x2 *>(pa + int64_t(r) * M);
+                    rb[r] = *reinterpret_cast<const f32x2 *>(pb + int64_t(r) * N);
                 }
-    } else {                                               // the partial tile in accumulator order, see splitk.hpp
-        f32x4 *dst = reinterpret_cast<f32x4 *>(out) +
-                     (int64_t(split) * (nb_count * mb_count) + (mb * nb_count + nb)) * (BM * BN / 4) + tid;
+            }
+        }
+    };
+    auto unit = [](int c, int o) { return c * 64 + ((o ^ c ^ (c >> 2)) & 3) * 16; };      // of column c, tokens 8 o .. 8 o + 7
+    float most_a = 0.f, most_b = 0.f;                                           // largest magnitudes of this thread's elements
+    auto most = [](float a, float b, float m) {
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a), "v"(b));
+        return m;
+    };
+    auto store = [&]() {
 #pragma unroll
-        for (int i = 0; i < C::FM; ++i)
+        for (int r = 0; r < 8; ++r) {
+            most_a = most(ra[r][0], ra[r][1], most_a);
+            most_b = most(rb[r][0], rb[r][1], most_b);
+        }
 #pragma unroll
-            for (int j = 0; j < C::FN; ++j)
+        for (int h = 0; h < 2; ++h) {                                           // dY, R(a^)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    dst[((i * C::FN + j) * 4 + q) * NT] =
-                        f32x4{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
+            for (int c = 0; c < 2; ++c) {
+                u32x4 third[3];
+#pragma unroll
+                for (int r = 0; r < 8; r += 2) {
+                    uint32_t p1, p2, p3;
+                    if (h == 0) split_thirds(ra[r][c], ra[r + 1][c], p1, p2, p3);
+                    else split_thirds(rb[r][c], rb[r + 1][c], p1, p2, p3);
+                    third[0][r / 2] = p1;
+                    third[1][r / 2] = p2;
+                    third[2][r / 2] = p3;
+                }
+#pragma unroll
+                for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4 *>(lds + (h * 3 + p) * THIRD + unit(q + c, wave)) = third[p];
+            }
+        }
+    };
+    clear(acc);
+    clear(small);
+    if (kb_begin < kb_end) fetch(kb_begin);
+    for (int kb = kb_begin; kb < kb_end; ++kb) {
+        __syncthreads();                                                        // the previous step's tiles have been read
+        store();
+        __syncthreads();
+        if (kb + 1 < kb_end) fetch(kb + 1);
+#pragma unroll
+        for (int kk = 0; kk < BK / 16; ++kk) {
+            bf16x8 a[3][C::FM], b[3][C::FN];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i)
+                    a[p][i] = *reinterpret_cast<const bf16x8 *>(lds + p * THIRD + unit(wm * C::WM + i * 32 + (lane & 31), kk * 2 + (lane >> 5)));
+#pragma unroll
+                for (int j = 0; j < C::FN; ++j)
+                    b[p][j] = *reinterpret_cast<const bf16x8 *>(lds + (3 + p) * THIRD + unit(wn * C::WN + j * 32 + (lane & 31), kk * 2 + (lane >> 5)));
+            }
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::FN; ++j) {
+                        f32x16 &s = p == 5 ? acc[i][j] : small[i][j];
+                        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[p]][i], b[PB[p]][j], s, 0, 0, 0);
+                    }
+        }
     }
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] += small[i][j][e];
+    // (a NaN is not the largest; it is in the sums)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        most_a = __builtin_fmaxf(most_a, __shfl_xor(most_a, o, 64));
+        most_b = __builtin_fmaxf(most_b, __shfl_xor(most_b, o, 64));
+    }
+    __shared__ float most_of[2][4];
+    if (lane == 0) {
+        most_of[0][wave] = most_a;
+        most_of[1][wave] = most_b;
+    }
+    __syncthreads();
+    float both = 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        both += __builtin_fmaxf(__builtin_fmaxf(most_of[h][0], most_of[h][1]), __builtin_fmaxf(most_of[h][2], most_of[h][3]));
+    const float lost = float((kb_end - kb_begin) * BK) * 0x1p-101f * both;      // n 2^-126 of them, times 2^25
+    bool odd = false;                                                           // a sum the thirds do not vouch for
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float s = __builtin_fabsf(acc[i][j][e]);
+                odd |= !(s < __builtin_inff()) || (s < lost && s != 0.f);
+            }
+    if (__syncthreads_or(odd)) {
+        float *sA = reinterpret_cast<float *>(lds), *sB = sA + BK * C::PA;
+        clear(acc);
+        for (int kb = kb_begin; kb < kb_end; ++kb) {
+            fetch(kb);
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                *reinterpret_cast<f32x2 *>(sA + (wave * 8 + r) * C::PA + q) = ra[r];
+                *reinterpret_cast<f32x2 *>(sB + (wave * 8 + r) * C::PB + q) = rb[r];
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int kk = 0; kk < BK / 2; ++kk)
+#pragma unroll
+                for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(sA[(kk * 2 + (lane >> 5)) * C::PA + wm * C::WM + i * 32 + (lane & 31)],
+                                                                         sB[(kk * 2 + (lane >> 5)) * C::PB + wn * C::WN + j * 32 + (lane & 31)],
+                                                                         acc[i][j], 0, 0, 0);
+        }
+    }
+    exact_epilogue<C>(acc, splits, split, nb_count, mb_count, nb, mb, M, N, out);
 }
 
 constexpr int EXACT_TILE_BYTES = 32 * 1024;                // of R(a^), per recover workgroup, at most
@@ -393,7 +610,11 @@ dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const R
     const bool wide_y = p.cout % 4 == 0, wide_x = p.cin % 4 == 0;      // 16-byte rows
     if constexpr (sizeof(RAW) == 4) {
         if (!p.conv) {
-            if (wide_y && wide_x) go(exact_gemm_kernel<RAW, C, ROWS16, ROWS16>);
+            if (wide_y && wide_x && C::BM == SPLIT_BM && !dev_env("DROPIT_EXACT_FMA", 0))
+                exact_split_kernel<<<grid, 256, 0, stream>>>(reinterpret_cast<const float *>(dY), reinterpret_cast<const float *>(x),
+                                                             p.ntok, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count,
+                                                             plan.nkb, plan.splits, out);
+            else if (wide_y && wide_x) go(exact_gemm_kernel<RAW, C, ROWS16, ROWS16>);
             else go(exact_gemm_kernel<RAW, C, ROWS1, ROWS1>);
         } else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
         else if (wide_y) go(exact_gemm_kernel<RAW, C, ROWS16, ALONG_COLUMNS>);

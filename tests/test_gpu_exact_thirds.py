@@ -1,0 +1,69 @@
+"""GPU: fp32 fully-connected layers large enough for the product from bf16 thirds, at ragged edges (token blocks, tiles, one
+and many slices), against 64 bits; and what the thirds cannot carry -- infinities, NaN, values that round to infinity in bf16,
+terms below the normal numbers -- which takes the fp32 instruction instead.  n terms in fp32, rounded once per 16: 2e-7 in the
+2-norm covers n = 8192 (0.9 of it is what the fp32 instruction shows at 6304 tokens)."""
+import pytest
+import torch
+
+import paper_2202_13808_amd as dropit
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def layer(ntok, cin, cout, x_scale=1.0, dy_scale=0.02):
+    gen = torch.Generator(device=DEV).manual_seed(ntok)
+    x = torch.randn(ntok, cin, generator=gen, device=DEV) * x_scale
+    return x, torch.randn(ntok, cout, generator=gen, device=DEV) * dy_scale
+
+
+def product(x, dy, gamma):
+    vals, idx = dropit.compress(x, gamma)
+    assert dropit.weight_grad_path(x.shape, x.dtype, vals.numel(), dy.shape[1]) == "fma"
+    flat = torch.zeros(x.numel(), dtype=torch.float64, device=DEV)
+    flat[idx.long()] = vals.double()
+    xr = flat.view(x.shape)
+    return dropit.weight_grad(vals, idx, x.shape, dy, dy.shape[1]), dy.double().t() @ xr, xr
+
+
+@pytest.mark.parametrize("ntok,cin,cout,gamma", [
+    (700, 1024, 1024, 0.8),       # whole tiles, a partial token block
+    (417, 1028, 1500, 0.9),       # ragged in both columns, a single token in the last block
+    (64, 3068, 3072, 0.6),        # two token blocks, one slice straight into dW
+    (33, 3072, 3060, 0.9),        # ... the second one nearly empty
+    (8191, 388, 260, 0.7),        # many slices, thin edges
+    (6304, 384, 1536, 0.9),
+])
+def test_sizes(ntok, cin, cout, gamma):
+    got, want, _ = product(*layer(ntok, cin, cout), gamma)
+    err = ((got.double() - want).norm() / want.norm()).item()
+    print("thirds", ntok, cin, cout, gamma, "%.2e" % err, flush=True)
+    assert err < 2e-7
+
+
+def test_not_finite():
+    """The pattern of infinities and NaN is that of the sums in 64 bits, the rest stays as accurate."""
+    x, dy = layer(700, 1024, 1024)
+    dy[3, 5] = float("inf")
+    dy[400, 900] = float("nan")
+    x[699, 1000] = float("-inf")
+    x[17, 200] = 3.4e38                            # finite, infinite as bf16
+    dy[17, :8] = 1e-3
+    got, want, _ = product(x, dy, 0.8)
+    want32 = want.to(torch.float32)                # (sums beyond fp32 are infinite in either)
+    assert torch.equal(torch.isnan(got), torch.isnan(want32))
+    finite = torch.isfinite(want32)
+    assert torch.equal(torch.isinf(got), torch.isinf(want32)) and torch.equal(got[~finite & ~torch.isnan(got)], want32[~finite & ~torch.isnan(want32)])
+    plain = finite.clone()
+    plain[:, 200] = False                          # (the column of the large value: its sums cancel nothing, checked below)
+    assert ((got.double() - want)[plain].norm() / want[plain].norm()).item() < 2e-7
+    large = finite[:, 200]
+    assert ((got.double() - want)[large, 200].abs() <= 1e-6 * want[large, 200].abs()).all()
+
+
+@pytest.mark.parametrize("x_scale,dy_scale", [(1e-33, 1.0), (1.0, 1e-34), (1e-18, 1e-19), (1e30, 1e-36), (1e18, 1e18)])      # (the last: sums of 1e37, a tenth of the largest fp32)
+def test_far_from_one(x_scale, dy_scale):
+    got, want, _ = product(*layer(700, 1024, 1024, x_scale, dy_scale), 0.8)
+    err = ((got.double() - want).norm() / want.norm()).item()
+    print("thirds far", x_scale, dy_scale, "%.2e" % err, flush=True)
+    assert err < 4e-7                              # the fp32 instruction's bound at 700 tokens, twice over
