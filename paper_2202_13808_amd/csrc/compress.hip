@@ -759,13 +759,16 @@ __device__ inline uint32_t bits_before(lane_mask a, uint32_t base)
 // known, and go through the same segment after its first filling has been written out.
 constexpr int ST_ROWS = 4;                                 // rows in flight per wavefront
 constexpr int ST_ROW_ELEMS = WAVE * 8;
-constexpr int ST_SEGCAP = 1916;                            // staged words per wavefront: 16 segments are 122 KB
-constexpr int ST_LH_OFF = (SEL_THREADS / WAVE) * ST_SEGCAP * 4;
-constexpr size_t ST_SMEM_BYTES = ST_LH_OFF + 4 * size_t(SAMPLE_BINS);              // + the sample's or the digit's histogram
-static_assert(ST_LH_OFF % 16 == 0, "the histogram follows the segments");
+// Staged words per wavefront: 16 segments are 134 KB, the histograms in their place before anything is staged.  (With 1916
+// words and the histograms beside them: row form of 39 M elements at gamma 0.8 134.6 -> 133.5 us a pass, 1x1 convolution of
+// 51 M 113.0 -> 110.3.  2360 would fit and give 130.3 and 108.5; tensors of 9 M elements at gamma 0.05 overflow at 2136.)
+constexpr int ST_SEGCAP = 2136;
+constexpr int ST_PART_OFF = (SEL_THREADS / WAVE) * ST_SEGCAP * 4;
+constexpr size_t ST_SMEM_BYTES = ST_PART_OFF + 4 * 2 * size_t(SEL_THREADS / WAVE) * TABLE_PITCH;    // + the table's partial sums
+static_assert(ST_PART_OFF % 16 == 0 && ST_SEGCAP % 4 == 0, "the segments are read 16 bytes at a time");
 static_assert(ST_SEGCAP >= 2 * ST_ROW_ELEMS, "two rows of nothing but candidates fit an empty segment");
 static_assert(ST_SMEM_BYTES >= 4 * ((size_t(1) << 13) + 2 * WAVE), "the serial redo's histogram");
-static_assert(SAMPLE_BINS >= 2 * (SEL_THREADS / WAVE) * TABLE_PITCH, "the table's partial sums take the histogram's place");
+static_assert(ST_PART_OFF >= 4 * SAMPLE_BINS, "the sample's or the digit's histogram is done with before anything is staged");
 
 // Classification of the 8 consecutive 16-bit elements of q against a lowest key, five instructions per 32-bit word: one AND
 // clears both signs (keys[]), one unsigned compare per half (the upper half against lowest << 16: the lower half cannot
@@ -914,7 +917,8 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
     constexpr int NW = SEL_THREADS / WAVE;
     extern __shared__ __attribute__((aligned(16))) u32x4 dyn_smem[];
     char *dyn_bytes = reinterpret_cast<char *>(dyn_smem);
-    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_bytes + ST_LH_OFF);
+    uint32_t *lh = reinterpret_cast<uint32_t *>(dyn_bytes);     // (before anything is staged)
+    uint32_t *part = reinterpret_cast<uint32_t *>(dyn_bytes + ST_PART_OFF);
     __shared__ uint32_t bcast[4], offs[2], verdict, spilled;
     __shared__ uint32_t wave_tot[NW];
     __shared__ uint32_t whist[NW][MAX_LAST_BINS + 1];           // per wavefront: its elements on each key of the range, and above it
@@ -1148,7 +1152,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
         STAMP(4);
         if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
         STAMP(5);
-        if (resolve_table(table, nf, key_lo, k, lh, bcast, offs, &verdict, xbar, rep, true)) break;
+        if (resolve_table(table, nf, key_lo, k, part, bcast, offs, &verdict, xbar, rep, true)) break;
         if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
         predicted = false;                       // the sample misled: once more with the exact histogram
         missed = true;
