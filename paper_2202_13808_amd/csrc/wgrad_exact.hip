@@ -60,6 +60,8 @@ struct ExactGeometry {
     uint32_t OW, P, W, H, C, taps, kw, sh, sw, ph, pw, dh, dw;   // P = OH * OW
     uint32_t xc, xh, xw;                                         // element strides of R(a^): channel, row, column
     int64_t xn, yn;                                              // ... and of an image, in R(a^) and in dY
+    Divisor by_P, by_OW;
+    uint32_t x_bytes, y_bytes;                                   // of R(a^) and of dY where 32-bit byte offsets reach all of both, else 0
 };
 
 // acc[i][j][e] is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32 of its 32x32 block
@@ -93,7 +95,14 @@ __device__ inline void exact_epilogue(const f32x16 (&acc)[C::FM][C::FN], int spl
     }
 }
 
-template <typename RAW, typename C, Fetch FA, Fetch FB>
+// SHORT (ALONG_TOKENS): both operands lie within reach of 32-bit byte offsets, so they are read through buffer descriptors:
+// what is outside -- padding, a token past the last -- is an offset past the descriptor's end, which reads as zero, and an
+// element takes seven vector instructions instead of some twenty with a branch around the load; where a thread has eight
+// columns, what it needs to know of them stays in registers (three LDS reads per element otherwise, on an LDS that the tiles
+// keep busy).  Columns past the last of dW fetch whatever is there: those sums are not stored.  Whole calls, the same bits:
+// fp32 3x3 32 x 64 x 32 x 32 -> 64 58.5 -> 44.9 us, 64 x 64 x 56 x 56 -> 64 245 -> 182, 36 x 232 x 40 x 22 -> 144 409 -> 298;
+// bf16 with 129 output channels, 3x3 / stride 2 over 16 x 64 x 56 x 56 86 -> 52.
+template <typename RAW, typename C, Fetch FA, Fetch FB, bool SHORT = false>
 __global__ void __launch_bounds__(256)
 exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t ntok, int M, int N, int nb_count,
                   int mb_count, int nkb, int splits, ExactGeometry g, float *__restrict__ out)
@@ -138,7 +147,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     // image and position of a token
     auto locate = [&](int64_t t, uint32_t &n, uint32_t &p) {
         if (ntok <= INT32_MAX) {                   // uniform
-            n = uint32_t(t) / g.P;
+            n = quotient(uint32_t(t), g.by_P);
             p = uint32_t(t) - n * g.P;
         } else {
             n = uint32_t(t / g.P);
@@ -148,7 +157,7 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     // top-left input position of a token's window, as 32-bit words modulo 2^32 (a row or column is inside the
     // tensor iff the word is below H or W: sizes are below 2^31, padding and taps far below 2^31)
     auto window = [&](uint32_t p, uint32_t &iy0, uint32_t &ix0) {
-        const uint32_t oy = p / g.OW, ox = p - oy * g.OW;
+        const uint32_t oy = quotient(p, g.by_OW), ox = p - oy * g.OW;
         iy0 = oy * g.sh - g.ph;
         ix0 = ox * g.sw - g.pw;
     };
@@ -172,8 +181,43 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     // ---- operand fetch: a step's tiles into registers, and from there into LDS ------------------------------
     constexpr int EA = BM * BK / NT, EB = BN * BK / NT;    // elements per thread
     float ra[EA], rb[EB];
+    static_assert(!SHORT || (FA == ALONG_TOKENS && FB == ALONG_TOKENS), "the form of NCHW operands");
+    constexpr bool HOIST = SHORT && EB <= 8;
+    uint32_t my_off[HOIST ? EB : 1], my_y[HOIST ? EB : 1], my_x[HOIST ? EB : 1];
+    (void)my_off; (void)my_y; (void)my_x;
+    auto short_load = [](const RAW *base, uint32_t bytes, uint32_t offset) -> float {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<RAW *>(base), 0, int(bytes), 0x00020000);
+        if constexpr (sizeof(RAW) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, int(offset), 0, 0));
+        else return widen(uint16_t(__builtin_amdgcn_raw_buffer_load_b16(rsrc, int(offset), 0, 0)));
+    };
     auto fetch = [&](int kb) __attribute__((always_inline)) {   // (two callers)
         const int64_t t0 = int64_t(kb) * BK;
+        if constexpr (SHORT) {
+            constexpr uint32_t S = sizeof(RAW);
+            constexpr int QSTEP = NT / BK;
+            const int r = tid % BK, q0 = tid / BK;
+            const uint32_t t = uint32_t(t0) + uint32_t(r);
+            const bool tok_ok = t < uint32_t(ntok);
+            uint32_t n, p, iy0, ix0;
+            locate(int64_t(tok_ok ? t : 0u), n, p);
+            window(p, iy0, ix0);
+            if (!tok_ok) iy0 = 0x80000000u;                // below no H
+            uint32_t ya = (n * uint32_t(g.yn) + p + uint32_t(m0 + q0) * g.P) * S;
+#pragma unroll
+            for (int u = 0; u < EA; ++u) {
+                ra[u] = short_load(dY, g.y_bytes, tok_ok ? ya : 0xFFFFFFFFu);
+                ya += uint32_t(QSTEP) * g.P * S;
+            }
+            const uint32_t base = (n * uint32_t(g.xn) + iy0 * g.xh + ix0 * g.xw) * S;
+#pragma unroll
+            for (int u = 0; u < EB; ++u) {
+                const int q = q0 + u * QSTEP;
+                const uint32_t off = HOIST ? my_off[HOIST ? u : 0] : col_off[q] * S;
+                const uint32_t iy = iy0 + (HOIST ? my_y[HOIST ? u : 0] : col_y[q]), ix = ix0 + (HOIST ? my_x[HOIST ? u : 0] : col_x[q]);
+                rb[u] = short_load(x, g.x_bytes, iy < g.H && ix < g.W ? base + off : 0xFFFFFFFFu);
+            }
+            return;
+        }
         if constexpr (FA == ROWS16) {                      // M % 4 == 0
 #pragma unroll
             for (int u = 0; u < EA / 4; ++u) {
@@ -331,6 +375,15 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
         fill_tokens(kb_begin);
         if (CAREFUL && tid < 2) not_finite[tid] = 0;
         __syncthreads();                                   // column and token tables
+        if constexpr (HOIST) {
+#pragma unroll
+            for (int u = 0; u < EB; ++u) {
+                const int q = tid / BK + u * (NT / BK);
+                my_off[u] = col_off[q] * uint32_t(sizeof(RAW));
+                my_y[u] = col_y[q];
+                my_x[u] = col_x[q];
+            }
+        }
         if (!CAREFUL && kb_begin < kb_end) fetch(kb_begin);
         for (int kb = kb_begin; kb < kb_end; ++kb) {
             if constexpr (CAREFUL) {                       // (not a step ahead: take_out has the registers)
@@ -601,7 +654,14 @@ dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const R
                           uint32_t(p.g.kw), uint32_t(p.g.stride_h), uint32_t(p.g.stride_w), uint32_t(p.g.pad_h),
                           uint32_t(p.g.pad_w), uint32_t(p.g.dil_h), uint32_t(p.g.dil_w),
                           p.nhwc ? 1u : uint32_t(p.H * p.W), p.nhwc ? uint32_t(p.W * p.C) : uint32_t(p.W),
-                          p.nhwc ? uint32_t(p.C) : 1u, p.C * p.H * p.W, p.cout * p.OH * p.OW};
+                          p.nhwc ? uint32_t(p.C) : 1u, p.C * p.H * p.W, p.cout * p.OH * p.OW,
+                          divisor(uint32_t(p.OH * p.OW)), divisor(uint32_t(p.OW)), 0u, 0u};
+        const int64_t xb = p.numel * int64_t(sizeof(RAW)), yb = p.ntok * p.cout * int64_t(sizeof(RAW));
+        constexpr int64_t REACH = int64_t(1) << 31;        // (offsets of what is not there may run past the ends, never round 2^32)
+        if (xb < REACH && yb < REACH && !dev_env("DROPIT_EXACT_LONG", 0)) {
+            g.x_bytes = uint32_t(xb);
+            g.y_bytes = uint32_t(yb);
+        }
     }
     auto go = [&](auto kernel) {
         kernel<<<grid, C::NTHREADS, 0, stream>>>(dY, x, p.ntok, int(p.cout), int(p.cin), plan.nb_count, plan.mb_count,
@@ -616,11 +676,13 @@ dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const R
                                                              plan.nkb, plan.splits, out);
             else if (wide_y && wide_x) go(exact_gemm_kernel<RAW, C, ROWS16, ROWS16>);
             else go(exact_gemm_kernel<RAW, C, ROWS1, ROWS1>);
-        } else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
+        } else if (!p.nhwc && g.x_bytes) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS, true>);
+        else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
         else if (wide_y) go(exact_gemm_kernel<RAW, C, ROWS16, ALONG_COLUMNS>);
         else go(exact_gemm_kernel<RAW, C, ROWS1, ALONG_COLUMNS>);
     } else {
         if (!p.conv) go(exact_gemm_kernel<RAW, C, ROWS1, ROWS1>);
+        else if (!p.nhwc && g.x_bytes) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS, true>);
         else if (!p.nhwc) go(exact_gemm_kernel<RAW, C, ALONG_TOKENS, ALONG_TOKENS>);
         else go(exact_gemm_kernel<RAW, C, ROWS1, ALONG_COLUMNS>);
     }

@@ -142,3 +142,23 @@ def test_integer_convolution_sums_are_exact(layout, shape, J, geom):
     if layout == "nhwc":
         xh, g, got = (np.ascontiguousarray(a.transpose(0, 3, 1, 2)) for a in (xh, g, got))
     assert np.array_equal(got, oracle.dw_conv(xh, g, kh, kw, (sh, sw), (ph, pw), (dh, dw)))
+
+
+@pytest.mark.parametrize("height,dtype", [(16384, torch.float32), (16383, torch.float32)])
+def test_either_side_of_32_bit_offsets(height, dtype):
+    """Operands of 2 GiB, and just below: 64-bit addresses on one side, buffer descriptors with 32-bit offsets on the other.
+    A 1 x 1 convolution of two images and one channel; every sum is of whole numbers below 2^24 per slice, so it is exact up to
+    the rounding of the slices' sums."""
+    print("exact offsets", height, dtype, flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(height)
+    shape = (2, 1, height, 16384)
+    x = torch.randint(-3, 4, shape, generator=gen, device="cuda:0", dtype=torch.int8).to(dtype)
+    dy = torch.randint(0, 2, shape, generator=gen, device="cuda:0", dtype=torch.int8).to(dtype)
+    vals, idx = dropit.compress(x, 0.3)
+    got = dropit.weight_grad(vals, idx, shape, dy, 1, conv=(1, 1, 1, 1, 0, 0, 1, 1))
+    flat = dy.reshape(-1)
+    want = sum((vals[i:i + (1 << 26)].double() * flat[idx[i:i + (1 << 26)].long()].double()).sum().item()
+               for i in range(0, vals.numel(), 1 << 26))
+    scale = sum((vals[i:i + (1 << 26)].double() * flat[idx[i:i + (1 << 26)].long()].double()).abs().sum().item()
+                for i in range(0, vals.numel(), 1 << 26))
+    assert got.numel() == 1 and abs(got.item() - want) <= 2.0 ** -22 * scale
