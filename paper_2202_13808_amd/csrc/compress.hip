@@ -38,6 +38,7 @@
 // fp32, digit histograms of the whole tensor -> sample, staged candidates and the threshold's bin as a list (gamma 0.9):
 //   0.07 M elements 24.1 -> 17.1 us, 0.6 M 26.9 -> 18.9, 2.4 M 33.9 -> 21.3, 8.4 M 47.4 -> 25.2, 50 M 152.6 -> 88.8.
 #include "common.hpp"
+#include "wgrad_internal.hpp"
 #include "dev_hooks.hpp"
 #include <atomic>
 #include <cstdlib>
@@ -905,11 +906,137 @@ __device__ inline bool resolve_table(const uint32_t *table, uint32_t nf, uint32_
     return *verdict != 0;
 }
 
+// ---- the cheaper index forms straight from the output phase (16-bit element types) -------------------
+// FORM_ROWS: 16-bit positions within rows of `len` elements instead of flat indices; FORM_MASK: a bit per element.  Both with
+// starts[r] = number of kept elements before element r * len.  A wavefront owns a contiguous range of the tensor, so it owns
+// the starts and the mask words in it (ranges begin at multiples of 64 elements), and it meets its kept elements in flat order.
+// Against writing flat indices and converting them in a kernel of its own (two for the mask): row form of 39 M elements at
+// gamma 0.8, pass EMIT_ROWS; mask of 9.7 M at 0.9, call EMIT_MASK.
+struct FormArgs {
+    uint16_t *col;
+    uint32_t *mask;
+    int32_t *starts;
+    Divisor len;
+    uint32_t nstarts;                                      // entries of starts but the closing one, which is k
+};
+
+// One wavefront's state while it walks its kept elements.
+template <int FORM>
+struct FormWriter {
+    FormArgs a;
+    uint32_t last_row;         // row of the last kept element; rows up to it have their starts (uniform)
+    uint32_t word, bits;       // FORM_MASK: the word that is being filled (uniform)
+    uint32_t *window;          // ... and 256 words of LDS of the wavefront's own
+
+    __device__ void begin(const FormArgs &args, uint32_t first, uint32_t *lds)
+    {
+        a = args;
+        // the rows that start at `first` or later are this wavefront's
+        last_row = first == 0 ? 0xFFFFFFFFu : quotient(first - 1, a.len);       // (-1: compared as last_row + 1)
+        word = first >> 5;
+        bits = 0;
+        window = lds;
+    }
+    // the lanes of `kept`, in lane order: element `flat` goes to output slot `slot`
+    __device__ void elements(bool kept, lane_mask b, uint32_t flat, uint32_t slot, uint32_t k)
+    {
+        if (b == 0) return;
+        const int lane = threadIdx.x & (WAVE - 1);
+        const uint32_t row = quotient(flat, a.len);
+        const lane_mask lower = b & ((lane_mask(1) << lane) - 1);
+        const int src = lower ? 63 - __builtin_clzll(lower) : 0;
+        uint32_t prev = uint32_t(__builtin_amdgcn_ds_bpermute(src * 4, int(row)));
+        prev = lower ? prev : last_row;
+        if (kept && slot < k) {                            // (always, for consistent counts)
+            if constexpr (FORM == FORM_ROWS) a.col[slot] = static_cast<uint16_t>(flat - row * a.len.d);
+            for (uint32_t r = prev + 1; r <= row && r < a.nstarts; ++r) a.starts[r] = static_cast<int32_t>(slot);
+        }
+        last_row = uint32_t(__builtin_amdgcn_readlane(int(row), 63 - __builtin_clzll(b)));
+    }
+    // FORM_MASK: the bits of up to 4 x 64 kept elements, in flat order (flat[u] where kept[u])
+    __device__ void mask_batch(const bool (&kept)[4], const uint32_t (&flat)[4])
+    {
+        const int lane = threadIdx.x & (WAVE - 1);
+        uint32_t top = 0;                                  // the last kept element's word
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const lane_mask b = __ballot(kept[u]);
+            if (b) top = uint32_t(__builtin_amdgcn_readlane(int(flat[u]), 63 - __builtin_clzll(b))) >> 5;
+        }
+        top = max(top, word);
+        for (;;) {                                         // windows of 256 words; one, unless little is kept
+            u32x4 zero = {0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4 *>(window + lane * 4) = zero;
+            asm volatile("" ::: "memory");
+            if (lane == 0) window[0] = bits;
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t at = (flat[u] >> 5) - word;
+                if (kept[u] && at < 256u) atomicOr(&window[at], 1u << (flat[u] & 31u));
+            }
+            asm volatile("" ::: "memory");
+            const bool more = top - word >= 256u;
+            const uint32_t done = more ? 256u : top - word;                    // whole words
+            for (uint32_t i = lane; i < done; i += WAVE) a.mask[word + i] = window[i];
+            if (!more) {
+                bits = uint32_t(__builtin_amdgcn_readfirstlane(int(window[done])));
+                word = top;
+                break;
+            }
+            word += 256u;
+            bits = 0;
+        }
+    }
+    // the range ends before element `end`, `slot` elements have been kept before it
+    __device__ void finish(uint32_t end, uint32_t slot)
+    {
+        const uint32_t lane = threadIdx.x & (WAVE - 1);
+        const uint32_t stop = min(quotient(end - 1, a.len) + 1, a.nstarts);      // rows that start before `end`
+        for (uint32_t r = last_row + 1 + lane; r < stop; r += WAVE) a.starts[r] = static_cast<int32_t>(slot);
+        if constexpr (FORM == FORM_MASK)
+            for (uint32_t w = word + lane; w < (end + 31) >> 5; w += WAVE) a.mask[w] = w == word ? bits : 0u;
+    }
+};
+
+// The forms from the pairs the serial redo has written (one workgroup; every word and start written whole).
+template <int FORM>
+__device__ inline void forms_from_pairs(const int32_t *idx, int64_t numel, uint32_t k, const FormArgs &a)
+{
+    auto before = [&](uint32_t flat) {                     // pairs before element `flat`
+        uint32_t lo = 0, hi = k;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (static_cast<uint32_t>(idx[mid]) < flat) lo = mid + 1; else hi = mid;
+        }
+        return lo;
+    };
+    for (uint32_t r = threadIdx.x; r <= a.nstarts; r += SEL_THREADS)
+        a.starts[r] = static_cast<int32_t>(r < a.nstarts ? before(r * a.len.d) : k);
+    if constexpr (FORM == FORM_ROWS) {
+        for (uint32_t j = threadIdx.x; j < k; j += SEL_THREADS) {
+            const uint32_t flat = static_cast<uint32_t>(idx[j]);
+            a.col[j] = static_cast<uint16_t>(flat - quotient(flat, a.len) * a.len.d);
+        }
+    } else {
+        for (uint32_t w = threadIdx.x; w < (numel + 31) / 32; w += SEL_THREADS) {
+            uint32_t bits = 0;
+            for (uint32_t j = before(w * 32); j < k; ++j) {
+                const uint32_t at = static_cast<uint32_t>(idx[j]) - w * 32;
+                if (at >= 32u) break;
+                bits |= 1u << at;
+            }
+            a.mask[w] = bits;
+        }
+    }
+}
+
 // 16-bit element types.
+template <int FORM>
 __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k,
                                            SelState *st, uint32_t *hist0, uint32_t *table, uint16_t *__restrict__ vals,
                                            int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks,
-                                           ExitReport &rep)
+                                           ExitReport &rep, const FormArgs &form)
 {
     constexpr int VEC = 8;
     constexpr uint32_t MASK = KeyTraits<uint16_t>::MASK;
@@ -1186,9 +1313,11 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
     auto keep = [&](uint32_t pos, uint32_t raw, uint32_t i) {
         if (pos < k) {                     // always true for consistent counts
             vals[pos] = static_cast<uint16_t>(raw);
-            idx[pos] = static_cast<int32_t>(i);
+            if constexpr (FORM == FORM_FLAT) idx[pos] = static_cast<int32_t>(i);
         }
     };
+    FormWriter<FORM> writer;               // (its window: the first 256 staged words, which are in registers by the time it is used)
+    if constexpr (FORM != FORM_FLAT) writer.begin(form, static_cast<uint32_t>(wv0 * VEC), seg);
     // All or none of this wavefront's keys equal to t are kept, except in the one wavefront where the budget runs out.
     const uint32_t wave_eq = uint32_t(__builtin_amdgcn_readlane(int(e), wave));
     const bool split = my_eq < m && my_eq + wave_eq > m;
@@ -1202,30 +1331,47 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
             uint32_t w[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) w[j] = q0 + j * WAVE + lane < n_w ? seg[q0 + j * WAVE + lane] : 0u;
+            [[maybe_unused]] bool in[4];
+            [[maybe_unused]] uint32_t at[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t key = (w[j] >> 16) & MASK;
+                const uint32_t key = (w[j] >> 16) & MASK, flat = flat0 + (w[j] & 0xFFFFu);
                 const bool there = q0 + j * WAVE + lane < n_w;
+                bool kept;
+                uint32_t slot;
                 if (!split) {              // uniform over the wavefront
-                    const bool kept = there && key >= least;
+                    kept = there && key >= least;
                     const lane_mask b = __ballot(kept);
-                    if (kept) keep(bits_before(b, my_slot), w[j] >> 16, flat0 + (w[j] & 0xFFFFu));
+                    slot = bits_before(b, my_slot);
+                    if (kept) keep(slot, w[j] >> 16, flat);
                     my_slot += __builtin_popcountll(b);
                 } else {
                     const bool gt = there && key > t, eq = there && key == t;
                     const lane_mask bg = __ballot(gt), be = __ballot(eq);
                     const uint32_t eb = bits_before(be, my_eq), gb = bits_before(bg, my_gt);
-                    if (gt || (eq && eb < m)) keep(gb + min(eb, m), w[j] >> 16, flat0 + (w[j] & 0xFFFFu));
+                    kept = gt || (eq && eb < m);
+                    slot = gb + min(eb, m);
+                    if (kept) keep(slot, w[j] >> 16, flat);
                     my_gt += __builtin_popcountll(bg);
                     my_eq += __builtin_popcountll(be);
                 }
+                if constexpr (FORM != FORM_FLAT) {
+                    writer.elements(kept, __ballot(kept), flat, slot, k);
+                    in[j] = kept;
+                    at[j] = flat;
+                }
             }
+            if constexpr (FORM == FORM_MASK) writer.mask_batch(in, at);
         }
         if (staged_rows >= nrows) break;
         first = staged_rows;               // the rows that did not fit: read again, only what is kept is staged now
         staged_rows = stage_rows(t, first, n_w);
     }
     STAMP(7);
+    if constexpr (FORM != FORM_FLAT) {     // (numel is a multiple of eight: no ragged end)
+        if (wvecs > 0) writer.finish(static_cast<uint32_t>(wv1 * VEC), split ? my_gt + min(my_eq, m) : my_slot);
+        if (last_chunk && tid == 0) form.starts[form.nstarts] = static_cast<int32_t>(k);
+    }
     if (last_chunk && tid == 0) {
         uint32_t run_gt = chunk_gt, run_eq = chunk_eq;
         for (int64_t i = nvf * VEC; i < numel; ++i) {
@@ -2280,17 +2426,17 @@ select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k
     }
 }
 
-template <typename RAW>
+template <typename RAW, int FORM = FORM_FLAT>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vpc, uint32_t k, SelState *st,
                     uint32_t *hist0, uint32_t *hist1, uint32_t *table, RAW *__restrict__ vals,
-                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks)
+                    int32_t *__restrict__ idx, uint32_t spin_limit, unsigned long long gen, SampleRanks ranks, FormArgs form)
 {
     ExitReport rep;
     rep.mine = 0u;
     SelOutcome outcome;
     if constexpr (sizeof(RAW) == 2)
-        outcome = select16_body(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, ranks, rep);
+        outcome = select16_body<FORM>(x, numel, nvf, vpc, k, st, hist0, table, vals, idx, spin_limit, gen, ranks, rep, form);
     else
         outcome = select32_body(x, numel, nvf, vpc, k, st, hist0, hist1, table, vals, idx, spin_limit, gen, ranks, rep);
     // Exit protocol: every workgroup reports once, when it is past its last grid barrier or gives up at one (the high
@@ -2325,8 +2471,14 @@ select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64
         s_redo = redo ? 1u : 0u;
     }
     __syncthreads();
-    if (s_redo)
+    if (s_redo) {
         select_serial<RAW>(x, numel, nvf, k, vals, idx, reinterpret_cast<uint32_t *>(dyn_smem), s_wave_tot, s_bcast);
+        if constexpr (FORM != FORM_FLAT) {
+            __threadfence_block();         // the pairs of the workgroup's own threads
+            __syncthreads();
+            forms_from_pairs<FORM>(idx, numel, k, form);
+        }
+    }
 }
 
 // ---- random dropping (Sec. 3.3, Random Elements) ------------------------------------------------
@@ -2421,9 +2573,10 @@ unsigned long long next_generation()
     return g ? g : counter.fetch_add(1) + 1;
 }
 
-template <typename RAW>
+// FORM other than FORM_FLAT: what `form` names, by the persistent kernel (form_emitted says where that is), idx being scratch.
+template <typename RAW, int FORM = FORM_FLAT>
 dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, int32_t *idx,
-                           char *ws, hipStream_t stream)
+                           char *ws, hipStream_t stream, const FormArgs &form = FormArgs{})
 {
     const Geometry g = geometry<RAW>(numel);
     SelState *st = reinterpret_cast<SelState *>(ws + SelWorkspace::state_off);
@@ -2446,7 +2599,7 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
     // only up to 32 K elements where the persistent kernel can predict the threshold: it takes 11.1 to 11.5 us from there to
     // 128 K, this form 10.5 (gamma 0.9) or 15.6 (0.6) at 32 K and 15 or 25 at 64 K.
     const int64_t nvec = numel / KeyTraits<RAW>::VEC;
-    if (mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS &&
+    if (FORM == FORM_FLAT && mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS &&
         (sizeof(RAW) == 4 || nvec <= SMALL_VECTORS / 2 * SEL_THREADS || spread.lo == 0.0f)) {
         trace_mark(stream);
         const int vectors = int(nvec);
@@ -2489,10 +2642,10 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
             hipDeviceProp_t prop;
             int per_cu = 0;
             if (hipGetDeviceProperties(&prop, dev) == hipSuccess &&
-                hipFuncSetAttribute(reinterpret_cast<const void *>(select_fused_kernel<RAW>),
+                hipFuncSetAttribute(reinterpret_cast<const void *>(select_fused_kernel<RAW, FORM>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(smem_bytes)) == hipSuccess &&
-                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_fused_kernel<RAW>, SEL_THREADS,
+                hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, select_fused_kernel<RAW, FORM>, SEL_THREADS,
                                                              smem_bytes) == hipSuccess &&
                 per_cu > 0 && prop.multiProcessorCount > 0)
                 fresh = std::min(per_cu * prop.multiProcessorCount, SEL_MAX_CHUNKS);
@@ -2512,12 +2665,13 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
             RAW *vals_t = static_cast<RAW *>(vals);
             unsigned long long gen = next_generation();
             SampleRanks ranks = spread;
+            FormArgs form_t = form;
             trace_mark(stream);
             if (mode == 2) {               // the runtime guarantees co-residency, at the price of slow queue switches
                 void *args[] = {(void *)&xr, (void *)&numel, (void *)&nvf, (void *)&vpc, (void *)&k32, (void *)&st,
                                 (void *)&hist0, (void *)&hist1, (void *)&table, (void *)&vals_t, (void *)&idx,
-                                (void *)&spin_limit, (void *)&gen, (void *)&ranks};
-                if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(select_fused_kernel<RAW>),
+                                (void *)&spin_limit, (void *)&gen, (void *)&ranks, (void *)&form_t};
+                if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(select_fused_kernel<RAW, FORM>),
                                                dim3(static_cast<unsigned>(chunks)), dim3(SEL_THREADS), args,
                                                smem_bytes, stream) == hipSuccess) {
                     trace_mark(stream);
@@ -2525,12 +2679,13 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
                 }
                 (void)hipGetLastError();   // cooperative launch unavailable (e.g. stream capture): ordinary launch
             }
-            select_fused_kernel<RAW><<<dim3(static_cast<unsigned>(chunks)), dim3(SEL_THREADS), smem_bytes, stream>>>(
-                xr, numel, nvf, vpc, k32, st, hist0, hist1, table, vals_t, idx, spin_limit, gen, ranks);
+            select_fused_kernel<RAW, FORM><<<dim3(static_cast<unsigned>(chunks)), dim3(SEL_THREADS), smem_bytes, stream>>>(
+                xr, numel, nvf, vpc, k32, st, hist0, hist1, table, vals_t, idx, spin_limit, gen, ranks, form_t);
             trace_mark(stream);
             return launch_status();
         }
     }
+    if constexpr (FORM != FORM_FLAT) return DROPIT_EUNSUPPORTED;     // (the caller converts flat indices)
     clear_state();
     const dim3 grid(g.chunks), block(SEL_THREADS);
     trace_mark(stream);
@@ -2554,6 +2709,20 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
 
 }  // namespace
 }  // namespace dropit
+
+// The select with one of the cheaper index forms as its output, idx being scratch of k words.  DROPIT_EUNSUPPORTED, and nothing
+// done, where it has to write flat indices: fp32, tensors of one workgroup, a ragged end, separate kernels.
+dropit_status dropit::compress_form(const void *x, int64_t numel, dropit_dtype dt, int64_t k, void *vals, int32_t *idx, int kind,
+                                    uint16_t *col, uint32_t *mask, int32_t *starts, uint32_t len, int64_t nstarts, char *ws,
+                                    hipStream_t stream)
+{
+    if (dt != DROPIT_BF16 || numel % 8 != 0 || k < 1 || select_mode() == 1) return DROPIT_EUNSUPPORTED;
+    if (numel <= int64_t(SMALL_VECTORS) * SEL_THREADS * 8 || x == nullptr || !aligned(x, 16) || vals == nullptr || !aligned(vals, 2))
+        return DROPIT_EUNSUPPORTED;                        // (dropit_compress says what is wrong)
+    const FormArgs form = {col, mask, starts, divisor(len), uint32_t(nstarts)};
+    return kind == FORM_ROWS ? run_compress<uint16_t, FORM_ROWS>(x, numel, k, vals, idx, ws, stream, form)
+                             : run_compress<uint16_t, FORM_MASK>(x, numel, k, vals, idx, ws, stream, form);
+}
 
 dropit::TraceState &dropit::trace_state()
 {

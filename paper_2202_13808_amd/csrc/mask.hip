@@ -121,9 +121,12 @@ extern "C" dropit_status dropit_compress_mask(const void *x, const int64_t *shap
     if (workspace_bytes < dropit_compress_mask_workspace_bytes(numel, k, dt)) return DROPIT_EWORKSPACE;
     const size_t select_bytes = round_up(dropit_compress_workspace_bytes(numel, dt), 256);
     int32_t *idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + select_bytes);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const dropit_status direct = compress_form(x, numel, dt, k, vals, idx, FORM_MASK, nullptr, mask, blockptr, MASK_BLOCK,
+                                               mask_blocks(numel), static_cast<char *>(workspace), stream);
+    if (direct != DROPIT_EUNSUPPORTED) return direct;
     const dropit_status st = dropit_compress(x, shape, ndim, dt, gamma, vals, idx, workspace, select_bytes, hip_stream);
     if (st != DROPIT_OK) return st;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     mask_zero_kernel<<<grid_for(mask_words(numel)), 256, 0, stream>>>(mask, mask_words(numel));
     mask_from_idx_kernel<<<grid_for(k + 1), 256, 0, stream>>>(idx, k, numel, mask_blocks(numel), mask, blockptr);
     trace_mark(stream);

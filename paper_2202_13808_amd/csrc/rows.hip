@@ -126,9 +126,12 @@ extern "C" dropit_status dropit_compress_rows(const void *x, const int64_t *shap
     if (workspace_bytes < dropit_compress_rows_workspace_bytes(rs.numel, k, dt)) return DROPIT_EWORKSPACE;
     const size_t select_bytes = round_up(dropit_compress_workspace_bytes(rs.numel, dt), 256);
     int32_t *idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + select_bytes);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const dropit_status direct = compress_form(x, rs.numel, dt, k, vals, idx, FORM_ROWS, col, nullptr, rowptr,
+                                               static_cast<uint32_t>(rs.row_len), rs.rows, static_cast<char *>(workspace), stream);
+    if (direct != DROPIT_EUNSUPPORTED) return direct;
     const dropit_status st = dropit_compress(x, shape, ndim, dt, gamma, vals, idx, workspace, select_bytes, hip_stream);
     if (st != DROPIT_OK) return st;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const Divisor len = divisor(static_cast<uint32_t>(rs.row_len));
     // Fewer than eight pairs per row (2 M rows of two, gamma 0.99: call 43.6 us with one pair to a thread and two divisions,
     // 94.2 with eight, 35.6 now), or too few pairs for eight to a thread to fill the chip.

@@ -95,6 +95,12 @@ dropit_status conv_window_recover(const ConvWindow &w, int64_t N, const void *va
 dropit_status conv_window_gemm(const FcProblem &p, const FcDensePlan &plan, const ConvWindow &w, const void *dY,
                                const uint16_t *xd, float *partial, float *dW, hipStream_t stream);
 
+// dropit_compress with a cheaper index form as its output (compress.hip); DROPIT_EUNSUPPORTED: convert flat indices instead
+enum { FORM_FLAT = 0, FORM_ROWS = 1, FORM_MASK = 2 };
+dropit_status compress_form(const void *x, int64_t numel, dropit_dtype dt, int64_t k, void *vals, int32_t *idx, int kind,
+                            uint16_t *col, uint32_t *mask, int32_t *starts, uint32_t len, int64_t nstarts, char *ws,
+                            hipStream_t stream);
+
 // Row starts of the index-sorted pairs: row_ptr[r] = number of pairs whose flat index lies before row r, r = 0..R
 // (row_ptr[R] = k).  The tensor is a run of planes, a plane is cut into `nseg` rows of `seg` consecutive elements (the
 // last one may be shorter); one row per plane is the plain case of rows of equal length.  One pass over idx: every
