@@ -900,12 +900,14 @@ fc_bucket_kernel(const uint16_t *__restrict__ vals, const int32_t *__restrict__ 
 #define DROPIT_GEMM_CFG 256, 256, 32, 4, 2, 4, 2, 1
 #endif
 // Four wavefronts of 64 x 64, two workgroups per compute unit: half the rate of the wide tile at best (its fragments and
-// direct loads keep the LDS busy for 768 of the 512 cycles that its MFMAs need), but a quarter of the result: less padding,
+// direct loads keep the LDS busy for 768 cycles per token block and pair of workgroups where its MFMAs need 512), but a quarter of the result: less padding,
 // more workgroups where there are few tiles, and half the partial tiles where the whole chip works.  Which of the two a
-// product takes: choose_tile.  (Eight wavefronts of 32 x 64: the same time.  Three stages and three workgroups per compute
-// unit, or 128 x 256 and 256 x 128 tiles of four wavefronts with three stages: up to a fifth slower over 37 shapes.)
+// product takes: choose_tile.  Fragments are read behind the barrier (the other
+// workgroup covers it) rather than a block early, for one more block of loads in flight: 25216 x 384 -> 1152 43.1 -> 42.5 us a
+// call, 1 to 2 % over eight shapes.  (Eight wavefronts of 32 x 64, or five stages: the same time.  Three stages: 49.  128 x 256
+// and 256 x 128 tiles of four wavefronts with three stages: up to a fifth slower over 37 shapes.)
 #ifndef DROPIT_GEMM_CFG_SMALL
-#define DROPIT_GEMM_CFG_SMALL 128, 128, 32, 2, 2, 4, 2, 1
+#define DROPIT_GEMM_CFG_SMALL 128, 128, 32, 2, 2, 4, 2, 0
 #endif
 using Cfg = GemmCfg<DROPIT_GEMM_CFG>;
 using CfgSmall = GemmCfg<DROPIT_GEMM_CFG_SMALL>;
