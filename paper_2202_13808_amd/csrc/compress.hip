@@ -664,7 +664,7 @@ constexpr int SAMPLE_STRETCH = 4;                     // a piece starts at a mul
 constexpr int SAMPLE_PIECE = SEL_THREADS / SAMPLE_PIECES;   // ... and is this many vectors long: one vector per thread
 constexpr int SAMPLE_ELEMS = SEL_THREADS * 8;
 constexpr int64_t SAMPLE_LARGE = int64_t(1) << 21;    // from here on the state's `path` says how the prediction went
-constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 15;
+constexpr int64_t SAMPLE_MIN_NUMEL = int64_t(1) << 14;
 static_assert(SAMPLE_MIN_NUMEL / 8 / SAMPLE_STRETCH >= SAMPLE_PIECES, "a place per stretch at least");
 constexpr int SAMPLE_SHIFT = 3, SAMPLE_BINS = 1 << (15 - SAMPLE_SHIFT);    // 8 keys per bin
 constexpr int BRACKET_MAX_BINS = MAX_LAST_BINS >> SAMPLE_SHIFT;
@@ -2352,9 +2352,11 @@ select_small_kernel(const RAW *__restrict__ x, int numel, int nvf, uint32_t k, S
     }
 }
 
-// 16-bit tensors of one vector per thread: digit histograms over all elements (11 + 4 bits) are the shorter program, and at
-// this size fetching it and the barriers are all there is: 1 K elements 5.1 us against 6.9 in the form above, 8 K 6.3 against
-// 7.2; 16 K 8.9 against 8.6.
+// 16-bit tensors of PER consecutive vectors per thread: digit histograms over all elements (11 + 4 bits) are the shorter
+// program, and at this size fetching it and the barriers are all there is.  gamma 0.9 / 0.6, this form against the one above:
+// 8 K elements 5.5 / 6.4 us against 7.2 / 8.4, 11 K 6.9 / 8.1 against 8.3 / 9.7, 16 K 8.2 / 9.8 against 8.6 / 11.1.
+constexpr int ROW_VECTORS = 2 * SEL_THREADS;               // the largest it takes
+template <int PER>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k, uint16_t *__restrict__ vals,
                   int32_t *__restrict__ idx)
@@ -2366,9 +2368,13 @@ select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k
     __shared__ uint32_t bcast[2];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int ntail = numel - nvf * VEC;                             // the ragged end, in thread 0
-    const u32x4 q = tid < nvf ? reinterpret_cast<const u32x4 *>(x)[tid] : u32x4{0u, 0u, 0u, 0u};
+    u32x4 q[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) q[i] = tid * PER + i < nvf ? reinterpret_cast<const u32x4 *>(x)[tid * PER + i] : u32x4{0u, 0u, 0u, 0u};
     auto for_all = [&](auto f) {
-        if (tid < nvf) for_each_raw(uint16_t(0), q, [&](uint32_t raw, int) { f(raw); });
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (tid * PER + i < nvf) for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int) { f(raw); });
         if (tid == 0)
             for (int e = 0; e < ntail; ++e) f(x[nvf * VEC + e]);
     };
@@ -2397,12 +2403,14 @@ select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k
     pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 11>{});
     pass(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
     const uint32_t t = prefix, m = k_rem;                            // the threshold key and its tie budget
-    uint32_t cnt = 0;                                                // low 16 bits: #gt, high 16 bits: #eq (8192 elements at most)
-    if (tid < nvf)
-        for_each_raw(uint16_t(0), q, [&](uint32_t raw, int) {
-            const uint32_t key = raw & MASK;
-            cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
-        });
+    uint32_t cnt = 0;                                                // low 16 bits: #gt, high 16 bits: #eq (16384 elements at most)
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (tid * PER + i < nvf)
+            for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int) {
+                const uint32_t key = raw & MASK;
+                cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
+            });
     uint32_t total;
     const uint32_t before = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
     uint32_t my_gt = before & 0xFFFFu, my_eq = before >> 16;
@@ -2419,7 +2427,11 @@ select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k
         my_gt += gt ? 1u : 0u;
         my_eq += eq ? 1u : 0u;
     };
-    if (cnt) for_each_raw(uint16_t(0), q, [&](uint32_t raw, int e) { emit(raw, tid * VEC + e); });
+    if (cnt) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (tid * PER + i < nvf) for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int e) { emit(raw, (tid * PER + i) * VEC + e); });
+    }
     if (tid == 0) {
         my_gt = total & 0xFFFFu;
         my_eq = total >> 16;
@@ -2597,20 +2609,22 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
     const int mode = select_mode();
     const SampleRanks spread = numel >= SAMPLE_MIN_NUMEL ? sample_ranks(static_cast<uint32_t>(k), numel, SAMPLE_ELEMS) : SampleRanks{0.0f, 0.0f};
     // Small tensors (default mode only: the other modes are there to exercise the other forms): one workgroup.  16-bit ones
-    // only up to 32 K elements where the persistent kernel can predict the threshold: it takes 11.1 to 11.5 us from there to
-    // 128 K, this form 10.5 (gamma 0.9) or 15.6 (0.6) at 32 K and 15 or 25 at 64 K.
+    // above 32 K elements, or 16 K where more than a quarter is kept, only if the persistent kernel cannot predict the
+    // threshold: it takes 11.1 to 11.5 us from there to 128 K, this form 8.6 (gamma 0.9) or 11.0 (0.6) at 16 K, 10.5 or 15.6 at
+    // 32 K and 15 or 25 at 64 K.
     const int64_t nvec = numel / KeyTraits<RAW>::VEC;
-    if (FORM == FORM_FLAT && mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS &&
-        (sizeof(RAW) == 4 || nvec <= SMALL_VECTORS / 2 * SEL_THREADS || spread.lo == 0.0f)) {
+    const bool predictable = sizeof(RAW) == 2 && spread.lo != 0.0f && (nvec > SMALL_VECTORS / 2 * SEL_THREADS || 4 * k > numel);
+    if (FORM == FORM_FLAT && mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS && (!predictable || nvec <= ROW_VECTORS)) {
         trace_mark(stream);
         const int vectors = int(nvec);
         if constexpr (sizeof(RAW) == 2) {
-            if (vectors <= SEL_THREADS) {
-                select_row_kernel<<<1, SEL_THREADS, 0, stream>>>(xr, int(numel), vectors, static_cast<uint32_t>(k),
-                                                                 static_cast<RAW *>(vals), idx);
+            const auto row = [&](auto kernel) {
+                kernel<<<1, SEL_THREADS, 0, stream>>>(xr, int(numel), vectors, static_cast<uint32_t>(k), static_cast<RAW *>(vals), idx);
                 trace_mark(stream);
                 return launch_status();
-            }
+            };
+            if (vectors <= SEL_THREADS) return row(select_row_kernel<1>);
+            if (vectors <= ROW_VECTORS) return row(select_row_kernel<2>);
         }
         const SampleRanks ranks = vectors >= SMALL_SAMPLE_MIN ? sample_ranks(static_cast<uint32_t>(k), numel, vectors)
                                                               : SampleRanks{0.0f, 0.0f};
