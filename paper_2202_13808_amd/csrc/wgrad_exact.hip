@@ -443,10 +443,13 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
 // Two workgroups per compute unit, one converting while the other multiplies.  Whole call 6304 x 384 -> 1536 80 -> 59 us (the matrix
 // instructions of the product alone take 20), 6304 x 1536 -> 384 93 -> 74.5; two LDS stages and
 // one 256 x 128 workgroup of eight wavefronts 65, loads of four bytes instead of eight 68.
-// What the thirds cannot carry shows in the sums: an infinity, a NaN, or a value that rounds to infinity in bf16 makes one of
-// them not finite; and where the last third of a value is below the normal numbers (2^-126, taken as lost here) a sum of n
-// terms is off by n 2^-126 of the other operand's largest value.  A workgroup with a sum that is not finite, or not zero and
-// so small that this would be 2^-25 of it, does its slice again with the fp32 instruction.
+// What the thirds cannot carry shows in the sums and in the smallest elements: an infinity, a NaN, or a value that rounds to
+// infinity in bf16 makes a sum not finite; and where the last third of a value is below the normal numbers (2^-126, taken as
+// lost here), or a product of parts below the subnormal ones, a sum of n terms is off by n 2^-126 of the other operand's
+// largest value, n 2^-146 for the products.  A workgroup with a sum that is not finite, or so small that this would be 2^-25
+// of it, does its slice again with the fp32 instruction.  A sum that is exactly zero is most often one of no terms at all; it
+// counts as small where an element of the tiles but zero is below 2^-103, whose last third may be lost (below 2^-134 all
+// three are), or the product of the smallest two is, whose parts' products may be.
 constexpr int SPLIT_BM = 128, SPLIT_BN = 128;
 
 __device__ inline void split_thirds(float a, float b, uint32_t &p1, uint32_t &p2, uint32_t &p3)      // a in the lower halves
@@ -461,6 +464,20 @@ __device__ inline void split_thirds(float a, float b, uint32_t &p1, uint32_t &p2
     a -= __uint_as_float(p2 << 16);
     b -= __uint_as_float(p2 & 0xFFFF0000u);
     p3 = pack(a, b);
+}
+
+// largest over the 64 lanes, in every lane
+__device__ inline uint32_t wave_max(uint32_t v)
+{
+#define DROPIT_DPP_MAX(ctrl, row_mask) v = max(v, uint32_t(__builtin_amdgcn_update_dpp(int(v), int(v), ctrl, row_mask, 0xf, false)))
+    DROPIT_DPP_MAX(0x111, 0xf);   // row_shr:1, 2, 4, 8
+    DROPIT_DPP_MAX(0x112, 0xf);
+    DROPIT_DPP_MAX(0x114, 0xf);
+    DROPIT_DPP_MAX(0x118, 0xf);
+    DROPIT_DPP_MAX(0x142, 0xa);   // row_bcast:15, 31
+    DROPIT_DPP_MAX(0x143, 0xc);
+#undef DROPIT_DPP_MAX
+    return uint32_t(__builtin_amdgcn_readlane(int(v), WAVE - 1));
 }
 
 __global__ void __launch_bounds__(256, 2)
@@ -495,7 +512,8 @@ exact_split_kernel(const float *__restrict__ dY, const float *__restrict__ x, in
     // a step's tiles: lane = two columns, wavefront = 8 tokens, of dY and of R(a^)
     f32x2 ra[8], rb[8];
     // (columns past the last re-read the last two, those sums are not stored; tokens past the last are zero)
-    const int q = lane * 2, qm = min(m0 + q, M - 2), qn = min(n0 + q, N - 2);   // M and N are even
+    const int q = lane * 2;
+    int qm = min(m0 + q, M - 2), qn = min(n0 + q, N - 2);                       // M and N are even
     auto fetch = [&](int kb) {
         const int64_t t = int64_t(kb) * BK + wave * 8;
         const float *pa = dY + t * M + qm, *pb = x + t * N + qn;
@@ -518,15 +536,21 @@ exact_split_kernel(const float *__restrict__ dY, const float *__restrict__ x, in
     };
     auto unit = [](int c, int o) { return c * 64 + ((o ^ c ^ (c >> 2)) & 3) * 16; };      // of column c, tokens 8 o .. 8 o + 7
     float most_a = 0.f, most_b = 0.f;                                           // largest magnitudes of this thread's elements
-    auto most = [](float a, float b, float m) {
+    auto larger = [](float a, float b, float m) {
         asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a), "v"(b));
         return m;
+    };
+    uint32_t least_a = ~0u, least_b = ~0u;                                      // smallest ones but zero: twice the bits less one
+    auto smaller = [](float a, float b, uint32_t m) {
+        return min(min(m, (__float_as_uint(a) << 1) - 1u), (__float_as_uint(b) << 1) - 1u);
     };
     auto store = [&]() {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            most_a = most(ra[r][0], ra[r][1], most_a);
-            most_b = most(rb[r][0], rb[r][1], most_b);
+            most_a = larger(ra[r][0], ra[r][1], most_a);
+            most_b = larger(rb[r][0], rb[r][1], most_b);
+            least_a = smaller(ra[r][0], ra[r][1], least_a);
+            least_b = smaller(rb[r][0], rb[r][1], least_b);
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {                                           // dY, R(a^)
@@ -585,36 +609,46 @@ exact_split_kernel(const float *__restrict__ dY, const float *__restrict__ x, in
         for (int j = 0; j < C::FN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] += small[i][j][e];
-    // (a NaN is not the largest; it is in the sums)
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        most_a = __builtin_fmaxf(most_a, __shfl_xor(most_a, o, 64));
-        most_b = __builtin_fmaxf(most_b, __shfl_xor(most_b, o, 64));
-    }
-    __shared__ float most_of[2][4];
-    if (lane == 0) {
-        most_of[0][wave] = most_a;
-        most_of[1][wave] = most_b;
-    }
-    __syncthreads();
-    float both = 0.f;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-        both += __builtin_fmaxf(__builtin_fmaxf(most_of[h][0], most_of[h][1]), __builtin_fmaxf(most_of[h][2], most_of[h][3]));
-    const float lost = float((kb_end - kb_begin) * BK) * 0x1p-101f * both;      // n 2^-126 of them, times 2^25
-    bool odd = false;                                                           // a sum the thirds do not vouch for
+    // Does a sum need the fp32 instruction?  The extremes of the elements and of the sums, over the workgroup
+    uint32_t most_s = 0u, least_s = ~0u, zeros = ~0u;
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
         for (int j = 0; j < C::FN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float s = __builtin_fabsf(acc[i][j][e]);
-                odd |= !(s < __builtin_inff()) || (s < lost && s != 0.f);
+                const uint32_t twice = __float_as_uint(acc[i][j][e]) << 1;
+                most_s = max(most_s, twice);
+                least_s = min(least_s, twice - 1u);
+                zeros = min(zeros, twice);
             }
-    if (__syncthreads_or(odd)) {
+    __shared__ __attribute__((aligned(16))) uint32_t extremes[4][8];            // the largest of each, a row per wavefront
+    {
+        // (a NaN element is not the largest; it is in the sums)
+        const uint32_t mine[7] = {__float_as_uint(most_a), __float_as_uint(most_b), ~least_a, ~least_b, most_s, ~least_s, ~zeros};
+#pragma unroll
+        for (int h = 0; h < 7; ++h) {
+            const uint32_t m = wave_max(mine[h]);
+            if (lane == 0) extremes[wave][h] = m;
+        }
+    }
+    __syncthreads();
+    uint32_t most[7];
+#pragma unroll
+    for (int h = 0; h < 7; ++h) most[h] = max(max(extremes[0][h], extremes[1][h]), max(extremes[2][h], extremes[3][h]));
+    // (of elements and sums but zeros: infinity if there are none)
+    auto smallest = [](uint32_t inverted) { return inverted == 0u ? __builtin_inff() : __uint_as_float((~inverted >> 1) + 1u); };
+    const float least_y = smallest(most[2]), least_x = smallest(most[3]);
+    const bool tiny = least_y < 0x1p-103f || least_x < 0x1p-103f || least_y * least_x < 0x1p-103f;
+    // n 2^-126 of the operands, n 2^-146 of the products, times 2^25
+    const float lost = float((kb_end - kb_begin) * BK) * (0x1p-101f * (__uint_as_float(most[0]) + __uint_as_float(most[1])) + 0x1p-121f);
+    if (most[4] >= 0xFF000000u || smallest(most[5]) < lost || (tiny && most[6] == ~0u)) {      // uniform
         float *sA = reinterpret_cast<float *>(lds), *sB = sA + BK * C::PA;
         clear(acc);
+        int again = q;
+        asm volatile("" : "+v"(again));                                          // (no addresses kept for this through the other loop)
+        qm = min(m0 + again, M - 2);
+        qn = min(n0 + again, N - 2);
         for (int kb = kb_begin; kb < kb_end; ++kb) {
             fetch(kb);
             __syncthreads();

@@ -67,3 +67,44 @@ def test_far_from_one(x_scale, dy_scale):
     err = ((got.double() - want).norm() / want.norm()).item()
     print("thirds far", x_scale, dy_scale, "%.2e" % err, flush=True)
     assert err < 4e-7                              # the fp32 instruction's bound at 700 tokens, twice over
+
+
+def subnormal(rows, columns, seed):
+    """Values of a few hundred units of 2^-149, either sign: all three parts of the smaller ones are zero in bf16."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    bits = torch.randint(1, 1000, (rows, columns), generator=gen, device=DEV, dtype=torch.int32)
+    sign = torch.randint(0, 2, (rows, columns), generator=gen, device=DEV, dtype=torch.int32)
+    return (bits | (sign << 31)).view(torch.float32)
+
+
+@pytest.mark.parametrize("where", ["x", "dy", "all of x"])
+def test_sums_of_lost_terms(where):
+    """A column of subnormal values against values of 1e30: its sums are ordinary numbers, and all that the thirds carry of
+    them can be exactly zero."""
+    x, dy = layer(700, 1024, 1024, 1.0 if where != "dy" else 1e30, 1.0 if where == "dy" else 1e30)
+    if where == "x":
+        x[:, 200:210] = subnormal(700, 10, 1)
+    elif where == "dy":
+        dy[:, 900:910] = subnormal(700, 10, 2)
+    else:
+        x = subnormal(700, 1024, 3)
+    got, want, _ = product(x, dy, 0.0)
+    part = (slice(900, 910), slice(None)) if where == "dy" else (slice(None), slice(200, 210))
+    err = ((got.double() - want)[part].norm() / want[part].norm()).item()
+    print("thirds lost", where, "%.2e" % err, "largest", want[part].abs().max().item(), flush=True)
+    assert err < 4e-7
+    assert ((got.double() - want).norm() / want.norm()).item() < 4e-7
+
+
+def test_leading_parts_that_cancel():
+    """2^-120 (1 + 2^-20) against -2^-120: the difference is the bit that lies below bf16's subnormal numbers."""
+    x, dy = torch.zeros(700, 1024, device=DEV), layer(700, 1024, 1024)[1]
+    x[0], x[1], dy[0], dy[1] = 2.0 ** -120 * (1 + 2.0 ** -20), -2.0 ** -120, 2.0 ** 100, 2.0 ** 100
+    got, want, _ = product(x, dy, 0.0)
+    assert bool((want == 2.0 ** -40).all()) and torch.equal(got.double(), want)
+
+
+def test_products_below_the_subnormal_numbers():
+    """Terms of 2^-145 and parts of them far below 2^-149: an fp32 sum of them is off by half of that per term."""
+    got, want, _ = product(*layer(700, 1024, 1024, 2.0 ** -75, 2.0 ** -70), 0.0)
+    assert (got.double() - want).abs().max().item() <= 700 * 2.0 ** -149
