@@ -199,7 +199,8 @@ dropit_wgrad_path dropit_weight_grad_path(const int64_t *x_shape, int ndim, drop
  *
  * bf16 inputs are multiplied exactly and accumulated in fp32; fp32 inputs use
  * true fp32 multiply-adds, or, for large fully-connected layers, the products of three bf16
- * parts of each factor, which leave out less than 2^-25 of a product, accumulated in fp32.  Infinities and NaN: a window position over the padding
+ * parts of each factor, all but that of the two smallest (at most 2^-34 of the product),
+ * accumulated in fp32.  Infinities and NaN: a window position over the padding
  * is no term of the sum on the exact path (DROPIT_PATH_FMA); the bf16 matrix-core
  * convolutions multiply the zeros that stand there, so an infinity or NaN of dY at
  * a border also makes the taps that hang over it NaN.  k == 0 gives dW = 0.  The bias gradient does not

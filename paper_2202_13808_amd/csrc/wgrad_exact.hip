@@ -18,7 +18,7 @@
 //      to cover them.
 //   3. the K-slices' sums are added in a fixed order (splitk.hpp).
 // Products and accumulation are true fp32 multiply-adds in a fixed order: dW is bit-reproducible.  (Large fp32 fully-connected
-// layers take a faster product of the same accuracy, see "fp32 products from bf16 thirds".)
+// layers take a faster product, see "fp32 products from bf16 thirds".)
 // A window position over the padding is no term of the sum: an infinity or NaN of dY must not meet the zero that stands
 // there in the tile.  A workgroup whose sums are not all finite (padded convolutions only: one look at them at the end)
 // does its slice again, with the tokens whose dY is not finite taken out of the matrix product and added by vector
@@ -431,18 +431,20 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
 }
 
 // ---- fp32 products from bf16 thirds -----------------------------------------------------------------
-// A fp32 number is the sum of three bf16 numbers, 8 significand bits each (a = a1 + a2 + a3, every difference exact), so a
-// product of two is the sum of nine bf16 products, exact in fp32; the six of a1 b1, a1 b2, a2 b1, a2 b2, a1 b3 and a3 b1
-// leave out less than 2^-25 of |a b| -- below the rounding of a single fp32 addition -- and take 192 cycles of the bf16 matrix
-// instructions for 16 tokens of a 32 x 32 block, where the fp32 instruction takes 512.  a1 b1 has sums of its own, so that
-// they are rounded once per 16 tokens and not six times (against 64 bits, 6304 tokens, gamma 0.9: 0.8e-7 in the 2-norm; the
-// fp32 instruction 1.4e-7; one set of sums 2.4e-7).
+// A fp32 number is the sum of three bf16 numbers, 8 significand bits each (a = a1 + a2 + a3, every difference exact; a2 is at
+// most 2^-8, a3 2^-17 of a), so a product of two is the sum of nine bf16 products, exact in fp32.  All but a3 b3, at most
+// 2^-34 of |a b|, are summed: 256 cycles of the bf16 matrix instructions for 16 tokens of a 32 x 32 block, where the fp32
+// instruction takes 512.  (Without a2 b3 and a3 b2, 2^-24 of |a b| between them, the call below takes 66 us, and a sum of one
+// term is off by up to 1.15e-7 of itself instead of the 6e-8 that rounding it takes.)  a1 b1 has sums of its own, so that they
+// are rounded once per 16 tokens and not eight times (against 64 bits, 6304 tokens, gamma 0.9: 0.8e-7 in the 2-norm; the
+// fp32 instruction 1.4e-7; six products in one set of sums 2.4e-7).
 // The thirds are made on the way from the fetch to LDS (five vector instructions per element, beside the other workgroup's
 // matrix instructions) and lie there as [third][column][32 tokens], so that an operand is one 16-byte read; the 16-byte unit o
 // of column c is kept at o ^ swizzle(c), which spreads the reads (consecutive columns, one o) and the stores over the banks.
-// Two workgroups per compute unit, one converting while the other multiplies.  Whole call 6304 x 384 -> 1536 80 -> 59 us (the matrix
-// instructions of the product alone take 20), 6304 x 1536 -> 384 93 -> 74.5; two LDS stages and
-// one 256 x 128 workgroup of eight wavefronts 65, loads of four bytes instead of eight 68.
+// Two workgroups per compute unit, one converting while the other multiplies.  Whole call, fp32 instruction -> this:
+// 6304 x 384 -> 1536 86 -> 72 us, 6304 x 1536 -> 384 94 -> 81, 2048 x 1024 -> 1024 56 -> 50, 700 x 1024 -> 1024 36 -> 34.5;
+// 120 random layers 0.73 to 0.98 of the time.  (With six products, two LDS stages and one 256 x 128 workgroup of eight
+// wavefronts took 10 % more, loads of four bytes instead of eight 15 %.)
 // What the thirds cannot carry shows in the sums and in the smallest elements: an infinity, a NaN, or a value that rounds to
 // infinity in bf16 makes a sum not finite; and where the last third of a value is below the normal numbers (2^-126, taken as
 // lost here), or a product of parts below the subnormal ones, a sum of n terms is off by n 2^-126 of the other operand's
@@ -591,14 +593,14 @@ exact_split_kernel(const float *__restrict__ dY, const float *__restrict__ x, in
                 for (int j = 0; j < C::FN; ++j)
                     b[p][j] = *reinterpret_cast<const bf16x8 *>(lds + (3 + p) * THIRD + unit(wn * C::WN + j * 32 + (lane & 31), kk * 2 + (lane >> 5)));
             }
-            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+            constexpr int PA[8] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[8] = {1, 2, 0, 2, 1, 0, 1, 0};     // small ones first
 #pragma unroll
-            for (int p = 0; p < 6; ++p)
+            for (int p = 0; p < 8; ++p)
 #pragma unroll
                 for (int i = 0; i < C::FM; ++i)
 #pragma unroll
                     for (int j = 0; j < C::FN; ++j) {
-                        f32x16 &s = p == 5 ? acc[i][j] : small[i][j];
+                        f32x16 &s = p == 7 ? acc[i][j] : small[i][j];
                         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[p]][i], b[PB[p]][j], s, 0, 0, 0);
                     }
         }

@@ -108,3 +108,20 @@ def test_products_below_the_subnormal_numbers():
     """Terms of 2^-145 and parts of them far below 2^-149: an fp32 sum of them is off by half of that per term."""
     got, want, _ = product(*layer(700, 1024, 1024, 2.0 ** -75, 2.0 ** -70), 0.0)
     assert (got.double() - want).abs().max().item() <= 700 * 2.0 ** -149
+
+
+def test_sums_of_one_term():
+    """One kept element per column: the product rounded once, 2^-24 of it, and less than 2^-30 for the parts that are added
+    up below the first (seven additions at 2^-8 of the product).  1.00ff8p0 has the largest second and third parts."""
+    x, dy = torch.zeros(700, 1024, device=DEV), layer(700, 1024, 1024, dy_scale=1.0)[1]
+    column = torch.arange(1024, device=DEV)
+    x[column % 700, column] = layer(1024, 1, 1)[0][:, 0] + 4.0
+    worst = float.fromhex("0x1.00ff8p0")
+    x[column[::7] % 700, column[::7]] = worst
+    dy[:, ::5] = worst
+    dy[dy == 0] = 1.0                              # (two of the numbers drawn)
+    got, want, _ = product(x, dy, 1.0 - 1024.5 / x.numel())
+    assert int((want != 0).sum()) == want.numel()
+    err = ((got.double() - want).abs() / want.abs()).max().item()
+    print("thirds one term %.4e" % err, flush=True)
+    assert err <= 2.0 ** -24 + 2.0 ** -30
