@@ -309,9 +309,9 @@ dropit_status dropit_weight_grad_mask(const void *vals, const uint32_t *mask, co
  *   2            mode 0's kernel through a cooperative launch: the runtime then guarantees
  *                co-residency, at the price of tens of microseconds of queue switching per
  *                call; cannot be recorded into a HIP graph (falls back to mode 0's launch).
- *   3            test hook: mode 0 with zero patience at the grid barriers (one look, and the
- *                last workgroup gives up whatever it sees), which forces the serial redo; every
- *                kernel still exits normally.
+ *   3            test hook: mode 0 with zero patience at the grid barriers (a workgroup looks
+ *                once), and with the serial redo whether or not one gave up; every kernel still
+ *                exits normally.
  * Modes 0, 1 and 3 use only ordinary kernel launches and can be captured into a HIP graph.
  * Returns DROPIT_EINVAL for any other mode.
  */

@@ -475,7 +475,7 @@ __device__ inline void dev_store64(unsigned long long *p, unsigned long long v)
 // device is not shared, so the wait is bounded: returns false (in every thread of the workgroup)
 // if the others did not all arrive within `spin_limit` polls or if some workgroup already gave
 // up.  The caller then skips to the kernel's exit protocol.  Without any patience (spin_limit 0, mode 3) a workgroup polls once,
-// and may find the others there; the last workgroup of the grid gives up whatever it finds, so the redo is certain.
+// and may find the others there: the exit protocol then sees to it that the selection is redone all the same.
 // Every wavefront first waits for its own outstanding stores and atomics: a workgroup barrier alone orders LDS only, and
 // without this wait the arrival could overtake the histogram merges of the other wavefronts.  (With 8192 bins to merge it
 // is 1.5 us of each fp32 digit pass.)
@@ -488,8 +488,7 @@ __device__ inline bool grid_barrier(SelState *st, uint32_t *xbar, uint32_t round
         if (lane == 0)
             __hip_atomic_fetch_add(&xbar[(blockIdx.x & 7u) * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_s_sleep(16);           // ~0.5 us
-        // arrivals of group `lane`; without patience more than there can be in the grid's last workgroup
-        const uint32_t goal = lane >= 8u || lane >= G ? 0u : spin_limit == 0 && blockIdx.x == G - 1 ? 0xFFFFFFFFu : round * ((G - lane + 7u) / 8u);
+        const uint32_t goal = lane < 8u && lane < G ? round * ((G - lane + 7u) / 8u) : 0u;    // arrivals of group `lane`
         uint32_t spins = 0, ok = 1;
         for (;;) {
             const bool short_of = goal != 0u && dev_load(&xbar[lane * 64]) < goal;
@@ -2475,7 +2474,7 @@ select_fused_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64
     if (threadIdx.x == REPORT_TID) {
         const uint32_t seen = rep.mine != 0 && rep.group != 0 ? rep.common + rep.group : 0u;
         const bool last = (seen & 0xFFFFu) == gridDim.x;
-        const bool redo = alone || (last && (seen >> 16) != 0);
+        const bool redo = alone || (last && ((seen >> 16) != 0 || spin_limit == 0));
         // The last report: nobody will look at the published word any more.  Take it back, so that the next launch that
         // carries the same generation number (a replay of a captured graph) cannot take this call's leftovers for its own.
         if (last) {
