@@ -2353,36 +2353,38 @@ select_small_kernel(const RAW *__restrict__ x, int numel, int nvf, uint32_t k, S
     }
 }
 
-// 16-bit tensors of PER consecutive vectors per thread: digit histograms over all elements (11 + 4 bits) are the shorter
-// program, and at this size fetching it and the barriers are all there is.  gamma 0.9 / 0.6, this form against the one above:
-// 8 K elements 5.5 / 6.4 us against 7.2 / 8.4, 11 K 6.9 / 8.1 against 8.3 / 9.7, 16 K 8.2 / 9.8 against 8.6 / 11.1.
-constexpr int ROW_VECTORS = 2 * SEL_THREADS;               // the largest it takes
-template <int PER>
+// The same with digit histograms over all elements (11 + 4 bits, fp32 13 + 13 + 5), PER rows of a vector per thread, written row
+// by row: the shorter program, which is all that counts up to 16 K 16-bit elements, and the one whose time depends least on
+// the values, which counts where much is kept: the form above stages all of that, and reads again what does not fit.
+constexpr int ROW_VECTORS = 3 * SEL_THREADS;               // the most that 16-bit tensors come with
+template <typename RAW, int PER>
 __global__ void __launch_bounds__(SEL_THREADS)
-select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k, uint16_t *__restrict__ vals,
-                  int32_t *__restrict__ idx)
+select_row_kernel(const RAW *__restrict__ x, int numel, int nvf, uint32_t k, RAW *__restrict__ vals, int32_t *__restrict__ idx)
 {
-    constexpr int VEC = 8, NB = 1 << 11;
-    constexpr uint32_t MASK = KeyTraits<uint16_t>::MASK;
-    __shared__ uint32_t lh[NB + 2 * WAVE];
+    constexpr int VEC = KeyTraits<RAW>::VEC, KEY_BITS = sizeof(RAW) == 4 ? 31 : 15, FIRST_BITS = sizeof(RAW) == 4 ? 13 : 11;
+    constexpr uint32_t MASK = KeyTraits<RAW>::MASK;
+    __shared__ uint32_t lh[(1 << FIRST_BITS) + 2 * WAVE];
     __shared__ uint32_t wave_tot[SEL_THREADS / WAVE];
     __shared__ uint32_t bcast[2];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int ntail = numel - nvf * VEC;                             // the ragged end, in thread 0
     u32x4 q[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) q[i] = tid * PER + i < nvf ? reinterpret_cast<const u32x4 *>(x)[tid * PER + i] : u32x4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < PER; ++i) {
+        const int v = i * SEL_THREADS + tid;
+        q[i] = v < nvf ? reinterpret_cast<const u32x4 *>(x)[v] : u32x4{0u, 0u, 0u, 0u};
+    }
     auto for_all = [&](auto f) {
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-            if (tid * PER + i < nvf) for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int) { f(raw); });
+            if (i * SEL_THREADS + tid < nvf) for_each_raw(RAW(0), q[i], [&](uint32_t raw, int) { f(raw); });
         if (tid == 0)
             for (int e = 0; e < ntail; ++e) f(x[nvf * VEC + e]);
     };
     uint32_t prefix = 0, k_rem = k;
     auto pass = [&](auto shift_c, auto bits_c) {
         constexpr int SHIFT = decltype(shift_c)::value, BITS = decltype(bits_c)::value;
-        constexpr bool FIRST = SHIFT + BITS == 15;
+        constexpr bool FIRST = SHIFT + BITS == KEY_BITS;
         __syncthreads();
         for (int i = tid; i < (1 << BITS) + 2 * WAVE; i += SEL_THREADS) lh[i] = 0;
         __syncthreads();
@@ -2401,41 +2403,51 @@ select_row_kernel(const uint16_t *__restrict__ x, int numel, int nvf, uint32_t k
         __syncthreads();
         resolve_digit_local<(1 << BITS), BITS>(lh, prefix, k_rem, wave_tot, bcast);
     };
-    pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 11>{});
-    pass(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
+    if constexpr (sizeof(RAW) == 4) {
+        pass(std::integral_constant<int, 18>{}, std::integral_constant<int, 13>{});
+        pass(std::integral_constant<int, 5>{}, std::integral_constant<int, 13>{});
+        pass(std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
+    } else {
+        pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 11>{});
+        pass(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
+    }
     const uint32_t t = prefix, m = k_rem;                            // the threshold key and its tie budget
-    uint32_t cnt = 0;                                                // low 16 bits: #gt, high 16 bits: #eq (16384 elements at most)
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-        if (tid * PER + i < nvf)
-            for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int) {
-                const uint32_t key = raw & MASK;
-                cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
-            });
-    uint32_t total;
-    const uint32_t before = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
-    uint32_t my_gt = before & 0xFFFFu, my_eq = before >> 16;
+    uint32_t run_gt = 0, run_eq = 0;                                 // before the row
+    uint32_t my_gt = 0, my_eq = 0;
     auto emit = [&](uint32_t raw, int i) {
         const uint32_t key = raw & MASK;
         const bool gt = key > t, eq = key == t;
         if (gt || (eq && my_eq < m)) {
             const uint32_t pos = my_gt + min(my_eq, m);
             if (pos < k) {                                           // always true for consistent counts
-                vals[pos] = static_cast<uint16_t>(raw);
+                vals[pos] = static_cast<RAW>(raw);
                 idx[pos] = i;
             }
         }
         my_gt += gt ? 1u : 0u;
         my_eq += eq ? 1u : 0u;
     };
-    if (cnt) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (tid * PER + i < nvf) for_each_raw(uint16_t(0), q[i], [&](uint32_t raw, int e) { emit(raw, (tid * PER + i) * VEC + e); });
+    for (int i = 0; i < PER; ++i) {
+        if (i > 0 && i * SEL_THREADS >= nvf) break;                  // uniform
+        const int v = i * SEL_THREADS + tid;
+        uint32_t cnt = 0;                                            // low 16 bits: #gt, high 16 bits: #eq (8192 elements at most)
+        if (v < nvf)
+            for_each_raw(RAW(0), q[i], [&](uint32_t raw, int) {
+                const uint32_t key = raw & MASK;
+                cnt += (key > t ? 1u : 0u) + (key == t ? 0x10000u : 0u);
+            });
+        uint32_t total;
+        const uint32_t before = block_exclusive_scan<SEL_THREADS>(cnt, wave_tot, total);
+        my_gt = run_gt + (before & 0xFFFFu);
+        my_eq = run_eq + (before >> 16);
+        if (cnt) for_each_raw(RAW(0), q[i], [&](uint32_t raw, int e) { emit(raw, v * VEC + e); });
+        run_gt += total & 0xFFFFu;
+        run_eq += total >> 16;
     }
     if (tid == 0) {
-        my_gt = total & 0xFFFFu;
-        my_eq = total >> 16;
+        my_gt = run_gt;
+        my_eq = run_eq;
         for (int e = 0; e < ntail; ++e) emit(x[nvf * VEC + e], nvf * VEC + e);
     }
 }
@@ -2609,23 +2621,32 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
     };
     const int mode = select_mode();
     const SampleRanks spread = numel >= SAMPLE_MIN_NUMEL ? sample_ranks(static_cast<uint32_t>(k), numel, SAMPLE_ELEMS) : SampleRanks{0.0f, 0.0f};
-    // Small tensors (default mode only: the other modes are there to exercise the other forms): one workgroup.  16-bit ones
-    // above 32 K elements, or 16 K where more than a quarter is kept, only if the persistent kernel cannot predict the
-    // threshold: it takes 11.1 to 11.5 us from there to 128 K, this form 8.6 (gamma 0.9) or 11.0 (0.6) at 16 K, 10.5 or 15.6 at
-    // 32 K and 15 or 25 at 64 K.
+    // Small tensors (default mode only: the other modes are there to exercise the other forms): one workgroup, in the form of
+    // rows or the one of staged candidates.
+    // fp32: rows where more than 3/8 is kept, whose time the values hardly change (32 K elements at gamma 0.6, normal / ReLU /
+    // GELU: 20 / 20 / 21 us; staged 18 / 18 / 23; at 0.3 22 / 23 / 22 and 26 / 34 / 26; at 0.7 20 / 19 / 20 and 17 / 16 / 16).
+    // 16-bit: rows up to 16 K elements, and to 24 K where more than an eighth is kept (20 K at gamma 0.6, 0.7, 0.8, 0.9: 11.2,
+    // 10.4, 9.8, 9.8 us; staged 12.5, 11.5, 10.5, 9.2; persistent 11.2, 11.0 where it can predict the threshold, 15 where it
+    // cannot, as in ReLU at 0.6 and GELU at 0.7).  Above, staged to 32 K where at most a quarter is kept, else the persistent
+    // kernel: 11 to 16 us from there to 128 K, staged 15 or 25 at 64 K.  Staged to 64 K where the threshold's rank lies outside
+    // a sample.
     const int64_t nvec = numel / KeyTraits<RAW>::VEC;
-    const bool predictable = sizeof(RAW) == 2 && spread.lo != 0.0f && (nvec > SMALL_VECTORS / 2 * SEL_THREADS || 4 * k > numel);
-    if (FORM == FORM_FLAT && mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS && (!predictable || nvec <= ROW_VECTORS)) {
+    const bool sampled = spread.lo != 0.0f;
+    const bool rows = sizeof(RAW) == 4 ? 8 * k > 3 * numel : nvec <= 2 * SEL_THREADS || (nvec <= ROW_VECTORS && sampled && 8 * k > numel);
+    const bool persistent = sizeof(RAW) == 2 && sampled && !rows && (nvec > SMALL_VECTORS / 2 * SEL_THREADS || 4 * k > numel);
+    if (FORM == FORM_FLAT && mode == 0 && nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS && !persistent) {
         trace_mark(stream);
         const int vectors = int(nvec);
-        if constexpr (sizeof(RAW) == 2) {
-            const auto row = [&](auto kernel) {
+        if (rows) {
+            const auto run = [&](auto kernel) {
                 kernel<<<1, SEL_THREADS, 0, stream>>>(xr, int(numel), vectors, static_cast<uint32_t>(k), static_cast<RAW *>(vals), idx);
                 trace_mark(stream);
                 return launch_status();
             };
-            if (vectors <= SEL_THREADS) return row(select_row_kernel<1>);
-            if (vectors <= ROW_VECTORS) return row(select_row_kernel<2>);
+            if (vectors <= SEL_THREADS) return run(select_row_kernel<RAW, 1>);
+            if (vectors <= 2 * SEL_THREADS) return run(select_row_kernel<RAW, 2>);
+            if constexpr (sizeof(RAW) == 2) return run(select_row_kernel<RAW, 3>);
+            else return vectors <= 4 * SEL_THREADS ? run(select_row_kernel<RAW, 4>) : run(select_row_kernel<RAW, SMALL_VECTORS>);
         }
         const SampleRanks ranks = vectors >= SMALL_SAMPLE_MIN ? sample_ranks(static_cast<uint32_t>(k), numel, vectors)
                                                               : SampleRanks{0.0f, 0.0f};
