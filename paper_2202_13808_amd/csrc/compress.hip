@@ -697,9 +697,9 @@ inline SampleRanks sample_ranks(uint32_t k, int64_t numel, int sample)
 
 // From the sample's histogram (in LDS; bin 0, the zeros, is not counted: it holds what the others leave of the sample): the
 // bins that hold the two ranks.
-// Returns false (in every thread) if there is no usable bracket (more than BRACKET_MAX_BINS bins).
+// Returns false (in every thread) if there is no usable bracket (more than `most` bins).
 template <int NB>
-__device__ inline bool sample_bracket(const uint32_t *hist, SampleRanks ranks, uint32_t *wave_tot,
+__device__ inline bool sample_bracket(const uint32_t *hist, SampleRanks ranks, uint32_t most, uint32_t *wave_tot,
                                       uint32_t *bcast /*[2]*/, uint32_t &b_lo, uint32_t &b_hi)
 {
     constexpr int PER = (NB + SEL_THREADS - 1) / SEL_THREADS;
@@ -734,7 +734,7 @@ __device__ inline bool sample_bracket(const uint32_t *hist, SampleRanks ranks, u
     __syncthreads();
     b_hi = bcast[0];
     b_lo = bcast[1];
-    const bool ok = b_hi != 0xFFFFFFFFu && b_lo != 0xFFFFFFFFu && b_hi - b_lo < static_cast<uint32_t>(BRACKET_MAX_BINS);
+    const bool ok = b_hi != 0xFFFFFFFFu && b_lo != 0xFFFFFFFFu && b_hi - b_lo < most;
     __syncthreads();
     return ok;
 }
@@ -1109,7 +1109,7 @@ __device__ inline SelOutcome select16_body(const uint16_t *__restrict__ x, int64
             __syncthreads();
             STAMP(9);
             uint32_t b_lo, b_hi;
-            predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, wave_tot, bcast, b_lo, b_hi);
+            predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, BRACKET_MAX_BINS, wave_tot, bcast, b_lo, b_hi);
             if (predicted) {
                 key_lo = b_lo << SAMPLE_SHIFT;
                 nf = (b_hi - b_lo + 1) << SAMPLE_SHIFT;
@@ -1454,6 +1454,8 @@ template <> struct Staged<uint32_t> {
 // list in flat order, and every workgroup finds the threshold in the list by itself: two exchanges and one read of x, where
 // digit histograms (13 + 13 + 5 bits) take three and read the tensor, or its parked head, four times.  A bin of more elements
 // than the list holds (large tensors, ties) is histogrammed by the next 11 bits instead, and a second table settles the rest.
+// A bracket of 8 to 28 sample bins, as where the threshold lies far below the largest magnitudes, gets bins of 2^17 or 2^18 keys,
+// if the sample finds no more elements in a bin of 2^19 than the list holds.
 // No bracket, one that fails, or a threshold among the smallest magnitudes: the exact histogram of the first 13 bits gives
 // the range, and the same steps follow.
 constexpr int SEG32_CAP = 1152;                            // staged elements (8 bytes) per wavefront: 16 segments are 144 KB
@@ -1483,7 +1485,7 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
     __shared__ uint32_t bcast[4], offs[2], verdict;
     __shared__ uint32_t wave_tot[NW];
     __shared__ uint32_t whist[NW][MAX_LAST_BINS + 1];           // per wavefront: its elements in each bin of the range, and above it
-    __shared__ __attribute__((aligned(16))) uint32_t digits[2][256];
+    __shared__ __attribute__((aligned(16))) uint32_t digits[3][256];
     __shared__ uint32_t wave_gt[NW], wave_eq[NW], list_gt[NW], list_eq[NW];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
@@ -1547,10 +1549,18 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         __syncthreads();
         uint32_t b_lo, b_hi;
         // (a range that reaches down to the smallest keys would make every element a candidate)
-        predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, wave_tot, bcast, b_lo, b_hi) && b_lo > 0;
+        predicted = sample_bracket<SAMPLE_BINS>(lh, ranks, 4 * BRACKET_MAX_BINS, wave_tot, bcast, b_lo, b_hi) && b_lo > 0;
+        const uint32_t bins = b_hi - b_lo + 1;
+        // wider than the table holds bins of 2^16 keys: bins of 2^17 or 2^18, if the list will hold any of them
+        const int wider = bins <= uint32_t(BRACKET_MAX_BINS) ? 0 : bins <= 2 * uint32_t(BRACKET_MAX_BINS) ? 1 : 2;
+        if (predicted && wider != 0) {                          // uniform
+            const uint32_t most = static_cast<uint32_t>(float(LIST32_CAP) * float(SAMPLE_ELEMS) / static_cast<float>(numel));
+            predicted = __syncthreads_or(uint32_t(tid) < bins && lh[b_lo + tid] > most) == 0;
+        }
         if (predicted) {
+            shift = BIN_SHIFT + wider;
             key_lo = b_lo << SAMPLE_SHIFT32;
-            nf = (b_hi - b_lo + 1) << (SAMPLE_SHIFT32 - BIN_SHIFT);
+            nf = bins << (SAMPLE_SHIFT32 - shift);
         }
     } else if (blockIdx.x == 0) {
         publish_words(st, cleared, gen);
@@ -1706,7 +1716,10 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         STAMP(3);
         if (const SelOutcome o = exchange_counts()) return o;
         STAMP(5);
-        if (resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, false)) break;
+        // (a bin wider than 2^16 keys is settled by the list alone)
+        if (resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, false) &&
+            (shift <= BIN_SHIFT || bcast[2] <= uint32_t(LIST32_CAP)))
+            break;
         if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
         predicted = false;                       // the sample misled: once more with the exact histogram
         missed = true;
@@ -1757,7 +1770,7 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
                 if (rel < bin_size && pos < uint32_t(LIST32_CAP)) dev_store(&list[pos++], rel);
             }
         }
-        if (tid < 512) digits[tid >> 8][tid & 255] = 0u;
+        if (tid < 3 * 256) digits[tid >> 8][tid & 255] = 0u;
         if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
         STAMP(6);
         uint32_t e[LIST32_PER], mine0 = 0;
@@ -1766,11 +1779,11 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
             if (uint32_t(j * SEL_THREADS + tid) < left) e[j] = dev_load(list + j * SEL_THREADS + tid);
         if (uint32_t(lane) < mine) mine0 = dev_load(list + own + lane);
         report_past_barriers(xbar, rep, false);
-        // two digits of 8 bits at most; every wavefront resolves each for itself, a lane four bins in descending order
+        // two digits of 8 bits, and what a wider bin leaves; every wavefront resolves each for itself, a lane four bins in
+        // descending order
         uint32_t rel_t = 0;
         int rem = shift;
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
+        auto next_digit = [&](int pass) {
             const int take = min(rem, 8), low = rem - take;
 #pragma unroll
             for (int j = 0; j < LIST32_PER; ++j) {
@@ -1805,7 +1818,10 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
             rel_t = rel_t << take | uint32_t(__builtin_amdgcn_readlane(int(digit), finder));
             k_rem = uint32_t(__builtin_amdgcn_readlane(int(rest), finder));
             rem = low;
-        }
+        };
+        next_digit(0);
+        next_digit(1);
+        if (__builtin_expect(rem > 0, 0)) next_digit(2);         // uniform
         t = bin_lo + rel_t;
         m = k_rem;
         // above and equal to t: in the list before this chunk, in this wavefront's own entries and above the bin
