@@ -1457,7 +1457,8 @@ template <> struct Staged<uint32_t> {
 // A bracket of 8 to 28 sample bins, as where the threshold lies far below the largest magnitudes, gets bins of 2^17 or 2^18 keys,
 // if the sample finds no more elements in a bin of 2^19 than the list holds.
 // No bracket, one that fails, or a threshold among the smallest magnitudes: the exact histogram of the first 13 bits gives
-// the range, and the same steps follow.
+// the range, and the same steps follow; for the smallest magnitudes the range is the zeros at first, where a threshold down
+// there most likely lies (ReLU): that table alone settles it.
 constexpr int SEG32_CAP = 1152;                            // staged elements (8 bytes) per wavefront: 16 segments are 144 KB
 constexpr int PART32_OFF = (SEL_THREADS / WAVE) * SEG32_CAP * 8;           // the table's partial sums, the second digit's histogram
 constexpr int PART32_WORDS = 2 * (SEL_THREADS / WAVE) * TABLE_PITCH;
@@ -1665,9 +1666,12 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         return grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3]) ? SEL_DONE : SEL_GAVE_UP;
     };
 
-    bool missed = false;
+    bool missed = false, first_digit = false;
     for (;;) {
-        if (!predicted) {
+        if (!predicted && first_digit) {               // not the zeros: the smallest magnitudes in 32 bins
+            nf = 32;
+            shift = 31 - BITS32_FIRST - 5;
+        } else if (!predicted) {
             // exact first digit: every element of the chunk through an LDS histogram, merged with global atomics
             constexpr int NB = 1 << BITS32_FIRST, SHIFT1 = 31 - BITS32_FIRST;
             if (!missed && blockIdx.x == 0) publish_hist(&st->ready_hist, gen);
@@ -1707,9 +1711,10 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
             if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
             uint32_t prefix = 0, k_rem = k;
             resolve_digit_local<NB, BITS32_FIRST>(hist0, prefix, k_rem, wave_tot, bcast);
+            first_digit = true;
             key_lo = prefix << SHIFT1;
-            nf = 32;
-            shift = SHIFT1 - 5;
+            nf = prefix ? 32 : 1;                      // among the smallest magnitudes it is most likely a zero
+            shift = prefix ? SHIFT1 - 5 : 0;
         }
         STAMP(2);
         staged_rows = stage_rows(key_lo, 0, n_w);
@@ -1720,9 +1725,9 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         if (resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, false) &&
             (shift <= BIN_SHIFT || bcast[2] <= uint32_t(LIST32_CAP)))
             break;
-        if (!predicted) return SEL_GAVE_UP;     // cannot happen with an exact digit; the serial path would still answer
-        predicted = false;                       // the sample misled: once more with the exact histogram
-        missed = true;
+        if (!predicted && shift != 0) return SEL_GAVE_UP;      // cannot happen with an exact digit; the serial path would still answer
+        missed |= predicted;                     // the sample misled: once more with the exact histogram
+        predicted = false;
     }
     // The k-th key is the k_rem-th largest of the `left` keys in bin `bin`; offs: the chunks before this one, above that bin
     // and in it.
@@ -1731,7 +1736,7 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
     const uint32_t above_before = offs[0], in_before = offs[1];
     const uint32_t bin_lo = key_lo + (bin << shift), bin_size = 1u << shift;
     uint32_t t, m, my_gt, my_eq, chunk_gt, chunk_eq, wave_eq_mine;
-    if (left <= uint32_t(LIST32_CAP)) {
+    if (shift != 0 && left <= uint32_t(LIST32_CAP)) {
         // ---- the bin's keys as a list in flat order ----
         uint32_t before = 0, mine = whist[wave][bin], all = 0;
 #pragma unroll
@@ -1860,32 +1865,36 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
         chunk_gt = gt0 + uint32_t(__builtin_amdgcn_readlane(int(gi), NW - 1));
         chunk_eq = eq0 + uint32_t(__builtin_amdgcn_readlane(int(ei), NW - 1));
     } else {
-        // ---- the bin's next 11 bits from a histogram, then single keys from a second table ----
-        const int low = shift - BITS32_SECOND;                    // 5 or 2 bits are left after it
-        for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) part[i] = 0;
-        __syncthreads();
-        for_candidates([&](uint32_t key) {
-            const uint32_t rel = key - bin_lo;
-            if (rel < bin_size) atomicAdd(&part[rel >> low], 1u);
-        });
-        if (last_chunk && tid == 0)
-            for (int64_t i = tail0; i < numel; ++i) {
-                const uint32_t rel = (x[i] & MASK) - bin_lo;
+        if (shift != 0) {
+            // ---- the bin's next 11 bits from a histogram, then single keys from a second table ----
+            const int low = shift - BITS32_SECOND;                    // 5 or 2 bits are left after it
+            for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) part[i] = 0;
+            __syncthreads();
+            for_candidates([&](uint32_t key) {
+                const uint32_t rel = key - bin_lo;
                 if (rel < bin_size) atomicAdd(&part[rel >> low], 1u);
+            });
+            if (last_chunk && tid == 0)
+                for (int64_t i = tail0; i < numel; ++i) {
+                    const uint32_t rel = (x[i] & MASK) - bin_lo;
+                    if (rel < bin_size) atomicAdd(&part[rel >> low], 1u);
+                }
+            __syncthreads();
+            for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) {
+                const uint32_t c = part[i];
+                if (c) atomicAdd(&hist1[i], c);
             }
-        __syncthreads();
-        for (int i = tid; i < PART32_WORDS; i += SEL_THREADS) {
-            const uint32_t c = part[i];
-            if (c) atomicAdd(&hist1[i], c);
+            if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
+            uint32_t digit = 0;
+            resolve_digit_local<1 << BITS32_SECOND, BITS32_SECOND>(hist1, digit, k_rem, wave_tot, bcast);
+            key_lo = bin_lo + (digit << low);
+            nf = 1u << low;
+            shift = 0;
+            if (const SelOutcome o = exchange_counts()) return o;
+            if (!resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, true)) return SEL_GAVE_UP;   // cannot happen
+        } else {
+            report_past_barriers(xbar, rep, false);              // (bins of one key)
         }
-        if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
-        uint32_t digit = 0;
-        resolve_digit_local<1 << BITS32_SECOND, BITS32_SECOND>(hist1, digit, k_rem, wave_tot, bcast);
-        key_lo = bin_lo + (digit << low);
-        nf = 1u << low;
-        shift = 0;
-        if (const SelOutcome o = exchange_counts()) return o;
-        if (!resolve_table(table, nf, 0u, k, part, bcast, offs, &verdict, xbar, rep, true)) return SEL_GAVE_UP;   // cannot happen
         t = key_lo + bcast[0];
         m = bcast[1];
         const uint32_t trel = bcast[0];
