@@ -919,27 +919,31 @@ static_assert(Cfg::BM == CfgFused::BM && Cfg::BN == CfgFused::BN && Cfg::BK == C
               Cfg::BK == CfgFusedHalf::BK, "one regrouping serves both fused tiles");
 
 // A product over `nkb` token blocks in tiles of C: how it is cut, and what it costs beyond the other choices' common part.
+// `summed`: the slice sum runs for one slice too.
 struct Cut {
     int nb_count, mb_count, splits;
     double us;
 };
 
 template <typename C>
-Cut cut_product(const FcProblem &p, int nkb)
+Cut cut_product(const FcProblem &p, int nkb, bool summed)
 {
     Cut c;
     c.nb_count = int((p.cin + C::BN - 1) / C::BN);
     c.mb_count = int((p.cout + C::BM - 1) / C::BM);
     const int64_t tiles = int64_t(c.nb_count) * c.mb_count, slots = 256 * C::WGS_PER_CU;
     constexpr bool WIDE = C::WGS_PER_CU == 1;
-    // Fitted to the calls of 37 shapes (both tiles each, worst miss 8 us of 103 where the two differ by 25): a round of
-    // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.47 in small ones (two; 0.33 where one
-    // has the compute unit to itself), and the partial tiles 0.24 us per MB, written and read; whatever its size a wide
-    // product takes another 3.3 us.
+    // Fitted to the calls of 37 shapes and looked at over 170 others (both tiles each; worst miss 1.8 us of 52): a round of
+    // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.49 in small ones (two; 0.33 where one
+    // has the compute unit to itself), 0.53 where a row of small tiles is longer than 16, so that the workgroups of one XCD
+    // share less (8425 x 2058 -> 1848 92 us in wide tiles, 101 in small ones); the partial tiles 0.24 us per MB, written and
+    // read, and their sum 1.9 to launch; whatever its size a wide product takes another 3.3 us.
+    const double step = WIDE ? 0.66 : c.nb_count > 16 ? 0.53 : 0.49;
     auto cost = [&](int64_t splits) {
         const int64_t groups = tiles * splits, rounds = (groups + slots - 1) / slots, steps = (nkb + splits - 1) / splits;
         const double partial_mb = splits > 1 ? double(groups) * C::BM * C::BN * 4e-6 : 0.0;
-        return double(rounds * steps) * (WIDE ? 0.66 : groups <= 256 ? 0.33 : 0.47) + 0.24 * partial_mb + (WIDE ? 3.3 : 0.0);
+        return double(rounds * steps) * (!WIDE && groups <= 256 ? 0.33 : step) + 0.24 * partial_mb +
+               (splits > 1 && !summed ? 1.9 : 0.0) + (WIDE ? 3.3 : 0.0);
     };
     const int64_t most = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(slots / tiles, nkb), 256));
     auto allowed = [&](int64_t splits) { return std::max<int64_t>(1, std::min<int64_t>(splits, most)); };
@@ -953,6 +957,9 @@ Cut cut_product(const FcProblem &p, int nkb)
     if (!WIDE && tiles * splits > 256 && tiles * splits < 384)
         for (const int64_t other : {allowed(512 / tiles), allowed(256 / tiles)})
             if (cost(other) < cost(splits)) splits = other;
+    // ... and one slice where the sum's launch outweighs the steps saved: most products of up to nine blocks, larger results
+    // of up to twice as many (247 x 1048 -> 304 13.8 -> 12.0 us, 480 x 629 -> 1440 18.0 -> 14.6; 121 x 1800 -> 80 12.1 -> 11.1)
+    if (cost(1) <= cost(splits)) splits = 1;
     splits = allowed(dev_env("DROPIT_FC_SPLITS", splits));
     c.splits = int(splits);
     c.us = cost(splits);
@@ -962,10 +969,10 @@ Cut cut_product(const FcProblem &p, int nkb)
 // Calls in wide / small tiles: 1576 x 384 -> 1536 26.9 / 19.4 us, 25216 x 384 -> 1152 54 / 43, 25216 x 1536 -> 384 79 / 64,
 // 8192 x 1024 -> 1024 42 / 38; 12608 x 768 -> 3072 70.7 / 76.9, 16384 x 3072 -> 768 103 / 127 (large results that wide
 // tiles divide evenly keep them).
-GemmTile choose_tile(const FcProblem &p, int nkb)
+GemmTile choose_tile(const FcProblem &p, int nkb, bool summed)
 {
     if (const long forced = dev_env("DROPIT_GEMM_TILE", -1); forced >= 0) return forced == 0 ? GemmTile::WIDE : GemmTile::SMALL;
-    return cut_product<Cfg>(p, nkb).us < cut_product<CfgSmall>(p, nkb).us ? GemmTile::WIDE : GemmTile::SMALL;
+    return cut_product<Cfg>(p, nkb, summed).us < cut_product<CfgSmall>(p, nkb, summed).us ? GemmTile::WIDE : GemmTile::SMALL;
 }
 
 }  // namespace
@@ -991,12 +998,12 @@ static size_t tile_elems(GemmTile t)
     return t == GemmTile::WIDE ? Cfg::BM * Cfg::BN : CfgSmall::BM * CfgSmall::BN;
 }
 
-FcDensePlan fc_dense_plan(const FcProblem &p, bool fused)
+FcDensePlan fc_dense_plan(const FcProblem &p, bool fused, bool summed)
 {
     FcDensePlan plan;
     plan.nkb = int((p.ntok + Cfg::BK - 1) / Cfg::BK);
-    plan.tile = choose_tile(p, plan.nkb);
-    const Cut cut = plan.tile == GemmTile::WIDE ? cut_product<Cfg>(p, plan.nkb) : cut_product<CfgSmall>(p, plan.nkb);
+    plan.tile = choose_tile(p, plan.nkb, summed);
+    const Cut cut = plan.tile == GemmTile::WIDE ? cut_product<Cfg>(p, plan.nkb, summed) : cut_product<CfgSmall>(p, plan.nkb, summed);
     plan.nb_count = cut.nb_count;
     plan.mb_count = cut.mb_count;
     plan.splits = cut.splits;

@@ -77,3 +77,18 @@ def test_through_the_window(layout, n, c, h, w, j, stride):
     if layout == "nhwc":
         want = want.permute(0, 2, 3, 1)
     check(got, want.contiguous(), (layout, n, c, h, w, j, stride))
+
+
+@pytest.mark.parametrize("ntok,cin,cout", [
+    (121, 1800, 80), (288, 136, 264), (289, 500, 136),      # few blocks: one slice straight into dW, in small tiles
+    (480, 629, 1440),                                       # ... more of them in more tiles
+    (1900, 2224, 1304),                                     # rows of more than sixteen small tiles
+])
+def test_one_slice_and_long_rows(ntok, cin, cout):
+    test_fully_connected(ntok, cin, cout)
+
+
+@pytest.mark.parametrize("n,c,h,w,j", [(1, 128, 14, 14, 256), (2, 256, 9, 9, 136), (1, 512, 4, 5, 1032)])
+def test_channel_major_results_of_few_blocks(n, c, h, w, j):
+    """The slice sum runs for these whatever the slices: it writes dW [J][C][taps]."""
+    test_through_the_window("nchw", n, c, h, w, j, 1)
