@@ -99,7 +99,7 @@ __device__ inline void exact_epilogue(const f32x16 (&acc)[C::FM][C::FN], int spl
 // what is outside -- padding, a token past the last -- is an offset past the descriptor's end, which reads as zero, and an
 // element takes seven vector instructions instead of some twenty with a branch around the load; where a thread has eight
 // columns, what it needs to know of them stays in registers (three LDS reads per element otherwise, on an LDS that the tiles
-// keep busy).  Columns past the last of dW fetch whatever is there: those sums are not stored.  Whole calls, the same bits:
+// keep busy).  Rows and columns past the last of dW fetch whatever is there: those sums are not stored.  Whole calls, the same bits:
 // fp32 3x3 32 x 64 x 32 x 32 -> 64 58.5 -> 44.9 us, 64 x 64 x 56 x 56 -> 64 245 -> 182, 36 x 232 x 40 x 22 -> 144 409 -> 298;
 // bf16 with 129 output channels, 3x3 / stride 2 over 16 x 64 x 56 x 56 86 -> 52.
 template <typename RAW, typename C, Fetch FA, Fetch FB, bool SHORT = false>
@@ -297,7 +297,8 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     auto note_not_finite = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < EA; ++u)
-            if ((__float_as_uint(ra[u]) & 0x7fffffffu) >= 0x7f800000u) atomicOr(&not_finite[kb & 1], 1u << row_a(u));
+            if ((__float_as_uint(ra[u]) & 0x7fffffffu) >= 0x7f800000u && (!SHORT || m0 + tid / BK + u * (NT / BK) < M))
+                atomicOr(&not_finite[kb & 1], 1u << row_a(u));
     };
     auto store = [&]() __attribute__((always_inline)) {
         if constexpr (FA == ROWS16) {
@@ -417,12 +418,20 @@ exact_gemm_kernel(const RAW *__restrict__ dY, const RAW *__restrict__ x, int64_t
     if constexpr (CONV) {
         if ((g.ph | g.pw) != 0) {                          // uniform
             float z = 0.f;
+            auto look = [&](auto inside) {
 #pragma unroll
-            for (int i = 0; i < C::FM; ++i)
+                for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-                for (int j = 0; j < C::FN; ++j)
+                    for (int j = 0; j < C::FN; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) z = __builtin_fmaf(acc[i][j][e], 0.f, z);
+                        for (int e = 0; e < 16; ++e) z = __builtin_fmaf(inside(i, j, e) ? acc[i][j][e] : 0.f, 0.f, z);
+            };
+            if (SHORT && (m0 + BM > M || n0 + BN > N))     // uniform; what lies past dW holds other images' sums
+                look([&](int i, int j, int e) {
+                    return m0 + wm * C::WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3) < M &&
+                           n0 + wn * C::WN + j * 32 + (lane & 31) < N;
+                });
+            else look([](int, int, int) { return true; });
             if (__syncthreads_or(!(z == 0.f))) accumulate(std::true_type{});
         }
     }
@@ -693,7 +702,9 @@ dropit_status launch_exact(const ExactProblem &p, const ExactPlan &plan, const R
                           p.nhwc ? uint32_t(p.C) : 1u, p.C * p.H * p.W, p.cout * p.OH * p.OW,
                           divisor(uint32_t(p.OH * p.OW)), divisor(uint32_t(p.OW)), 0u, 0u};
         const int64_t xb = p.numel * int64_t(sizeof(RAW)), yb = p.ntok * p.cout * int64_t(sizeof(RAW));
-        constexpr int64_t REACH = int64_t(1) << 31;        // (offsets of what is not there may run past the ends, never round 2^32)
+        // (Rows past the last and columns past the last add planes to an offset: it may pass the end or wrap around, and fetch
+        // zeros or anything of the operand.  The descriptor bounds it, and those sums are neither stored nor looked at.)
+        constexpr int64_t REACH = int64_t(1) << 31;
         if (xb < REACH && yb < REACH && !dev_env("DROPIT_EXACT_LONG", 0)) {
             g.x_bytes = uint32_t(xb);
             g.y_bytes = uint32_t(yb);

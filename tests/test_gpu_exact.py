@@ -144,7 +144,7 @@ def test_integer_convolution_sums_are_exact(layout, shape, J, geom):
     assert np.array_equal(got, oracle.dw_conv(xh, g, kh, kw, (sh, sw), (ph, pw), (dh, dw)))
 
 
-@pytest.mark.parametrize("height,dtype", [(16384, torch.float32), (16383, torch.float32)])
+@pytest.mark.parametrize("height,dtype", [(16384, torch.float32), (16383, torch.float32), (32768, torch.bfloat16), (32767, torch.bfloat16)])
 def test_either_side_of_32_bit_offsets(height, dtype):
     """Operands of 2 GiB, and just below: 64-bit addresses on one side, buffer descriptors with 32-bit offsets on the other.
     A 1 x 1 convolution of two images and one channel; every sum is of whole numbers below 2^24 per slice, so it is exact up to
@@ -162,3 +162,26 @@ def test_either_side_of_32_bit_offsets(height, dtype):
     scale = sum((vals[i:i + (1 << 26)].double() * flat[idx[i:i + (1 << 26)].long()].double()).abs().sum().item()
                 for i in range(0, vals.numel(), 1 << 26))
     assert got.numel() == 1 and abs(got.item() - want) <= 2.0 ** -22 * scale
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("J", [3, 70])
+def test_infinities_of_the_next_image(dtype, J):
+    """A tile's rows past the last output channel reach into the next image: an infinity there, at the first channels, is in the
+    sums of its own channels alone, padded or not, whichever slices the images are in."""
+    print("exact next image", dtype, J, flush=True)
+    shape, conv, OH, OW = (24, 5, 15, 17), (3, 3, 2, 2, 1, 1, 1, 1), 8, 9
+    x, g = activation(shape, "normal", 31, dtype), oracle.widen(gradient((24, J, OH, OW), 0.02, 32, dtype)).astype(np.float32)
+    g[3, 0, 4, 4], g[11, 1, 0, 0], g[23, 0, 7, 8] = np.inf, np.nan, -np.inf
+    dy = g if dtype == "f32" else f32_to_bf16_bits(g)
+    vals, idx = dropit.compress(to_device(x), 0.5)
+    assert dropit.weight_grad_path(shape, vals.dtype, vals.numel(), J, conv) == "fma"
+    got = to_host(dropit.weight_grad(vals, idx, shape, to_device(dy), J, conv=conv)).astype(np.float64)
+    xh = oracle.densify(*oracle.compress(x, oracle.keep_count(x.size, 0.5)), shape)
+    ref = oracle.dw_conv(xh, oracle.widen(dy), 3, 3, (2, 2), (1, 1))
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert fin[2:].all() and not fin[:2].all()
+    size = oracle.dw_conv(np.abs(xh), np.abs(np.where(np.isfinite(g), oracle.widen(dy), 0)), 3, 3, (2, 2), (1, 1))
+    nu = (24 * OH * OW + 256) * 2.0 ** -24
+    assert (np.abs(got[fin] - ref[fin]) <= nu / (1 - nu) * size[fin]).all()
