@@ -33,12 +33,13 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(float *p, int64_t n)
 // order through LDS.  Four rows of dW to a workgroup and up to sixteen shares: the chain of dependent LDS reads, one per
 // token, is what a few workgroups of 256 threads with all tokens each spent their time on (calls in a queue
 // of calls: 256 tokens of 64 -> 128 10.9 us, 4.8 now; 1024 of 16 -> 64 29.7 and 5.5; 128 of 128 -> 4096 10.2 and 7.1).
-// Sixteen rows where four would make more workgroups than the chip holds.
+// Sixteen rows where four would make more workgroups than the chip holds, or more than one to a compute unit for little work
+// (75 tokens of 64 -> 1928 5.0 with four, 4.5 with sixteen; 128 of 128 -> 1928 5.7 and 6.5).
 constexpr int SMALL_NUMEL = 16384;         // elements of x: 64 KB of fp32 in LDS
 constexpr int SMALL_TOKENS = 1024;         // tokens: the dY slice is SMALL_TOKENS x JB fp32, 64 KB at most
 constexpr int SMALL_THREADS = 1024, SMALL_SHARES = 16, SMALL_MAX_JB = 16;
 
-inline int small_rows(int64_t cout) { return cout <= 2048 ? 4 : SMALL_MAX_JB; }
+inline int small_rows(int64_t numel, int64_t cout) { return cout <= 1024 || (cout <= 2048 && numel > 8192) ? 4 : SMALL_MAX_JB; }
 
 template <typename RAW, int JB>
 __global__ void __launch_bounds__(SMALL_THREADS)
@@ -310,7 +311,7 @@ static dropit_status run(const Problem &p, const void *vals, const int32_t *idx,
         trace_mark(stream);
         auto go = [&](auto raw_) {
             using RAW = decltype(raw_);
-            return small_rows(p.cout) == 4 ? launch_fc_small<RAW, 4>(vals, idx, k, dY, p.ntok, p.cin, p.cout, dW, stream)
+            return small_rows(p.numel, p.cout) == 4 ? launch_fc_small<RAW, 4>(vals, idx, k, dY, p.ntok, p.cin, p.cout, dW, stream)
                                            : launch_fc_small<RAW, SMALL_MAX_JB>(vals, idx, k, dY, p.ntok, p.cin, p.cout, dW, stream);
         };
         if (const dropit_status st = dt == DROPIT_BF16 ? go(uint16_t(0)) : go(uint32_t(0)); st != DROPIT_OK) return st;

@@ -60,7 +60,8 @@ def test_select(kind, dtype, numel):
     (7, 24, 4), (8, 24, 6),   # just below and at two shares
     (128, 128, 130),          # eight shares
     (1024, 16, 33),           # sixteen
-    (1024, 4, 2048),          # the most workgroups of four rows
+    (1024, 4, 2048),          # little work: sixteen rows to a workgroup
+    (1024, 12, 2048),         # the most workgroups of four rows
     (31, 20, 2049),           # sixteen rows to a workgroup, the last one nearly empty
     (4, 4096, 2100),
 ])
