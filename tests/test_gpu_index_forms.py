@@ -1,7 +1,7 @@
 """GPU: the row and mask forms written by the select itself (16-bit tensors above 64 K elements without a ragged end), against
 the oracle: rows of every kind of length (shorter than a vector, longer than a wavefront's range, one row), blocks and mask
 words that end inside a wavefront's range, few and many kept elements, segments that overflow, ties that split a wavefront, a
-forced serial redo and graph replays."""
+forced serial redo, a sample that misleads, graph replays, and guard words around what is written."""
 import numpy as np
 import pytest
 import torch
@@ -78,3 +78,123 @@ def test_serial_redo():
 def test_converted(shape):
     """One workgroup, or a ragged end: flat indices, converted."""
     check(activation((int(np.prod(shape)),), "normal", 8, "bf16"), shape, 0.9)
+
+
+def misleading(numel, scale):
+    """Sampled pieces (512 of two vectors, one per stretch at a hashed place) of another scale than the rest."""
+    nvf = numel // 8
+    stretch, sampled = nvf // 4 // 512, np.zeros(nvf, dtype=bool)
+    for i in range(512):
+        first = (i * stretch + ((((i + 1) * 0x9E3779B1) & 0xFFFFFFFF) >> 8) % stretch) * 4
+        sampled[first:first + 2] = True
+    base = np.random.default_rng(numel).standard_normal(numel, dtype=np.float32)
+    return f32_to_bf16_bits(base * np.where(np.repeat(sampled, 8), np.float32(scale), np.float32(1.0)))
+
+
+@pytest.mark.parametrize("mode", [0, 3])
+@pytest.mark.parametrize("scale", [0.01, 100.0])
+def test_misled(scale, mode):
+    """The retry, which begins when the workgroups have already reported; without patience some give up in it."""
+    dropit.set_select_mode(mode)
+    try:
+        for shape in ((1024, 128), (32768, 64), (1 << 18, 8)):
+            check(misleading(shape[0] * shape[1], scale), shape, 0.9)
+    finally:
+        dropit.set_select_mode(0)
+
+
+def guarded(words, dtype):
+    whole = torch.full((words + 128,), 0x5A5A if dtype == torch.int16 else 0x5A5A5A5A, dtype=dtype, device="cuda:0")
+    return whole, whole[64:64 + words]
+
+
+def intact(whole):
+    edge = torch.cat((whole[:64], whole[-64:]))
+    return bool((edge == edge[0]).all()) and int(edge[0]) in (0x5A5A, 0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("shape,gamma", [((8193, 8), 0.9), ((32772, 2), 0.99), ((1000, 1032), 0.6), ((3, 65536), 0.9), ((700003, 8), 0.05),
+                                         ((2420, 1000), 0.9)])
+@pytest.mark.parametrize("mode", [0, 3])
+def test_nothing_is_written_outside_the_outputs(shape, gamma, mode):
+    size = int(np.prod(shape))
+    x = activation((size,), "gelu", 7 + size % 89, "bf16")
+    xd, k = to_device(x).reshape(shape), oracle.keep_count(size, gamma)
+    want_v, want_i = oracle.compress(x, k)
+    lib, code, dims = dropit.lib(), dropit.binding._dtype_code(xd.dtype), dropit.binding._shape_array(shape)
+    stream, rows, blocks = torch.cuda.current_stream().cuda_stream, size // shape[-1], (size + 1023) // 1024
+    vals_w, vals = guarded(k, torch.int16)
+    col_w, col = guarded(k, torch.int16)
+    starts_w, starts = guarded(rows + 1, torch.int32)
+    mask_w, mask = guarded((size + 31) // 32, torch.int32)
+    block_w, block = guarded(blocks + 1, torch.int32)
+    print("index forms guarded", shape, gamma, mode, flush=True)
+    dropit.set_select_mode(mode)
+    try:
+        n = lib.dropit_compress_rows_workspace_bytes(size, k, code)
+        ws = torch.full((n,), 0xEE, dtype=torch.uint8, device="cuda:0")
+        assert lib.dropit_compress_rows(xd.data_ptr(), dims, 2, code, gamma, vals.data_ptr(), col.data_ptr(), starts.data_ptr(),
+                                        ws.data_ptr(), n, stream) == 0
+        torch.cuda.synchronize()
+        assert intact(vals_w) and intact(col_w) and intact(starts_w)
+        assert np.array_equal(col.cpu().numpy().view(np.uint16), (want_i % shape[-1]).astype(np.uint16))
+        assert np.array_equal(starts.cpu().numpy(), np.searchsorted(want_i, np.arange(rows + 1, dtype=np.int64) * shape[-1]))
+        n = lib.dropit_compress_mask_workspace_bytes(size, k, code)
+        ws = torch.full((n,), 0xEE, dtype=torch.uint8, device="cuda:0")
+        vals.zero_()
+        assert lib.dropit_compress_mask(xd.data_ptr(), dims, 2, code, gamma, vals.data_ptr(), mask.data_ptr(), block.data_ptr(),
+                                        ws.data_ptr(), n, stream) == 0
+        torch.cuda.synchronize()
+    finally:
+        dropit.set_select_mode(0)
+    assert intact(vals_w) and intact(mask_w) and intact(block_w)
+    assert vals.cpu().numpy().view(np.uint16).tobytes() == want_v.tobytes()
+    bits = np.zeros((size + 31) // 32 * 32, dtype=np.uint8)
+    bits[want_i] = 1
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), np.packbits(bits, bitorder="little").view(np.uint32))
+    assert np.array_equal(block.cpu().numpy(), np.searchsorted(want_i, np.arange(blocks + 1, dtype=np.int64) * 1024))
+
+
+def test_replays():
+    """Captured calls of both forms over changing inputs, eager calls between the replays."""
+    shape, gamma = (3000, 104), 0.9
+    size = shape[0] * shape[1]
+    k, code, dims = oracle.keep_count(size, gamma), dropit.binding.BF16, dropit.binding._shape_array(shape)
+    lib, blocks = dropit.lib(), (size + 1023) // 1024
+    xd = to_device(activation((size,), "normal", 1, "bf16")).reshape(shape)
+    dev = xd.device
+    vals_r, vals_m = (torch.empty(k, dtype=torch.bfloat16, device=dev) for _ in range(2))
+    col, starts = torch.empty(k, dtype=torch.int16, device=dev), torch.empty(shape[0] + 1, dtype=torch.int32, device=dev)
+    mask, block = torch.empty((size + 31) // 32, dtype=torch.int32, device=dev), torch.empty(blocks + 1, dtype=torch.int32, device=dev)
+    nr, nm = lib.dropit_compress_rows_workspace_bytes(size, k, code), lib.dropit_compress_mask_workspace_bytes(size, k, code)
+    ws_r, ws_m = torch.empty(nr, dtype=torch.uint8, device=dev), torch.empty(nm, dtype=torch.uint8, device=dev)
+
+    def both():
+        stream = torch.cuda.current_stream().cuda_stream
+        assert lib.dropit_compress_rows(xd.data_ptr(), dims, 2, code, gamma, vals_r.data_ptr(), col.data_ptr(), starts.data_ptr(),
+                                        ws_r.data_ptr(), nr, stream) == 0
+        assert lib.dropit_compress_mask(xd.data_ptr(), dims, 2, code, gamma, vals_m.data_ptr(), mask.data_ptr(), block.data_ptr(),
+                                        ws_m.data_ptr(), nm, stream) == 0
+
+    both()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        both()
+    for replay, dist in enumerate(("gelu", "normal", "relu", "gelu", "normal")):
+        x = activation((size,), dist, 60 + replay, "bf16")
+        xd.copy_(to_device(x).reshape(shape))
+        for t in (vals_r, vals_m, col, starts, mask, block):
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want_v, want_i = oracle.compress(x, k)
+        assert to_host(vals_r).tobytes() == want_v.tobytes() and to_host(vals_m).tobytes() == want_v.tobytes(), replay
+        assert np.array_equal(col.cpu().numpy().view(np.uint16), (want_i % shape[1]).astype(np.uint16))
+        assert np.array_equal(starts.cpu().numpy(), np.searchsorted(want_i, np.arange(shape[0] + 1, dtype=np.int64) * shape[1]))
+        bits = np.zeros((size + 31) // 32 * 32, dtype=np.uint8)
+        bits[want_i] = 1
+        assert np.array_equal(mask.cpu().numpy().view(np.uint32), np.packbits(bits, bitorder="little").view(np.uint32))
+        assert np.array_equal(block.cpu().numpy(), np.searchsorted(want_i, np.arange(blocks + 1, dtype=np.int64) * 1024))
+        check(activation((200000,), dist, replay, "bf16"), (200, 1000), 0.8)
