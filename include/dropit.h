@@ -304,7 +304,8 @@ dropit_status dropit_weight_grad_mask(const void *vals, const uint32_t *mask, co
  *                nodes): for callers that must not depend on co-residency at all.  Use it when
  *                other kernels that hold compute units or LDS for long (another select on a
  *                second stream, a persistent kernel) run on the device at the same time: mode 0
- *                then waits out its patience (milliseconds) and redoes the selection serially,
+ *                then waits out its patience (milliseconds; 0.1 ms for tensors of up to 64 K
+ *                elements, which are quickly redone) and redoes the selection serially,
  *                correct but orders of magnitude later than its usual 25 - 50 us.
  *   2            mode 0's kernel through a cooperative launch: the runtime then guarantees
  *                co-residency, at the price of tens of microseconds of queue switching per

@@ -445,7 +445,10 @@ compact_kernel(const RAW *__restrict__ x, int64_t numel, int64_t nvf, int64_t vp
 // resident all at once then costs those milliseconds plus the serial redo, not a second.  Waiting for workgroup 0's
 // clearing pass is another matter: it is dispatched first and needs a few microseconds, and a workgroup that stops
 // waiting for it leaves the exit count short (nobody then puts `ready` back to 0), so that wait is long.
-constexpr uint32_t SPIN_LIMIT = 1u << 16;
+// Tensors of up to 64 K elements, whose redo takes some 50 us, wait 0.1 ms: beside a large select on another stream, each with
+// workgroups on compute units that the other still needs, they give way (calls of 60 K elements beside ones of 10 M, worst of
+// 400 rounds 28 ms, of 1500 now 1).
+constexpr uint32_t SPIN_LIMIT = 1u << 16, SPIN_LIMIT_SMALL = 400;
 constexpr uint32_t READY_SPIN_LIMIT = 1u << 26;
 
 __device__ inline uint32_t dev_load(const uint32_t *p)
@@ -763,7 +766,8 @@ constexpr int ST_ROWS = 4;                                 // rows in flight per
 constexpr int ST_ROW_ELEMS = WAVE * 8;
 // Staged words per wavefront: 16 segments are 134 KB, the histograms in their place before anything is staged.  (With 1916
 // words and the histograms beside them: row form of 39 M elements at gamma 0.8 134.6 -> 133.5 us a pass, 1x1 convolution of
-// 51 M 113.0 -> 110.3.  2360 would fit and give 130.3 and 108.5; tensors of 9 M elements at gamma 0.05 overflow at 2136.)
+// 51 M 113.0 -> 110.3.  2360 would fit and give 130.3 and 108.5; what stands against it is only that the tests have 9 M elements
+// at gamma 0.05 overflow the segments, which they do not there.)
 constexpr int ST_SEGCAP = 2136;
 constexpr int ST_PART_OFF = (SEL_THREADS / WAVE) * ST_SEGCAP * 4;
 constexpr size_t ST_SMEM_BYTES = ST_PART_OFF + 4 * 2 * size_t(SEL_THREADS / WAVE) * TABLE_PITCH;    // + the table's partial sums
@@ -2723,7 +2727,7 @@ dropit_status run_compress(const void *x, int64_t numel, int64_t k, void *vals, 
             int64_t vpc = std::max<int64_t>(((nvf + chunks - 1) / chunks + 7) / 8 * 8, 8);
             chunks = std::max<int64_t>((nvf + vpc - 1) / vpc, 1);
             uint32_t k32 = static_cast<uint32_t>(k);
-            uint32_t spin_limit = mode == 3 ? 0u : SPIN_LIMIT;
+            uint32_t spin_limit = mode == 3 ? 0u : nvec <= int64_t(SMALL_VECTORS) * SEL_THREADS ? SPIN_LIMIT_SMALL : SPIN_LIMIT;
             RAW *vals_t = static_cast<RAW *>(vals);
             unsigned long long gen = next_generation();
             SampleRanks ranks = spread;
