@@ -236,15 +236,25 @@ def main():
     # (checked dispatch by dispatch: GEMM 53.5 us in the trace, 57.9 - 4.6 = 53.3 us here); left in,
     # every kernel would read 4-5 us long.
     # The marks must already be queued when the GPU reaches them, or the reading is the host's pace of
-    # submitting them: a few milliseconds of kernels go in front.
+    # submitting them: some milliseconds of work go in front, of a kind that is submitted several times
+    # faster than it runs.  (Steps of the workload are not: the GPU is done with a call of a few
+    # microseconds before the host has submitted the next, and on a slow host the overhead then read
+    # longer than the kernels it is taken from.)
+    fill = torch.ones(16 << 20, dtype=torch.float32, device=dev)
+
+    def keep_busy():
+        for _ in range(300):                 # 20 us or more each, about 4 us to submit
+            fill.mul_(1.0)
+
     pe = [torch.cuda.Event(enable_timing=True) for _ in range(65)]
-    for i in range(max(8, int(3.0 / max(ms_per_step, 1e-3)))):
-        step(i)
+    keep_busy()
+    torch.cuda.synchronize()
+    keep_busy()
     for e in pe:
         e.record()
     torch.cuda.synchronize()
     event_overhead_ms = float(np.median(event_ms(pe)))
-    n_c = n_g = 0
+    keep_busy()
     for i in range(n_meas):
         x, dy = xs[i % copies], dys[i % copies]
         dropit.trace_events(ce[i])
