@@ -1673,6 +1673,8 @@ __device__ inline SelOutcome select32_body(const uint32_t *__restrict__ x, int64
     bool missed = false, first_digit = false;
     for (;;) {
         if (!predicted && first_digit) {               // not the zeros: the smallest magnitudes in 32 bins
+            // the table is about to be written again, and others may still be reading it
+            if (!grid_barrier(st, xbar, ++barriers, spin_limit, &bcast[3])) return SEL_GAVE_UP;
             nf = 32;
             shift = 31 - BITS32_FIRST - 5;
         } else if (!predicted) {

@@ -87,6 +87,27 @@ def test_threshold_just_above_the_zeros(numel):
             run(x, gamma)
 
 
+@pytest.mark.parametrize("numel", [33000, 300003, 5000000])
+def test_two_tables_in_a_row(numel):
+    """A threshold just above the zeros takes two tables, one after the other in the same lines: workgroups with little to stage
+    must not write the second before the others have read the first.  All of the work lies in the last workgroups here."""
+    x = np.zeros(numel, dtype=np.float32)
+    rng = np.random.default_rng(numel)
+    some = numel // 8
+    x[-some:] = rng.integers(1, 1 << 17, some).astype(np.uint32).view(np.float32)
+    k = numel // 16
+    gamma = 1.0 - (k + 0.5) / numel
+    assert oracle.keep_count(numel, gamma) == k
+    want_v, want_i = oracle.compress(x, k)
+    xd = to_device(x)
+    ws = torch.empty(dropit.compress_workspace_bytes(numel, xd.dtype), dtype=torch.uint8, device="cuda:0")
+    for rep in range(40):
+        vals, idx = dropit.compress(xd, gamma, workspace=ws)
+        torch.cuda.synchronize()
+        assert int(ws[:64].cpu().numpy().view(np.uint32)[14]) == 0, rep
+        assert np.array_equal(to_host(idx), want_i) and to_host(vals).tobytes() == want_v.tobytes(), rep
+
+
 def test_without_patience():
     rng = np.random.default_rng(4)
     relu = np.maximum(rng.standard_normal(300003), 0).astype(np.float32)
