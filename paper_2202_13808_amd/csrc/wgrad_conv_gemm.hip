@@ -119,7 +119,7 @@ ConvGemmPlan conv_gemm_plan(const ConvProblem &p)
 {
     ConvGemmPlan plan;
     plan.fp = FcProblem{p.N * p.H * p.W, 9 * p.C, p.J, p.k};
-    plan.gemm = fc_dense_plan(plan.fp, false, true);
+    plan.gemm = fc_dense_plan(plan.fp, false, true, 9);
     const int64_t HW = p.H * p.W;
     // 64 channels: a token's segment is then a whole 128-byte line; fewer where that leaves compute units without a block
     plan.cb = 64;

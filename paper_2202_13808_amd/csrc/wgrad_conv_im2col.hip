@@ -341,7 +341,8 @@ ConvIm2colPlan conv_im2col_plan(const ConvGeneral &p)
 {
     ConvIm2colPlan plan;
     plan.fp = FcProblem{p.N * p.OH * p.OW, p.C * p.g.kh * p.g.kw, p.J, p.k};
-    plan.gemm = fc_dense_plan(plan.fp);
+    plan.window = window_preferred(p);
+    plan.gemm = fc_dense_plan(plan.fp, false, false, plan.window ? int(p.g.kh * p.g.kw) : 1);
     plan.dyt_bytes = p.nhwc ? 0 : round_up(size_t(plan.fp.ntok) * p.J * 2, 256);
 
     // Tiled form: column blocks whose segment of a token's row is whole 16-byte units.  With C % 8 == 0
@@ -359,7 +360,6 @@ ConvIm2colPlan conv_im2col_plan(const ConvGeneral &p)
     plan.rowptr_bytes = 0;
     plan.pointwise = conv_pointwise_preferred(p);
     if (plan.pointwise) plan.pw = conv_pointwise_plan(p);
-    plan.window = window_preferred(p);
     plan.xd_bytes = conv_window_bytes(p.N, p.C, p.H, p.W);
     int64_t blk = units_total, rowlen = plan.gemm.pitch;
     if (p.C % 8 == 0) {

@@ -919,14 +919,15 @@ static_assert(Cfg::BM == CfgFused::BM && Cfg::BN == CfgFused::BN && Cfg::BK == C
               Cfg::BK == CfgFusedHalf::BK, "one regrouping serves both fused tiles");
 
 // A product over `nkb` token blocks in tiles of C: how it is cut, and what it costs beyond the other choices' common part.
-// `summed`: the slice sum runs for one slice too.
+// `summed`: the slice sum runs for one slice too.  `taps`: the columns of a row are this many positions of a window over the
+// same few.
 struct Cut {
     int nb_count, mb_count, splits;
     double us;
 };
 
 template <typename C>
-Cut cut_product(const FcProblem &p, int nkb, bool summed)
+Cut cut_product(const FcProblem &p, int nkb, bool summed, int taps)
 {
     Cut c;
     c.nb_count = int((p.cin + C::BN - 1) / C::BN);
@@ -936,9 +937,10 @@ Cut cut_product(const FcProblem &p, int nkb, bool summed)
     // Fitted to the calls of 37 shapes and looked at over 170 others (both tiles each; worst miss 1.8 us of 52): a round of
     // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.49 in small ones (two; 0.33 where one
     // has the compute unit to itself), 0.53 where a row of small tiles is longer than 16, so that the workgroups of one XCD
-    // share less (8425 x 2058 -> 1848 92 us in wide tiles, 101 in small ones); the partial tiles 0.24 us per MB, written and
-    // read, and their sum 1.9 to launch; whatever its size a wide product takes another 3.3 us.
-    const double step = WIDE ? 0.66 : c.nb_count > 16 ? 0.53 : 0.49;
+    // share less (8425 x 2058 -> 1848 92 us in wide tiles, 101 in small ones), 0.47 through a window, whose taps read the same
+    // rows (64 images of 256 -> 256 channels at 14 x 14 39.7 us with 14 slices, 42.2 with the 7 that 0.53 leads to); the partial
+    // tiles 0.24 us per MB, written and read, and their sum 1.9 to launch; whatever its size a wide product takes another 3.3 us.
+    const double step = WIDE ? 0.66 : taps > 1 ? 0.47 : c.nb_count > 16 ? 0.53 : 0.49;
     auto cost = [&](int64_t splits) {
         const int64_t groups = tiles * splits, rounds = (groups + slots - 1) / slots, steps = (nkb + splits - 1) / splits;
         const double partial_mb = splits > 1 ? double(groups) * C::BM * C::BN * 4e-6 : 0.0;
@@ -969,10 +971,10 @@ Cut cut_product(const FcProblem &p, int nkb, bool summed)
 // Calls in wide / small tiles: 1576 x 384 -> 1536 26.9 / 19.4 us, 25216 x 384 -> 1152 54 / 43, 25216 x 1536 -> 384 79 / 64,
 // 8192 x 1024 -> 1024 42 / 38; 12608 x 768 -> 3072 70.7 / 76.9, 16384 x 3072 -> 768 103 / 127 (large results that wide
 // tiles divide evenly keep them).
-GemmTile choose_tile(const FcProblem &p, int nkb, bool summed)
+GemmTile choose_tile(const FcProblem &p, int nkb, bool summed, int taps)
 {
     if (const long forced = dev_env("DROPIT_GEMM_TILE", -1); forced >= 0) return forced == 0 ? GemmTile::WIDE : GemmTile::SMALL;
-    return cut_product<Cfg>(p, nkb, summed).us < cut_product<CfgSmall>(p, nkb, summed).us ? GemmTile::WIDE : GemmTile::SMALL;
+    return cut_product<Cfg>(p, nkb, summed, taps).us < cut_product<CfgSmall>(p, nkb, summed, taps).us ? GemmTile::WIDE : GemmTile::SMALL;
 }
 
 }  // namespace
@@ -998,12 +1000,13 @@ static size_t tile_elems(GemmTile t)
     return t == GemmTile::WIDE ? Cfg::BM * Cfg::BN : CfgSmall::BM * CfgSmall::BN;
 }
 
-FcDensePlan fc_dense_plan(const FcProblem &p, bool fused, bool summed)
+FcDensePlan fc_dense_plan(const FcProblem &p, bool fused, bool summed, int taps)
 {
     FcDensePlan plan;
     plan.nkb = int((p.ntok + Cfg::BK - 1) / Cfg::BK);
-    plan.tile = choose_tile(p, plan.nkb, summed);
-    const Cut cut = plan.tile == GemmTile::WIDE ? cut_product<Cfg>(p, plan.nkb, summed) : cut_product<CfgSmall>(p, plan.nkb, summed);
+    plan.tile = choose_tile(p, plan.nkb, summed, taps);
+    const Cut cut = plan.tile == GemmTile::WIDE ? cut_product<Cfg>(p, plan.nkb, summed, taps)
+                                                : cut_product<CfgSmall>(p, plan.nkb, summed, taps);
     plan.nb_count = cut.nb_count;
     plan.mb_count = cut.mb_count;
     plan.splits = cut.splits;

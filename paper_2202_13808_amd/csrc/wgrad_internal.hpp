@@ -28,7 +28,8 @@ struct FcDensePlan {
 
 // bf16 fully-connected weight gradient: recover R(a^) densely, then a direct-to-LDS GEMM (wgrad_fc_dense.hip)
 bool fc_dense_supported(const FcProblem &p);
-FcDensePlan fc_dense_plan(const FcProblem &p, bool fused = false, bool summed = false);   // summed: the slice sum runs for one slice too
+// summed: the slice sum runs for one slice too; taps: of the window that the product reads through
+FcDensePlan fc_dense_plan(const FcProblem &p, bool fused = false, bool summed = false, int taps = 1);
 dropit_status fc_dense_run(const FcProblem &p, const FcDensePlan &plan, const void *vals, const int32_t *idx,
                            const void *dY, float *dW, char *ws, hipStream_t stream);
 
