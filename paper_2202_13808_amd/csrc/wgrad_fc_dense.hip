@@ -936,11 +936,10 @@ Cut cut_product(const FcProblem &p, int nkb, bool summed, int taps)
     constexpr bool WIDE = C::WGS_PER_CU == 1;
     // Fitted to the calls of 37 shapes and looked at over 170 others (both tiles each; worst miss 1.8 us of 52): a round of
     // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.49 in small ones (two; 0.33 where one
-    // has the compute unit to itself), 0.53 where a row of small tiles is longer than 16, so that the workgroups of one XCD
-    // share less (8425 x 2058 -> 1848 92 us in wide tiles, 101 in small ones), 0.47 through a window, whose taps read the same
+    // has the compute unit to itself), 0.47 through a window, whose taps read the same
     // rows (64 images of 256 -> 256 channels at 14 x 14 39.7 us with 14 slices, 42.2 with the 7 that 0.53 leads to); the partial
     // tiles 0.24 us per MB, written and read, and their sum 1.9 to launch; whatever its size a wide product takes another 3.3 us.
-    const double step = WIDE ? 0.66 : taps > 1 ? 0.47 : c.nb_count > 16 ? 0.53 : 0.49;
+    const double step = WIDE ? 0.66 : taps > 1 ? 0.47 : 0.49;
     auto cost = [&](int64_t splits) {
         const int64_t groups = tiles * splits, rounds = (groups + slots - 1) / slots, steps = (nkb + splits - 1) / splits;
         const double partial_mb = splits > 1 ? double(groups) * C::BM * C::BN * 4e-6 : 0.0;
@@ -965,6 +964,16 @@ Cut cut_product(const FcProblem &p, int nkb, bool summed, int taps)
     splits = allowed(dev_env("DROPIT_FC_SPLITS", splits));
     c.splits = int(splits);
     c.us = cost(splits);
+    // From memory (operands that no earlier pass left in the caches) two small tiles on a compute unit are slower than that:
+    // 3.4 us, and 0.04 per block where the rows of R(a^), 0.05 where those of dY, do not begin on 128-byte lines, of which a
+    // row of a small tile then touches three for two, one of a wide tile five for four.  Calls in wide / small tiles, new
+    // operands each: 9890 x 474 -> 2744 50.3 / 59.2 us (warm 52.0 / 48.1), 9890 x 448 -> 2752 49.9 / 51.8, 14310 x 385 -> 1536
+    // 45.3 / 49.3, 25216 x 384 -> 1152 55.0 / 52.0, 6117 x 576 -> 1344 36.9 / 32.3.  Over 200 random layers the choice is 0.2 %
+    // from the better tile in the mean (1.6 % without these terms, worst 17.6).
+    if (!WIDE && taps == 1 && tiles * splits > 256) {
+        const int64_t groups = tiles * splits, blocks = (groups + slots - 1) / slots * ((nkb + splits - 1) / splits);
+        c.us += 3.4 + double(blocks) * (((p.cin + 7) / 8 % 8 != 0 ? 0.04 : 0.0) + (p.cout % 64 != 0 ? 0.05 : 0.0));
+    }
     return c;
 }
 
@@ -990,7 +999,8 @@ bool fc_dense_supported(const FcProblem &p)
 
 bool fc_fused_supported(const FcProblem &p)
 {
-    // the wide tile only; the column blocks of a token block are counted in LDS; pair positions are 32-bit
+    // (up to 128 output channels neither of its tiles, 256 x 256 or 128 x 256, is worth its rows); the column blocks of a token
+    // block are counted in LDS; pair positions are 32-bit
     return fc_dense_supported(p) && p.cout > 128 && (p.cin + Cfg::BN - 1) / Cfg::BN <= BUCKET_MAX_NB &&
            p.k < (int64_t(1) << 31);
 }
