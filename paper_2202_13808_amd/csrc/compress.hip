@@ -36,7 +36,7 @@
 //   bf16 0.6 M elements 17.7 -> 12.7 us, 3.2 M 22 -> 16.0, 9.7 M 26.3 -> 20.3, 50 M (gamma 0.9) 53.8 -> 44.4,
 //   39 M (gamma 0.8) 78.7 -> 48, 51 M (gamma 0.8) 93.6 -> 65.
 // fp32, digit histograms of the whole tensor -> sample, staged candidates and the threshold's bin as a list (gamma 0.9):
-//   0.07 M elements 24.1 -> 17.1 us, 0.6 M 26.9 -> 18.9, 2.4 M 33.9 -> 21.3, 8.4 M 47.4 -> 25.2, 50 M 152.6 -> 88.8.
+//   0.07 M elements 24.2 -> 17.5 us, 0.6 M 28.9 -> 19.7, 2.4 M 35.5 -> 21.8, 8.4 M 50.1 -> 29.4, 50 M 166 -> 103.
 #include "common.hpp"
 #include "wgrad_internal.hpp"
 #include "dev_hooks.hpp"

@@ -934,7 +934,7 @@ Cut cut_product(const FcProblem &p, int nkb, bool summed, int taps)
     c.mb_count = int((p.cout + C::BM - 1) / C::BM);
     const int64_t tiles = int64_t(c.nb_count) * c.mb_count, slots = 256 * C::WGS_PER_CU;
     constexpr bool WIDE = C::WGS_PER_CU == 1;
-    // Fitted to the calls of 37 shapes and looked at over 170 others (both tiles each; worst miss 1.8 us of 52): a round of
+    // Fitted to the calls of 37 shapes and looked at over 170 others (both tiles each, on operands in the caches; worst miss 1.8 us of 52): a round of
     // workgroups takes 0.66 us per token block in wide tiles (one per compute unit), 0.49 in small ones (two; 0.33 where one
     // has the compute unit to itself), 0.47 through a window, whose taps read the same
     // rows (64 images of 256 -> 256 channels at 14 x 14 39.7 us with 14 slices, 42.2 with the 7 that 0.53 leads to); the partial
